@@ -165,10 +165,10 @@ int he_ct_pt_mac(he_ctx* ctx, const he_plan* plan, uint32_t limbs, const uint64_
  * HIP graph capture, tight serving loops, harnesses that forbid hipMalloc.  The same operation, arguments,
  * flags and errors as he_ct_pt_mac, but the workspace is a fixed array of HE_STATIC_SCRATCH_BYTES inside
  * the library's device code (each GPU a context was created on holds its copy until the process ends),
- * and the call allocates nothing, on the host's HIP side or the device's.  A plan, level and flags whose
- * he_plan_workspace_bytes() exceeds HE_STATIC_SCRATCH_BYTES is refused with HE_ERR_WORKSPACE (with
- * HE_RESCALE the accumulators of all outputs must fit: use he_ct_pt_mac, or flags = 0 followed by
- * he_rescale, for larger layers).  All calls on one GPU share that GPU's array, whatever their context or
+ * and the call allocates nothing, on the host's HIP side or the device's.  With HE_RESCALE the accumulators of all
+ * outputs must fit HE_STATIC_SCRATCH_BYTES, else the call is refused with HE_ERR_WORKSPACE (use he_ct_pt_mac, or
+ * flags = 0 followed by he_rescale, for larger layers); tables of gathered scalar weights that do not fit next to them
+ * are worked off in slices.  All calls on one GPU share that GPU's array, whatever their context or
  * stream: calls that overlap in time on one GPU race; calls on one stream do not.  Nothing in the array
  * has to be cleared between calls (every word a call reads it has written itself).
  */

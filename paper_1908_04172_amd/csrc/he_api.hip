@@ -14,7 +14,10 @@
 // object, in place of the caller's workspace.  In host code the array's name is only a handle for
 // hipGetSymbolAddress; the device address (one per GPU) is looked up once per device, with that device
 // current, when a context is created there, and every later use goes through that address.
-static __device__ __align__(256) unsigned char scratch[HE_STATIC_SCRATCH_BYTES];
+// Behind the documented size there is room for one slice of gathered weights at the largest level, so that a call whose
+// accumulators fit always finds room for its tables, in slices.
+static constexpr size_t STATIC_TABLE_BYTES = (size_t)4 * 4 * 128 * sizeof(u64) * HE_MAX_LIMBS;
+static __device__ __align__(256) unsigned char scratch[HE_STATIC_SCRATCH_BYTES + STATIC_TABLE_BYTES];
 static constexpr int MAX_DEVICES = 64;
 static std::mutex scratch_mutex;
 static void* scratch_address[MAX_DEVICES];  // [device], null until looked up
@@ -185,6 +188,29 @@ void fill_limb_const(LimbConst& c, u64 q, u64 psi, u32 N) {
     c.neg_four_q = 0 - 4 * q;
 }
 
+void fill_digit_const(DigitConst& d, const LimbConst& c) {  // (see DigitConst)
+    const u64 q = c.q;
+    u32 bits = 0;
+    while (q >> bits) ++bits;
+    const u32 kappa = bits < 32 ? 0 : (bits - 32) / 8 + 1, n_hi = bits / 8 + 1 - kappa;
+    const u32 s = 40 + bits - 8 * kappa - 8 * n_hi;
+    d.q = q;
+    d.pow8_shoup = h_shoup(256 % q, q);
+    const u64 lo_offset = kappa ? 1ull << (8 * kappa + 22) : 0;
+    d.hi_offset = 1ull << (8 * n_hi + 22);
+    const u64 both = (u64)(((u128)lo_offset + h_mulmod(h_powmod(2, 8 * n_hi + 22, q), h_powmod(2, 8 * kappa, q), q)) % q);
+    d.start = lo_offset + (both ? q - both : 0);
+    d.top = q < (1ull << 61) ? 4 * q : 2 * q;
+    d.mult = (u32)((((u128)1) << (s + 8 * kappa + 8 * n_hi - 9)) / q);
+    d.mult_shift = s - 32;
+    d.hi_shift = 8 * n_hi - 9;
+    d.kappa8 = 8 * kappa;
+    d.lazy = c.mac_lazy;
+    d.b8 = 1 << 8;
+    d.b16 = 1 << 16;
+    d.b24 = 1 << 24;
+}
+
 int check_level(const he_ctx* ctx, u32 limbs, u32 min_limbs) {
     if (!ctx) return HE_ERR_ARG;
     if (limbs < min_limbs || limbs > ctx->L) return HE_ERR_LEVEL;
@@ -293,22 +319,22 @@ void build_tiles(const u32* off, const u32* term_ct, u32 n_out, u32 cap, std::ve
     }
 }
 
-// Stable sort of the tiles into capacity classes caps[0] < caps[1] < caps[2].
-void classify(std::vector<Tile>& tiles, const u32 caps[3], u32 class_begin[4]) {
+// Stable sort of the tiles into the capacity classes caps[0] < caps[1] < ...
+void classify(std::vector<Tile>& tiles, const u32* caps, u32 n_caps, u32* class_begin) {
     std::vector<Tile> sorted;
     sorted.reserve(tiles.size());
-    for (int cls = 0; cls < 3; ++cls) {
+    for (u32 cls = 0; cls < n_caps; ++cls) {
         class_begin[cls] = (u32)sorted.size();
         for (const Tile& t : tiles) {
             const u32 lo = cls ? caps[cls - 1] : 0;
             if (t.count > lo && t.count <= caps[cls]) sorted.push_back(t);
         }
     }
-    class_begin[3] = (u32)sorted.size();
+    class_begin[n_caps] = (u32)sorted.size();
     tiles.swap(sorted);
 }
 
-const u32 CAPS_S[3] = {1, 4, 16};
+const u32 CAPS_S[SCALAR_CLASSES] = {1, 4, 8, 16};
 const u32 CAPS_P[3] = {1, 2, 4};
 
 }  // namespace
@@ -360,6 +386,7 @@ int he_ctx_create(he_ctx** out, uint32_t log2N, uint32_t L, const uint64_t* modu
             LimbConst& c = ctx->limbs.c[i];
             const u128 cap_q = c.ntt_mode == 2 ? 3 + 4 * log2N : c.ntt_mode == 1 ? 4 : 2;
             c.mac_lazy = (12 + cap_q) * (u128)c.q < ((u128)1 << 64);
+            fill_digit_const(ctx->digits.c[i], c);
         }
         if (ctx->q[i] < (1ull << 30)) {  // the limb has a packed 32-bit form
             Limb32& c = ctx->limbs32.c[i];
@@ -631,50 +658,73 @@ int he_plan_create(he_ctx* ctx, uint32_t n_in, uint32_t n_out, uint32_t n_pt, co
     p->off.assign(off, off + n_out + 1);
     p->tiles_s_dev = p->tiles_p_dev = nullptr;
     p->wbase_s_dev = nullptr;
-    p->wowner_s_dev = nullptr;
+    p->owners_dev = p->lists_dev = nullptr;
+    p->digit_tiles_dev = nullptr;
     p->off_dev = p->term_ct_dev = p->term_pt_dev = nullptr;
     std::vector<Tile> ts, tp;
-    build_tiles(off, term_ct, n_out, CAPS_S[2], ts);
+    build_tiles(off, term_ct, n_out, CAPS_S[SCALAR_CLASSES - 1], ts);
     build_tiles(off, term_ct, n_out, CAPS_P[2], tp);
-    classify(ts, CAPS_S, p->class_begin_s);
-    classify(tp, CAPS_P, p->class_begin_p);
+    classify(ts, CAPS_S, SCALAR_CLASSES, p->class_begin_s);
+    classify(tp, CAPS_P, 3, p->class_begin_p);
     p->n_tiles_s = (u32)ts.size();
     p->n_tiles_p = (u32)tp.size();
     // Groups of one class that multiply by the same plaintexts in the same arrangement (all windows of a
-    // convolution that have the same shape) share one table of gathered weights: the table then stays
-    // in the scalar cache instead of being fetched anew by every group.  wowner[i] = 1 for the group
-    // that fills the table.
-    std::vector<u64> wbase(ts.size() + 1, 0);
-    std::vector<u32> wowner(ts.size() + 1, 0);
+    // convolution that have the same shape) share one table of gathered weights, which then stays in the caches (and
+    // in a workgroup's LDS) instead of being fetched anew by every group.  The tiles of a class are sorted by table,
+    // stably: the windows of one shape stay in raster order, and neighbours share inputs.
+    std::vector<u32> owners, lists;
+    std::vector<DigitTile> dts(ts.size());
     u64 elems = 0;
-    for (int cls = 0; cls < 3; ++cls) {
-        p->min_terms_s[cls] = p->class_begin_s[cls] < p->class_begin_s[cls + 1] ? ~0u : 0;
-        p->max_terms_s[cls] = 0;
-        p->max_count_s[cls] = 0;
-        std::map<std::vector<u32>, u64> tables;
-        std::vector<u32> key;
-        for (u32 i = p->class_begin_s[cls]; i < p->class_begin_s[cls + 1]; ++i) {
+    p->max_terms = 0;
+    p->wbase_s.resize(ts.size());
+    p->table_s.resize(ts.size());
+    for (u32 cls = 0; cls < SCALAR_CLASSES; ++cls) {
+        const u32 begin = p->class_begin_s[cls], end = p->class_begin_s[cls + 1];
+        p->min_terms_s[cls] = begin < end ? ~0u : 0;
+        std::map<std::vector<u32>, u32> tables;
+        std::vector<u32> key, table(end - begin);
+        for (u32 i = begin; i < end; ++i) {
             p->min_terms_s[cls] = std::min(p->min_terms_s[cls], ts[i].n_terms);
-            p->max_terms_s[cls] = std::max(p->max_terms_s[cls], ts[i].n_terms);
-            p->max_count_s[cls] = std::max(p->max_count_s[cls], ts[i].count);
+            p->max_terms = std::max(p->max_terms, ts[i].n_terms);
             key.assign(1, ts[i].n_terms);
             for (u32 g = 0; g < ts[i].count; ++g)
                 key.insert(key.end(), term_pt + off[ts[i].out0 + g], term_pt + off[ts[i].out0 + g] + ts[i].n_terms);
-            const auto found = tables.find(key);
-            if (found != tables.end()) {
-                wbase[i] = found->second;
-                continue;
+            table[i - begin] = tables.emplace(key, (u32)tables.size()).first->second;
+        }
+        std::vector<u32> order(end - begin);
+        for (u32 i = 0; i < end - begin; ++i) order[i] = i;
+        std::stable_sort(order.begin(), order.end(), [&](u32 x, u32 y) { return table[x] < table[y]; });
+        const std::vector<Tile> was(ts.begin() + begin, ts.begin() + end);
+        for (u32 i = 0; i < end - begin; ++i) {
+            const Tile& t = was[order[i]];
+            ts[begin + i] = t;
+            if (i == 0 || table[order[i]] != table[order[i - 1]]) {
+                owners.push_back(begin + i);
+                // per 16 terms: one word per term (single outputs), else four tiles of 128 words per four outputs
+                p->table_end.push_back(elems + (u64)((t.n_terms + 15) / 16) * (cls == 0 ? 16 : 512 * output_tiles(t.count)));
             }
-            tables.emplace(key, elems);
-            wbase[i] = elems;
-            wowner[i] = 1;
-            elems += (u64)((ts[i].n_terms + 3) / 4 * 4) * (cls == 2 ? 24 : CAPS_S[cls]);  // terms padded to whole blocks of 4; 24 words per term in 16-output tables
+            p->wbase_s[begin + i] = elems;
+            p->table_s[begin + i] = (u32)owners.size() - 1;
+            dts[begin + i] = DigitTile{t.out0, t.count, t.n_terms, (u32)(lists.size() / LIST_CHUNK), elems, 0, 0};
+            if (cls > 0)
+                for (u32 chunk = 0; chunk < t.n_terms; chunk += LIST_CHUNK)
+                    for (u32 k = 0; k < LIST_CHUNK; ++k) {  // position [half][block][j] is term block * 4 + half * 2 + j
+                        const u32 u = chunk + (k / 2 % 4) * 4 + (k / 8) * 2 + k % 2;
+                        lists.push_back(term_ct[t.term0 + std::min(u, t.n_terms - 1)]);
+                    }
+            if (i + 1 == end - begin || table[order[i]] != table[order[i + 1]]) {
+                elems = p->table_end.back();
+                for (u32 k = owners.back(); k <= begin + i; ++k) dts[k].same_until = begin + i + 1;
+            }
         }
     }
-    p->wtab_elems = elems + 24;  // padding: the 16-output kernel requests one term's entry past its last
+    p->tiles_s = ts;
+    p->wtab_elems = elems;
     if (upload(&p->tiles_s_dev, ts.data(), ts.size()) != HE_OK || upload(&p->tiles_p_dev, tp.data(), tp.size()) != HE_OK ||
-        upload(&p->wbase_s_dev, wbase.data(), ts.size()) != HE_OK || upload(&p->wowner_s_dev, wowner.data(), ts.size()) != HE_OK || upload(&p->off_dev, off, (size_t)n_out + 1) != HE_OK ||
-        upload(&p->term_ct_dev, term_ct, n_terms) != HE_OK || upload(&p->term_pt_dev, term_pt, n_terms) != HE_OK) {
+        upload(&p->wbase_s_dev, p->wbase_s.data(), ts.size()) != HE_OK || upload(&p->owners_dev, owners.data(), owners.size()) != HE_OK ||
+        upload(&p->digit_tiles_dev, dts.data(), dts.size()) != HE_OK || upload(&p->lists_dev, lists.data(), lists.size()) != HE_OK ||
+        upload(&p->off_dev, off, (size_t)n_out + 1) != HE_OK || upload(&p->term_ct_dev, term_ct, n_terms) != HE_OK ||
+        upload(&p->term_pt_dev, term_pt, n_terms) != HE_OK) {
         he_plan_destroy(p);
         return HE_ERR_DEVICE;
     }
@@ -685,7 +735,7 @@ int he_plan_create(he_ctx* ctx, uint32_t n_in, uint32_t n_out, uint32_t n_pt, co
 int he_plan_destroy(he_plan* p) {
     if (!p) return HE_ERR_ARG;
     if (p->device >= 0 && hipSetDevice(p->device) == hipSuccess) {
-        void* bufs[] = {p->tiles_s_dev, p->tiles_p_dev, p->wbase_s_dev, p->wowner_s_dev, p->off_dev, p->term_ct_dev, p->term_pt_dev};
+        void* bufs[] = {p->tiles_s_dev, p->tiles_p_dev, p->wbase_s_dev, p->owners_dev, p->digit_tiles_dev, p->lists_dev, p->off_dev, p->term_ct_dev, p->term_pt_dev};
         for (void* b : bufs)
             if (b) (void)hipFree(b);
     }
@@ -702,19 +752,22 @@ int he_plan_workspace_bytes(const he_plan* plan, uint32_t limbs, int pt_kind, ui
     int rc = check_level(plan->ctx, limbs, (flags & HE_RESCALE) ? 2 : 1);
     if (rc != HE_OK) return rc;
     size_t b = 0;
-    if (pt_kind == HE_PT_SCALAR) b += align256((size_t)plan->wtab_elems * limbs * sizeof(u64));
+    if (pt_kind == HE_PT_SCALAR) b += align256(scalar_table_bytes(plan, limbs));
     if (flags & HE_RESCALE) b += align256((size_t)plan->n_out * 2 * limbs * plan->ctx->N * sizeof(u64));
     *bytes = b;
     return HE_OK;
 }
 
-int he_ct_pt_mac(he_ctx* ctx, const he_plan* plan, uint32_t limbs, const uint64_t* ct_in, const uint64_t* pt,
-                 int pt_kind, const uint64_t* bias, uint64_t* ct_out, uint32_t flags, void* workspace,
-                 size_t workspace_bytes, void* stream) {
+// he_ct_pt_mac.  table_bytes: room for gathered weights at the start of the workspace, where the caller has less than the
+// plan's tables take (they are then worked off in slices); 0: all of it, as he_plan_workspace_bytes counts it.
+static int ct_pt_mac_entry(he_ctx* ctx, const he_plan* plan, uint32_t limbs, const uint64_t* ct_in, const uint64_t* pt, int pt_kind,
+                           const uint64_t* bias, uint64_t* ct_out, uint32_t flags, void* workspace, size_t workspace_bytes,
+                           size_t table_bytes, void* stream) {
     if (!ctx || !plan || plan->ctx != ctx) return HE_ERR_ARG;
     size_t need = 0;
     int rc = he_plan_workspace_bytes(plan, limbs, pt_kind, flags, &need);
     if (rc != HE_OK) return rc;
+    if (table_bytes) need = need - align256(scalar_table_bytes(plan, limbs)) + table_bytes;
     if (plan->n_out == 0) return HE_OK;
     if (!ct_out || (plan->n_terms && (!ct_in || !pt))) return HE_ERR_ARG;
     if (need && (!workspace || workspace_bytes < need)) return HE_ERR_WORKSPACE;
@@ -737,16 +790,23 @@ int he_ct_pt_mac(he_ctx* ctx, const he_plan* plan, uint32_t limbs, const uint64_
     char* ws = (char*)workspace;
     u64* wtab = nullptr;
     if (pt_kind == HE_PT_SCALAR) {
+        if (!table_bytes) table_bytes = align256(scalar_table_bytes(plan, limbs));
         wtab = (u64*)ws;
-        ws += align256((size_t)plan->wtab_elems * limbs * sizeof(u64));
+        ws += table_bytes;
     }
     hipStream_t s = (hipStream_t)stream;
     if (flags & HE_RESCALE) {
         u64* acc = (u64*)ws;
-        if ((rc = launch_mac(ctx, plan, limbs, ct_in, pt, pt_kind, bias, acc, wtab, MAC_FOR_RESCALE, s)) != HE_OK) return rc;
+        if ((rc = launch_mac(ctx, plan, limbs, ct_in, pt, pt_kind, bias, acc, wtab, table_bytes, MAC_FOR_RESCALE, s)) != HE_OK) return rc;
         return launch_rescale(ctx, limbs, acc, ct_out, plan->n_out, s);
     }
-    return launch_mac(ctx, plan, limbs, ct_in, pt, pt_kind, bias, ct_out, wtab, (flags & HE_ACCUMULATE) ? MAC_ACCUMULATE : 0u, s);
+    return launch_mac(ctx, plan, limbs, ct_in, pt, pt_kind, bias, ct_out, wtab, table_bytes, (flags & HE_ACCUMULATE) ? MAC_ACCUMULATE : 0u, s);
+}
+
+int he_ct_pt_mac(he_ctx* ctx, const he_plan* plan, uint32_t limbs, const uint64_t* ct_in, const uint64_t* pt,
+                 int pt_kind, const uint64_t* bias, uint64_t* ct_out, uint32_t flags, void* workspace,
+                 size_t workspace_bytes, void* stream) {
+    return ct_pt_mac_entry(ctx, plan, limbs, ct_in, pt, pt_kind, bias, ct_out, flags, workspace, workspace_bytes, 0, stream);
 }
 
 // The first half of he_ct_pt_mac(HE_RESCALE) on its own (he_test.h): the accumulators as the fused call leaves them for
@@ -763,7 +823,7 @@ int he_test_mac_for_rescale(he_ctx* ctx, const he_plan* plan, uint32_t limbs, co
     if (need && (!workspace || workspace_bytes < need)) return HE_ERR_WORKSPACE;
     if ((rc = check_mac_launch(ctx, plan, limbs, pt_kind)) != HE_OK) return rc;
     if ((rc = need_device(ctx)) != HE_OK) return rc;
-    return launch_mac(ctx, plan, limbs, ct_in, pt, pt_kind, bias, acc_out, (u64*)workspace, MAC_FOR_RESCALE, (hipStream_t)stream);
+    return launch_mac(ctx, plan, limbs, ct_in, pt, pt_kind, bias, acc_out, (u64*)workspace, need, MAC_FOR_RESCALE, (hipStream_t)stream);
 }
 
 int he_ct_pt_mac_static(he_ctx* ctx, const he_plan* plan, uint32_t limbs, const uint64_t* ct_in, const uint64_t* pt,
@@ -772,11 +832,18 @@ int he_ct_pt_mac_static(he_ctx* ctx, const he_plan* plan, uint32_t limbs, const 
     size_t need = 0;
     int rc = he_plan_workspace_bytes(plan, limbs, pt_kind, flags, &need);
     if (rc != HE_OK) return rc;
-    if (need > HE_STATIC_SCRATCH_BYTES) return HE_ERR_WORKSPACE;  // the fixed array is all there is
+    // Where the tables of gathered weights do not fit next to the accumulators, they are worked off in slices.
+    size_t table_bytes = 0;
+    if (need > HE_STATIC_SCRATCH_BYTES) {
+        if (pt_kind != HE_PT_SCALAR) return HE_ERR_WORKSPACE;  // the fixed array is all there is
+        const size_t rest = need - align256(scalar_table_bytes(plan, limbs));
+        if (rest > HE_STATIC_SCRATCH_BYTES) return HE_ERR_WORKSPACE;
+        table_bytes = HE_STATIC_SCRATCH_BYTES + STATIC_TABLE_BYTES - rest;
+    }
     if (ctx->device < 0 || !ctx->static_scratch) return HE_ERR_DEVICE;
     // the same path as he_ct_pt_mac (whose host code allocates nothing), on this GPU's fixed array
-    return he_ct_pt_mac(ctx, plan, limbs, ct_in, pt, pt_kind, bias, ct_out, flags, ctx->static_scratch, HE_STATIC_SCRATCH_BYTES,
-                        stream);
+    return ct_pt_mac_entry(ctx, plan, limbs, ct_in, pt, pt_kind, bias, ct_out, flags, ctx->static_scratch,
+                           HE_STATIC_SCRATCH_BYTES + STATIC_TABLE_BYTES, table_bytes, stream);
 }
 
 int he_ct_pt_add(he_ctx* ctx, uint32_t limbs, uint64_t* ct, uint32_t n, const uint64_t* pt, int pt_kind,
@@ -944,7 +1011,7 @@ int he_ct_pt_mac32(he_ctx* ctx, const he_plan* plan, uint32_t limbs, const uint3
     if (flags & HE_RESCALE) {
         // the workspace is sized for the 64-bit form: the weight table first, the accumulators after it
         char* ws = (char*)workspace;
-        if (pt_kind == HE_PT_SCALAR) ws += align256((size_t)plan->wtab_elems * limbs * sizeof(u64));
+        if (pt_kind == HE_PT_SCALAR) ws += align256(scalar_table_bytes(plan, limbs));
         u32* acc = (u32*)ws;
         if ((rc = launch_mac32(ctx, plan, limbs, ct_in, pt, pt_kind, bias, acc, workspace, 0, s)) != HE_OK) return rc;
         return launch_rescale32(ctx, limbs, acc, ct_out, plan->n_out, s);

@@ -322,6 +322,76 @@ HE_HD void acc_restart(MacAcc& a, const LimbConst& c) {  // reduce in place and 
 }
 
 // ---------------------------------------------------------------------------------------------
+// MAC sums on the int8 matrix cores (scalar plaintexts).  A residue x is cut into its eight balanced digits
+// base 256, x = sum_j d_j * 256^j with d_j in [-128, 127], and a plaintext w into the digits e_jk of the eight
+// residues w * 256^j mod q (centred), so that
+//   x * w = sum_j d_j * (w * 256^j mod q) = sum_k 256^k * sum_j d_j * e_jk   (mod q):
+// a contraction of length 8 per term with eight int8 results S_k per output.  No digit of x has to be moved: the
+// eight bytes of a residue are eight consecutive elements of the operand as they lie in memory.
+// |S_k| grows by at most 8 * 128 * 128 = 2^17 per term, so 4080 terms stay below 2^29 (longer sums are taken in parts).
+//
+// The eight sums of an output are kept as R_0..R_7: with b the bit length of q and the cut kappa = floor((b - 32) / 8)
+// + 1 (0 for b < 32), digit k goes to R_k for k < kappa and to R_(4 + k - kappa) above: the centred residues have
+// floor(b / 8) + 1 digits, of which d <= 4 lie above the cut (d = 4 whenever kappa > 0); the other R stay zero.  So
+//   sum = lo + hi * 256^kappa,   lo = R_0 + R_1*2^8 + R_2*2^16 + R_3*2^24,   hi = R_4 + R_5*2^8 + R_6*2^16 + R_7*2^24
+// with |lo| < 2^(8 kappa + 22) and |hi| < 2^(8 d + 22).  Both are made positive by adding those powers, and what that
+// adds is taken back by a constant below q that lo's starting value carries.  Then lo < 2^(8 kappa + 23) <= q, and
+// hi < 2^(8 d + 23) is reduced by a one-word Barrett step: with y = floor(hi / 2^(8 d - 9)) < 2^32 and
+// M = floor(2^(s + 8 kappa + 8 d - 9) / q), s = 40 + b - 8 kappa - 8 d >= 32, M < 2^32, the quotient estimate
+// floor(y * M / 2^s) < 2^32 is short of hi * 256^kappa / q by less than 1 (what y drops) + 1 (what M drops) + 1, so the
+// remainder is below 3q, and the sum with lo, the constant and a bias residue below 6q.  (For q >= 2^60 the first
+// three bounds are 2^-4 q and smaller: below 3.2q, which fits 64 bits up to 2^62.)
+struct DigitConst {
+    u64 q;
+    u64 pow8_shoup;        // Shoup companion of 256
+    u64 start;             // offset of lo, plus what takes both offsets back
+    u64 hi_offset;
+    u64 top;               // first multiple of q for the conditional subtractions: 4q, or 2q for q >= 2^61
+    u32 mult;              // M
+    u32 mult_shift;        // s - 32
+    u32 hi_shift;          // 8 d - 9
+    u32 kappa8;            // 8 kappa
+    u32 lazy;              // 1: the rescale kernel takes the unreduced sum (LimbConst::mac_lazy)
+    int32_t b8, b16, b24;  // 2^8, 2^16, 2^24, as data: multiplied by a literal they become shifts and additions, four
+                           // instructions instead of one multiply-add
+};
+constexpr u32 DIGIT_MAX_TERMS = 4080;
+#define HE_DIGIT_BIAS 0x8080808080808080ull
+
+// the balanced digits of x < 2^62 (or of a centred residue, as a two's complement word), one per byte
+HE_HD u64 balanced_digits(u64 x) { return (x + HE_DIGIT_BIAS) ^ HE_DIGIT_BIAS; }
+
+// lo or hi of an output's eight sums, plus `start`: four signed 32x32+64-bit multiply-adds
+HE_HD u64 digit_sum4(int32_t r0, int32_t r1, int32_t r2, int32_t r3, u64 start, const DigitConst& c) {
+    int64_t v = (int64_t)start + (int64_t)r0;
+    v = (int64_t)r1 * c.b8 + v;
+    v = (int64_t)r2 * c.b16 + v;
+    return (u64)((int64_t)r3 * c.b24 + v);
+}
+
+// Congruent to the sum plus the bias residue and below 6q; start: DigitConst::start + bias.
+HE_HD u64 digit_reduce_lazy(const int32_t (&r)[8], u64 start, const DigitConst& c) {
+    const u64 hi = digit_sum4(r[4], r[5], r[6], r[7], c.hi_offset, c);
+    const u64 lo = digit_sum4(r[0], r[1], r[2], r[3], start, c);
+    const u32 est = mul_hi32((u32)(hi >> c.hi_shift), c.mult) >> c.mult_shift;
+    const u64 nq = 0 - c.q;
+    const u64 low = mad_wide(est, (u32)nq, (hi << c.kappa8) + lo);
+    u32 high = (u32)(low >> 32) + est * (u32)(nq >> 32);
+#if defined(__HIP_DEVICE_COMPILE__)
+    asm("" : "+v"(high));
+#endif
+    return ((u64)high << 32) | (u32)low;
+}
+
+// the canonical residue
+HE_HD u64 digit_reduce(const int32_t (&r)[8], u64 start, const DigitConst& c) {
+    u64 v = digit_reduce_lazy(r, start, c);
+    v = sub_if_ge(v, 0 - c.top);
+    v = sub_if_ge(v, 0 - 2 * c.q);
+    return sub_if_ge(v, 0 - c.q);
+}
+
+// ---------------------------------------------------------------------------------------------
 // 32-bit moduli (below 2^30), the primitives of the packed path.
 
 // Alg. 6 (BarrettReduction64): z mod q for a 64-bit z, ratio = floor(2^64 / q).  The estimate

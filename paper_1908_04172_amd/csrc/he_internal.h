@@ -19,6 +19,11 @@ struct LimbTable {
     LimbConst c[HE_MAX_LIMBS];
 };
 
+// Per-limb constants of the MAC on the matrix cores (he_mac_digits.hip), handed to its kernels by value.
+struct DigitTable {
+    DigitConst c[HE_MAX_LIMBS];
+};
+
 // Constants for dropping limb j while keeping limb i < j (Eq. (2) in RNS form).
 struct DropConst {
     u64 p_inv, p_inv_shoup;  // q_j^-1 mod q_i and its Shoup companion
@@ -61,6 +66,7 @@ struct he_ctx {
     u32 log2N, N, L;
     u64 q[HE_MAX_LIMBS], psi[HE_MAX_LIMBS];
     LimbTable limbs;
+    DigitTable digits;
     DropConst drop[HE_MAX_LIMBS][HE_MAX_LIMBS];  // [dropped j][kept i]
     // device tables
     u64* tw_fwd;      // [L][N][2]: (psi^brv(k), Shoup companion), k in [0, N)
@@ -86,22 +92,46 @@ struct Tile {
     u32 n_terms; // terms per output of the group
 };
 
+// Groups of scalar plaintexts are sorted into classes by their output count: 1 (streaming kernel), 2..4, 5..8 and 9..16
+// (matrix cores, in tiles of four outputs).
+constexpr u32 SCALAR_CLASSES = 4;
+__host__ __device__ inline u32 output_tiles(u32 count) { return count <= 4 ? 1 : count <= 8 ? 2 : 4; }
+
+// What the matrix-core kernel needs of a group, read with one scalar load.
+struct DigitTile {
+    u32 out0, count, n_terms;
+    u32 list;        // where its term list starts in he_plan::lists_dev, in chunks of 16 terms
+    u64 words;       // where its table starts, in 64-bit words from the limb's part
+    u32 same_until;  // the first tile behind it (of its class) that uses another table
+    u32 pad;
+};
+constexpr u32 LIST_CHUNK = 16;  // terms per chunk of a list (and of a table's padding)
+
 struct he_plan {
     he_ctx* ctx;
     int device;            // the context's device, kept so that the plan can be destroyed after its context
     u32 n_in, n_out, n_pt, n_terms;
     std::vector<u32> off;  // host copy, for argument checks
-    // tiles sorted by class; a class-k tile is run by the kernel instance with capacity cap[k]
-    u32 class_begin_s[4];  // scalar plaintexts: capacities 1, 4, 16 outputs per thread
+    // tiles sorted by class
+    u32 class_begin_s[SCALAR_CLASSES + 1];
     u32 class_begin_p[4];  // polynomial plaintexts: capacities 1, 2, 4 outputs per thread
-    u32 min_terms_s[3];    // fewest terms of any scalar tile of the class (0 for an empty class)
-    u32 max_terms_s[3];    // most terms of any scalar tile of the class
-    u32 max_count_s[3];    // most outputs of any scalar tile of the class
+    u32 min_terms_s[SCALAR_CLASSES];  // fewest terms of any scalar tile of the class (0 for an empty class)
+    u32 max_terms;         // most terms of any tile
     Tile* tiles_s_dev;
     Tile* tiles_p_dev;
-    u64* wbase_s_dev;      // per scalar tile: start of its weights in the gathered table, per limb
-    u32* wowner_s_dev;     // per scalar tile: 1 if it fills the table at wbase (tiles with equal plaintexts share one)
-    u64 wtab_elems;        // residues per limb in the gathered weight table
+    // Tables of gathered weights (scalar plaintexts): tiles with equal plaintexts share one.  Within a class the tiles
+    // are sorted by table, so that a range of tiles needs a range of tables.
+    u64* wbase_s_dev;      // per scalar tile: start of its table, in 64-bit words from the limb's part
+    DigitTile* digit_tiles_dev;  // per scalar tile
+    // Term lists of the tiles with several outputs, in chunks of 16 (the last one padded with the last term's
+    // ciphertext), each in the order [half][block of 4 terms][2]: what the two halves of a wavefront read
+    u32* lists_dev;
+    u32* owners_dev;       // per table: the first tile that uses it, which describes how to fill it
+    std::vector<Tile> tiles_s;
+    std::vector<u64> wbase_s;
+    std::vector<u32> table_s;     // per scalar tile: its table
+    std::vector<u64> table_end;   // per table: where it ends, in words
+    u64 wtab_elems;        // words per limb of all tables
     u32 n_tiles_s, n_tiles_p;
     u32* off_dev;
     u32* term_ct_dev;
@@ -147,8 +177,24 @@ enum : u32 {
                           // kept limbs of scalar-plaintext sums may be left unreduced (LimbConst::mac_lazy)
 };
 int check_mac_launch(he_ctx* ctx, const he_plan* plan, u32 limbs, int pt_kind);
+// wtab: room for `wtab_bytes` of gathered weights; less than scalar_table_bytes() is worked off in slices, down to
+// min_scalar_table_bytes()
 int launch_mac(he_ctx* ctx, const he_plan* plan, u32 limbs, const u64* ct_in, const u64* pt, int pt_kind,
-               const u64* bias, u64* out, u64* wtab, u32 accumulate, hipStream_t s);
+               const u64* bias, u64* out, u64* wtab, size_t wtab_bytes, u32 accumulate, hipStream_t s);
+inline size_t scalar_table_bytes(const he_plan* plan, u32 limbs) { return (size_t)plan->wtab_elems * limbs * sizeof(u64); }
+// tables are padded to 16 terms: 128 words per four terms and four outputs
+inline size_t min_scalar_table_bytes(u32 limbs) { return (size_t)4 * 4 * 128 * limbs * sizeof(u64); }
+
+// One pass of the scalar MAC over ranges of a plan's groups (all of them, or a slice whose tables fit the room given).
+struct ScalarSlice {
+    u32 begin[SCALAR_CLASSES], end[SCALAR_CLASSES];  // tiles of each class
+    u32 table_begin, table_end;                      // the tables they use
+    u64 tab_skip, tab_words;                         // where these start in the plan's numbering; words per limb
+    u32 t_begin, t_end;                              // range of every group's terms
+};
+int launch_mac_digits(he_ctx* ctx, const he_plan* plan, const ScalarSlice& sl, u32 limbs, const u64* ct_in, const u64* pt, const u64* bias,
+                      u64* out, u64* wtab, u32 mode, hipStream_t s);
+u64 mac_digits_blocks(const he_ctx* ctx, const he_plan* plan, u32 limbs);
 int launch_ntt(he_ctx* ctx, u32 limbs, u64* data, u32 n_polys, bool inverse, hipStream_t s, const u64* src = nullptr);
 int launch_rescale(he_ctx* ctx, u32 limbs, const u64* in, u64* out, u32 n, hipStream_t s);
 int launch_rate(he_ctx* ctx, int kind, u32 limb, u32 iters, double* ops_per_s);

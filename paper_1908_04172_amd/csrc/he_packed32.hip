@@ -65,19 +65,26 @@ constexpr u32 GATHER32_BLOCKS = 16;  // workgroups that share the gathering of o
 constexpr u32 MAC32_BLOCK = 4;  // terms per unrolled block; an input is requested a block before its use
 __host__ __device__ inline u32 padded_terms32(u32 n_terms) { return (n_terms + MAC32_BLOCK - 1) / MAC32_BLOCK * MAC32_BLOCK; }
 
-// wtab32[limb*wtab_elems + wbase + t*G + g] = pt[term_pt[off[out0+g] + t]][limb] for g < count and t < n_terms, else 0,
+// A group's table starts at its place among the 64-bit path's tables for single outputs; those of larger groups take an
+// eighth of the 64-bit form's words each and are packed accordingly behind `singles`, where the first of them starts (at
+// the 64-bit distances, often a power of two, they would collide in the scalar cache).
+template <int G>
+__device__ __forceinline__ u64 table32(u64 wbase, u64 singles) { return G == 1 ? wbase : singles + (wbase - singles) / 8; }
+
+// wtab32[limb*wtab_elems + table32(wbase) + t*G + g] = pt[term_pt[off[out0+g] + t]][limb] for g < count and t < n_terms, else 0,
 // for t up to n_terms rounded up to whole blocks: the scalar plaintexts of a group laid out in the order the MAC
 // loop reads them (the plan's table offsets are shared with the 64-bit path, whose entries are larger; groups with
 // the same plaintext indices share a table).
 template <int G>
-__global__ void __launch_bounds__(256) gather_weights32_kernel(const Tile* tiles, const u64* wbase, const u32* wowner, u32 n_tiles,
+__global__ void __launch_bounds__(256) gather_weights32_kernel(const Tile* tiles, const u64* wbase, const u32* owners, u32 n_tables,
                                                                u32 limbs, const u32* off, const u32* term_pt, const u64* pt,
-                                                               u32* wtab, u64 wtab_elems) {
-    const u32 tile_i = blockIdx.x / GATHER32_BLOCKS, sub = blockIdx.x % GATHER32_BLOCKS;
-    if (tile_i >= n_tiles || !wowner[tile_i]) return;
+                                                               u32* wtab, u64 wtab_elems, u64 singles) {
+    const u32 table = blockIdx.x / GATHER32_BLOCKS, sub = blockIdx.x % GATHER32_BLOCKS;
+    if (table >= n_tables) return;
+    const u32 tile_i = owners[table];
     const Tile tile = tiles[tile_i];
     const u64 per_limb = (u64)padded_terms32(tile.n_terms) * G;
-    u32* dst = wtab + wbase[tile_i];
+    u32* dst = wtab + table32<G>(wbase[tile_i], singles);
     for (u64 i = (u64)sub * blockDim.x + threadIdx.x; i < per_limb * limbs; i += (u64)GATHER32_BLOCKS * blockDim.x) {
         const u32 limb = (u32)(i / per_limb);
         const u64 rem = i % per_limb;
@@ -94,7 +101,7 @@ __global__ void __launch_bounds__(256) gather_weights32_kernel(const Tile* tiles
 template <int G>
 __global__ void __launch_bounds__(MAC32_THREADS)
 mac_scalar32_kernel(Limb32Table lt, u32 limbs, u32 N, const Tile* tiles, u32 n_tiles, const u64* wbase, const u32* term_ct,
-                    const u32* wtab, u64 wtab_elems, const u32* ct_in, const u64* bias, u32* out, u32 accumulate) {
+                    const u32* wtab, u64 wtab_elems, u64 singles, const u32* ct_in, const u64* bias, u32* out, u32 accumulate) {
     const u32 slices = N / MAC32_SLICE;
     u32 b = blockIdx.x;
     const u32 slice = b % slices; b /= slices;
@@ -105,7 +112,7 @@ mac_scalar32_kernel(Limb32Table lt, u32 limbs, u32 N, const Tile* tiles, u32 n_t
     const u32 K = uniform_load(&tiles[tile_i].n_terms), count = uniform_load(&tiles[tile_i].count);
     const u32 out0 = uniform_load(&tiles[tile_i].out0);
     const u32* tc = term_ct + uniform_load(&tiles[tile_i].term0);
-    const u32* w = wtab + (u64)limb * wtab_elems + uniform_load(wbase + tile_i);
+    const u32* w = wtab + (u64)limb * wtab_elems + table32<G>(uniform_load(wbase + tile_i), singles);
     const u32 pair = slice * MAC32_THREADS + threadIdx.x;
     const size_t ct_pairs = (size_t)limbs * N;  // uint2 elements per ciphertext (2 components x limbs x N / 2)
     const uint2* x_base = reinterpret_cast<const uint2*>(ct_in) + ((size_t)comp * limbs + limb) * (N / 2) + pair;
@@ -507,13 +514,15 @@ static int launch_scalar32_class(he_ctx* ctx, const he_plan* plan, int cls, u32 
     if (count == 0) return HE_OK;
     const Tile* tiles = plan->tiles_s_dev + begin;
     const u64* wbase = plan->wbase_s_dev + begin;
-    hipLaunchKernelGGL((gather_weights32_kernel<G>), dim3(count * GATHER32_BLOCKS), dim3(256), 0, s, tiles, wbase, plan->wowner_s_dev + begin, count, limbs,
-                       plan->off_dev, plan->term_pt_dev, pt, wtab, plan->wtab_elems);
+    const u64 singles = plan->class_begin_s[1] ? plan->table_end[plan->table_s[plan->class_begin_s[1] - 1]] : 0;
+    const u32 table = plan->table_s[begin], n_tables = plan->table_s[begin + count - 1] + 1 - table;
+    hipLaunchKernelGGL((gather_weights32_kernel<G>), dim3(n_tables * GATHER32_BLOCKS), dim3(256), 0, s, plan->tiles_s_dev, plan->wbase_s_dev,
+                       plan->owners_dev + table, n_tables, limbs, plan->off_dev, plan->term_pt_dev, pt, wtab, plan->wtab_elems, singles);
     HE_HIP(hipGetLastError());
     const u64 blocks = (u64)count * limbs * 2 * (ctx->N / MAC32_SLICE);
     if (blocks > 0x7FFFFFFFull) return HE_ERR_RANGE;
     hipLaunchKernelGGL((mac_scalar32_kernel<G>), dim3((u32)blocks), dim3(MAC32_THREADS), 0, s, ctx->limbs32, limbs, ctx->N, tiles, count,
-                       wbase, plan->term_ct_dev, wtab, plan->wtab_elems, ct_in, bias, out, accumulate);
+                       wbase, plan->term_ct_dev, wtab, plan->wtab_elems, singles, ct_in, bias, out, accumulate);
     HE_HIP(hipGetLastError());
     return HE_OK;
 }
@@ -533,7 +542,7 @@ static int launch_poly32_class(he_ctx* ctx, const he_plan* plan, int cls, u32 li
 
 // the grid sizes launch_mac32 would use, checked without launching anything
 int check_mac32_launch(he_ctx* ctx, const he_plan* plan, u32 limbs, int pt_kind) {
-    for (int cls = 0; cls < 3; cls++) {
+    for (u32 cls = 0; cls < (pt_kind == HE_PT_SCALAR ? SCALAR_CLASSES : 3u); cls++) {
         const u64 count = pt_kind == HE_PT_SCALAR ? plan->class_begin_s[cls + 1] - plan->class_begin_s[cls]
                                                   : plan->class_begin_p[cls + 1] - plan->class_begin_p[cls];
         if (count * limbs * (pt_kind == HE_PT_SCALAR ? 2 : 1) * (ctx->N / MAC32_SLICE) > 0x7FFFFFFFull) return HE_ERR_RANGE;
@@ -550,7 +559,8 @@ int launch_mac32(he_ctx* ctx, const he_plan* plan, u32 limbs, const u32* ct_in, 
         u32* wtab = static_cast<u32*>(workspace);
         if ((rc = launch_scalar32_class<1>(ctx, plan, 0, limbs, ct_in, p, bias, out, wtab, accumulate, s)) != HE_OK) return rc;
         if ((rc = launch_scalar32_class<4>(ctx, plan, 1, limbs, ct_in, p, bias, out, wtab, accumulate, s)) != HE_OK) return rc;
-        if ((rc = launch_scalar32_class<16>(ctx, plan, 2, limbs, ct_in, p, bias, out, wtab, accumulate, s)) != HE_OK) return rc;
+        if ((rc = launch_scalar32_class<8>(ctx, plan, 2, limbs, ct_in, p, bias, out, wtab, accumulate, s)) != HE_OK) return rc;
+        if ((rc = launch_scalar32_class<16>(ctx, plan, 3, limbs, ct_in, p, bias, out, wtab, accumulate, s)) != HE_OK) return rc;
     } else {
         const u32* p = static_cast<const u32*>(pt);
         if ((rc = launch_poly32_class<1>(ctx, plan, 0, limbs, ct_in, p, bias, out, accumulate, s)) != HE_OK) return rc;

@@ -1,0 +1,116 @@
+"""The scalar MAC on the matrix cores at the sizes where it can go wrong: group sizes around its tiles of four outputs and
+its classes, term counts around its chunks of 16, around what it keeps in the LDS (64) and beyond what its 32-bit sums take
+(4080), moduli of every width class, extreme operands; and tables that are worked off in slices.  Exact residues."""
+import numpy as np
+import pytest
+
+import oracle
+from paper_1908_04172_amd import workloads as wl
+
+torch = pytest.importorskip("torch")
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def he():
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_1908_04172_amd import he as he_mod
+    he_mod.lib()
+    return he_mod
+
+
+def dev(a):
+    return torch.from_numpy(np.ascontiguousarray(a).view(np.int64)).cuda()
+
+
+def host(t):
+    return t.cpu().numpy().view(np.uint64)
+
+
+def groups_plan(groups, n_in, n_pt, seed):
+    """One group of `count` outputs over `terms` random ciphertexts per (count, terms)."""
+    rng = np.random.default_rng(seed)
+    off, tc, tp = [0], [], []
+    for count, terms in groups:
+        cts = rng.integers(0, n_in, terms)
+        for _ in range(count):
+            tc.append(cts)
+            tp.append(rng.integers(0, n_pt, terms))
+            off.append(off[-1] + terms)
+    cat = lambda xs: np.concatenate(xs).astype(np.uint32)
+    return wl.Plan(n_in, len(off) - 1, n_pt, np.asarray(off, np.uint32), cat(tc), cat(tp))
+
+
+def operands(plan, q, N, seed, extreme):
+    ct = wl.uniform_residues((plan.n_in, 2), q, N, seed)
+    w = wl.uniform_residues((plan.n_pt,), q, 1, seed + 1)[..., 0]
+    b = wl.uniform_residues((plan.n_out,), q, 1, seed + 2)[..., 0]
+    if extreme:  # q - 1, and residues whose digits are all -128 or next to it, against weights q - 1 and around q / 2
+        for i, qi in enumerate(q):
+            digits = [0x8080808080808080 % qi, 0x7F7F7F7F7F7F7F7F % qi, qi - 1, 0]
+            for c in range(plan.n_in):
+                ct[c, :, i, :] = digits[c % 4] if c % 4 < 3 else ct[c, :, i, :]
+            w[0::3, i], w[1::3, i] = qi - 1, qi // 2 + 1
+            b[:, i] = qi - 1
+    return ct, w, b
+
+
+def run(he, ctx, plan, ct, w, b, **kw):
+    hp = ctx.plan(plan.n_in, plan.n_out, plan.n_pt, plan.off, plan.term_ct, plan.term_pt)
+    return host(ctx.ct_pt_mac(hp, dev(ct), dev(w), he.PT_SCALAR, bias=None if b is None else dev(b), **kw))
+
+
+@pytest.mark.parametrize("bits", [[20, 24, 30], [31, 32, 33, 39], [40, 41, 47, 48], [49, 50, 55, 56], [57, 60, 61, 62]], ids=str)
+@pytest.mark.parametrize("extreme", [False, True])
+def test_group_sizes_and_term_counts_on_moduli_of_every_width(he, bits, extreme):
+    N = 1 << 10
+    q = wl.modulus_chain(bits, N)
+    ctx = he.Context(10, q)
+    groups = [(c, t) for c in (2, 4, 5, 8, 9, 16) for t in (1, 16, 17)] + [(3, 15), (7, 64), (16, 65), (2, 129), (16, 128)]
+    plan = groups_plan(groups, 40, 50, sum(bits))
+    ct, w, b = operands(plan, q, N, 7 + sum(bits), extreme)
+    want = oracle.mac(ct, q, plan.off, plan.term_ct, plan.term_pt, w, oracle.PT_SCALAR, b)
+    assert np.array_equal(run(he, ctx, plan, ct, w, b), want)
+    layer, _ = oracle.layer(ct, q, ctx.psi, plan.off, plan.term_ct, plan.term_pt, w, oracle.PT_SCALAR, b)
+    assert np.array_equal(run(he, ctx, plan, ct, w, b, flags=he.RESCALE), layer)
+
+
+@pytest.mark.parametrize("terms", [4079, 4080, 4081, 8161])
+def test_sums_beyond_the_range_of_the_32_bit_accumulators(he, terms):
+    N = 1 << 10
+    q = wl.modulus_chain([62, 50, 30], N)
+    ctx = he.Context(10, q)
+    plan = groups_plan([(16, terms), (5, 3), (2, terms), (1, terms)], 4, 6, terms)
+    ct, w, b = operands(plan, q, N, terms, True)
+    want = oracle.mac(ct, q, plan.off, plan.term_ct, plan.term_pt, w, oracle.PT_SCALAR, b)
+    assert np.array_equal(run(he, ctx, plan, ct, w, b), want)
+    layer, _ = oracle.layer(ct, q, ctx.psi, plan.off, plan.term_ct, plan.term_pt, w, oracle.PT_SCALAR, b)
+    assert np.array_equal(run(he, ctx, plan, ct, w, b, flags=he.RESCALE), layer)
+
+
+@pytest.mark.parametrize("K,M,rescale", [(9000, 16, True), (600, 528, False)])
+def test_tables_larger_than_the_fixed_scratch_are_worked_off_in_slices(he, K, M, rescale):
+    """One table that does not fit (passes over its terms), and many (ranges of groups)."""
+    N = 1 << 10
+    q = wl.modulus_chain([60, 50, 50, 40], N)
+    ctx = he.Context(10, q)
+    n_in = 5
+    tc = np.random.default_rng(K).integers(0, n_in, K)
+    rng = np.random.default_rng(M)
+    plan = wl.Plan(n_in, M, 64, (np.arange(M + 1) * K).astype(np.uint32), np.tile(tc, M).astype(np.uint32),
+                   rng.integers(0, 64, K * M).astype(np.uint32))
+    hp = ctx.plan(plan.n_in, plan.n_out, plan.n_pt, plan.off, plan.term_ct, plan.term_pt)
+    flags = he.RESCALE if rescale else 0
+    assert hp.workspace_bytes(4, he.PT_SCALAR, flags) > he.STATIC_SCRATCH_BYTES
+    ct, w, b = operands(plan, q, N, K, False)
+    out = torch.full((M, 2, 4 - rescale, N), -1, dtype=torch.int64, device="cuda")
+    ctx.ct_pt_mac_static(hp, dev(ct), dev(w), he.PT_SCALAR, out, bias=dev(b), flags=flags)
+    assert torch.equal(out, ctx.ct_pt_mac(hp, dev(ct), dev(w), he.PT_SCALAR, bias=dev(b), flags=flags))
+    some = [0, 1, M // 2, M - 1]
+    sub = plan.subset(some)
+    if rescale:
+        want, _ = oracle.layer(ct, q, ctx.psi, sub.off, sub.term_ct, sub.term_pt, w, oracle.PT_SCALAR, b[some])
+    else:
+        want = oracle.mac(ct, q, sub.off, sub.term_ct, sub.term_pt, w, oracle.PT_SCALAR, b[some])
+    assert np.array_equal(host(out[some]), want)
