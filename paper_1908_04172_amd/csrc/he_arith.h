@@ -391,6 +391,20 @@ HE_HD u64 digit_reduce(const int32_t (&r)[8], u64 start, const DigitConst& c) {
     return sub_if_ge(v, 0 - c.q);
 }
 
+// The same for a modulus below 2^30 in packed 32-bit storage: four digits, four sums, kappa = 0, so that lo is zero and the
+// four sums are hi's.  |S_k| grows by at most 2^16 per term.  start: (DigitConst::start + bias) mod q; the sum is below
+// 3q + q < 2^32, of which the low words suffice.
+HE_HD u32 balanced_digits32(u32 x) { return (x + 0x80808080u) ^ 0x80808080u; }
+HE_HD u32 digit_reduce32(const int32_t (&r)[4], u32 start, const DigitConst& c) {
+    const u64 hi = digit_sum4(r[0], r[1], r[2], r[3], c.hi_offset, c);
+    const u32 q = (u32)c.q, est = mul_hi32((u32)(hi >> c.hi_shift), c.mult) >> c.mult_shift;
+    u32 v = (u32)hi - est * q + start;
+    const u32 t = v - 2 * q;  // wraps to a larger number exactly when v < 2q
+    v = t < v ? t : v;
+    const u32 u = v - q;
+    return u < v ? u : v;
+}
+
 // ---------------------------------------------------------------------------------------------
 // 32-bit moduli (below 2^30), the primitives of the packed path.
 

@@ -95,7 +95,7 @@ struct Tile {
 // Groups of scalar plaintexts are sorted into classes by their output count: 1 (streaming kernel), 2..4, 5..8 and 9..16
 // (matrix cores, in tiles of four outputs).
 constexpr u32 SCALAR_CLASSES = 4;
-__host__ __device__ inline u32 output_tiles(u32 count) { return count <= 4 ? 1 : count <= 8 ? 2 : 4; }
+__host__ __device__ constexpr u32 output_tiles(u32 count) { return count <= 4 ? 1 : count <= 8 ? 2 : 4; }
 
 // What the matrix-core kernel needs of a group, read with one scalar load.
 struct DigitTile {
@@ -194,6 +194,8 @@ struct ScalarSlice {
 };
 int launch_mac_digits(he_ctx* ctx, const he_plan* plan, const ScalarSlice& sl, u32 limbs, const u64* ct_in, const u64* pt, const u64* bias,
                       u64* out, u64* wtab, u32 mode, hipStream_t s);
+int launch_mac_digits32(he_ctx* ctx, const he_plan* plan, const ScalarSlice& sl, u32 limbs, const u32* ct_in, const u64* pt, const u64* bias,
+                        u32* out, u64* wtab, u32 mode, hipStream_t s);
 u64 mac_digits_blocks(const he_ctx* ctx, const he_plan* plan, u32 limbs);
 int launch_ntt(he_ctx* ctx, u32 limbs, u64* data, u32 n_polys, bool inverse, hipStream_t s, const u64* src = nullptr);
 int launch_rescale(he_ctx* ctx, u32 limbs, const u64* in, u64* out, u32 n, hipStream_t s);

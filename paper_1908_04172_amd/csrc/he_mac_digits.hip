@@ -8,6 +8,8 @@
 //    one slot, as they lie in memory (their digits: one addition and an exclusive or per residue);
 //  - of a result tile a lane holds 16 rows of one column; the table's rows are ordered so that those are the eight
 //    sums of two outputs, and the final reduction of an output needs nothing from another lane.
+// Residues in packed 32-bit storage (moduli below 2^30) have four digits and four sums: an instruction takes eight terms
+// times eight outputs, the rest is the same.
 //
 // A term costs 64 int8 multiply-adds (2048 terms per compute unit and 32 cycles) instead of three or four 32-bit ones on
 // the vector ALU, which only splits digits, forms addresses and reduces, about 25 instructions per output at the end.
@@ -15,7 +17,10 @@
 // them); a convolution window's 27 terms, the memory itself.  Measured against the same loop on 32-bit multiply-adds
 // (the layer's MAC launch alone): dense 845 -> 100 at N = 2^13, L = 4: 1150 -> 355 us; dense 96 -> 24 at 2^15, L = 8:
 // 358 -> 188 us; convolution 32x32x3, 3x3x16, at 2^14, L = 8: 5940 -> 3500 us (17 GB: 4.9 TB/s); 28x28, 5x5x5, at 2^13,
-// L = 4: 435 -> 296 us; dense 64 -> 16 at 2^12, L = 2: 37 -> 15 us.
+// L = 4: 435 -> 296 us; dense 64 -> 16 at 2^12, L = 2: 37 -> 15 us.  Packed, dense 1024 -> 256 at 2^12, L = 2: 352 -> 83 us.
+// (On random digits the chip sustains 2.8 to 3.2 int8 POP/s, on constant ones 4.3: a long sum's arithmetic is priced with
+// the former, 235 us of the 330 that 845 -> 96 takes; what else it waits for is the inputs, 75 us, and the meetings of
+// the wavefronts around the table's stages, 35 us.)
 // Tried: conditional loads at the ends of groups (the compiler's waits then drain the pipeline: 6200 us for the 2^14
 // convolution); registers above the limit for two wavefronts per SIMD, whose reloads drain it as well (4500 us).
 #include <algorithm>
@@ -30,18 +35,27 @@ typedef u32 u32x4 __attribute__((ext_vector_type(4)));
 typedef int v16i __attribute__((ext_vector_type(16)));
 
 constexpr u32 THREADS = 256, WAVES = THREADS / 64;
-constexpr u32 BLOCK_TERMS = 4;                              // terms of one matrix instruction
-constexpr u32 CHUNK_BLOCKS = 4;                             // blocks that are in flight together (a chunk)
+constexpr u32 CHUNK_TERMS = LIST_CHUNK;                     // terms that are in flight together (a chunk)
 constexpr u32 RESIDENT_CHUNKS = 4;                          // tables of up to so many chunks stay in the LDS as a whole
-constexpr u32 CHUNK_TERMS = BLOCK_TERMS * CHUNK_BLOCKS;
-static_assert(CHUNK_TERMS == LIST_CHUNK, "the plan's lists and tables are padded to chunks");
-constexpr u32 TILE_WORDS = 128;                             // 64-bit words of a table tile: 4 terms x 4 outputs x 64 digits
+constexpr u32 TILE_WORDS = 128;                             // 64-bit words of a table tile, one operand of 64 lanes x 16 bytes
 constexpr u32 GROUPS_PER_WG = 16;                           // groups a workgroup runs through, at most
 constexpr u64 MIN_WORKGROUPS = 2048;                        // ... while the launch keeps at least this many workgroups
 static_assert(DIGIT_MAX_TERMS % CHUNK_TERMS == 0, "the parts of a long sum are whole chunks");
 
-constexpr int CT = 2;                                       // column tiles (of 32 slots) of a wavefront
-constexpr u32 SLOTS = WAVES * 32 * CT;                      // slots of a workgroup
+// What the storage form of a residue sets (V = u64 or u32): its digits D fill sizeof(V) bytes of the contraction, an
+// output has D sums.
+template <typename V>
+struct Form {
+    static constexpr u32 D = sizeof(V);
+    static constexpr u32 BLOCK_TERMS = 32 / D;              // terms of one matrix instruction
+    static constexpr u32 LANE_TERMS = 16 / D;               // ... of which a lane holds so many
+    static constexpr u32 CHUNK_BLOCKS = CHUNK_TERMS / BLOCK_TERMS;
+    static constexpr u32 TILE_OUTPUTS = 32 / D;             // outputs of one result tile
+    static constexpr u32 LANE_OUTPUTS = 16 / D;             // ... of which a lane holds so many
+    static constexpr int CT = 16 / D;                       // column tiles (of 32 slots) of a wavefront: a lane's 16 bytes of a row
+    static constexpr u32 SLOTS = WAVES * 32 * CT;           // slots of a workgroup
+    __host__ __device__ static constexpr u32 tiles(u32 count) { return D == 8 ? output_tiles(count) : count <= 8 ? 1 : 2; }
+};
 
 template <typename T>
 __device__ __forceinline__ T uniform_load(const T* p) {  // read-only, workgroup-uniform data: a scalar load
@@ -53,17 +67,21 @@ __device__ __forceinline__ T uniform_load(const T* p) {  // read-only, workgroup
 __device__ __forceinline__ void lds_barrier() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
 
 // ---------------------------------------------------------------------------------------------
-// The table: for every distinct group of plaintexts and every limb, tiles [block of 4 terms][4 outputs] of 64 lanes x
-// 16 bytes, the matrix instruction's operand as the lanes read it.  Lane (row r, half h) holds row r's elements of terms
-// 2h and 2h + 1.  Row r belongs to output 2*((r >> 2) & 1) + (r >> 4) and its sum R_m, m = (r >> 3 & 1) * 4 + (r & 3).
-// Terms beyond the group's (up to whole chunks) and outputs beyond its count are zeros.  One thread: one (term, output, limb).
+// The table: for every distinct group of plaintexts and every limb, tiles [block of terms][outputs] of 64 lanes x 16 bytes,
+// the matrix instruction's operand as the lanes read it.  Lane (row r, half h) holds row r's elements of half h's terms of
+// the block: positions h * LANE_TERMS .. of the order in which the term lists are stored (he_plan::lists_dev).  Row r
+// belongs to half (r >> 2) & 1 of the tile's outputs and there to sum (r & 3) + 4 * (r >> 3) of the 16 of that half's lanes.
+// Terms beyond the group's (up to whole chunks) and outputs beyond its count are zeros.  One thread: one (term, output,
+// limb).
+template <typename V>
 __global__ void __launch_bounds__(256) gather_digits_kernel(DigitTable dt, const Tile* tiles, const u64* wbase, const u32* owners, u32 limbs,
                                                             const u32* off, const u32* term_pt, const u64* pt, u64* tab, u64 tab_words,
                                                             u64 tab_skip, u32 t_begin, u32 t_end) {
+    using F = Form<V>;
     const u32 tile_i = uniform_load(owners + blockIdx.y);
     const Tile tile = tiles[tile_i];
     const u32 first = min(t_begin, tile.n_terms), K = min(t_end, tile.n_terms) - first;
-    const u32 ot = output_tiles(tile.count), G = 4 * ot;
+    const u32 ot = F::tiles(tile.count), G = F::TILE_OUTPUTS * ot;
     const u32 Kp = (K + CHUNK_TERMS - 1) / CHUNK_TERMS * CHUNK_TERMS;
     const u64 total = (u64)Kp * G * limbs;
     u64* dst = tab + (wbase[tile_i] - tab_skip);
@@ -72,41 +90,46 @@ __global__ void __launch_bounds__(256) gather_digits_kernel(DigitTable dt, const
         const u64 rest = i / limbs;
         const u32 t = (u32)(rest / G), o = (u32)(rest % G);  // (limb fastest, then output: neighbouring plaintexts)
         const DigitConst& c = dt.c[limb];
-        u64 row[8] = {};
+        V row[F::D] = {};
         if (o < tile.count && t < K) {
             u64 v = pt[(size_t)term_pt[off[tile.out0 + o] + first + t] * limbs + limb];
 #pragma unroll
-            for (int j = 0; j < 8; j++) {
+            for (u32 j = 0; j < F::D; j++) {
                 const u64 d = balanced_digits(v > c.q / 2 ? v - c.q : v);
                 const u64 low = c.kappa8 ? d & (~0ull >> (64 - c.kappa8)) : 0, high = d >> c.kappa8;
 #pragma unroll
-                for (int m = 0; m < 4; m++) {
-                    row[m] |= ((low >> (8 * m)) & 255) << (8 * j);
-                    row[4 + m] |= ((high >> (8 * m)) & 255) << (8 * j);
+                for (u32 m = 0; m < 4; m++) {
+                    if constexpr (F::D == 8) row[m] |= ((low >> (8 * m)) & 255) << (8 * j);
+                    row[F::D - 4 + m] |= (V)((high >> (8 * m)) & 255) << (8 * j);
                 }
                 v = shoup_mul(v, 256, c.pow8_shoup, c.q);
             }
         }
-        u64* out = dst + (u64)limb * tab_words + ((u64)(t / BLOCK_TERMS) * ot + o / 4) * TILE_WORDS;
-        const u32 tt = t % BLOCK_TERMS, oo = o % 4;
+        // where the term is in its chunk's list order [half][block of 4][2], and so in the table
+        const u32 half = (t >> 1) & 1, at = ((t >> 2) & 3) * 2 + (t & 1);
+        const u32 block = t / CHUNK_TERMS * F::CHUNK_BLOCKS + at / F::LANE_TERMS;
+        const u32 oo = o % F::TILE_OUTPUTS;
+        V* out = reinterpret_cast<V*>(dst + (u64)limb * tab_words + ((u64)block * ot + o / F::TILE_OUTPUTS) * TILE_WORDS);
 #pragma unroll
-        for (u32 m = 0; m < 8; m++) {
-            const u32 r = ((oo & 1) * 2 + (m >> 2)) * 8 + (oo >> 1) * 4 + (m & 3);
-            out[(r + 32 * (tt >> 1)) * 2 + (tt & 1)] = row[m];
+        for (u32 m = 0; m < F::D; m++) {
+            const u32 k = oo % F::LANE_OUTPUTS * F::D + m;  // which of the lane's 16 sums
+            const u32 r = (k & 3) + 8 * (k >> 2) + 4 * (oo / F::LANE_OUTPUTS);
+            out[(r + 32 * half) * F::LANE_TERMS + at % F::LANE_TERMS] = row[m];
         }
     }
 }
 
 // ---------------------------------------------------------------------------------------------
+template <typename V>
 struct MacArgs {
     const DigitTile* tiles;
     const u32* lists;
     const u64* tab;         // gathered tables
     u64 tab_words;          // words per limb
     u64 tab_skip;           // where the tables in `tab` start in the plan's numbering
-    const u64* ct_in;
+    const V* ct_in;
     const u64* bias;
-    u64* out;
+    V* out;
     u32 limbs, N;
     u32 t_begin, t_end;     // the range of every group's terms to take, multiples of 16 (all of them: 0, 2^32 - 1)
     u32 mode;               // MAC_* bits
@@ -125,12 +148,14 @@ struct Cursor {
     u32 piece;            // the group's table, in 16-byte pieces from the limb's part
 };
 
-__device__ __forceinline__ u32 chunks_of(const MacArgs& a, const DigitTile& t) {
+template <typename V>
+__device__ __forceinline__ u32 chunks_of(const MacArgs<V>& a, const DigitTile& t) {
     const u32 K = min(a.t_end, t.n_terms) - min(a.t_begin, t.n_terms);
     return __builtin_amdgcn_readfirstlane((K + CHUNK_TERMS - 1) / CHUNK_TERMS);
 }
 
-__device__ __forceinline__ void enter_group(Cursor& p, const MacArgs& a, u32 tile) {
+template <typename V>
+__device__ __forceinline__ void enter_group(Cursor& p, const MacArgs<V>& a, u32 tile) {
     const DigitTile t = load_tile(a.tiles + tile);
     const u32 first = min(a.t_begin, t.n_terms);
     // (readfirstlane: the cursor stays in scalar registers)
@@ -142,15 +167,18 @@ __device__ __forceinline__ void enter_group(Cursor& p, const MacArgs& a, u32 til
 }
 
 // The chunk after this one; after the last one of the stream the cursor stays (its loads are repeated, never used).
-__device__ __forceinline__ void step(Cursor& p, const MacArgs& a, u32 tile_end) {
+template <typename V>
+__device__ __forceinline__ void step(Cursor& p, const MacArgs<V>& a, u32 tile_end) {
     if (p.chunk + 1 < p.n_chunks) p.chunk = __builtin_amdgcn_readfirstlane(p.chunk + 1);
     else if (p.tile + 1 < tile_end) enter_group(p, a, p.tile + 1);
 }
 
-// A wavefront's share of a group of outputs: OT x CT result tiles, for slots slot .. slot + 63 of one row, the even
-// ones in column tile 0 and the odd ones in column tile 1.
-template <int OT>
+// A wavefront's share of a group of outputs: OT x CT result tiles.  Column tile k holds slot k of the lanes' CT adjacent
+// slots.
+template <typename V, int OT>
 struct Sums {
+    static constexpr int CT = Form<V>::CT;
+    static constexpr u32 D = Form<V>::D;
     v16i t[OT][CT];
     __device__ __forceinline__ void clear() {
 #pragma unroll
@@ -160,31 +188,35 @@ struct Sums {
 #pragma unroll
                 for (int i = 0; i < 16; i++) t[o][k][i] = 0;
     }
-    // the eight sums of output 4*o + 2*half + i at the even (k = 0) or odd slot
-    __device__ __forceinline__ void get(int32_t (&r)[8], int o, int k, int i) const {
+    // the sums of this lane's output i of tile o at its slot k
+    __device__ __forceinline__ void get(int32_t (&r)[D], int o, int k, int i) const {
 #pragma unroll
-        for (int m = 0; m < 8; m++) r[m] = t[o][k][i * 8 + m];
+        for (u32 m = 0; m < D; m++) r[m] = t[o][k][i * D + m];
     }
 };
 
 // What a workgroup works on: one slice of one (component, limb) row.
+template <typename V>
 struct Slice {
     u32 comp, limb, lane, half;
     u32 ct_stride;       // bytes (below 2^32 for 16 limbs of 2^15 residues)
-    const char* x_base;  // this lane's two slots of ciphertext 0
+    const char* x_base;  // this lane's slots of ciphertext 0
     const v4i* tab;      // the limb's tables
-    u64* dst;            // this lane's two slots of output 0
+    V* dst;              // this lane's slots of output 0
 };
 
 // Final reduction, bias (Alg. 4) and store of one group.  The caller has waited for its loads in flight: a later wait
 // for one of them would wait for these stores as well.
-template <int OT>
-__device__ __forceinline__ void store_group(const Sums<OT>& sums, const MacArgs& a, const Slice& w, const DigitConst& c, u32 out0, u32 count) {
+template <typename V, int OT>
+__device__ __forceinline__ void store_group(const Sums<V, OT>& sums, const MacArgs<V>& a, const Slice<V>& w, const DigitConst& c, u32 out0, u32 count) {
+    using F = Form<V>;
+    constexpr u32 LANE_OUTPUTS = F::LANE_OUTPUTS, TILE_OUTPUTS = F::TILE_OUTPUTS, D = F::D;
+    constexpr int CT = F::CT;
     const size_t out_stride = (size_t)2 * a.limbs * a.N;
     u32 half = w.half;
     asm volatile("" : "+v"(half));  // what follows is derived here, not kept in registers through the loop over terms
-    u64* dst = w.dst + (size_t)out0 * out_stride + half * (2 * out_stride);
-    const bool lazy = (a.mode & MAC_FOR_RESCALE) && w.limb + 1 < a.limbs && c.lazy;
+    V* dst = w.dst + (size_t)out0 * out_stride + half * (LANE_OUTPUTS * out_stride);
+    const bool lazy = D == 8 && (a.mode & MAC_FOR_RESCALE) && w.limb + 1 < a.limbs && c.lazy;
     const bool accumulate = a.mode & MAC_ACCUMULATE;
     // The bias residues come in with scalar loads, those of the next four outputs while four are reduced.  (Without a
     // bias the loads read the group's descriptor and are masked.)
@@ -192,52 +224,61 @@ __device__ __forceinline__ void store_group(const Sums<OT>& sums, const MacArgs&
     const char* bias0 = has_bias ? reinterpret_cast<const char*>(a.bias + (size_t)out0 * a.limbs + w.limb) : reinterpret_cast<const char*>(a.tiles);
     const u32 bias_step = has_bias ? a.limbs * 8 : 0;
     const u64 mask = has_bias ? ~0ull : 0;
-    auto load_bias = [&](u64 (&b)[4], u32 o) {
+    // step s handles outputs s * 2 .. of both halves
+    constexpr int STEPS = OT * LANE_OUTPUTS / 2;
+    auto output_of = [&](int s, int i, u32 h) -> u32 {  // output i (0, 1) of step s in half h
+        return (u32)(s * 2 / LANE_OUTPUTS) * TILE_OUTPUTS + h * LANE_OUTPUTS + (u32)(s * 2 % LANE_OUTPUTS) + i;
+    };
+    auto load_bias = [&](u64 (&b)[4], int s) {
 #pragma unroll
-        for (u32 g = 0; g < 4; g++) b[g] = uniform_load(reinterpret_cast<const u64*>(bias0 + min(4 * o + g, count - 1) * bias_step));
+        for (u32 g = 0; g < 4; g++) b[g] = uniform_load(reinterpret_cast<const u64*>(bias0 + min(output_of(s, g & 1, g >> 1), count - 1) * bias_step));
     };
     auto reduce_all = [&](auto reduce) {
         u64 next[4];
         load_bias(next, 0);
 #pragma unroll
-        for (int o = 0; o < OT; o++) {
-            u64 start[4];
+        for (int s = 0; s < STEPS; s++) {
+            u64 start[4];  // [half][i]
 #pragma unroll
             for (int g = 0; g < 4; g++) {
-                start[g] = c.start + (next[g] & mask);
+                start[g] = D == 8 ? c.start + (next[g] & mask) : add_mod(c.start, next[g] & mask, c.q);
                 asm volatile("" : "+s"(start[g]));
             }
-            if (o + 1 < OT) load_bias(next, o + 1);
+            if (s + 1 < STEPS) load_bias(next, s + 1);
 #pragma unroll
             for (int i = 0; i < 2; i++) {
                 const u64 st = half ? start[2 + i] : start[i];
-                const bool mine = o * 4 + half * 2 + i < count;
-                u64* const at = dst + (o * 4 + i) * out_stride;
-                u64 v[CT];
+                const bool mine = output_of(s, i, half) < count;
+                V* const at = dst + output_of(s, i, 0) * out_stride;
+                V v[CT];
 #pragma unroll
                 for (int k = 0; k < CT; k++) {
-                    int32_t r[8];
-                    sums.get(r, o, k, i);
+                    int32_t r[D];
+                    sums.get(r, s * 2 / LANE_OUTPUTS, k, s * 2 % LANE_OUTPUTS + i);
                     v[k] = reduce(r, st);
                 }
                 if (mine) {
+                    typedef V row_piece __attribute__((ext_vector_type(CT)));  // 16 bytes
                     if (accumulate) {
-                        const ulonglong2 old = *reinterpret_cast<const ulonglong2*>(at);
-                        v[0] = add_mod(v[0], old.x, c.q);
-                        v[1] = add_mod(v[1], old.y, c.q);
+                        const row_piece old = *reinterpret_cast<const row_piece*>(at);
+#pragma unroll
+                        for (int k = 0; k < CT; k++) v[k] = add_mod(v[k], old[k], c.q);
                     }
-                    ulonglong2 both;
-                    both.x = v[0];
-                    both.y = v[1];
-                    *reinterpret_cast<ulonglong2*>(at) = both;
+                    row_piece all;
+#pragma unroll
+                    for (int k = 0; k < CT; k++) all[k] = v[k];
+                    *reinterpret_cast<row_piece*>(at) = all;
                 }
                 __builtin_amdgcn_sched_barrier(0);  // one output at a time: its temporaries are few
             }
         }
     };
-    // (one uniform branch for the whole group)
-    if (lazy) reduce_all([&](const int32_t (&r)[8], u64 st) { return digit_reduce_lazy(r, st, c); });
-    else reduce_all([&](const int32_t (&r)[8], u64 st) { return digit_reduce(r, st, c); });
+    if constexpr (D == 8) {  // (one uniform branch for the whole group)
+        if (lazy) reduce_all([&](const int32_t (&r)[8], u64 st) { return digit_reduce_lazy(r, st, c); });
+        else reduce_all([&](const int32_t (&r)[8], u64 st) { return digit_reduce(r, st, c); });
+    } else {
+        reduce_all([&](const int32_t (&r)[4], u64 st) { return digit_reduce32(r, (u32)st, c); });
+    }
 }
 
 // the balanced digits of two residues, given as 32-bit words
@@ -246,17 +287,26 @@ __device__ __forceinline__ v4i digits_of(u32 a0, u32 a1, u32 b0, u32 b1) {
     return v4i{(int)(u32)a, (int)(u32)(a >> 32), (int)(u32)b, (int)(u32)(b >> 32)};
 }
 
+// A block's matrix operand for column tile k from the lane's residues of its LANE_TERMS terms
+__device__ __forceinline__ v4i operand(const u32x4 (&x)[2], int k) { return digits_of(x[0][2 * k], x[0][2 * k + 1], x[1][2 * k], x[1][2 * k + 1]); }
+__device__ __forceinline__ v4i operand(const u32x4 (&x)[4], int k) {
+    return v4i{(int)balanced_digits32(x[0][k]), (int)balanced_digits32(x[1][k]), (int)balanced_digits32(x[2][k]), (int)balanced_digits32(x[3][k])};
+}
+
 // Groups tile_first .. tile_end - 1 as one stream of chunks (16 terms each, the last of a group padded with zero
 // weights).  A wavefront multiplies the inputs it requested a chunk ago, requests those of the next chunk, also across
 // the end of a group, and the term list of the chunk after that; all of it is straight-line code, so that a wait is
 // for the loads it needs and no others.
 // RESIDENT: the groups share one table, which the workgroup has put into the LDS; the wavefronts do not meet.
 // Otherwise the workgroup brings the next chunk's table tiles into the other half of the LDS meanwhile.
-template <int OT, bool RESIDENT>
-__device__ __forceinline__ void mac_stream(const MacArgs& a, const Slice& w, const DigitConst& c, u32 tile_first, u32 tile_end, v4i* lds) {
+template <typename V, int OT, bool RESIDENT>
+__device__ __forceinline__ void mac_stream(const MacArgs<V>& a, const Slice<V>& w, const DigitConst& c, u32 tile_first, u32 tile_end, v4i* lds) {
+    using F = Form<V>;
+    constexpr u32 CHUNK_BLOCKS = F::CHUNK_BLOCKS, LANE_TERMS = F::LANE_TERMS;
+    constexpr int CT = F::CT;
     constexpr u32 CHUNK_PIECES = CHUNK_BLOCKS * OT * 64;  // 16-byte pieces of a chunk's tiles
-    constexpr u32 PER_THREAD = CHUNK_PIECES / THREADS;
-    static_assert(CHUNK_PIECES % THREADS == 0, "every thread brings the same number of pieces");
+    constexpr u32 PER_THREAD = CHUNK_PIECES < THREADS ? 1 : CHUNK_PIECES / THREADS;
+    static_assert(CHUNK_PIECES % THREADS == 0 || THREADS % CHUNK_PIECES == 0, "every thread brings the same number of pieces");
     Cursor cur, nxt, after;
     enter_group(cur, a, tile_first);
     nxt = cur;
@@ -264,41 +314,40 @@ __device__ __forceinline__ void mac_stream(const MacArgs& a, const Slice& w, con
     after = nxt;
     step(after, a, tile_end);
 
-    u32 idx[CHUNK_BLOCKS][2];      // ciphertexts of the two terms per block that this lane reads, next chunk
-    u32x4 x[CHUNK_BLOCKS][2];      // residues of this chunk, at two slots
-    auto request_idx = [&](const Cursor& p, u32 b) {  // two blocks' at a time: 16 bytes
-        const u32x4 v = *reinterpret_cast<const u32x4*>(a.lists + (size_t)(p.list + p.chunk) * LIST_CHUNK + (8 * w.half + 2 * b));
-        idx[b][0] = v[0];
-        idx[b][1] = v[1];
-        idx[b + 1][0] = v[2];
-        idx[b + 1][1] = v[3];
+    u32 idx[8];                            // ciphertexts of the eight terms that this lane reads in the next chunk
+    u32x4 x[CHUNK_BLOCKS][LANE_TERMS];     // residues of this chunk, 16 bytes of a row each
+    auto request_idx = [&](const Cursor& p, u32 part) {  // four at a time: 16 bytes
+        const u32x4 v = *reinterpret_cast<const u32x4*>(a.lists + (size_t)(p.list + p.chunk) * LIST_CHUNK + (8 * w.half + 4 * part));
+#pragma unroll
+        for (u32 k = 0; k < 4; k++) idx[4 * part + k] = v[k];
     };
     auto request_x = [&](u32 b) {
 #pragma unroll
-        for (u32 j = 0; j < 2; j++) x[b][j] = *reinterpret_cast<const u32x4*>(w.x_base + (u64)idx[b][j] * w.ct_stride);
+        for (u32 j = 0; j < LANE_TERMS; j++) x[b][j] = *reinterpret_cast<const u32x4*>(w.x_base + (u64)idx[b * LANE_TERMS + j] * w.ct_stride);
     };
+    // (with fewer pieces than threads some pieces are brought twice)
     v4i stage[PER_THREAD];
     auto request_tiles = [&](const Cursor& p) {
         const v4i* src = w.tab + (p.piece + (u64)p.chunk * CHUNK_PIECES);
 #pragma unroll
-        for (u32 i = 0; i < PER_THREAD; i++) stage[i] = src[i * THREADS + threadIdx.x];
+        for (u32 i = 0; i < PER_THREAD; i++) stage[i] = src[(i * THREADS + threadIdx.x) % CHUNK_PIECES];
     };
     auto write_tiles = [&](u32 buf) {
 #pragma unroll
-        for (u32 i = 0; i < PER_THREAD; i++) lds[buf * CHUNK_PIECES + i * THREADS + threadIdx.x] = stage[i];
+        for (u32 i = 0; i < PER_THREAD; i++) lds[buf * CHUNK_PIECES + (i * THREADS + threadIdx.x) % CHUNK_PIECES] = stage[i];
     };
     u32 buf = 0;
     if constexpr (!RESIDENT) request_tiles(cur);
-#pragma unroll
-    for (u32 b = 0; b < CHUNK_BLOCKS; b += 2) request_idx(cur, b);
+    request_idx(cur, 0);
+    request_idx(cur, 1);
 #pragma unroll
     for (u32 b = 0; b < CHUNK_BLOCKS; b++) request_x(b);
-#pragma unroll
-    for (u32 b = 0; b < CHUNK_BLOCKS; b += 2) request_idx(nxt, b);
+    request_idx(nxt, 0);
+    request_idx(nxt, 1);
     if constexpr (!RESIDENT) write_tiles(0);
     while (true) {
         const u32 tile = cur.tile, chunks = cur.n_chunks;
-        Sums<OT> sums;
+        Sums<V, OT> sums;
         // FIRST: the first block's products start the sums
         auto run_chunk = [&](u32 chunk, auto first) {
             constexpr bool FIRST = decltype(first)::value;
@@ -309,16 +358,19 @@ __device__ __forceinline__ void mac_stream(const MacArgs& a, const Slice& w, con
             const v4i* tiles = lds + (RESIDENT ? chunk : buf) * CHUNK_PIECES + w.lane;
 #pragma unroll
             for (u32 b = 0; b < CHUNK_BLOCKS; b++) {
-                const v4i in0 = digits_of(x[b][0][0], x[b][0][1], x[b][1][0], x[b][1][1]);
-                const v4i in1 = digits_of(x[b][0][2], x[b][0][3], x[b][1][2], x[b][1][3]);
+                v4i in[CT];
+#pragma unroll
+                for (int k = 0; k < CT; k++) in[k] = operand(x[b], k);
                 request_x(b);
-                if (b % 2 == 1) request_idx(after, b - 1);
+                if ((b + 1) * LANE_TERMS == 4) request_idx(after, 0);
+                if ((b + 1) * LANE_TERMS == 8) request_idx(after, 1);
 #pragma unroll
                 for (int o = 0; o < OT; o++) {
                     const v4i t = tiles[(b * OT + o) * 64];
                     const v16i zero = {};
-                    sums.t[o][0] = __builtin_amdgcn_mfma_i32_32x32x32_i8(t, in0, FIRST && b == 0 ? zero : sums.t[o][0], 0, 0, 0);
-                    sums.t[o][1] = __builtin_amdgcn_mfma_i32_32x32x32_i8(t, in1, FIRST && b == 0 ? zero : sums.t[o][1], 0, 0, 0);
+#pragma unroll
+                    for (int k = 0; k < CT; k++)
+                        sums.t[o][k] = __builtin_amdgcn_mfma_i32_32x32x32_i8(t, in[k], FIRST && b == 0 ? zero : sums.t[o][k], 0, 0, 0);
                 }
                 __builtin_amdgcn_sched_barrier(0);
             }
@@ -333,9 +385,9 @@ __device__ __forceinline__ void mac_stream(const MacArgs& a, const Slice& w, con
 #pragma unroll
         for (u32 b = 0; b < CHUNK_BLOCKS; b++)
 #pragma unroll
-            for (u32 j = 0; j < 2; j++) asm volatile("" : "+v"(x[b][j]));  // the next chunk's inputs have arrived
+            for (u32 j = 0; j < LANE_TERMS; j++) asm volatile("" : "+v"(x[b][j]));  // the next chunk's inputs have arrived
         const DigitTile t = load_tile(a.tiles + tile);
-        store_group<OT>(sums, a, w, c, t.out0, t.count);
+        store_group<V, OT>(sums, a, w, c, t.out0, t.count);
         if (tile + 1 >= tile_end) break;
         cur.tile = tile + 1;
         cur.n_chunks = chunks_of(a, load_tile(a.tiles + tile + 1));
@@ -346,9 +398,10 @@ struct MacClass {
     u32 first, end, per_wg, blocks;  // the class's groups among the plan's tiles, groups per workgroup and workgroups
 };
 
-template <int OT>
-__device__ __forceinline__ void mac_class(u32 b, const MacArgs& a, const DigitTable& dt, const MacClass& m, v4i* lds) {
-    const u32 parts = a.N / SLOTS;
+template <typename V, int OT>
+__device__ __forceinline__ void mac_class(u32 b, const MacArgs<V>& a, const DigitTable& dt, const MacClass& m, v4i* lds) {
+    using F = Form<V>;
+    const u32 parts = a.N / F::SLOTS;
     const u32 runs = (m.end - m.first + m.per_wg - 1) / m.per_wg;
     // slice of the row fastest, then run of groups, then (component, limb): workgroups go to the eight XCDs round-robin
     // and the number of slices is even, so the same slice of neighbouring groups (which read the same or overlapping
@@ -356,13 +409,13 @@ __device__ __forceinline__ void mac_class(u32 b, const MacArgs& a, const DigitTa
     const u32 part = b % parts; b /= parts;
     const u32 tile_first = m.first + (b % runs) * m.per_wg; b /= runs;
     const u32 tile_end = min(tile_first + m.per_wg, m.end);
-    Slice w;
+    Slice<V> w;
     w.comp = b & 1;
     w.limb = b >> 1;
     w.lane = threadIdx.x % 64;
     w.half = w.lane / 32;
-    w.ct_stride = 2 * a.limbs * a.N * 8;
-    const size_t at = ((size_t)w.comp * a.limbs + w.limb) * a.N + part * SLOTS + threadIdx.x / 64 * (32 * CT) + 2 * (w.lane % 32);
+    w.ct_stride = 2 * a.limbs * a.N * sizeof(V);
+    const size_t at = ((size_t)w.comp * a.limbs + w.limb) * a.N + part * F::SLOTS + threadIdx.x / 64 * (32 * F::CT) + F::CT * (w.lane % 32);
     w.x_base = reinterpret_cast<const char*>(a.ct_in + at);
     w.dst = a.out + at;
     w.tab = reinterpret_cast<const v4i*>(a.tab + (u64)w.limb * a.tab_words);
@@ -375,51 +428,53 @@ __device__ __forceinline__ void mac_class(u32 b, const MacArgs& a, const DigitTa
         enter_group(p, a, tile);
         const DigitTile t = load_tile(a.tiles + tile);
         if (p.n_chunks == 0) {  // no terms: the bias alone
-            Sums<OT> zero;
+            Sums<V, OT> zero;
             zero.clear();
-            store_group<OT>(zero, a, w, c, t.out0, t.count);
+            store_group<V, OT>(zero, a, w, c, t.out0, t.count);
             tile++;
         } else if (p.n_chunks <= RESIDENT_CHUNKS) {
             const u32 end = min(tile_end, t.same_until);
-            const u32 pieces = p.n_chunks * CHUNK_BLOCKS * OT * 64;
+            const u32 pieces = p.n_chunks * F::CHUNK_BLOCKS * OT * 64;
             lds_barrier();  // (the table of the groups before is no longer read)
             for (u32 i = threadIdx.x; i < pieces; i += THREADS) lds[i] = w.tab[p.piece + i];
             lds_barrier();
-            mac_stream<OT, true>(a, w, c, tile, end, lds);
+            mac_stream<V, OT, true>(a, w, c, tile, end, lds);
             tile = end;
         } else {
             // the rest of the run: groups with long sums follow one another (tables of a class are in the order of
             // their first use, so a shorter one may still come and takes the same path)
             lds_barrier();
-            mac_stream<OT, false>(a, w, c, tile, tile_end, lds);
+            mac_stream<V, OT, false>(a, w, c, tile, tile_end, lds);
             tile = tile_end;
         }
     }
 }
 
-// Groups of 9..16 (OT = 4), 5..8 (2) and 2..4 (1) outputs.  The accumulators, OT x CT x 16 registers, set how many
-// wavefronts a SIMD holds.
-template <int OT>
-__global__ void __launch_bounds__(THREADS, OT == 4 ? 2 : OT == 2 ? 3 : 4) mac_digits_kernel(DigitTable dt, MacArgs a, MacClass m) {
-    __shared__ v4i lds[RESIDENT_CHUNKS * CHUNK_BLOCKS * OT * 64];
-    mac_class<OT>(blockIdx.x, a, dt, m, lds);
+// 64-bit residues: groups of 9..16 (OT = 4), 5..8 (2) and 2..4 (1) outputs; packed ones: of 9..16 (2) and up to 8 (1).
+// The accumulators, OT x CT x 16 registers, set how many wavefronts a SIMD holds.
+template <typename V, int OT>
+__global__ void __launch_bounds__(THREADS, OT * Form<V>::CT == 8 ? 2 : OT * Form<V>::CT == 4 ? 3 : 4)
+mac_digits_kernel(DigitTable dt, MacArgs<V> a, MacClass m) {
+    __shared__ v4i lds[RESIDENT_CHUNKS * Form<V>::CHUNK_BLOCKS * OT * 64];
+    mac_class<V, OT>(blockIdx.x, a, dt, m, lds);
 }
 
 // A plan with groups of several classes in one launch: the first workgroups take the largest class, and the smaller
 // ones (often the ragged end of a layer) fill in while it drains.
-__global__ void __launch_bounds__(THREADS, 2) mac_digits_mixed_kernel(DigitTable dt, MacArgs a, MacClass c16, MacClass c8, MacClass c4) {
-    __shared__ v4i lds[RESIDENT_CHUNKS * CHUNK_BLOCKS * 4 * 64];
-    if (blockIdx.x < c16.blocks) mac_class<4>(blockIdx.x, a, dt, c16, lds);
-    else if (blockIdx.x < c16.blocks + c8.blocks) mac_class<2>(blockIdx.x - c16.blocks, a, dt, c8, lds);
-    else mac_class<1>(blockIdx.x - c16.blocks - c8.blocks, a, dt, c4, lds);
+template <typename V>
+__global__ void __launch_bounds__(THREADS, 2) mac_digits_mixed_kernel(DigitTable dt, MacArgs<V> a, MacClass c16, MacClass c8, MacClass c4) {
+    constexpr int OT16 = Form<V>::tiles(16), OT8 = Form<V>::tiles(8), OT4 = Form<V>::tiles(4);
+    __shared__ v4i lds[RESIDENT_CHUNKS * Form<V>::CHUNK_BLOCKS * OT16 * 64];
+    if (blockIdx.x < c16.blocks) mac_class<V, OT16>(blockIdx.x, a, dt, c16, lds);
+    else if (blockIdx.x < c16.blocks + c8.blocks) mac_class<V, OT8>(blockIdx.x - c16.blocks, a, dt, c8, lds);
+    else mac_class<V, OT4>(blockIdx.x - c16.blocks - c8.blocks, a, dt, c4, lds);
 }
-
-}  // namespace
 
 // Groups per workgroup and workgroups of one class over the tiles [first, end).  Several groups per workgroup pay the
 // start of a run (descriptor -> term list -> inputs, and a convolution's table) once; a group without terms stays alone.
-static MacClass mac_class_of(const he_ctx* ctx, const he_plan* plan, u32 limbs, u32 cls, u32 first, u32 end, u32 t_begin) {
-    const u64 per_run = (u64)limbs * 2 * (ctx->N / SLOTS);
+template <typename V>
+MacClass mac_class_of(const he_ctx* ctx, const he_plan* plan, u32 limbs, u32 cls, u32 first, u32 end, u32 t_begin) {
+    const u64 per_run = (u64)limbs * 2 * (ctx->N / Form<V>::SLOTS);
     const u32 count = end - first;
     u32 per_wg = plan->min_terms_s[cls] > t_begin ? GROUPS_PER_WG : 1;  // (a stream has no group without terms in it)
     while (per_wg > 1 && (u64)((count + per_wg - 1) / per_wg) * per_run < MIN_WORKGROUPS) per_wg /= 2;
@@ -427,21 +482,14 @@ static MacClass mac_class_of(const he_ctx* ctx, const he_plan* plan, u32 limbs, 
     return MacClass{first, end, per_wg, (u32)std::min<u64>(blocks, 0x7FFFFFFFull)};
 }
 
-// an upper bound of the workgroups that launch_mac_digits starts for the whole plan
-u64 mac_digits_blocks(const he_ctx* ctx, const he_plan* plan, u32 limbs) {
-    u64 blocks = 0;
-    for (u32 cls = 1; cls < SCALAR_CLASSES; cls++)
-        blocks += mac_class_of(ctx, plan, limbs, cls, plan->class_begin_s[cls], plan->class_begin_s[cls + 1], ~0u).blocks;
-    return blocks;
-}
-
-int launch_mac_digits(he_ctx* ctx, const he_plan* plan, const ScalarSlice& sl, u32 limbs, const u64* ct_in, const u64* pt, const u64* bias,
-                      u64* out, u64* wtab, u32 mode, hipStream_t s) {
+template <typename V>
+int launch_mac_digits_t(he_ctx* ctx, const he_plan* plan, const ScalarSlice& sl, u32 limbs, const V* ct_in, const u64* pt, const u64* bias, V* out,
+                        u64* wtab, u32 mode, hipStream_t s) {
     MacClass c[SCALAR_CLASSES];
     u64 blocks = 0;
     u32 first = ~0u;  // the first tile of the slice in these classes
     for (u32 cls = 1; cls < SCALAR_CLASSES; cls++) {
-        c[cls] = mac_class_of(ctx, plan, limbs, cls, sl.begin[cls], sl.end[cls], sl.t_begin);
+        c[cls] = mac_class_of<V>(ctx, plan, limbs, cls, sl.begin[cls], sl.end[cls], sl.t_begin);
         blocks += c[cls].blocks;
         if (sl.begin[cls] < sl.end[cls]) first = std::min(first, sl.begin[cls]);
     }
@@ -452,16 +500,38 @@ int launch_mac_digits(he_ctx* ctx, const he_plan* plan, const ScalarSlice& sl, u
     const u32 n_tables = sl.table_end - table0;
     const u32 per_table = (u32)std::max<u64>(1, std::min<u64>((entries + 255) / 256, std::max<u64>(1, 4096 / n_tables)));
     for (u32 t = 0; t < n_tables; t += 32768) {  // (the grid's second dimension is limited to 65535)
-        hipLaunchKernelGGL(gather_digits_kernel, dim3(per_table, std::min<u32>(n_tables - t, 32768)), dim3(256), 0, s, ctx->digits, plan->tiles_s_dev,
-                           plan->wbase_s_dev, plan->owners_dev + table0 + t, limbs, plan->off_dev, plan->term_pt_dev, pt, wtab, sl.tab_words,
-                           sl.tab_skip, sl.t_begin, sl.t_end);
+        hipLaunchKernelGGL(gather_digits_kernel<V>, dim3(per_table, std::min<u32>(n_tables - t, 32768)), dim3(256), 0, s, ctx->digits,
+                           plan->tiles_s_dev, plan->wbase_s_dev, plan->owners_dev + table0 + t, limbs, plan->off_dev, plan->term_pt_dev, pt, wtab,
+                           sl.tab_words, sl.tab_skip, sl.t_begin, sl.t_end);
     }
-    const MacArgs a{plan->digit_tiles_dev, plan->lists_dev, wtab, sl.tab_words, sl.tab_skip, ct_in, bias, out, limbs, ctx->N,
-                    sl.t_begin, sl.t_end, mode};
-    if (c[3].blocks == blocks) hipLaunchKernelGGL(mac_digits_kernel<4>, dim3((u32)blocks), dim3(THREADS), 0, s, ctx->digits, a, c[3]);
-    else if (c[2].blocks == blocks) hipLaunchKernelGGL(mac_digits_kernel<2>, dim3((u32)blocks), dim3(THREADS), 0, s, ctx->digits, a, c[2]);
-    else if (c[1].blocks == blocks) hipLaunchKernelGGL(mac_digits_kernel<1>, dim3((u32)blocks), dim3(THREADS), 0, s, ctx->digits, a, c[1]);
-    else hipLaunchKernelGGL(mac_digits_mixed_kernel, dim3((u32)blocks), dim3(THREADS), 0, s, ctx->digits, a, c[3], c[2], c[1]);
+    const MacArgs<V> a{plan->digit_tiles_dev, plan->lists_dev, wtab, sl.tab_words, sl.tab_skip, ct_in, bias, out, limbs, ctx->N, sl.t_begin,
+                       sl.t_end, mode};
+    const dim3 grid((u32)blocks), block(THREADS);
+    constexpr int OT16 = Form<V>::tiles(16), OT8 = Form<V>::tiles(8), OT4 = Form<V>::tiles(4);
+    if (c[3].blocks == blocks) hipLaunchKernelGGL((mac_digits_kernel<V, OT16>), grid, block, 0, s, ctx->digits, a, c[3]);
+    else if (c[2].blocks == blocks) hipLaunchKernelGGL((mac_digits_kernel<V, OT8>), grid, block, 0, s, ctx->digits, a, c[2]);
+    else if (c[1].blocks == blocks) hipLaunchKernelGGL((mac_digits_kernel<V, OT4>), grid, block, 0, s, ctx->digits, a, c[1]);
+    else hipLaunchKernelGGL(mac_digits_mixed_kernel<V>, grid, block, 0, s, ctx->digits, a, c[3], c[2], c[1]);
     HE_HIP(hipGetLastError());
     return HE_OK;
+}
+
+}  // namespace
+
+// an upper bound of the workgroups that launch_mac_digits starts for the whole plan, in either form
+u64 mac_digits_blocks(const he_ctx* ctx, const he_plan* plan, u32 limbs) {
+    u64 blocks = 0;
+    for (u32 cls = 1; cls < SCALAR_CLASSES; cls++)
+        blocks += mac_class_of<u64>(ctx, plan, limbs, cls, plan->class_begin_s[cls], plan->class_begin_s[cls + 1], ~0u).blocks;
+    return blocks;
+}
+
+int launch_mac_digits(he_ctx* ctx, const he_plan* plan, const ScalarSlice& sl, u32 limbs, const u64* ct_in, const u64* pt, const u64* bias,
+                      u64* out, u64* wtab, u32 mode, hipStream_t s) {
+    return launch_mac_digits_t<u64>(ctx, plan, sl, limbs, ct_in, pt, bias, out, wtab, mode, s);
+}
+
+int launch_mac_digits32(he_ctx* ctx, const he_plan* plan, const ScalarSlice& sl, u32 limbs, const u32* ct_in, const u64* pt, const u64* bias,
+                        u32* out, u64* wtab, u32 mode, hipStream_t s) {
+    return launch_mac_digits_t<u32>(ctx, plan, sl, limbs, ct_in, pt, bias, out, wtab, mode, s);
 }

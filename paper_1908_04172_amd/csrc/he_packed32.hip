@@ -1,11 +1,12 @@
 // Packed 32-bit storage for limbs whose moduli are below 2^30: the paper's 32-bit optimisation
 // (Sec. "Ciphertext-plaintext Multiplication": BarrettReduction64, Alg. 6, and the scalar multiply of
 // Alg. 8) carried through to the memory system.  Residue tensors are uint32 [ct][2][limbs][N], half the
-// bytes of the 64-bit form; a product of two residues fits 60 bits, so a MAC term is ONE 32x32+64-bit
-// multiply-add into a single 64-bit sum (four into three sums in the 64-bit path), fifteen terms go by
-// between two reductions, and a reduction is Alg. 6: one high product with floor(2^64 / q), one low
-// product, one conditional subtraction.  The transforms are the register-resident ones of the 64-bit path
-// with 32-bit butterflies; the rescale keeps the dropped limb's coefficients in registers throughout.
+// bytes of the 64-bit form.  Scalar plaintexts of groups of outputs run on the matrix cores (he_mac_digits.hip); for
+// single outputs and full-polynomial plaintexts a product of two residues fits 60 bits, so a MAC term is ONE
+// 32x32+64-bit multiply-add into a single 64-bit sum, fifteen terms go by between two folds, and a reduction is Alg. 6:
+// one high product with floor(2^64 / q), one low product, one conditional subtraction.  The transforms are the
+// register-resident ones of the 64-bit path with 32-bit butterflies; the rescale keeps the dropped limb's coefficients
+// in registers throughout.
 #include <algorithm>
 
 #include "he_internal.h"
@@ -62,46 +63,28 @@ constexpr u32 MAC32_THREADS = 256;
 constexpr u32 MAC32_SLICE = 2 * MAC32_THREADS;  // residues of a row one workgroup covers (two per thread)
 
 constexpr u32 GATHER32_BLOCKS = 16;  // workgroups that share the gathering of one group's table
-constexpr u32 MAC32_BLOCK = 4;  // terms per unrolled block; an input is requested a block before its use
-__host__ __device__ inline u32 padded_terms32(u32 n_terms) { return (n_terms + MAC32_BLOCK - 1) / MAC32_BLOCK * MAC32_BLOCK; }
 
-// A group's table starts at its place among the 64-bit path's tables for single outputs; those of larger groups take an
-// eighth of the 64-bit form's words each and are packed accordingly behind `singles`, where the first of them starts (at
-// the 64-bit distances, often a power of two, they would collide in the scalar cache).
-template <int G>
-__device__ __forceinline__ u64 table32(u64 wbase, u64 singles) { return G == 1 ? wbase : singles + (wbase - singles) / 8; }
-
-// wtab32[limb*wtab_elems + table32(wbase) + t*G + g] = pt[term_pt[off[out0+g] + t]][limb] for g < count and t < n_terms, else 0,
-// for t up to n_terms rounded up to whole blocks: the scalar plaintexts of a group laid out in the order the MAC
-// loop reads them (the plan's table offsets are shared with the 64-bit path, whose entries are larger; groups with
-// the same plaintext indices share a table).
-template <int G>
+// Outputs that share their inputs with no other (groups of outputs run on the matrix cores: he_mac_digits.hip): word t of
+// a group's table, at its place among the 64-bit path's tables, is pt[term_pt[off[out0] + t]][limb] as 32 bits.
 __global__ void __launch_bounds__(256) gather_weights32_kernel(const Tile* tiles, const u64* wbase, const u32* owners, u32 n_tables,
                                                                u32 limbs, const u32* off, const u32* term_pt, const u64* pt,
-                                                               u32* wtab, u64 wtab_elems, u64 singles) {
+                                                               u64* wtab, u64 wtab_elems) {
     const u32 table = blockIdx.x / GATHER32_BLOCKS, sub = blockIdx.x % GATHER32_BLOCKS;
     if (table >= n_tables) return;
     const u32 tile_i = owners[table];
     const Tile tile = tiles[tile_i];
-    const u64 per_limb = (u64)padded_terms32(tile.n_terms) * G;
-    u32* dst = wtab + table32<G>(wbase[tile_i], singles);
-    for (u64 i = (u64)sub * blockDim.x + threadIdx.x; i < per_limb * limbs; i += (u64)GATHER32_BLOCKS * blockDim.x) {
-        const u32 limb = (u32)(i / per_limb);
-        const u64 rem = i % per_limb;
-        const u32 t = (u32)(rem / G), g = (u32)(rem % G);
-        dst[(u64)limb * wtab_elems + rem] =
-            g < tile.count && t < tile.n_terms ? (u32)pt[(size_t)term_pt[off[tile.out0 + g] + t] * limbs + limb] : 0;
+    const u64 K = tile.n_terms;
+    for (u64 i = (u64)sub * blockDim.x + threadIdx.x; i < K * limbs; i += (u64)GATHER32_BLOCKS * blockDim.x) {
+        const u32 limb = (u32)(i / K), t = (u32)(i % K);
+        u32* dst = reinterpret_cast<u32*>(wtab + limb * wtab_elems + wbase[tile_i]);
+        dst[t] = (u32)pt[(size_t)term_pt[off[tile.out0] + t] * limbs + limb];
     }
 }
 
-// One thread = two adjacent residues of one (component, limb) row x a group of G outputs.  Terms run in blocks of
-// four (the terms that pad a group to whole blocks have zero weights and the last real term's input again); a ring
-// of four inputs keeps each request a whole block of multiply-adds ahead of its use, and a term's G weights are
-// requested (scalar loads) while the term before is multiplied.
-template <int G>
+// One thread = two adjacent residues of one (component, limb) row of one output.
 __global__ void __launch_bounds__(MAC32_THREADS)
-mac_scalar32_kernel(Limb32Table lt, u32 limbs, u32 N, const Tile* tiles, u32 n_tiles, const u64* wbase, const u32* term_ct,
-                    const u32* wtab, u64 wtab_elems, u64 singles, const u32* ct_in, const u64* bias, u32* out, u32 accumulate) {
+mac_scalar32_single_kernel(Limb32Table lt, u32 limbs, u32 N, const Tile* tiles, u32 n_tiles, const u64* wbase, const u32* term_ct,
+                           const u64* wtab, u64 wtab_elems, const u32* ct_in, const u64* bias, u32* out, u32 accumulate) {
     const u32 slices = N / MAC32_SLICE;
     u32 b = blockIdx.x;
     const u32 slice = b % slices; b /= slices;
@@ -109,74 +92,39 @@ mac_scalar32_kernel(Limb32Table lt, u32 limbs, u32 N, const Tile* tiles, u32 n_t
     const u32 comp = b & 1;
     const u32 limb = b >> 1;
     const Limb32& c = lt.c[limb];
-    const u32 K = uniform_load(&tiles[tile_i].n_terms), count = uniform_load(&tiles[tile_i].count);
-    const u32 out0 = uniform_load(&tiles[tile_i].out0);
+    const u32 K = uniform_load(&tiles[tile_i].n_terms), o = uniform_load(&tiles[tile_i].out0);
     const u32* tc = term_ct + uniform_load(&tiles[tile_i].term0);
-    const u32* w = wtab + (u64)limb * wtab_elems + table32<G>(uniform_load(wbase + tile_i), singles);
+    const u32* w = reinterpret_cast<const u32*>(wtab + limb * wtab_elems + uniform_load(wbase + tile_i));
     const u32 pair = slice * MAC32_THREADS + threadIdx.x;
     const size_t ct_pairs = (size_t)limbs * N;  // uint2 elements per ciphertext (2 components x limbs x N / 2)
     const uint2* x_base = reinterpret_cast<const uint2*>(ct_in) + ((size_t)comp * limbs + limb) * (N / 2) + pair;
-    u64 acc[G][2];
-#pragma unroll
-    for (int g = 0; g < G; g++) acc[g][0] = acc[g][1] = 0;
-    if (K > 0) {
-        const u32 Kp = padded_terms32(K), last = K - 1;
-        uint2 xq[MAC32_BLOCK];
-#pragma unroll
-        for (u32 j = 0; j < MAC32_BLOCK; j++) xq[j] = x_base[(size_t)uniform_load(tc + min(j, last)) * ct_pairs];
-        u32 w_next[G];
-#pragma unroll
-        for (int g = 0; g < G; g++) w_next[g] = uniform_load(w + g);
-        u32 since = 0;
-        for (u32 t = 0; t < Kp; t += MAC32_BLOCK) {
-#pragma unroll
-            for (u32 j = 0; j < MAC32_BLOCK; j++) {
-                const uint2 x = xq[j];
-                xq[j] = x_base[(size_t)uniform_load(tc + min(t + MAC32_BLOCK + j, last)) * ct_pairs];
-                u32 wv[G];
-#pragma unroll
-                for (int g = 0; g < G; g++) wv[g] = w_next[g];
-                // (after the last term this reads the entry that follows the group's table: another table or the
-                // padding at the end of the limb's part; never used)
-#pragma unroll
-                for (int g = 0; g < G; g++) w_next[g] = uniform_load(w + (size_t)(t + j + 1) * G + g);
-#pragma unroll
-                for (int g = 0; g < G; g++) {
-                    acc[g][0] += (u64)x.x * wv[g];
-                    acc[g][1] += (u64)x.y * wv[g];
-                }
-            }
-            since += MAC32_BLOCK;
-            if (since + MAC32_BLOCK > TERMS_PER_REDUCTION && t + MAC32_BLOCK < Kp) {
-                since = 0;
-#pragma unroll
-                for (int g = 0; g < G; g++) {
-                    acc[g][0] = fold48(acc[g][0], c);
-                    acc[g][1] = fold48(acc[g][1], c);
-                }
-            }
+    u64 acc0 = 0, acc1 = 0;
+    u32 since = 0;
+#pragma unroll 4
+    for (u32 t = 0; t < K; t++) {
+        const uint2 x = x_base[(size_t)uniform_load(tc + t) * ct_pairs];
+        const u32 wv = uniform_load(w + t);
+        acc0 += (u64)x.x * wv;
+        acc1 += (u64)x.y * wv;
+        if (++since == TERMS_PER_REDUCTION && t + 1 < K) {
+            since = 0;
+            acc0 = fold48(acc0, c);
+            acc1 = fold48(acc1, c);
         }
     }
-    const bool with_bias = bias != nullptr && comp == 0;  // Alg. 4: the bias goes to component 0 only
-#pragma unroll
-    for (int g = 0; g < G; g++) {
-        if ((u32)g < count) {
-            const u32 o = out0 + g;
-            u32 r0 = barrett64(acc[g][0], c), r1 = barrett64(acc[g][1], c);
-            if (with_bias) {
-                const u32 bv = (u32)bias[(size_t)o * limbs + limb];
-                r0 = add_mod32(r0, bv, c.q);
-                r1 = add_mod32(r1, bv, c.q);
-            }
-            uint2* dst = reinterpret_cast<uint2*>(out) + (((size_t)o * 2 + comp) * limbs + limb) * (N / 2) + pair;
-            if (accumulate) {  // HE_ACCUMULATE: add what the output holds (uniform branch)
-                const uint2 old = *dst;
-                r0 = add_mod32(r0, old.x, c.q);
-                r1 = add_mod32(r1, old.y, c.q);
-            }
-            *dst = make_uint2(r0, r1);
-        }
+    u32 r0 = barrett64(acc0, c), r1 = barrett64(acc1, c);
+    if (bias != nullptr && comp == 0) {  // Alg. 4: the bias goes to component 0 only
+        const u32 bv = (u32)bias[(size_t)o * limbs + limb];
+        r0 = add_mod32(r0, bv, c.q);
+        r1 = add_mod32(r1, bv, c.q);
     }
+    uint2* dst = reinterpret_cast<uint2*>(out) + (((size_t)o * 2 + comp) * limbs + limb) * (N / 2) + pair;
+    if (accumulate) {  // HE_ACCUMULATE: add what the output holds (uniform branch)
+        const uint2 old = *dst;
+        r0 = add_mod32(r0, old.x, c.q);
+        r1 = add_mod32(r1, old.y, c.q);
+    }
+    *dst = make_uint2(r0, r1);
 }
 
 // Alg. 7 summed, 32-bit moduli: one thread = two adjacent residues of one limb x G <= 4 outputs x both
@@ -507,23 +455,32 @@ int launch_unpack32(he_ctx* ctx, const u32* in, u64* out, size_t count, hipStrea
     return HE_OK;
 }
 
-template <int G>
-static int launch_scalar32_class(he_ctx* ctx, const he_plan* plan, int cls, u32 limbs, const u32* ct_in, const u64* pt,
-                                 const u64* bias, u32* out, u32* wtab, u32 accumulate, hipStream_t s) {
-    const u32 begin = plan->class_begin_s[cls], count = plan->class_begin_s[cls + 1] - begin;
-    if (count == 0) return HE_OK;
-    const Tile* tiles = plan->tiles_s_dev + begin;
-    const u64* wbase = plan->wbase_s_dev + begin;
-    const u64 singles = plan->class_begin_s[1] ? plan->table_end[plan->table_s[plan->class_begin_s[1] - 1]] : 0;
-    const u32 table = plan->table_s[begin], n_tables = plan->table_s[begin + count - 1] + 1 - table;
-    hipLaunchKernelGGL((gather_weights32_kernel<G>), dim3(n_tables * GATHER32_BLOCKS), dim3(256), 0, s, plan->tiles_s_dev, plan->wbase_s_dev,
-                       plan->owners_dev + table, n_tables, limbs, plan->off_dev, plan->term_pt_dev, pt, wtab, plan->wtab_elems, singles);
-    HE_HIP(hipGetLastError());
-    const u64 blocks = (u64)count * limbs * 2 * (ctx->N / MAC32_SLICE);
-    if (blocks > 0x7FFFFFFFull) return HE_ERR_RANGE;
-    hipLaunchKernelGGL((mac_scalar32_kernel<G>), dim3((u32)blocks), dim3(MAC32_THREADS), 0, s, ctx->limbs32, limbs, ctx->N, tiles, count,
-                       wbase, plan->term_ct_dev, wtab, plan->wtab_elems, singles, ct_in, bias, out, accumulate);
-    HE_HIP(hipGetLastError());
+static int launch_scalar32(he_ctx* ctx, const he_plan* plan, u32 limbs, const u32* ct_in, const u64* pt, const u64* bias, u32* out, u64* wtab,
+                           u32 accumulate, hipStream_t s) {
+    const u32 count = plan->class_begin_s[1];
+    if (count > 0) {
+        const u32 n_tables = plan->table_s[count - 1] + 1;
+        hipLaunchKernelGGL(gather_weights32_kernel, dim3(n_tables * GATHER32_BLOCKS), dim3(256), 0, s, plan->tiles_s_dev, plan->wbase_s_dev,
+                           plan->owners_dev, n_tables, limbs, plan->off_dev, plan->term_pt_dev, pt, wtab, plan->wtab_elems);
+        const u64 blocks = (u64)count * limbs * 2 * (ctx->N / MAC32_SLICE);
+        hipLaunchKernelGGL(mac_scalar32_single_kernel, dim3((u32)blocks), dim3(MAC32_THREADS), 0, s, ctx->limbs32, limbs, ctx->N, plan->tiles_s_dev,
+                           count, plan->wbase_s_dev, plan->term_ct_dev, wtab, plan->wtab_elems, ct_in, bias, out, accumulate);
+        HE_HIP(hipGetLastError());
+    }
+    ScalarSlice sl;
+    for (u32 cls = 0; cls < SCALAR_CLASSES; cls++) {
+        sl.begin[cls] = cls == 0 ? 0 : plan->class_begin_s[cls];
+        sl.end[cls] = cls == 0 ? 0 : plan->class_begin_s[cls + 1];
+    }
+    sl.table_begin = 0;
+    sl.table_end = (u32)plan->table_end.size();
+    sl.tab_skip = 0;
+    sl.tab_words = plan->wtab_elems;
+    for (u64 t = 0; t == 0 || t < plan->max_terms; t += DIGIT_MAX_TERMS) {  // (sums beyond the range of the matrix cores')
+        sl.t_begin = (u32)t;
+        sl.t_end = (u32)std::min<u64>(t + DIGIT_MAX_TERMS, ~0u);
+        if (int rc = launch_mac_digits32(ctx, plan, sl, limbs, ct_in, pt, t == 0 ? bias : nullptr, out, wtab, t == 0 ? accumulate : 1u, s)) return rc;
+    }
     return HE_OK;
 }
 
@@ -542,11 +499,14 @@ static int launch_poly32_class(he_ctx* ctx, const he_plan* plan, int cls, u32 li
 
 // the grid sizes launch_mac32 would use, checked without launching anything
 int check_mac32_launch(he_ctx* ctx, const he_plan* plan, u32 limbs, int pt_kind) {
-    for (u32 cls = 0; cls < (pt_kind == HE_PT_SCALAR ? SCALAR_CLASSES : 3u); cls++) {
-        const u64 count = pt_kind == HE_PT_SCALAR ? plan->class_begin_s[cls + 1] - plan->class_begin_s[cls]
-                                                  : plan->class_begin_p[cls + 1] - plan->class_begin_p[cls];
-        if (count * limbs * (pt_kind == HE_PT_SCALAR ? 2 : 1) * (ctx->N / MAC32_SLICE) > 0x7FFFFFFFull) return HE_ERR_RANGE;
-        if (pt_kind == HE_PT_SCALAR && count * GATHER32_BLOCKS > 0x7FFFFFFFull) return HE_ERR_RANGE;
+    if (pt_kind == HE_PT_SCALAR) {
+        const u64 singles = plan->class_begin_s[1];
+        if (singles * limbs * 2 * (ctx->N / MAC32_SLICE) > 0x7FFFFFFFull || singles * GATHER32_BLOCKS > 0x7FFFFFFFull) return HE_ERR_RANGE;
+        return mac_digits_blocks(ctx, plan, limbs) > 0x7FFFFFFFull ? HE_ERR_RANGE : HE_OK;
+    }
+    for (u32 cls = 0; cls < 3; cls++) {
+        const u64 count = plan->class_begin_p[cls + 1] - plan->class_begin_p[cls];
+        if (count * limbs * (ctx->N / MAC32_SLICE) > 0x7FFFFFFFull) return HE_ERR_RANGE;
     }
     return HE_OK;
 }
@@ -555,12 +515,7 @@ int launch_mac32(he_ctx* ctx, const he_plan* plan, u32 limbs, const u32* ct_in, 
                  u32* out, void* workspace, u32 accumulate, hipStream_t s) {
     int rc;
     if (pt_kind == HE_PT_SCALAR) {
-        const u64* p = static_cast<const u64*>(pt);
-        u32* wtab = static_cast<u32*>(workspace);
-        if ((rc = launch_scalar32_class<1>(ctx, plan, 0, limbs, ct_in, p, bias, out, wtab, accumulate, s)) != HE_OK) return rc;
-        if ((rc = launch_scalar32_class<4>(ctx, plan, 1, limbs, ct_in, p, bias, out, wtab, accumulate, s)) != HE_OK) return rc;
-        if ((rc = launch_scalar32_class<8>(ctx, plan, 2, limbs, ct_in, p, bias, out, wtab, accumulate, s)) != HE_OK) return rc;
-        if ((rc = launch_scalar32_class<16>(ctx, plan, 3, limbs, ct_in, p, bias, out, wtab, accumulate, s)) != HE_OK) return rc;
+        return launch_scalar32(ctx, plan, limbs, ct_in, static_cast<const u64*>(pt), bias, out, static_cast<u64*>(workspace), accumulate, s);
     } else {
         const u32* p = static_cast<const u32*>(pt);
         if ((rc = launch_poly32_class<1>(ctx, plan, 0, limbs, ct_in, p, bias, out, accumulate, s)) != HE_OK) return rc;

@@ -89,6 +89,36 @@ def test_sums_beyond_the_range_of_the_32_bit_accumulators(he, terms):
     assert np.array_equal(run(he, ctx, plan, ct, w, b, flags=he.RESCALE), layer)
 
 
+def dev32(a):
+    return torch.from_numpy(np.ascontiguousarray(a).astype(np.uint32).view(np.int32)).cuda()
+
+
+def host32(t):
+    return t.cpu().numpy().view(np.uint32).astype(np.uint64)
+
+
+@pytest.mark.parametrize("bits,groups", [
+    ([17, 24, 29, 30], [(c, t) for c in (2, 4, 5, 8, 9, 16) for t in (1, 16, 17)] + [(3, 15), (7, 64), (16, 65), (2, 129), (1, 20)]),
+    ([30, 30], [(16, 4080), (16, 4081), (3, 8161), (8, 7), (1, 4097)]),
+], ids=["sizes", "long"])
+@pytest.mark.parametrize("extreme", [False, True])
+def test_packed_group_sizes_and_term_counts(he, bits, groups, extreme):
+    N = 1 << 10
+    q = wl.modulus_chain(bits, N)
+    ctx = he.Context(10, q)
+    plan = groups_plan(groups, 40, 50, len(groups))
+    ct, w, b = operands(plan, q, N, 3 + len(groups), extreme)
+    hp = ctx.plan(plan.n_in, plan.n_out, plan.n_pt, plan.off, plan.term_ct, plan.term_pt)
+    want = oracle.mac(ct, q, plan.off, plan.term_ct, plan.term_pt, w, oracle.PT_SCALAR, b)
+    out = ctx.ct_pt_mac32(hp, dev32(ct), dev(w), he.PT_SCALAR, bias=dev(b))
+    assert np.array_equal(host32(out), want)
+    ctx.ct_pt_mac32(hp, dev32(ct), dev(w), he.PT_SCALAR, flags=he.ACCUMULATE, out=out)
+    twice = oracle.mac(ct, q, plan.off, plan.term_ct, plan.term_pt, w, oracle.PT_SCALAR)
+    assert np.array_equal(host32(out), (want + twice) % np.asarray(q, np.uint64)[:, None])
+    layer, _ = oracle.layer(ct, q, ctx.psi, plan.off, plan.term_ct, plan.term_pt, w, oracle.PT_SCALAR, b)
+    assert np.array_equal(host32(ctx.ct_pt_mac32(hp, dev32(ct), dev(w), he.PT_SCALAR, bias=dev(b), flags=he.RESCALE)), layer)
+
+
 @pytest.mark.parametrize("K,M,rescale", [(9000, 16, True), (600, 528, False)])
 def test_tables_larger_than_the_fixed_scratch_are_worked_off_in_slices(he, K, M, rescale):
     """One table that does not fit (passes over its terms), and many (ranges of groups)."""
