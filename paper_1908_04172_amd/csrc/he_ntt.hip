@@ -14,14 +14,14 @@
 
 namespace {
 
-// The stages of pass P on the 16 registers of one thread.
-template <int LOGN, int P, bool INVERSE, int MODE>
-__device__ __forceinline__ void run_pass(u64 (&a)[16], const PassTwiddles<LOGN, P>& pt, const LimbConst& c) {
+// Stages K0 .. K1 - 1 of pass P on the 16 registers of one thread (in the inverse transform in falling order).
+template <int LOGN, int P, bool INVERSE, int MODE, int K0, int K1>
+__device__ __forceinline__ void run_stages(u64 (&a)[16], const PassTwiddles<LOGN, P>& pt, const LimbConst& c) {
     using S = PassShape<LOGN, P>;
     static_assert(!(INVERSE && MODE == 2), "the inverse transform has modes 0 and 1 only");
 #pragma unroll
-    for (int kk = 0; kk < S::NST; kk++) {
-        const int k = INVERSE ? S::NST - 1 - kk : kk;
+    for (int kk = K0; kk < K1; kk++) {
+        const int k = INVERSE ? K1 - 1 - (kk - K0) : kk;
         const int s = 4 * P + k;       // stage
         const int bit = S::NST - 1 - k;   // register-index bit that the stage pairs
 #pragma unroll
@@ -45,35 +45,50 @@ __device__ __forceinline__ void run_pass(u64 (&a)[16], const PassTwiddles<LOGN, 
     }
 }
 
+// A pass with the regrouping before it (FROM: the pass whose order the registers are in).  The twiddles of a pass that
+// reads them per lane are up to 15 two-word entries, 60 registers, next to 32 of residues: half of them, those of the
+// last stage, are therefore requested apart from the others, so that never more than about 50 are held and the kernels
+// fit 128 registers (four wavefronts per SIMD) almost without spills.  Forward: the stage's own are requested one stage
+// ahead; inverse (where it runs first): the others are requested while it runs.
+template <int LOGN, int P, bool INVERSE, int MODE, int FROM>
+__device__ __forceinline__ void pass_int(u64 (&a)[16], const u64* tw, u64* lds, u32 tid, const LimbConst& c) {
+    using S = PassShape<LOGN, P>;
+    constexpr int L = S::NST - 1;  // the last stage
+    const Twiddle* t = reinterpret_cast<const Twiddle*>(tw);
+    PassTwiddles<LOGN, P> pt;
+    if constexpr (S::UNIFORM || S::NST == 1) {
+        load_pass_twiddles<LOGN, P>(pt, t, tid);
+        if constexpr (FROM != P) regroup<LOGN, FROM, P>(a, lds, tid);
+        run_stages<LOGN, P, INVERSE, MODE, 0, S::NST>(a, pt, c);
+    } else if constexpr (!INVERSE) {
+        load_pass_twiddles<LOGN, P, 0, L>(pt, t, tid);
+        if constexpr (FROM != P) regroup<LOGN, FROM, P>(a, lds, tid);
+        run_stages<LOGN, P, false, MODE, 0, L - 1>(a, pt, c);
+        u32 tid_l = tid;
+        asm volatile("" : "+v"(tid_l), "+v"(a[0]), "+v"(a[15]));  // not before the stages above
+        load_pass_twiddles<LOGN, P, L, S::NST>(pt, t, tid_l);
+        run_stages<LOGN, P, false, MODE, L - 1, S::NST>(a, pt, c);
+    } else {
+        load_pass_twiddles<LOGN, P, L, S::NST>(pt, t, tid);
+        if constexpr (FROM != P) regroup<LOGN, FROM, P>(a, lds, tid);
+        u32 tid_l = tid;
+        asm volatile("" : "+v"(tid_l), "+v"(a[0]), "+v"(a[15]));
+        load_pass_twiddles<LOGN, P, 0, L>(pt, t, tid_l);
+        run_stages<LOGN, P, true, MODE, L, S::NST>(a, pt, c);
+        run_stages<LOGN, P, true, MODE, 0, L>(a, pt, c);
+    }
+}
+
 // Registers in pass-0 order, canonical -> registers in last-pass order, below 4q (mode 0), 8q
 // (mode 1) or (1 + 4*log2N)*q (mode 2).
 template <int LOGN, int MODE>
 __device__ __forceinline__ void ntt_forward(u64 (&a)[16], const u64* tw, u64* lds, u32 tid, const LimbConst& c) {
     using G = Geo<LOGN>;
     static_assert(G::NPASS >= 2 && G::NPASS <= 4, "two to four passes");
-    {
-        PassTwiddles<LOGN, 0> t0;
-        load_pass_twiddles<LOGN, 0>(t0, reinterpret_cast<const Twiddle*>(tw), tid);
-        run_pass<LOGN, 0, false, MODE>(a, t0, c);
-    }
-    {
-        PassTwiddles<LOGN, 1> t1;
-        load_pass_twiddles<LOGN, 1>(t1, reinterpret_cast<const Twiddle*>(tw), tid);
-        regroup<LOGN, 0, 1>(a, lds, tid);
-        run_pass<LOGN, 1, false, MODE>(a, t1, c);
-    }
-    if constexpr (G::NPASS > 2) {
-        PassTwiddles<LOGN, 2> t2;
-        load_pass_twiddles<LOGN, 2>(t2, reinterpret_cast<const Twiddle*>(tw), tid);
-        regroup<LOGN, 1, 2>(a, lds, tid);
-        run_pass<LOGN, 2, false, MODE>(a, t2, c);
-    }
-    if constexpr (G::NPASS > 3) {
-        PassTwiddles<LOGN, 3> t3;
-        load_pass_twiddles<LOGN, 3>(t3, reinterpret_cast<const Twiddle*>(tw), tid);
-        regroup<LOGN, 2, 3>(a, lds, tid);
-        run_pass<LOGN, 3, false, MODE>(a, t3, c);
-    }
+    pass_int<LOGN, 0, false, MODE, 0>(a, tw, lds, tid, c);
+    pass_int<LOGN, 1, false, MODE, 0>(a, tw, lds, tid, c);
+    if constexpr (G::NPASS > 2) pass_int<LOGN, 2, false, MODE, 1>(a, tw, lds, tid, c);
+    if constexpr (G::NPASS > 3) pass_int<LOGN, 3, false, MODE, 2>(a, tw, lds, tid, c);
 }
 
 // The forward transform in the limb's mode, of inputs below IN_Q * q (IN_Q <= 3: every mode takes them),
@@ -120,7 +135,7 @@ __device__ __forceinline__ void pass_f(double (&a)[16], const TwiddleF* tw, doub
     using G = Geo<LOGN>;
     constexpr bool KEEP = P == 0 || (P == G::NPASS - 1 && P >= 2 && G::REM <= 2);  // no reduction before this pass
     PassTwiddles<LOGN, P, TwiddleF> t;
-    load_pass_twiddles<LOGN, P, TwiddleF>(t, tw, tid);
+    load_pass_twiddles<LOGN, P>(t, tw, tid);
     if constexpr (P > 0) regroup<LOGN, P - 1, P>(a, lds, tid);
     if constexpr (!KEEP) {
 #pragma unroll
@@ -145,29 +160,11 @@ __device__ __forceinline__ void ntt_forward_f(double (&a)[16], const double* tw,
 template <int LOGN, int MODE>
 __device__ __forceinline__ void ntt_inverse(u64 (&a)[16], const u64* tw, u64* lds, u32 tid, const LimbConst& c) {
     using G = Geo<LOGN>;
-    if constexpr (G::NPASS > 3) {
-        PassTwiddles<LOGN, 3> t3;
-        load_pass_twiddles<LOGN, 3>(t3, reinterpret_cast<const Twiddle*>(tw), tid);
-        run_pass<LOGN, 3, true, MODE>(a, t3, c);
-    }
-    if constexpr (G::NPASS > 2) {
-        PassTwiddles<LOGN, 2> t2;
-        load_pass_twiddles<LOGN, 2>(t2, reinterpret_cast<const Twiddle*>(tw), tid);
-        if constexpr (G::NPASS > 3) regroup<LOGN, 3, 2>(a, lds, tid);
-        run_pass<LOGN, 2, true, MODE>(a, t2, c);
-    }
-    if constexpr (G::NPASS > 1) {
-        PassTwiddles<LOGN, 1> t1;
-        load_pass_twiddles<LOGN, 1>(t1, reinterpret_cast<const Twiddle*>(tw), tid);
-        if constexpr (G::NPASS > 2) regroup<LOGN, 2, 1>(a, lds, tid);
-        run_pass<LOGN, 1, true, MODE>(a, t1, c);
-    }
-    {
-        PassTwiddles<LOGN, 0> t0;
-        load_pass_twiddles<LOGN, 0>(t0, reinterpret_cast<const Twiddle*>(tw), tid);
-        if constexpr (G::NPASS > 1) regroup<LOGN, 1, 0>(a, lds, tid);
-        run_pass<LOGN, 0, true, MODE>(a, t0, c);
-    }
+    constexpr int LAST = G::NPASS - 1;
+    if constexpr (G::NPASS > 3) pass_int<LOGN, 3, true, MODE, 3>(a, tw, lds, tid, c);
+    if constexpr (G::NPASS > 2) pass_int<LOGN, 2, true, MODE, LAST < 3 ? LAST : 3>(a, tw, lds, tid, c);
+    pass_int<LOGN, 1, true, MODE, LAST < 2 ? LAST : 2>(a, tw, lds, tid, c);
+    pass_int<LOGN, 0, true, MODE, 1>(a, tw, lds, tid, c);
 }
 
 // The inverse transform on double-precision FMAs (see bfly_inv_f): registers in last-pass order, magnitude at most
@@ -180,7 +177,7 @@ __device__ __forceinline__ void pass_inv_f(double (&a)[16], const TwiddleF* tw, 
     using G = Geo<LOGN>;
     using S = PassShape<LOGN, P>;
     PassTwiddles<LOGN, P, TwiddleF> t;
-    load_pass_twiddles<LOGN, P, TwiddleF>(t, tw, tid);
+    load_pass_twiddles<LOGN, P>(t, tw, tid);
     if constexpr (P < G::NPASS - 1) {
         regroup<LOGN, P + 1, P>(a, lds, tid);
 #pragma unroll
@@ -261,6 +258,9 @@ __device__ __forceinline__ u64 canon4(u64 v, u64 q, u64 two_q) {  // [0,4q) -> [
 // split_top_kernel runs, each half is a transform of N points with twiddles of its own, laid out as a table of N
 // entries per (limb, half) (see he_ctx_create).  Work item w is half w % 2 of the long row (w / 2) * map.stride +
 // map.first, under limb map.limb_fixed if that is set, else under limb (long row) % limbs.
+// Four wavefronts per SIMD (128 registers) also where the workgroup alone would not ask for it: with 150 to 180 registers
+// a compute unit held ONE workgroup of N = 2^13 (64 KiB of LDS), whose memory and arithmetic phases had nothing to overlap
+// with; two take the rescale of 720 ciphertexts at L = 4 from 314 to 266 us and one of 845 at L = 3 from 267 to 224 us.
 enum { ROWS_PLAIN = 0, ROWS_SPREAD = 1, ROWS_SQUARE = 2, ROWS_HALVES = 3 };
 struct RowMap {
     u32 stride, first, limb_fixed;  // limb_fixed = NO_LIMB: none
@@ -268,7 +268,7 @@ struct RowMap {
 };
 constexpr u32 NO_LIMB = 0xFFFFFFFFu;
 template <int LOGN, bool INVERSE, int KIND = ROWS_PLAIN>
-__global__ void __launch_bounds__(Geo<LOGN>::T)
+__global__ void __launch_bounds__(Geo<LOGN>::T, 4)
 ntt_rows_kernel(LimbTable lt, u32 limbs, u64* data, const u64* tw_all, const double* tw_f_all, u32 rows,
                 const u64* spread_src = nullptr, u32 digits = 1, u32 last_id = 0, u64* aux = nullptr,
                 RowMap map = RowMap{1, 0, NO_LIMB}) {
@@ -428,7 +428,7 @@ ntt_rows_kernel(LimbTable lt, u32 limbs, u64* data, const u64* tw_all, const dou
 //
 // The parked t for limb i+1 is requested, and waited for, before the outputs of limb i are stored.
 template <int LOGN, bool SPLIT>
-__global__ void __launch_bounds__(Geo<LOGN>::T)
+__global__ void __launch_bounds__(Geo<LOGN>::T, 4)
 rescale_kernel(LimbTable lt, DropRow drop, u32 limbs, u32 parts, const u64* in, u64* out, const u64* tw_fwd,
                const u64* tw_inv, const double* tw_fwd_f, const double* tw_inv_f) {
     using G = Geo<LOGN>;

@@ -151,14 +151,14 @@ struct PassTwiddles {
     Tw t[PassShape<LOGN, P>::COUNT];
 };
 
-// All twiddles of pass P for this thread, requested in one go (the caller does this before the
-// regrouping that precedes the pass, so the loads overlap the LDS traffic).
-template <int LOGN, int P, typename Tw>
+// The twiddles of stages K0 .. K1 - 1 of pass P for this thread, requested in one go (all of a pass's: the caller does
+// this before the regrouping that precedes the pass, so the loads overlap the LDS traffic).
+template <int LOGN, int P, int K0 = 0, int K1 = PassShape<LOGN, P>::NST, typename Tw>
 __device__ __forceinline__ void load_pass_twiddles(PassTwiddles<LOGN, P, Tw>& pt, const Tw* tw, u32 tid) {
     using S = PassShape<LOGN, P>;
     asm("; twiddles of pass %1" : "+v"(tid) : "n"(P));  // addresses are derived here, not ahead of earlier passes
 #pragma unroll
-    for (int k = 0; k < S::NST; k++) {
+    for (int k = K0; k < K1; k++) {
         const int s = 4 * P + k;
         const int bit = S::NST - 1 - k;
 #pragma unroll
