@@ -413,6 +413,10 @@ ntt_rows_kernel(LimbTable lt, u32 limbs, u64* data, const u64* tw_all, const dou
 #pragma unroll
         for (u32 e = 0; e < 16; e++) a[e] = next[e];
         if (next_work >= rows) break;
+        // An inverse transform ends with the regrouping across wavefronts and begins with one inside them: without a
+        // barrier between two rows a wavefront could overwrite its block while a slower one still reads the last row's
+        // values from it.  (A forward transform begins with the regrouping that has the barrier.)
+        if constexpr (INVERSE) lds_barrier();
         work = next_work;
         place = next_place;
         held = next_held;

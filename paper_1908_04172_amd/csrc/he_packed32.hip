@@ -381,6 +381,7 @@ __global__ void __launch_bounds__(Geo<LOGN>::T) ntt32_rows_kernel(Limb32Table lt
         for (u32 e = 0; e < 16; e++) p[reg_index<LOGN, POUT>(tid, e)] = a[e];
 #pragma unroll
         for (u32 e = 0; e < 16; e++) a[e] = next[e];
+        if constexpr (INVERSE) lds_barrier();  // (see the 64-bit transform kernel)
     }
 }
 
