@@ -151,38 +151,50 @@ HE_HD u64 shoup_mul(u64 y, u64 w, u64 w_shoup, u64 q) {
 // scalar encoder's kernel and host entry point and by the general encoder, which passes its
 // already scaled coefficients with scale 1).  False (and all-ones residues) for a non-finite product.
 
-HE_HD bool encode_one(double value, double scale, const LimbConst* lc, u32 limbs, u64* out) {
-    const double v = value * scale;
+struct RoundedValue {
+    u64 z;          // magnitude: the integer itself, or above 2^63 the 53-bit factor of z * 2^e
+    u32 e;
+    bool negative, finite;
+};
+
+HE_HD RoundedValue round_value(double v) {
+    RoundedValue r;
     const double mag = v < 0 ? -v : v;
-    if (!(mag <= 1.7976931348623157e308)) {  // NaN or infinity
-        for (u32 i = 0; i < limbs; ++i) out[i] = ~0ull;
-        return false;
+    r.negative = v < 0;
+    r.finite = mag <= 1.7976931348623157e308;  // not NaN or infinity
+    r.e = 0;
+    if (mag < 9223372036854775808.0) {
+        const double whole = trunc(mag);
+        r.z = (u64)whole;
+        if (mag - whole >= 0.5) r.z += 1;  // mag - whole is exact; halves go away from zero
+    } else {
+        // mag = m * 2^e exactly, m a 53-bit integer, e >= 11
+        u64 bits;
+        __builtin_memcpy(&bits, &mag, sizeof bits);
+        r.z = (bits & 0xFFFFFFFFFFFFFull) | (1ull << 52);
+        r.e = (u32)(bits >> 52) - 1075u;
     }
-    const bool negative = v < 0;
-    for (u32 i = 0; i < limbs; ++i) {
-        const LimbConst& c = lc[i];
-        u64 r;
-        if (mag < 9223372036854775808.0) {
-            const double whole = trunc(mag);
-            u64 z = (u64)whole;
-            if (mag - whole >= 0.5) z += 1;  // mag - whole is exact; halves go away from zero
-            r = reduce64(z, c);
-        } else {
-            // mag = m * 2^e exactly, m a 53-bit integer, e >= 11
-            u64 bits;
-            __builtin_memcpy(&bits, &mag, sizeof bits);
-            const u64 m = (bits & 0xFFFFFFFFFFFFFull) | (1ull << 52);
-            u32 e = (u32)(bits >> 52) - 1075u;
-            u64 pow2 = 1, base = 2;
-            for (; e; e >>= 1) {
-                if (e & 1) pow2 = mul_mod(pow2, base, c);
-                base = mul_mod(base, base, c);
-            }
-            r = mul_mod(reduce64(m, c), pow2, c);
+    return r;
+}
+
+HE_HD u64 residue_of(const RoundedValue& v, const LimbConst& c) {
+    if (!v.finite) return ~0ull;
+    u64 r = v.z < c.q ? v.z : reduce64(v.z, c);
+    if (v.e) {
+        u64 pow2 = 1, base = 2;
+        for (u32 e = v.e; e; e >>= 1) {
+            if (e & 1) pow2 = mul_mod(pow2, base, c);
+            base = mul_mod(base, base, c);
         }
-        out[i] = (negative && r) ? c.q - r : r;
+        r = mul_mod(r, pow2, c);
     }
-    return true;
+    return (v.negative && r) ? c.q - r : r;
+}
+
+HE_HD bool encode_one(double value, double scale, const LimbConst* lc, u32 limbs, u64* out) {
+    const RoundedValue v = round_value(value * scale);
+    for (u32 i = 0; i < limbs; ++i) out[i] = residue_of(v, lc[i]);
+    return v.finite;
 }
 
 // ---------------------------------------------------------------------------------------------

