@@ -164,7 +164,7 @@ void fill_limb_const(LimbConst& c, u64 q, u64 psi, u32 N) {
     }
     c.ntt_mode = q < (1ull << 58) ? 2 : q < (1ull << 61) ? 1 : 0;
     c.fp_ok = q < (1ull << 50);
-    c.pad = 0;
+    c.fp_free = q < (1ull << 46);
     c.q_inv_f = 1.0 / (double)q;  // (a double holds q exactly; the division rounds to nearest)
     c.pow64 = (u64)((((u128)1) << 64) % q);
     c.pow64_shoup = h_shoup(c.pow64, q);
@@ -205,7 +205,7 @@ void fill_digit_const(DigitConst& d, const LimbConst& c) {  // (see DigitConst)
     d.mult_shift = s - 32;
     d.hi_shift = 8 * n_hi - 9;
     d.kappa8 = 8 * kappa;
-    d.lazy = c.mac_lazy;
+    d.lazy = c.mac_lazy && !c.fp_ok;  // (the combine step on doubles takes canonical residues)
     d.b8 = 1 << 8;
     d.b16 = 1 << 16;
     d.b24 = 1 << 24;
@@ -412,6 +412,7 @@ int he_ctx_create(he_ctx** out, uint32_t log2N, uint32_t L, const uint64_t* modu
             d.half_mod = (p >> 1) % qi;
             d.reduce_mode = p <= qi ? 0 : (p <= 2 * qi ? 1 : 2);
             d.fp64 = ctx->limbs.c[i].fp_ok && d.reduce_mode <= 1;
+            d.p_inv_f = ctx->limbs.c[i].fp_ok ? fp_centred(d.p_inv, qi) : 0.0;
         }
     if (device >= 0) {
         int rc = need_device(ctx);
@@ -1203,7 +1204,7 @@ int he_host_ntt_forward_fp64(he_ctx* ctx, uint32_t limb, const int64_t* in, uint
     const u32 npass = (log2N + 3) / 4, rem = log2N - 4 * (npass - 1);
     for (u32 s = 0; s < log2N; ++s) {
         const u32 pass = s / 4;
-        if (s % 4 == 0 && pass > 0 && !(pass == npass - 1 && pass >= 2 && rem <= 2))
+        if (!c.fp_free && s % 4 == 0 && pass > 0 && !(pass == npass - 1 && pass >= 2 && rem <= 2))
             for (u32 j = 0; j < N; ++j) a[j] = fp_reduce(a[j], qf, q_inv);
         const u32 m = 1u << s, t = N >> (s + 1);
         for (u32 i = 0; i < m; ++i)
@@ -1213,7 +1214,7 @@ int he_host_ntt_forward_fp64(he_ctx* ctx, uint32_t limb, const int64_t* in, uint
                 seen(a[j + t]);
             }
     }
-    for (u32 j = 0; j < N; ++j) out[j] = fp_to_canonical(fp_reduce(a[j], qf, q_inv), q);
+    for (u32 j = 0; j < N; ++j) out[j] = fp_to_canonical(fp_reduce(a[j], qf, q_inv), qf);
     if (max_over_q) *max_over_q = worst;
     return exact ? HE_OK : HE_ERR_RANGE;
 }
@@ -1270,7 +1271,7 @@ int he_host_ntt_inverse_fp64(he_ctx* ctx, uint32_t limb, const uint64_t* in, uin
                 seen(a[j + t]);
             }
     }
-    for (u32 j = 0; j < N; ++j) out[j] = fp_to_canonical(fp_reduce(a[j], qf, q_inv), q);
+    for (u32 j = 0; j < N; ++j) out[j] = fp_to_canonical(fp_reduce(a[j], qf, q_inv), qf);
     if (max_over_q) *max_over_q = worst;
     return exact ? HE_OK : HE_ERR_RANGE;
 }

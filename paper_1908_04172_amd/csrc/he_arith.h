@@ -32,7 +32,7 @@ struct LimbConst {
     u32 mac_lazy;     // 1: the rescale kernel can combine a MAC result that is only congruent to the sum and below 12q
                       // with its transformed correction without leaving 64 bits (depends on q, the butterfly mode and N)
     u32 fp_ok;        // 1: q < 2^50, the forward transform can run on double-precision FMAs (see bfly_fwd_f)
-    u32 pad;
+    u32 fp_free;      // 1: q < 2^46, that transform needs no reduction between its stages (see bfly_fwd_f)
     double q_inv_f;   // 1 / q, rounded to nearest
     u64 pow64, pow64_shoup;  // 2^64 mod q and its Shoup companion (acc_reduce_lazy)
 };
@@ -363,7 +363,7 @@ struct DigitConst {
     u32 mult_shift;        // s - 32
     u32 hi_shift;          // 8 d - 9
     u32 kappa8;            // 8 kappa
-    u32 lazy;              // 1: the rescale kernel takes the unreduced sum (LimbConst::mac_lazy)
+    u32 lazy;              // 1: the rescale kernel takes the unreduced sum (LimbConst::mac_lazy, limbs on integer butterflies)
     int32_t b8, b16, b24;  // 2^8, 2^16, 2^24, as data: multiplied by a literal they become shifts and additions, four
                            // instructions instead of one multiply-add
 };
@@ -502,6 +502,8 @@ __device__ __forceinline__ void bfly_inv(u64& x, u64& y, Twiddle t, const LimbCo
 // (0.5 + 1.1875*B) * q: from B = 1, four stages end below 4.63q; from B = 0.5 (after fp_reduce), four stages end
 // below 3.64q, six below 6.22q, seven below 7.88q -- all below 2^53 for q < 2^50.  (The bound on r uses exactness,
 // not the other way round: h - k*q + l is W*Y - k*q whatever k is, as long as it stays below 2^53.)
+// Below 2^46 (LimbConst::fp_free) the estimate is off by less than 3 * 2^-53 * B * 2^45 < 0.0118 B: a butterfly takes B*q
+// to at most (0.5 + 1.0118 B) * q, fourteen stages take 2q to 9.93q < 2^50, and nothing is reduced between the stages.
 struct TwiddleF {
     double w;  // the twiddle's representative in (-q/2, q/2)
 };
@@ -539,15 +541,12 @@ HE_HD void bfly_inv_f(double& x, double& y, TwiddleF t, double q, double q_inv) 
 // the representative of v < q in (-q/2, q/2), as a double (q < 2^52)
 HE_HD double fp_centred(u64 v, u64 q) { return v > q / 2 ? -(double)(int64_t)(q - v) : (double)(int64_t)v; }
 
-// the canonical residue of an integer-valued double y with |y| below 2^51 that is within q of zero: the integer
-// is read off the mantissa of y + 1.5 * 2^52, and q is added to a negative one
-HE_HD u64 fp_to_canonical(double y, u64 q) {
-    const int64_t v = (int64_t)(__builtin_bit_cast(u64, y + 6755399441055744.0) - 0x4338000000000000ull);
-    return (u64)v + ((u64)(v >> 63) & q);
+// the canonical residue of an integer-valued double y within q < 2^50 of zero: y plus 2^52, or plus 2^52 + q where it is
+// negative, has the residue as its mantissa (a comparison, two selects, an addition and a mask)
+HE_HD u64 fp_to_canonical(double y, double q) {
+    const double v = y + (y < 0 ? 4503599627370496.0 + q : 4503599627370496.0);
+    return __builtin_bit_cast(u64, v) & 0xFFFFFFFFFFFFFull;
 }
 
-// 1.5 * 2^52: adding it to an integer-valued double of magnitude below 2^51 puts that integer, as a two's
-// complement offset, into the low mantissa bits
-#define HE_FP_MAGIC 6755399441055744.0
 // a double holding the integer v < 2^52, from OR-ing it into the mantissa of 2^52
 HE_HD double fp_from_u52(u64 v) { return __builtin_bit_cast(double, v | 0x4330000000000000ull) - 4503599627370496.0; }

@@ -30,6 +30,7 @@ struct DropConst {
     u64 half_mod;            // floor(q_j / 2) mod q_i
     u32 reduce_mode;         // a value below q_j is below q_i already (0), after one subtraction (1), or needs a full reduction (2)
     u32 fp64;                // 1: q_i < 2^50 and q_j <= 2*q_i: the correction's transform runs on doubles (ntt_forward_f)
+    double p_inv_f;          // the representative of p_inv in (-q_i/2, q_i/2), for q_i < 2^50 (else 0)
 };
 
 // The constants of one dropped limb against every kept limb, passed to the rescale kernel by value

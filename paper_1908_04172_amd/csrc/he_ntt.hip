@@ -14,6 +14,18 @@
 
 namespace {
 
+// A wave-uniform selector, as a value of its own each time.  The alternatives of a limb (integer modes, doubles) are
+// written as one `if` after another on such values, not as if / else: the compiler lays an if / else out as "then, else"
+// in a row and keeps the sixteen residues that the else part would need alive through the then part, 32 registers that
+// end up in scratch memory.  (With this and the scalar addresses of row_at the transform kernels take 108 to 116 registers
+// and no scratch, and the rescale with its combine step on doubles takes 218 us for 720 ciphertexts of N = 2^13 at L = 4 and
+// 205 for 845 at L = 3, where it took 314 and 267 at 150 to 167 registers.)
+__device__ __forceinline__ u32 choice(u32 v) {
+    v = __builtin_amdgcn_readfirstlane(v);
+    asm volatile("" : "+s"(v));
+    return v;
+}
+
 // Stages K0 .. K1 - 1 of pass P on the 16 registers of one thread (in the inverse transform in falling order).
 template <int LOGN, int P, bool INVERSE, int MODE, int K0, int K1>
 __device__ __forceinline__ void run_stages(u64 (&a)[16], const PassTwiddles<LOGN, P>& pt, const LimbConst& c) {
@@ -97,25 +109,29 @@ __device__ __forceinline__ void ntt_forward(u64 (&a)[16], const u64* tw, u64* ld
 template <int LOGN, int IN_Q = 1>
 __device__ __forceinline__ u64 ntt_forward_any(u64 (&a)[16], const u64* tw, u64* lds, u32 tid, const LimbConst& c) {
     static_assert(IN_Q >= 1 && IN_Q <= 3 && IN_Q + 4 * LOGN + 1 <= 64, "mode 2: (IN_Q + 4*log2N + 1) * q stays below 2^64 for q < 2^58");
-    if (c.ntt_mode == 2) {
+    u64 cap = 0;
+    if (choice(c.ntt_mode) == 2) {
         ntt_forward<LOGN, 2>(a, tw, lds, tid, c);
-        return c.q * (4 * LOGN + IN_Q);
+        cap = c.q * (4 * LOGN + IN_Q);
     }
-    if (c.ntt_mode == 1) {
+    if (choice(c.ntt_mode) == 1) {
         ntt_forward<LOGN, 1>(a, tw, lds, tid, c);
 #pragma unroll
         for (u32 e = 0; e < 16; e++) a[e] = sub_if_ge(a[e], c.neg_four_q);
-        return c.four_q;
+        cap = c.four_q;
     }
-    ntt_forward<LOGN, 0>(a, tw, lds, tid, c);
-    return 2 * c.two_q;
+    if (choice(c.ntt_mode) == 0) {
+        ntt_forward<LOGN, 0>(a, tw, lds, tid, c);
+        cap = 2 * c.two_q;
+    }
+    return cap;
 }
 
 // The forward transform on double-precision FMAs, for limbs with LimbConst::fp_ok (see bfly_fwd_f): registers in
 // pass-0 order holding integers of magnitude at most q -> registers in last-pass order, magnitude below 6.22q
 // (3.64q when the last pass has four stages).  The values are brought back to q/2 before every pass but the
 // first and, when it has at most two stages and a full pass before it, the last: at most six stages run between
-// two reductions.
+// two reductions.  (Limbs with LimbConst::fp_free: no reduction at all, magnitude below 9.93q.)
 template <int LOGN, int P>
 __device__ __forceinline__ void run_pass_f(double (&a)[16], const PassTwiddles<LOGN, P, TwiddleF>& pt, double q, double q_inv) {
     using S = PassShape<LOGN, P>;
@@ -131,15 +147,17 @@ __device__ __forceinline__ void run_pass_f(double (&a)[16], const PassTwiddles<L
 }
 
 template <int LOGN, int P>
-__device__ __forceinline__ void pass_f(double (&a)[16], const TwiddleF* tw, double* lds, u32 tid, double q, double q_inv) {
+__device__ __forceinline__ void pass_f(double (&a)[16], const TwiddleF* tw, double* lds, u32 tid, const LimbConst& c, double q, double q_inv) {
     using G = Geo<LOGN>;
     constexpr bool KEEP = P == 0 || (P == G::NPASS - 1 && P >= 2 && G::REM <= 2);  // no reduction before this pass
     PassTwiddles<LOGN, P, TwiddleF> t;
     load_pass_twiddles<LOGN, P>(t, tw, tid);
     if constexpr (P > 0) regroup<LOGN, P - 1, P>(a, lds, tid);
     if constexpr (!KEEP) {
+        if (!c.fp_free) {
 #pragma unroll
-        for (u32 e = 0; e < 16; e++) a[e] = fp_reduce(a[e], q, q_inv);
+            for (u32 e = 0; e < 16; e++) a[e] = fp_reduce(a[e], q, q_inv);
+        }
     }
     run_pass_f<LOGN, P>(a, t, q, q_inv);
 }
@@ -150,10 +168,10 @@ __device__ __forceinline__ void ntt_forward_f(double (&a)[16], const double* tw,
     static_assert(G::NPASS >= 2 && G::NPASS <= 4, "two to four passes");
     const double q = (double)c.q, q_inv = c.q_inv_f;
     const TwiddleF* t = reinterpret_cast<const TwiddleF*>(tw);
-    pass_f<LOGN, 0>(a, t, lds, tid, q, q_inv);
-    pass_f<LOGN, 1>(a, t, lds, tid, q, q_inv);
-    if constexpr (G::NPASS > 2) pass_f<LOGN, 2>(a, t, lds, tid, q, q_inv);
-    if constexpr (G::NPASS > 3) pass_f<LOGN, 3>(a, t, lds, tid, q, q_inv);
+    pass_f<LOGN, 0>(a, t, lds, tid, c, q, q_inv);
+    pass_f<LOGN, 1>(a, t, lds, tid, c, q, q_inv);
+    if constexpr (G::NPASS > 2) pass_f<LOGN, 2>(a, t, lds, tid, c, q, q_inv);
+    if constexpr (G::NPASS > 3) pass_f<LOGN, 3>(a, t, lds, tid, c, q, q_inv);
 }
 
 // Registers in last-pass order, canonical -> registers in pass-0 order, below 2q, multiplied by N^-1.
@@ -221,19 +239,18 @@ __device__ __forceinline__ void ntt_inverse_f(double (&a)[16], const double* tw,
 // results), else on the integer butterflies (results below 2q).
 template <int LOGN>
 __device__ __forceinline__ void ntt_inverse_any(u64 (&a)[16], const u64* tw, const double* tw_f, u64* lds, u32 tid, const LimbConst& c) {
-    if (c.fp_ok) {
+    if (choice(c.fp_ok)) {
         const double q_f = (double)c.q;
         double f[16];
 #pragma unroll
         for (u32 e = 0; e < 16; e++) f[e] = fp_reduce(fp_from_u52(a[e]), q_f, c.q_inv_f);
         ntt_inverse_f<LOGN>(f, tw_f, reinterpret_cast<double*>(lds), tid, c);
 #pragma unroll
-        for (u32 e = 0; e < 16; e++) a[e] = fp_to_canonical(fp_reduce(f[e], q_f, c.q_inv_f), c.q);
-    } else if (c.ntt_mode != 0) {
-        ntt_inverse<LOGN, 1>(a, tw, lds, tid, c);
-    } else {
-        ntt_inverse<LOGN, 0>(a, tw, lds, tid, c);
+        for (u32 e = 0; e < 16; e++) a[e] = fp_to_canonical(fp_reduce(f[e], q_f, c.q_inv_f), q_f);
     }
+    const u32 integer = c.fp_ok ? 0 : c.ntt_mode != 0 ? 1 : 2;
+    if (choice(integer) == 1) ntt_inverse<LOGN, 1>(a, tw, lds, tid, c);
+    if (choice(integer) == 2) ntt_inverse<LOGN, 0>(a, tw, lds, tid, c);
 }
 
 __device__ __forceinline__ u64 canon4(u64 v, u64 q, u64 two_q) {  // [0,4q) -> [0,q)
@@ -246,7 +263,9 @@ __device__ __forceinline__ u64 canon4(u64 v, u64 q, u64 two_q) {  // [0,4q) -> [
 // the current one, so that the loads do not queue behind the stores and arrive while those drain.
 // KIND = ROWS_SPREAD (forward only): a row is not read from `data` but from a row of `spread_src`, a table of
 // coefficient rows [..][digits][N] whose row (.., j) holds integers below q_j; they are reduced
-// modulo the target limb first.  This is the digit expansion of a key switch: each
+// modulo the target limb first, unless q_j is at most twice that limb's modulus: both forms of the transform take
+// values below 2q (integer ones below 3q; doubles end the first pass below 6.62q < 2^53, see bfly_fwd_f).  Seven 50- and
+// 60-bit digits of 256 ciphertexts of N = 2^14 under eight limbs: 1165 us with a reduction of every digit, 890 us.  This is the digit expansion of a key switch: each
 // digit transformed under every limb, written to data [..][digits][limbs][N]; the limbs are
 // q_0..q_{limbs-2} and, at the last position, the special prime (limb `last_id` of the context).
 // KIND = ROWS_SQUARE (inverse only): row r = (ciphertext, limb j) is the slot-wise square of component 1 of that
@@ -260,7 +279,7 @@ __device__ __forceinline__ u64 canon4(u64 v, u64 q, u64 two_q) {  // [0,4q) -> [
 // map.first, under limb map.limb_fixed if that is set, else under limb (long row) % limbs.
 // Four wavefronts per SIMD (128 registers) also where the workgroup alone would not ask for it: with 150 to 180 registers
 // a compute unit held ONE workgroup of N = 2^13 (64 KiB of LDS), whose memory and arithmetic phases had nothing to overlap
-// with; two take the rescale of 720 ciphertexts at L = 4 from 314 to 266 us and one of 845 at L = 3 from 267 to 224 us.
+// with; two took the layer of 720 outputs at L = 4 from 575 to 530 us, an elementwise one of 845 at L = 3 from 383 to 341.
 enum { ROWS_PLAIN = 0, ROWS_SPREAD = 1, ROWS_SQUARE = 2, ROWS_HALVES = 3 };
 struct RowMap {
     u32 stride, first, limb_fixed;  // limb_fixed = NO_LIMB: none
@@ -306,7 +325,7 @@ ntt_rows_kernel(LimbTable lt, u32 limbs, u64* data, const u64* tw_all, const dou
     {
         const u64* p = source(blockIdx.x);
 #pragma unroll
-        for (u32 e = 0; e < 16; e++) a[e] = p[reg_index<LOGN, PIN>(threadIdx.x, e)];
+        for (u32 e = 0; e < 16; e++) a[e] = row_at<LOGN, PIN>(p, threadIdx.x, e);
     }
     // Work items are taken in slabs of gridDim.x, workgroup b taking item (b + k / hold) % gridDim.x of slab k: with a plain
     // stride a workgroup would meet the same limb in every slab whenever the limb count divides the grid, and the
@@ -333,8 +352,8 @@ ntt_rows_kernel(LimbTable lt, u32 limbs, u64* data, const u64* tw_all, const dou
         u32 tid_i = threadIdx.x;  // opaque per iteration: addresses are recomputed, not kept live
         asm volatile("" : "+v"(tid_i));
         const u32 tid = tid_i;
-        u32 src_row_unused = 0;
-        const u32 row = SPREAD ? spread_row(work, src_row_unused) : work;
+        u32 src_row = 0;
+        const u32 row = SPREAD ? spread_row(work, src_row) : work;
         const u32 long_row = (work >> 1) * map.stride + map.first;  // HALVES only
         const u32 limb = HALVES ? (map.limb_fixed != NO_LIMB ? map.limb_fixed : long_row % limbs) : row % limbs;
         const LimbConst& c = lt.c[limb];
@@ -343,30 +362,31 @@ ntt_rows_kernel(LimbTable lt, u32 limbs, u64* data, const u64* tw_all, const dou
         // (halves: the table has a block of N entries per limb and half)
         const u32 tw_limb = HALVES ? limb * 2 + (work & 1u) : SPREAD && limb == limbs - 1 ? last_id : limb;
         const u64* tw = tw_all + (size_t)tw_limb * G::N * 2;
-        const bool fp = !INVERSE && c.fp_ok;  // the forward transform of a limb below 2^50 runs on doubles
+        const u32 fp = !INVERSE && c.fp_ok;  // the forward transform of a limb below 2^50 runs on doubles
         if constexpr (SPREAD) {
+            if (lt.c[src_row % digits].q > c.two_q) {
 #pragma unroll
-            for (u32 e = 0; e < 16; e++) a[e] = reduce64(a[e], c);
+                for (u32 e = 0; e < 16; e++) a[e] = reduce64(a[e], c);
+            }
         }
         if constexpr (SQUARE) {
             u64* own = aux + ((size_t)row * (limbs + 1) + limb) * G::N;
 #pragma unroll
             for (u32 e = 0; e < 16; e++) {
                 a[e] = mul_mod(a[e], a[e], c);
-                own[reg_index<LOGN, PIN>(tid, e)] = a[e];
+                row_at<LOGN, PIN>(own, tid, e) = a[e];
             }
         }
         if constexpr (!INVERSE) {
-            if (fp) {
+            if (choice(fp)) {
                 double f[16];
 #pragma unroll
                 for (u32 e = 0; e < 16; e++) f[e] = fp_from_u52(a[e]);
                 ntt_forward_f<LOGN>(f, tw_f_all + (size_t)tw_limb * G::N, reinterpret_cast<double*>(lds), tid, c);
 #pragma unroll
                 for (u32 e = 0; e < 16; e++) a[e] = __builtin_bit_cast(u64, f[e]);
-            } else {
-                ntt_forward_any<LOGN>(a, tw, lds, tid, c);
             }
+            if (!choice(fp)) ntt_forward_any<LOGN, SPREAD ? 2 : 1>(a, tw, lds, tid, c);
         } else {
             ntt_inverse_any<LOGN>(a, tw, tw_f_all + (size_t)tw_limb * G::N, lds, tid, c);
         }
@@ -380,14 +400,14 @@ ntt_rows_kernel(LimbTable lt, u32 limbs, u64* data, const u64* tw_all, const dou
         if (next_work < rows) {
             const u64* p = source(next_work);
 #pragma unroll
-            for (u32 e = 0; e < 16; e++) next[e] = p[reg_index<LOGN, PIN>(tid_s, e)];
+            for (u32 e = 0; e < 16; e++) next[e] = row_at<LOGN, PIN>(p, tid_s, e);
         }
         if constexpr (!INVERSE) {
             if (fp) {
                 // reduced to |y| <= q/2 + 1, then the canonical residue
                 const double q_f = (double)c.q;
 #pragma unroll
-                for (u32 e = 0; e < 16; e++) a[e] = fp_to_canonical(fp_reduce(__builtin_bit_cast(double, a[e]), q_f, c.q_inv_f), c.q);
+                for (u32 e = 0; e < 16; e++) a[e] = fp_to_canonical(fp_reduce(__builtin_bit_cast(double, a[e]), q_f, c.q_inv_f), q_f);
             } else {
                 if (c.ntt_mode == 2) {
                     // below 57q: a Shoup product by 1 (whose companion is floor(2^64/q)) brings it below 4q
@@ -409,7 +429,7 @@ ntt_rows_kernel(LimbTable lt, u32 limbs, u64* data, const u64* tw_all, const dou
         }
         u64* p = HALVES ? const_cast<u64*>(source(work)) : data + (size_t)row * G::N;
 #pragma unroll
-        for (u32 e = 0; e < 16; e++) p[reg_index<LOGN, POUT>(tid_s, e)] = a[e];
+        for (u32 e = 0; e < 16; e++) row_at<LOGN, POUT>(p, tid_s, e) = a[e];
 #pragma unroll
         for (u32 e = 0; e < 16; e++) a[e] = next[e];
         if (next_work >= rows) break;
@@ -457,7 +477,7 @@ rescale_kernel(LimbTable lt, DropRow drop, u32 limbs, u32 parts, const u64* in, 
         const LimbConst& c = lt.c[last];
         const u64* row = src + (size_t)last * G::N;
 #pragma unroll
-        for (u32 e = 0; e < 16; e++) a[e] = row[reg_index<LOGN, G::NPASS - 1>(tid, e)];
+        for (u32 e = 0; e < 16; e++) a[e] = row_at<LOGN, G::NPASS - 1>(row, tid, e);
         ntt_inverse_any<LOGN>(a, tw_inv + (size_t)last * G::N * 2, tw_inv_f + (size_t)last * G::N, lds, tid, c);
         const u64 half = c.q >> 1;
         const u32 tid_s = fresh(tid);
@@ -466,7 +486,10 @@ rescale_kernel(LimbTable lt, DropRow drop, u32 limbs, u32 parts, const u64* in, 
             u64 v = a[e];
             v = v >= c.q ? v - c.q : v;
             a[e] = add_mod(v, half, c.q);
-            if (end - first > 1) park[reg_index<LOGN, 0>(tid_s, e)] = a[e];
+        }
+        if (end - first > 1) {
+#pragma unroll
+            for (u32 e = 0; e < 16; e++) row_at<LOGN, 0>(park, tid_s, e) = a[e];
         }
     }
     for (u32 i = first; i < end; i++) {
@@ -484,21 +507,50 @@ rescale_kernel(LimbTable lt, DropRow drop, u32 limbs, u32 parts, const u64* in, 
         // are acknowledged by the L2).  Hence the order below: every load the next iteration needs is issued AND
         // waited for before this iteration's stores are issued, and the transform that follows starts on scalar
         // loads (its first two passes' twiddles), with nothing to wait for behind the stores.
-        // The transformed correction stays below `cap` (a multiple of q), so x + cap - correction is
-        // positive, congruent to x - correction and fits 64 bits; the Shoup product takes it as it is.
-        u64 cap;
-        if (d.fp64) {
+        // (The two forms of a limb's iteration are separate code from the transform to the stores, see choice().)
+        auto finish = [&](auto combine) {
+            __builtin_amdgcn_sched_barrier(0);  // the loads not before the last stage: their registers are in use
+            const u32 tid_s = fresh(tid);
+            u64 x[16], next[16];
+#pragma unroll
+            for (u32 e = 0; e < 16; e++) x[e] = row_at<LOGN, G::NPASS - 1>(xrow, tid_s, e);
+#pragma unroll
+            for (u32 e = 0; e < 16; e++) next[e] = 0;
+            if (i + 1 < end) {
+#pragma unroll
+                for (u32 e = 0; e < 16; e++) next[e] = row_at<LOGN, 0>(park, tid_s, e);
+            }
+#pragma unroll
+            for (u32 e = 0; e < 16; e++) {
+                x[e] = combine(x[e], a[e]);
+            }
+#pragma unroll
+            for (u32 e = 0; e < 16; e++) {
+                a[e] = next[e];
+                asm volatile("" : "+v"(a[e]) :: "memory");  // t for the next limb has arrived: nothing is left to wait for
+            }
+#pragma unroll
+            for (u32 e = 0; e < 16; e++) row_at<LOGN, G::NPASS - 1>(orow, tid_s, e) = x[e];
+        };
+        if (choice(d.fp64)) {
             // q_i < 2^50 and p <= 2*q_i: the transform runs on doubles.  t - h as an integer lies in [-h, h],
-            // within q_i in magnitude; it is formed from t < 2^52 directly as a double.
-            const double half_f = (double)(lt.c[last].q >> 1);
+            // within q_i in magnitude; it is formed from t < 2^52 directly as a double (see fp_from_u52: 2^52 + h is exact).
+            const double offset = 4503599627370496.0 + (double)(lt.c[last].q >> 1), q_f = (double)c.q, p_inv = d.p_inv_f;
             double f[16];
 #pragma unroll
-            for (u32 e = 0; e < 16; e++) f[e] = fp_from_u52(a[e]) - half_f;
+            for (u32 e = 0; e < 16; e++) f[e] = __builtin_bit_cast(double, a[e] | 0x4330000000000000ull) - offset;
             ntt_forward_f<LOGN>(f, tw_fwd_f + (size_t)i * G::N, reinterpret_cast<double*>(lds), tid, c);
 #pragma unroll
             for (u32 e = 0; e < 16; e++) a[e] = __builtin_bit_cast(u64, f[e]);
-            cap = c.q + __builtin_bit_cast(u64, HE_FP_MAGIC);
-        } else {
+            // The combine step on doubles too: x - y of a canonical x and the correction y reduced to q/2 is below 1.51q
+            // in magnitude, and its product with p^-1 within 0.79q of zero: 17 instructions per value, where the integer
+            // form (mantissa differences, an exact Shoup product) took 31, a quarter of such a limb's iteration.
+            finish([&](u64 x, u64 y) {
+                const double diff = fp_from_u52(x) - fp_reduce(__builtin_bit_cast(double, y), q_f, c.q_inv_f);
+                return fp_to_canonical(fp_mulmod(p_inv, diff, q_f, c.q_inv_f), q_f);
+            });
+        }
+        if (!choice(d.fp64)) {
             // t < p is below 2*q_i unless p > 2*q_i (then a full reduction comes first); adding q_i - (h mod q_i)
             // gives a value congruent to t - h and below 3*q_i, which the forward transform takes as it is
             if (d.reduce_mode == 2) {
@@ -508,40 +560,16 @@ rescale_kernel(LimbTable lt, DropRow drop, u32 limbs, u32 parts, const u64* in, 
             const u64 minus_half = c.q - d.half_mod;
 #pragma unroll
             for (u32 e = 0; e < 16; e++) a[e] += minus_half;
-            cap = ntt_forward_any<LOGN, 3>(a, tw_fwd + (size_t)i * G::N * 2, lds, tid, c);
+            // The transformed correction stays below `cap` (a multiple of q), so x + cap - correction is
+            // positive, congruent to x - correction and fits 64 bits; the Shoup product takes it as it is.
+            u64 cap = ntt_forward_any<LOGN, 3>(a, tw_fwd + (size_t)i * G::N * 2, lds, tid, c);
             if (c.ntt_mode == 0) {  // 5q need not fit 64 bits, 3q does
 #pragma unroll
                 for (u32 e = 0; e < 16; e++) a[e] = sub_if_ge(a[e], c.neg_two_q);
                 cap = c.two_q;
             }
+            finish([&](u64 x, u64 y) { return shoup_mul(x + cap - y, d.p_inv, d.p_inv_shoup, c.q); });
         }
-        const u32 tid_s = fresh(tid);
-        u64 x[16], next[16];
-#pragma unroll
-        for (u32 e = 0; e < 16; e++) x[e] = xrow[reg_index<LOGN, G::NPASS - 1>(tid_s, e)];
-#pragma unroll
-        for (u32 e = 0; e < 16; e++) next[e] = 0;
-        if (i + 1 < end) {
-#pragma unroll
-            for (u32 e = 0; e < 16; e++) next[e] = park[reg_index<LOGN, 0>(tid_s, e)];
-        }
-        if (d.fp64) {
-            // the transformed correction y, reduced to |y| <= q/2 + 1, as the mantissa offset of y + 1.5 * 2^52:
-            // x + (q + bits of 1.5 * 2^52) - bits of (y + 1.5 * 2^52) = x + q - y, positive and below 14q
-            const double q_f = (double)c.q;
-#pragma unroll
-            for (u32 e = 0; e < 16; e++)
-                a[e] = __builtin_bit_cast(u64, fp_reduce(__builtin_bit_cast(double, a[e]), q_f, c.q_inv_f) + HE_FP_MAGIC);
-        }
-#pragma unroll
-        for (u32 e = 0; e < 16; e++) x[e] = shoup_mul(x[e] + cap - a[e], d.p_inv, d.p_inv_shoup, c.q);
-#pragma unroll
-        for (u32 e = 0; e < 16; e++) {
-            a[e] = next[e];
-            asm volatile("" : "+v"(a[e]) :: "memory");  // t for the next limb has arrived: nothing is left to wait for
-        }
-#pragma unroll
-        for (u32 e = 0; e < 16; e++) orow[reg_index<LOGN, G::NPASS - 1>(tid_s, e)] = x[e];
     }
 }
 
@@ -688,6 +716,14 @@ int launch_rescale_split(he_ctx* ctx, u32 limbs, u32 drop_id, const u64* in, u64
     return HE_OK;
 }
 
+// workgroups that a compute unit holds at once: its LDS, and four wavefronts per SIMD (the kernels' register limit)
+template <int LOGN>
+constexpr u32 resident_per_cu() {
+    using G = Geo<LOGN>;
+    const u32 by_lds = (160u << 10) / (G::N * (u32)sizeof(u64)), by_waves = 1024 / G::T;
+    return by_lds < by_waves ? by_lds : by_waves;
+}
+
 template <int LOGN>
 int launch_ntt_t(he_ctx* ctx, u32 limbs, u64* data, u32 rows, bool inverse, const u64* src, hipStream_t s) {
     using G = Geo<LOGN>;
@@ -695,7 +731,7 @@ int launch_ntt_t(he_ctx* ctx, u32 limbs, u64* data, u32 rows, bool inverse, cons
     const size_t lds = (size_t)G::N * sizeof(u64);
     // as many workgroups as stay resident at once (LDS and the 2048 threads of a compute unit bound
     // that), each looping over its share of the rows
-    const u32 per_cu = (u32)std::max<size_t>(1, std::min<size_t>((160u << 10) / lds, 2048 / G::T));
+    const u32 per_cu = resident_per_cu<LOGN>();
     const u32 grid = std::min<u32>(rows, 256 * per_cu);
     if (inverse) {
         static std::atomic<uint32_t> lds_allowed{0};
@@ -716,7 +752,7 @@ int launch_ntt_spread_t(he_ctx* ctx, u32 limbs, const u64* src, u64* out, u32 ro
     lt.c[limbs - 1] = ctx->limbs.c[ctx->L - 1];
     using G = Geo<LOGN>;
     const size_t lds = (size_t)G::N * sizeof(u64);
-    const u32 per_cu = (u32)std::max<size_t>(1, std::min<size_t>((160u << 10) / lds, 2048 / G::T));
+    const u32 per_cu = resident_per_cu<LOGN>();
     const u32 grid = std::min<u32>(rows, 256 * per_cu);
     static std::atomic<uint32_t> lds_allowed{0};
     if (int rc = allow_dynamic_lds((const void*)ntt_rows_kernel<LOGN, false, ROWS_SPREAD>, lds, ctx->device, lds_allowed, true)) return rc;
@@ -732,7 +768,7 @@ template <int LOGN>
 int launch_ntt_square_t(he_ctx* ctx, u32 limbs, const u64* ct, u64* d2, u64* digits, u32 rows, hipStream_t s) {
     using G = Geo<LOGN>;
     const size_t lds = (size_t)G::N * sizeof(u64);
-    const u32 per_cu = (u32)std::max<size_t>(1, std::min<size_t>((160u << 10) / lds, 2048 / G::T));
+    const u32 per_cu = resident_per_cu<LOGN>();
     const u32 grid = std::min<u32>(rows, 256 * per_cu);
     static std::atomic<uint32_t> lds_allowed{0};
     if (int rc = allow_dynamic_lds((const void*)ntt_rows_kernel<LOGN, true, ROWS_SQUARE>, lds, ctx->device, lds_allowed, true)) return rc;
@@ -761,7 +797,7 @@ int launch_rescale_t(he_ctx* ctx, u32 limbs, u32 drop_id, const u64* in, u64* ou
     for (u32 i = 0; i < HE_MAX_LIMBS; i++) row.d[i] = ctx->drop[drop_id][i];
     // with fewer polynomials than workgroups the chip holds at once, split each over several workgroups
     // (at most one per kept limb), as far as they still all run at the same time
-    const u32 resident = 256 * (u32)std::max<size_t>(1, std::min<size_t>((160u << 10) / lds, 2048 / G::T));
+    const u32 resident = 256 * resident_per_cu<LOGN>();
     const u32 parts = std::max(1u, std::min(limbs - 1, resident / (2 * n)));
     if (parts > 1)
         hipLaunchKernelGGL((rescale_kernel<LOGN, true>), dim3(2 * n * parts), dim3(G::T), lds, s, lt, row, limbs, parts,

@@ -13,6 +13,8 @@
 // load into scalar registers (the tables are never written by a kernel).  It takes no vector register, and it
 // does not queue behind the vector stores of the previous row as a vector load would.
 #pragma once
+#include <type_traits>
+
 #include "he_arith.h"
 
 namespace {
@@ -42,6 +44,16 @@ __host__ __device__ constexpr u32 reg_index(u32 tid, u32 e) {
         u32 wave = tid >> 6, lane = tid & 63u;
         return (wave << 10) | (e_hi << (G::REM + 6)) | (lane << G::REM) | e_lo;
     }
+}
+
+// The element of a row in memory that register e of thread tid holds in pass P.  The index is the thread's part plus the
+// register's (disjoint bits): the row and the register's part are the same for the wave and make a scalar address, the
+// thread's part is one 32-bit offset for all sixteen accesses.  (As one index per access they cost up to three vector
+// instructions and two registers each.)
+template <int LOGN, int P, typename V>
+__device__ __forceinline__ V& row_at(V* row, u32 tid, u32 e) {
+    typedef typename std::conditional<std::is_const<V>::value, const char, char>::type byte;
+    return *reinterpret_cast<V*>(reinterpret_cast<byte*>(row + reg_index<LOGN, P>(0, e)) + reg_index<LOGN, P>(tid, 0) * (u32)sizeof(V));
 }
 
 // True when, in pass P, every wavefront (64 consecutive threads) holds exactly the aligned block of

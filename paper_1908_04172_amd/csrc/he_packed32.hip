@@ -349,7 +349,7 @@ __global__ void __launch_bounds__(Geo<LOGN>::T) ntt32_rows_kernel(Limb32Table lt
     {
         const u32* p = data + (size_t)blockIdx.x * G::N;
 #pragma unroll
-        for (u32 e = 0; e < 16; e++) a[e] = p[reg_index<LOGN, PIN>(threadIdx.x, e)];
+        for (u32 e = 0; e < 16; e++) a[e] = row_at<LOGN, PIN>(p, threadIdx.x, e);
     }
     for (u32 row = blockIdx.x; row < rows; row += gridDim.x) {
         const u32 tid = threadIdx.x;
@@ -362,7 +362,7 @@ __global__ void __launch_bounds__(Geo<LOGN>::T) ntt32_rows_kernel(Limb32Table lt
         if (row + gridDim.x < rows) {  // sixteen registers: the next row travels while this one is transformed
             const u32* p = data + (size_t)(row + gridDim.x) * G::N;
 #pragma unroll
-            for (u32 e = 0; e < 16; e++) next[e] = p[reg_index<LOGN, PIN>(tid, e)];
+            for (u32 e = 0; e < 16; e++) next[e] = row_at<LOGN, PIN>(p, tid, e);
         }
         if constexpr (INVERSE) {
             ntt32_inverse<LOGN>(a, tw, lds32, tid, c);
@@ -378,7 +378,7 @@ __global__ void __launch_bounds__(Geo<LOGN>::T) ntt32_rows_kernel(Limb32Table lt
         for (u32 e = 0; e < 16; e++) asm volatile("" : "+v"(next[e])::"memory");
         u32* p = data + (size_t)row * G::N;
 #pragma unroll
-        for (u32 e = 0; e < 16; e++) p[reg_index<LOGN, POUT>(tid, e)] = a[e];
+        for (u32 e = 0; e < 16; e++) row_at<LOGN, POUT>(p, tid, e) = a[e];
 #pragma unroll
         for (u32 e = 0; e < 16; e++) a[e] = next[e];
         if constexpr (INVERSE) lds_barrier();  // (see the 64-bit transform kernel)
@@ -406,7 +406,7 @@ __global__ void __launch_bounds__(Geo<LOGN>::T) rescale32_kernel(Limb32Table lt,
         const Limb32& c = lt.c[last];
         const u32* row = src + (size_t)last * G::N;
 #pragma unroll
-        for (u32 e = 0; e < 16; e++) t[e] = row[reg_index<LOGN, LAST_PASS>(tid, e)];
+        for (u32 e = 0; e < 16; e++) t[e] = row_at<LOGN, LAST_PASS>(row, tid, e);
         ntt32_inverse<LOGN>(t, reinterpret_cast<const Twiddle32*>(tw_inv) + (size_t)last * G::N, lds32, tid, c);
         const u32 half = c.q >> 1;
 #pragma unroll
@@ -418,7 +418,7 @@ __global__ void __launch_bounds__(Geo<LOGN>::T) rescale32_kernel(Limb32Table lt,
         const u32* xrow = src + (size_t)i * G::N;
         u32 x[16], a[16];
 #pragma unroll
-        for (u32 e = 0; e < 16; e++) x[e] = xrow[reg_index<LOGN, LAST_PASS>(tid, e)];
+        for (u32 e = 0; e < 16; e++) x[e] = row_at<LOGN, LAST_PASS>(xrow, tid, e);
         // t < p is below 2*q_i unless p > 2*q_i (then Alg. 6 reduces it first); adding q_i - (h mod q_i) gives a
         // value congruent to t - h and below 3*q_i, which the forward transform takes
         const u32 minus_half = c.q - d.half_mod;
@@ -430,7 +430,7 @@ __global__ void __launch_bounds__(Geo<LOGN>::T) rescale32_kernel(Limb32Table lt,
         for (u32 e = 0; e < 16; e++) {
             const u32 corr = csub32(a[e], c.two_q);  // below 2q: x + 2q - corr is positive and below 3q < 2^32
             const u32 v = shoup32_add(x[e] + c.two_q - corr, Twiddle32{d.p_inv, d.p_inv_shoup}, c.q, 0);
-            orow[reg_index<LOGN, LAST_PASS>(tid, e)] = csub32(v, c.q);
+            row_at<LOGN, LAST_PASS>(orow, tid, e) = csub32(v, c.q);
         }
     }
 }

@@ -1,6 +1,11 @@
-"""The transform kernels where they can go wrong: rows that follow one another in a workgroup.  Exact residues."""
+"""The transform kernels where they can go wrong: rows that follow one another in a workgroup, moduli around 2^46 (below it
+the double-precision transform reduces nothing between its stages) and 2^50 (above it integer butterflies run), dropped
+primes wider and narrower than the kept ones, digits of a key switch above and below twice the target modulus, and runs of
+ciphertexts in the key product.  Exact residues."""
+import numpy as np
 import pytest
 
+import oracle
 from paper_1908_04172_amd import he as he_mod
 from paper_1908_04172_amd import workloads as wl
 
@@ -13,6 +18,27 @@ def he():
         pytest.skip("no GPU")
     he_mod.lib()
     return he_mod
+
+
+def dev(a):
+    return torch.from_numpy(np.ascontiguousarray(a).view(np.int64)).cuda()
+
+
+def host(t):
+    return t.cpu().numpy().view(np.uint64)
+
+
+@pytest.mark.parametrize("log2N,bits", [(10, 46), (13, 45), (14, 46)])
+def test_transform_without_reductions_on_the_host(log2N, bits):
+    """A limb below 2^46: every intermediate an exact integer, below the 9.93 q that fourteen stages can reach from 2 q."""
+    N = 1 << log2N
+    q = wl.ntt_primes(bits, N, 1)[0]
+    ctx = he_mod.Context(log2N, [wl.ntt_primes(60, N, 1)[0], q], device=None)
+    rng = np.random.default_rng(log2N)
+    for v in (rng.integers(-q, q + 1, N), np.full(N, q), np.where(rng.integers(0, 2, N) == 1, q, -q)):
+        got, worst = ctx.host_ntt_forward_fp64(1, v)
+        assert np.array_equal(got, oracle.ntt_fwd(np.mod(v, q).astype(np.uint64)[None, :], [q], [ctx.psi[1]])[0])
+        assert worst < 9.93
 
 
 @pytest.mark.gpu
@@ -44,3 +70,42 @@ def test_packed_inverse_rows_that_follow_one_another(he):
         y = x.clone()
         ctx.ntt_inv32(y)
         assert torch.equal(y, a)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("log2N", [10, 11, 12, 13, 14])
+@pytest.mark.parametrize("bits", [[60, 50, 46, 47, 49, 45, 46], [51, 50, 49, 50], [46, 30, 62, 47], [45, 46], [40, 40, 60]])
+def test_rescale_around_the_limits_of_the_transforms(he, log2N, bits):
+    N = 1 << log2N
+    q = wl.modulus_chain(bits, N)
+    ctx = he.Context(log2N, q)
+    ct = wl.uniform_residues((3, 2), q, N, 300 + log2N)
+    top = np.array(q, dtype=np.uint64)[:, None] - 1
+    ct[0, 0], ct[0, 1] = top, 0
+    ct[1, 0, :, ::2], ct[1, 1, -1] = top, 0
+    assert np.array_equal(host(ctx.rescale(dev(ct))), oracle.rescale(ct, q, ctx.psi))
+    x = ct.reshape(6, len(q), N)
+    d = dev(x)
+    ctx.ntt_fwd(d)
+    assert np.array_equal(host(d), oracle.ntt_fwd(x, q, ctx.psi))
+    ctx.ntt_inv(d)
+    assert np.array_equal(host(d), x)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("log2N,bits,n", [(10, [30, 62, 50, 49, 51, 46, 60], 3), (12, [60, 59, 50, 30, 31, 46, 47, 62], 2),
+                                          (10, [50] * 15 + [60], 2), (14, [50, 40, 60], 45)])
+def test_key_switch_of_mixed_widths_and_runs(he, log2N, bits, n):
+    """Digits wider and narrower than the limb they are expanded to; fifteen digits; and more ciphertexts than runs (45 in
+    runs of two, the last one shorter)."""
+    N = 1 << log2N
+    q = wl.modulus_chain(bits, N)
+    ctx = he.Context(log2N, q)
+    l = len(q) - 1
+    ct = wl.uniform_residues((n, 2), q[:l], N, 400 + log2N)
+    ct[0] = np.array(q[:l], dtype=np.uint64)[:, None] - 1
+    evk = wl.uniform_residues((l, 2), q, N, 401)
+    evk[0] = np.array(q, dtype=np.uint64)[:, None] - 1
+    got = host(ctx.ct_square_relin(dev(ct), dev(evk)))
+    some = [0, 1, n // 2, n - 1]
+    assert np.array_equal(got[some], oracle.square_relin(ct[some], q, ctx.psi, evk))
