@@ -205,7 +205,7 @@ void fill_digit_const(DigitConst& d, const LimbConst& c) {  // (see DigitConst)
     d.mult_shift = s - 32;
     d.hi_shift = 8 * n_hi - 9;
     d.kappa8 = 8 * kappa;
-    d.lazy = c.mac_lazy && !c.fp_ok;  // (the combine step on doubles takes canonical residues)
+    d.lazy = c.fp_ok ? 2 : c.mac_lazy;
     d.b8 = 1 << 8;
     d.b16 = 1 << 16;
     d.b24 = 1 << 24;

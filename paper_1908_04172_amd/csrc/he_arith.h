@@ -363,7 +363,8 @@ struct DigitConst {
     u32 mult_shift;        // s - 32
     u32 hi_shift;          // 8 d - 9
     u32 kappa8;            // 8 kappa
-    u32 lazy;              // 1: the rescale kernel takes the unreduced sum (LimbConst::mac_lazy, limbs on integer butterflies)
+    u32 lazy;              // 1: the rescale kernel takes the unreduced sum (LimbConst::mac_lazy, limbs on integer butterflies);
+                           // 2: it takes a sum below 4q (limbs whose combine step runs on doubles); 0: the canonical one
     int32_t b8, b16, b24;  // 2^8, 2^16, 2^24, as data: multiplied by a literal they become shifts and additions, four
                            // instructions instead of one multiply-add
 };
@@ -394,6 +395,9 @@ HE_HD u64 digit_reduce_lazy(const int32_t (&r)[8], u64 start, const DigitConst& 
 #endif
     return ((u64)high << 32) | (u32)low;
 }
+
+// The same below 4q, for q < 2^61.
+HE_HD u64 digit_reduce_lazy4(const int32_t (&r)[8], u64 start, const DigitConst& c) { return sub_if_ge(digit_reduce_lazy(r, start, c), 0 - c.top); }
 
 // the canonical residue
 HE_HD u64 digit_reduce(const int32_t (&r)[8], u64 start, const DigitConst& c) {

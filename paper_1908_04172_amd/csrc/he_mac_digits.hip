@@ -216,7 +216,7 @@ __device__ __forceinline__ void store_group(const Sums<V, OT>& sums, const MacAr
     u32 half = w.half;
     asm volatile("" : "+v"(half));  // what follows is derived here, not kept in registers through the loop over terms
     V* dst = w.dst + (size_t)out0 * out_stride + half * (LANE_OUTPUTS * out_stride);
-    const bool lazy = D == 8 && (a.mode & MAC_FOR_RESCALE) && w.limb + 1 < a.limbs && c.lazy;
+    const u32 lazy = D == 8 && (a.mode & MAC_FOR_RESCALE) && w.limb + 1 < a.limbs ? c.lazy : 0;
     const bool accumulate = a.mode & MAC_ACCUMULATE;
     // The bias residues come in with scalar loads, those of the next four outputs while four are reduced.  (Without a
     // bias the loads read the group's descriptor and are masked.)
@@ -274,7 +274,8 @@ __device__ __forceinline__ void store_group(const Sums<V, OT>& sums, const MacAr
         }
     };
     if constexpr (D == 8) {  // (one uniform branch for the whole group)
-        if (lazy) reduce_all([&](const int32_t (&r)[8], u64 st) { return digit_reduce_lazy(r, st, c); });
+        if (lazy == 1) reduce_all([&](const int32_t (&r)[8], u64 st) { return digit_reduce_lazy(r, st, c); });
+        else if (lazy == 2) reduce_all([&](const int32_t (&r)[8], u64 st) { return digit_reduce_lazy4(r, st, c); });
         else reduce_all([&](const int32_t (&r)[8], u64 st) { return digit_reduce(r, st, c); });
     } else {
         reduce_all([&](const int32_t (&r)[4], u64 st) { return digit_reduce32(r, (u32)st, c); });

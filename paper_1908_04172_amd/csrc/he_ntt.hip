@@ -542,11 +542,14 @@ rescale_kernel(LimbTable lt, DropRow drop, u32 limbs, u32 parts, const u64* in, 
             ntt_forward_f<LOGN>(f, tw_fwd_f + (size_t)i * G::N, reinterpret_cast<double*>(lds), tid, c);
 #pragma unroll
             for (u32 e = 0; e < 16; e++) a[e] = __builtin_bit_cast(u64, f[e]);
-            // The combine step on doubles too: x - y of a canonical x and the correction y reduced to q/2 is below 1.51q
-            // in magnitude, and its product with p^-1 within 0.79q of zero: 17 instructions per value, where the integer
-            // form (mantissa differences, an exact Shoup product) took 31, a quarter of such a limb's iteration.
+            // The combine step on doubles too: with x below 4q (a MAC's result, see DigitConst::lazy) and the correction y
+            // reduced to q/2, x - 2q - y is below 2.51q in magnitude and its product with p^-1 within 0.98q of zero: 17
+            // instructions per value, where the integer form (mantissa differences, an exact Shoup product) took 31, a
+            // quarter of such a limb's iteration.
+            const double x_offset = 4503599627370496.0 + 2.0 * q_f;
             finish([&](u64 x, u64 y) {
-                const double diff = fp_from_u52(x) - fp_reduce(__builtin_bit_cast(double, y), q_f, c.q_inv_f);
+                const double x_f = __builtin_bit_cast(double, x | 0x4330000000000000ull) - x_offset;
+                const double diff = x_f - fp_reduce(__builtin_bit_cast(double, y), q_f, c.q_inv_f);
                 return fp_to_canonical(fp_mulmod(p_inv, diff, q_f, c.q_inv_f), q_f);
             });
         }
