@@ -59,16 +59,18 @@ __device__ __forceinline__ void run_stages(u64 (&a)[16], const PassTwiddles<LOGN
 
 // A pass with the regrouping before it (FROM: the pass whose order the registers are in).  The twiddles of a pass that
 // reads them per lane are up to 15 two-word entries, 60 registers, next to 32 of residues: half of them, those of the
-// last stage, are therefore requested apart from the others, so that never more than about 50 are held and the kernels
-// fit 128 registers (four wavefronts per SIMD) almost without spills.  Forward: the stage's own are requested one stage
+// last stage, are therefore requested apart from the others, so that never more than about 50 are held and the stand-alone
+// transforms fit 128 registers (four wavefronts per SIMD) without spills.  Forward: the stage's own are requested one stage
 // ahead; inverse (where it runs first): the others are requested while it runs.
-template <int LOGN, int P, bool INVERSE, int MODE, int FROM>
+// WHOLE: all at once, one wait instead of two (the rescale, which takes no more registers for it: 2048 ciphertexts of
+// N = 2^12 at L = 4 319 us in two parts, 312 at once).
+template <int LOGN, int P, bool INVERSE, int MODE, int FROM, bool WHOLE>
 __device__ __forceinline__ void pass_int(u64 (&a)[16], const u64* tw, u64* lds, u32 tid, const LimbConst& c) {
     using S = PassShape<LOGN, P>;
     constexpr int L = S::NST - 1;  // the last stage
     const Twiddle* t = reinterpret_cast<const Twiddle*>(tw);
     PassTwiddles<LOGN, P> pt;
-    if constexpr (S::UNIFORM || S::NST == 1) {
+    if constexpr (S::UNIFORM || S::NST == 1 || WHOLE) {
         load_pass_twiddles<LOGN, P>(pt, t, tid);
         if constexpr (FROM != P) regroup<LOGN, FROM, P>(a, lds, tid);
         run_stages<LOGN, P, INVERSE, MODE, 0, S::NST>(a, pt, c);
@@ -93,35 +95,35 @@ __device__ __forceinline__ void pass_int(u64 (&a)[16], const u64* tw, u64* lds, 
 
 // Registers in pass-0 order, canonical -> registers in last-pass order, below 4q (mode 0), 8q
 // (mode 1) or (1 + 4*log2N)*q (mode 2).
-template <int LOGN, int MODE>
+template <int LOGN, int MODE, bool WHOLE>
 __device__ __forceinline__ void ntt_forward(u64 (&a)[16], const u64* tw, u64* lds, u32 tid, const LimbConst& c) {
     using G = Geo<LOGN>;
     static_assert(G::NPASS >= 2 && G::NPASS <= 4, "two to four passes");
-    pass_int<LOGN, 0, false, MODE, 0>(a, tw, lds, tid, c);
-    pass_int<LOGN, 1, false, MODE, 0>(a, tw, lds, tid, c);
-    if constexpr (G::NPASS > 2) pass_int<LOGN, 2, false, MODE, 1>(a, tw, lds, tid, c);
-    if constexpr (G::NPASS > 3) pass_int<LOGN, 3, false, MODE, 2>(a, tw, lds, tid, c);
+    pass_int<LOGN, 0, false, MODE, 0, WHOLE>(a, tw, lds, tid, c);
+    pass_int<LOGN, 1, false, MODE, 0, WHOLE>(a, tw, lds, tid, c);
+    if constexpr (G::NPASS > 2) pass_int<LOGN, 2, false, MODE, 1, WHOLE>(a, tw, lds, tid, c);
+    if constexpr (G::NPASS > 3) pass_int<LOGN, 3, false, MODE, 2, WHOLE>(a, tw, lds, tid, c);
 }
 
 // The forward transform in the limb's mode, of inputs below IN_Q * q (IN_Q <= 3: every mode takes them),
 // ending below `cap` (returned): 4q, 4q or (IN_Q + 4*log2N)*q.  In mode 1 the values are brought from below
 // 8q to below 4q, so that x + cap - value fits 64 bits for any canonical x.
-template <int LOGN, int IN_Q = 1>
+template <int LOGN, int IN_Q = 1, bool WHOLE = false>
 __device__ __forceinline__ u64 ntt_forward_any(u64 (&a)[16], const u64* tw, u64* lds, u32 tid, const LimbConst& c) {
     static_assert(IN_Q >= 1 && IN_Q <= 3 && IN_Q + 4 * LOGN + 1 <= 64, "mode 2: (IN_Q + 4*log2N + 1) * q stays below 2^64 for q < 2^58");
     u64 cap = 0;
     if (choice(c.ntt_mode) == 2) {
-        ntt_forward<LOGN, 2>(a, tw, lds, tid, c);
+        ntt_forward<LOGN, 2, WHOLE>(a, tw, lds, tid, c);
         cap = c.q * (4 * LOGN + IN_Q);
     }
     if (choice(c.ntt_mode) == 1) {
-        ntt_forward<LOGN, 1>(a, tw, lds, tid, c);
+        ntt_forward<LOGN, 1, WHOLE>(a, tw, lds, tid, c);
 #pragma unroll
         for (u32 e = 0; e < 16; e++) a[e] = sub_if_ge(a[e], c.neg_four_q);
         cap = c.four_q;
     }
     if (choice(c.ntt_mode) == 0) {
-        ntt_forward<LOGN, 0>(a, tw, lds, tid, c);
+        ntt_forward<LOGN, 0, WHOLE>(a, tw, lds, tid, c);
         cap = 2 * c.two_q;
     }
     return cap;
@@ -175,14 +177,14 @@ __device__ __forceinline__ void ntt_forward_f(double (&a)[16], const double* tw,
 }
 
 // Registers in last-pass order, canonical -> registers in pass-0 order, below 2q, multiplied by N^-1.
-template <int LOGN, int MODE>
+template <int LOGN, int MODE, bool WHOLE>
 __device__ __forceinline__ void ntt_inverse(u64 (&a)[16], const u64* tw, u64* lds, u32 tid, const LimbConst& c) {
     using G = Geo<LOGN>;
     constexpr int LAST = G::NPASS - 1;
-    if constexpr (G::NPASS > 3) pass_int<LOGN, 3, true, MODE, 3>(a, tw, lds, tid, c);
-    if constexpr (G::NPASS > 2) pass_int<LOGN, 2, true, MODE, LAST < 3 ? LAST : 3>(a, tw, lds, tid, c);
-    pass_int<LOGN, 1, true, MODE, LAST < 2 ? LAST : 2>(a, tw, lds, tid, c);
-    pass_int<LOGN, 0, true, MODE, 1>(a, tw, lds, tid, c);
+    if constexpr (G::NPASS > 3) pass_int<LOGN, 3, true, MODE, 3, WHOLE>(a, tw, lds, tid, c);
+    if constexpr (G::NPASS > 2) pass_int<LOGN, 2, true, MODE, LAST < 3 ? LAST : 3, WHOLE>(a, tw, lds, tid, c);
+    pass_int<LOGN, 1, true, MODE, LAST < 2 ? LAST : 2, WHOLE>(a, tw, lds, tid, c);
+    pass_int<LOGN, 0, true, MODE, 1, WHOLE>(a, tw, lds, tid, c);
 }
 
 // The inverse transform on double-precision FMAs (see bfly_inv_f): registers in last-pass order, magnitude at most
@@ -237,7 +239,7 @@ __device__ __forceinline__ void ntt_inverse_f(double (&a)[16], const double* tw,
 
 // The inverse transform of canonical values in the limb's form: on doubles for a limb below 2^50 (canonical
 // results), else on the integer butterflies (results below 2q).
-template <int LOGN>
+template <int LOGN, bool WHOLE = false>
 __device__ __forceinline__ void ntt_inverse_any(u64 (&a)[16], const u64* tw, const double* tw_f, u64* lds, u32 tid, const LimbConst& c) {
     if (choice(c.fp_ok)) {
         const double q_f = (double)c.q;
@@ -249,8 +251,8 @@ __device__ __forceinline__ void ntt_inverse_any(u64 (&a)[16], const u64* tw, con
         for (u32 e = 0; e < 16; e++) a[e] = fp_to_canonical(fp_reduce(f[e], q_f, c.q_inv_f), q_f);
     }
     const u32 integer = c.fp_ok ? 0 : c.ntt_mode != 0 ? 1 : 2;
-    if (choice(integer) == 1) ntt_inverse<LOGN, 1>(a, tw, lds, tid, c);
-    if (choice(integer) == 2) ntt_inverse<LOGN, 0>(a, tw, lds, tid, c);
+    if (choice(integer) == 1) ntt_inverse<LOGN, 1, WHOLE>(a, tw, lds, tid, c);
+    if (choice(integer) == 2) ntt_inverse<LOGN, 0, WHOLE>(a, tw, lds, tid, c);
 }
 
 __device__ __forceinline__ u64 canon4(u64 v, u64 q, u64 two_q) {  // [0,4q) -> [0,q)
@@ -451,20 +453,29 @@ ntt_rows_kernel(LimbTable lt, u32 limbs, u64* data, const u64* tw_all, const dou
 // the first kept limb takes t straight from the registers; for the others t is parked in memory.
 //
 // The parked t for limb i+1 is requested, and waited for, before the outputs of limb i are stored.
-template <int LOGN, bool SPLIT>
-__global__ void __launch_bounds__(Geo<LOGN>::T, 4)
-rescale_kernel(LimbTable lt, DropRow drop, u32 limbs, u32 parts, const u64* in, u64* out, const u64* tw_fwd,
+// Wavefronts per SIMD that the register allocation leaves room for.  Up to N = 2^12 three: the kernel takes 134 to 140
+// registers, and under 128 up to 16 of them were spilled (8192 ciphertexts of N = 2^12 at L = 2: 444 us at three, 476 at
+// four; 128 at L = 4: 28.4 and 33.5).  Above that four: it takes 127 or 128 anyway (at 2^14, 4 spilled), and at 2^13 the LDS
+// has room for two workgroups.
+template <int LOGN>
+constexpr int rescale_waves() { return LOGN <= 12 ? 3 : 4; }
+
+template <int LOGN>
+__global__ void __launch_bounds__(Geo<LOGN>::T, rescale_waves<LOGN>())
+rescale_kernel(LimbTable lt, DropRow drop, u32 limbs, u64 shares, const u64* in, u64* out, const u64* tw_fwd,
                const u64* tw_inv, const double* tw_fwd_f, const double* tw_inv_f) {
     using G = Geo<LOGN>;
     extern __shared__ __align__(16) u64 lds[];
-    // A polynomial is handled by `parts` workgroups when there are too few polynomials to fill the
-    // chip: each repeats the inverse transform of the dropped limb and takes a contiguous share
-    // [first, end) of the kept limbs.
-    // (SPLIT = false is the plain case, one workgroup per polynomial, with nothing of this computed.)
-    const size_t poly = SPLIT ? blockIdx.x / parts : blockIdx.x;  // ct*2 + component
-    const u32 part = SPLIT ? blockIdx.x % parts : 0;
+    // A polynomial is handled by several workgroups (gridDim.y) when there are too few polynomials to fill the chip: each
+    // repeats the inverse transform of the dropped limb and takes a contiguous share [first, end) of the kept limbs.
+    // `shares` holds where the shares begin, four bits each, from the host: a quotient formed here sits in vector registers,
+    // and with it the loop's counter and every address that depends on it (23 registers more were spilled at N = 2^14, with
+    // waits for their reloads between the loads and the stores of a limb: 64 ciphertexts at L = 8 116 us, now 91).  The
+    // polynomials run along x, so that workgroups with wide limbs in their share do not all meet on the same compute units
+    // (100 ciphertexts of N = 2^13 at L = 4: 44.6 us with the shares along x, 42.5).
+    const size_t poly = blockIdx.x;  // ct*2 + component
     const u32 last = limbs - 1;
-    const u32 first = SPLIT ? part * last / parts : 0, end = SPLIT ? (part + 1) * last / parts : last;
+    const u32 first = (u32)(shares >> (4 * blockIdx.y)) & 15, end = (u32)(shares >> (4 * blockIdx.y + 4)) & 15;
     const u64* src = in + poly * limbs * G::N;
     u64* dst = out + poly * (limbs - 1) * G::N;
     // t is parked in the output row of this workgroup's last limb: every thread re-reads only what it
@@ -478,7 +489,7 @@ rescale_kernel(LimbTable lt, DropRow drop, u32 limbs, u32 parts, const u64* in, 
         const u64* row = src + (size_t)last * G::N;
 #pragma unroll
         for (u32 e = 0; e < 16; e++) a[e] = row_at<LOGN, G::NPASS - 1>(row, tid, e);
-        ntt_inverse_any<LOGN>(a, tw_inv + (size_t)last * G::N * 2, tw_inv_f + (size_t)last * G::N, lds, tid, c);
+        ntt_inverse_any<LOGN, true>(a, tw_inv + (size_t)last * G::N * 2, tw_inv_f + (size_t)last * G::N, lds, tid, c);
         const u64 half = c.q >> 1;
         const u32 tid_s = fresh(tid);
 #pragma unroll
@@ -565,7 +576,7 @@ rescale_kernel(LimbTable lt, DropRow drop, u32 limbs, u32 parts, const u64* in, 
             for (u32 e = 0; e < 16; e++) a[e] += minus_half;
             // The transformed correction stays below `cap` (a multiple of q), so x + cap - correction is
             // positive, congruent to x - correction and fits 64 bits; the Shoup product takes it as it is.
-            u64 cap = ntt_forward_any<LOGN, 3>(a, tw_fwd + (size_t)i * G::N * 2, lds, tid, c);
+            u64 cap = ntt_forward_any<LOGN, 3, true>(a, tw_fwd + (size_t)i * G::N * 2, lds, tid, c);
             if (c.ntt_mode == 0) {  // 5q need not fit 64 bits, 3q does
 #pragma unroll
                 for (u32 e = 0; e < 16; e++) a[e] = sub_if_ge(a[e], c.neg_two_q);
@@ -719,11 +730,11 @@ int launch_rescale_split(he_ctx* ctx, u32 limbs, u32 drop_id, const u64* in, u64
     return HE_OK;
 }
 
-// workgroups that a compute unit holds at once: its LDS, and four wavefronts per SIMD (the kernels' register limit)
+// workgroups that a compute unit holds at once: its LDS, and the wavefronts per SIMD of the kernel's register limit
 template <int LOGN>
-constexpr u32 resident_per_cu() {
+constexpr u32 resident_per_cu(int waves = 4) {
     using G = Geo<LOGN>;
-    const u32 by_lds = (160u << 10) / (G::N * (u32)sizeof(u64)), by_waves = 1024 / G::T;
+    const u32 by_lds = (160u << 10) / (G::N * (u32)sizeof(u64)), by_waves = 256 * waves / G::T;
     return by_lds < by_waves ? by_lds : by_waves;
 }
 
@@ -793,21 +804,18 @@ int launch_rescale_t(he_ctx* ctx, u32 limbs, u32 drop_id, const u64* in, u64* ou
     const u64* tw_inv = ctx->tw_inv + (size_t)(drop_id - (limbs - 1)) * G::N * 2;
     const double* tw_inv_f = ctx->tw_inv_f + (size_t)(drop_id - (limbs - 1)) * G::N;
     const size_t lds = (size_t)G::N * sizeof(u64);
-    static std::atomic<uint32_t> lds_allowed{0}, lds_allowed_split{0};
-    if (int rc = allow_dynamic_lds((const void*)rescale_kernel<LOGN, false>, lds, ctx->device, lds_allowed, true)) return rc;
-    if (int rc = allow_dynamic_lds((const void*)rescale_kernel<LOGN, true>, lds, ctx->device, lds_allowed_split, true)) return rc;
+    static std::atomic<uint32_t> lds_allowed{0};
+    if (int rc = allow_dynamic_lds((const void*)rescale_kernel<LOGN>, lds, ctx->device, lds_allowed, true)) return rc;
     DropRow row;
     for (u32 i = 0; i < HE_MAX_LIMBS; i++) row.d[i] = ctx->drop[drop_id][i];
     // with fewer polynomials than workgroups the chip holds at once, split each over several workgroups
     // (at most one per kept limb), as far as they still all run at the same time
-    const u32 resident = 256 * resident_per_cu<LOGN>();
+    const u32 resident = 256 * resident_per_cu<LOGN>(rescale_waves<LOGN>());
     const u32 parts = std::max(1u, std::min(limbs - 1, resident / (2 * n)));
-    if (parts > 1)
-        hipLaunchKernelGGL((rescale_kernel<LOGN, true>), dim3(2 * n * parts), dim3(G::T), lds, s, lt, row, limbs, parts,
-                           in, out, ctx->tw_fwd, tw_inv, ctx->tw_fwd_f, tw_inv_f);
-    else
-        hipLaunchKernelGGL((rescale_kernel<LOGN, false>), dim3(2 * n), dim3(G::T), lds, s, lt, row, limbs, 1u, in, out,
-                           ctx->tw_fwd, tw_inv, ctx->tw_fwd_f, tw_inv_f);
+    u64 shares = 0;
+    for (u32 k = 0; k <= parts; k++) shares |= (u64)(k * (limbs - 1) / parts) << (4 * k);
+    hipLaunchKernelGGL((rescale_kernel<LOGN>), dim3(2 * n, parts), dim3(G::T), lds, s, lt, row, limbs, shares, in, out, ctx->tw_fwd, tw_inv,
+                       ctx->tw_fwd_f, tw_inv_f);
     HE_HIP(hipGetLastError());
     return HE_OK;
 }

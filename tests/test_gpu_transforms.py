@@ -93,6 +93,22 @@ def test_rescale_around_the_limits_of_the_transforms(he, log2N, bits):
 
 
 @pytest.mark.gpu
+@pytest.mark.parametrize("n", [1, 103, 120, 200, 400, 511, 700, 769, 1537])
+def test_rescale_of_few_polynomials_split_over_workgroups(he, n):
+    """Fifteen kept limbs, shared by fifteen workgroups per polynomial down to one: even and uneven shares."""
+    N, bits = 1 << 10, [60, 50] + [40] * 5 + [55] * 3 + [46] * 2 + [30] * 4
+    q = wl.modulus_chain(bits, N)
+    assert len(q) == 16
+    ctx = he.Context(10, q)
+    ct = wl.uniform_residues_torch((n, 2), q, N, 500 + n, "cuda")
+    out = ctx.rescale(ct)
+    some = sorted({0, n // 2, n - 1})
+    assert np.array_equal(host(out[some]), oracle.rescale(host(ct[some]), q, ctx.psi))
+    for k in range(0, n, 97):                                   # one at a time: as many workgroups as there are kept limbs
+        assert torch.equal(ctx.rescale(ct[k:k + 1].contiguous()), out[k:k + 1])
+
+
+@pytest.mark.gpu
 @pytest.mark.parametrize("log2N,bits,n", [(10, [30, 62, 50, 49, 51, 46, 60], 3), (12, [60, 59, 50, 30, 31, 46, 47, 62], 2),
                                           (10, [50] * 15 + [60], 2), (14, [50, 40, 60], 45)])
 def test_key_switch_of_mixed_widths_and_runs(he, log2N, bits, n):
