@@ -682,16 +682,19 @@ int he_plan_create(he_ctx* ctx, uint32_t n_in, uint32_t n_out, uint32_t n_pt, co
     for (u32 cls = 0; cls < SCALAR_CLASSES; ++cls) {
         const u32 begin = p->class_begin_s[cls], end = p->class_begin_s[cls + 1];
         p->min_terms_s[cls] = begin < end ? ~0u : 0;
+        p->max_terms_s[cls] = p->max_count_s[cls] = 0;
         std::map<std::vector<u32>, u32> tables;
         std::vector<u32> key, table(end - begin);
         for (u32 i = begin; i < end; ++i) {
             p->min_terms_s[cls] = std::min(p->min_terms_s[cls], ts[i].n_terms);
-            p->max_terms = std::max(p->max_terms, ts[i].n_terms);
+            p->max_terms_s[cls] = std::max(p->max_terms_s[cls], ts[i].n_terms);
+            p->max_count_s[cls] = std::max(p->max_count_s[cls], ts[i].count);
             key.assign(1, ts[i].n_terms);
             for (u32 g = 0; g < ts[i].count; ++g)
                 key.insert(key.end(), term_pt + off[ts[i].out0 + g], term_pt + off[ts[i].out0 + g] + ts[i].n_terms);
             table[i - begin] = tables.emplace(key, (u32)tables.size()).first->second;
         }
+        p->max_terms = std::max(p->max_terms, p->max_terms_s[cls]);
         std::vector<u32> order(end - begin);
         for (u32 i = 0; i < end - begin; ++i) order[i] = i;
         std::stable_sort(order.begin(), order.end(), [&](u32 x, u32 y) { return table[x] < table[y]; });

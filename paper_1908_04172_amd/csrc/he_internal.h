@@ -117,6 +117,8 @@ struct he_plan {
     u32 class_begin_s[SCALAR_CLASSES + 1];
     u32 class_begin_p[4];  // polynomial plaintexts: capacities 1, 2, 4 outputs per thread
     u32 min_terms_s[SCALAR_CLASSES];  // fewest terms of any scalar tile of the class (0 for an empty class)
+    u32 max_terms_s[SCALAR_CLASSES];  // most terms of any scalar tile of the class
+    u32 max_count_s[SCALAR_CLASSES];  // most outputs of any scalar tile of the class
     u32 max_terms;         // most terms of any tile
     Tile* tiles_s_dev;
     Tile* tiles_p_dev;

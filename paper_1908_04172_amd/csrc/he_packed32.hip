@@ -2,9 +2,9 @@
 // (Sec. "Ciphertext-plaintext Multiplication": BarrettReduction64, Alg. 6, and the scalar multiply of
 // Alg. 8) carried through to the memory system.  Residue tensors are uint32 [ct][2][limbs][N], half the
 // bytes of the 64-bit form.  Scalar plaintexts of groups of outputs run on the matrix cores (he_mac_digits.hip); for
-// single outputs and full-polynomial plaintexts a product of two residues fits 60 bits, so a MAC term is ONE
-// 32x32+64-bit multiply-add into a single 64-bit sum, fifteen terms go by between two folds, and a reduction is Alg. 6:
-// one high product with floor(2^64 / q), one low product, one conditional subtraction.  The transforms are the
+// single outputs, groups with few terms and full-polynomial plaintexts a product of two residues fits 60 bits, so a MAC
+// term is ONE 32x32+64-bit multiply-add into a single 64-bit sum, fifteen terms go by between two folds, and a reduction
+// is Alg. 6: one high product with floor(2^64 / q), one low product, one conditional subtraction.  The transforms are the
 // register-resident ones of the 64-bit path with 32-bit butterflies; the rescale keeps the dropped limb's coefficients
 // in registers throughout.
 #include <algorithm>
@@ -63,9 +63,12 @@ constexpr u32 MAC32_THREADS = 256;
 constexpr u32 MAC32_SLICE = 2 * MAC32_THREADS;  // residues of a row one workgroup covers (two per thread)
 
 constexpr u32 GATHER32_BLOCKS = 16;  // workgroups that share the gathering of one group's table
+constexpr u32 MAC32_BLOCK = 4;  // terms per unrolled block; an input is requested a block before its use
+__host__ __device__ inline u32 padded_terms32(u32 n_terms) { return (n_terms + MAC32_BLOCK - 1) / MAC32_BLOCK * MAC32_BLOCK; }
 
-// Outputs that share their inputs with no other (groups of outputs run on the matrix cores: he_mac_digits.hip): word t of
-// a group's table, at its place among the 64-bit path's tables, is pt[term_pt[off[out0] + t]][limb] as 32 bits.
+// Word t * G + g of a group's table, at its place among the 64-bit path's tables, is pt[term_pt[off[out0 + g] + t]][limb]
+// as 32 bits, zero for outputs beyond the group's count and, with several outputs, for the terms that pad it to whole blocks.
+template <int G>
 __global__ void __launch_bounds__(256) gather_weights32_kernel(const Tile* tiles, const u64* wbase, const u32* owners, u32 n_tables,
                                                                u32 limbs, const u32* off, const u32* term_pt, const u64* pt,
                                                                u64* wtab, u64 wtab_elems) {
@@ -73,11 +76,11 @@ __global__ void __launch_bounds__(256) gather_weights32_kernel(const Tile* tiles
     if (table >= n_tables) return;
     const u32 tile_i = owners[table];
     const Tile tile = tiles[tile_i];
-    const u64 K = tile.n_terms;
-    for (u64 i = (u64)sub * blockDim.x + threadIdx.x; i < K * limbs; i += (u64)GATHER32_BLOCKS * blockDim.x) {
-        const u32 limb = (u32)(i / K), t = (u32)(i % K);
+    const u64 per_limb = (u64)(G == 1 ? tile.n_terms : padded_terms32(tile.n_terms)) * G;
+    for (u64 i = (u64)sub * blockDim.x + threadIdx.x; i < per_limb * limbs; i += (u64)GATHER32_BLOCKS * blockDim.x) {
+        const u32 limb = (u32)(i / per_limb), entry = (u32)(i % per_limb), t = entry / G, g = entry % G;
         u32* dst = reinterpret_cast<u32*>(wtab + limb * wtab_elems + wbase[tile_i]);
-        dst[t] = (u32)pt[(size_t)term_pt[off[tile.out0] + t] * limbs + limb];
+        dst[entry] = g < tile.count && t < tile.n_terms ? (u32)pt[(size_t)term_pt[off[tile.out0 + g] + t] * limbs + limb] : 0;
     }
 }
 
@@ -125,6 +128,95 @@ mac_scalar32_single_kernel(Limb32Table lt, u32 limbs, u32 N, const Tile* tiles, 
         r1 = add_mod32(r1, old.y, c.q);
     }
     *dst = make_uint2(r0, r1);
+}
+
+// Groups of outputs with few terms (on_vector_alu; the others run on the matrix cores, he_mac_digits.hip).
+// One thread = two adjacent residues of one (component, limb) row x a group of G outputs.  Terms run in blocks of
+// four (the terms that pad a group to whole blocks have zero weights and the last real term's input again); a ring
+// of four inputs keeps each request a whole block of multiply-adds ahead of its use, and a term's G weights are
+// requested (scalar loads) while the term before is multiplied.
+// What bounds it: the memory while sums are short, then the multiply-adds (one per term, output and residue).  Launch of
+// 512 outputs at N = 2^12, L = 2, on the matrix cores and here: 256 groups of 4 outputs and 4 terms 38.1 and 22.8 us, of 4 and
+// 25 47.4 and 46.0, of 4 and 50 65.8 and 68.3; 113 of 9 and 9 36.8 and 29.3; 64 of 16 and 9 26.9 and 24.5, of 16 and 16 26.7 and 28.0.
+template <int G>
+__global__ void __launch_bounds__(MAC32_THREADS)
+mac_scalar32_kernel(Limb32Table lt, u32 limbs, u32 N, const Tile* tiles, u32 n_tiles, const u64* wbase, const u32* term_ct,
+                    const u64* wtab, u64 wtab_elems, const u32* ct_in, const u64* bias, u32* out, u32 accumulate) {
+    const u32 slices = N / MAC32_SLICE;
+    u32 b = blockIdx.x;
+    const u32 slice = b % slices; b /= slices;
+    const u32 tile_i = b % n_tiles; b /= n_tiles;
+    const u32 comp = b & 1;
+    const u32 limb = b >> 1;
+    const Limb32& c = lt.c[limb];
+    const u32 K = uniform_load(&tiles[tile_i].n_terms), count = uniform_load(&tiles[tile_i].count);
+    const u32 out0 = uniform_load(&tiles[tile_i].out0);
+    const u32* tc = term_ct + uniform_load(&tiles[tile_i].term0);
+    const u32* w = reinterpret_cast<const u32*>(wtab + limb * wtab_elems + uniform_load(wbase + tile_i));
+    const u32 pair = slice * MAC32_THREADS + threadIdx.x;
+    const size_t ct_pairs = (size_t)limbs * N;  // uint2 elements per ciphertext (2 components x limbs x N / 2)
+    const uint2* x_base = reinterpret_cast<const uint2*>(ct_in) + ((size_t)comp * limbs + limb) * (N / 2) + pair;
+    u64 acc[G][2];
+#pragma unroll
+    for (int g = 0; g < G; g++) acc[g][0] = acc[g][1] = 0;
+    if (K > 0) {
+        const u32 Kp = padded_terms32(K), last = K - 1;
+        uint2 xq[MAC32_BLOCK];
+#pragma unroll
+        for (u32 j = 0; j < MAC32_BLOCK; j++) xq[j] = x_base[(size_t)uniform_load(tc + min(j, last)) * ct_pairs];
+        u32 w_next[G];
+#pragma unroll
+        for (int g = 0; g < G; g++) w_next[g] = uniform_load(w + g);
+        u32 since = 0;
+        for (u32 t = 0; t < Kp; t += MAC32_BLOCK) {
+#pragma unroll
+            for (u32 j = 0; j < MAC32_BLOCK; j++) {
+                const uint2 x = xq[j];
+                xq[j] = x_base[(size_t)uniform_load(tc + min(t + MAC32_BLOCK + j, last)) * ct_pairs];
+                u32 wv[G];
+#pragma unroll
+                for (int g = 0; g < G; g++) wv[g] = w_next[g];
+                // (after the last term this reads the entry behind the group's: the plan's table is four times as large
+                // and more, see he_plan_create; never used)
+#pragma unroll
+                for (int g = 0; g < G; g++) w_next[g] = uniform_load(w + (size_t)(t + j + 1) * G + g);
+#pragma unroll
+                for (int g = 0; g < G; g++) {
+                    acc[g][0] += (u64)x.x * wv[g];
+                    acc[g][1] += (u64)x.y * wv[g];
+                }
+            }
+            since += MAC32_BLOCK;
+            if (since + MAC32_BLOCK > TERMS_PER_REDUCTION && t + MAC32_BLOCK < Kp) {
+                since = 0;
+#pragma unroll
+                for (int g = 0; g < G; g++) {
+                    acc[g][0] = fold48(acc[g][0], c);
+                    acc[g][1] = fold48(acc[g][1], c);
+                }
+            }
+        }
+    }
+    const bool with_bias = bias != nullptr && comp == 0;  // Alg. 4: the bias goes to component 0 only
+#pragma unroll
+    for (int g = 0; g < G; g++) {
+        if ((u32)g < count) {
+            const u32 o = out0 + g;
+            u32 r0 = barrett64(acc[g][0], c), r1 = barrett64(acc[g][1], c);
+            if (with_bias) {
+                const u32 bv = (u32)bias[(size_t)o * limbs + limb];
+                r0 = add_mod32(r0, bv, c.q);
+                r1 = add_mod32(r1, bv, c.q);
+            }
+            uint2* dst = reinterpret_cast<uint2*>(out) + (((size_t)o * 2 + comp) * limbs + limb) * (N / 2) + pair;
+            if (accumulate) {  // HE_ACCUMULATE: add what the output holds (uniform branch)
+                const uint2 old = *dst;
+                r0 = add_mod32(r0, old.x, c.q);
+                r1 = add_mod32(r1, old.y, c.q);
+            }
+            *dst = make_uint2(r0, r1);
+        }
+    }
 }
 
 // Alg. 7 summed, 32-bit moduli: one thread = two adjacent residues of one limb x G <= 4 outputs x both
@@ -456,28 +548,62 @@ int launch_unpack32(he_ctx* ctx, const u32* in, u64* out, size_t count, hipStrea
     return HE_OK;
 }
 
+template <int G>
+static void launch_scalar32_class(he_ctx* ctx, const he_plan* plan, u32 cls, u32 limbs, const u32* ct_in, const u64* pt, const u64* bias, u32* out,
+                                  u64* wtab, u32 accumulate, hipStream_t s) {
+    const u32 begin = plan->class_begin_s[cls], count = plan->class_begin_s[cls + 1] - begin;
+    if (count == 0) return;
+    const Tile* tiles = plan->tiles_s_dev + begin;
+    const u64* wbase = plan->wbase_s_dev + begin;
+    const u32 table = plan->table_s[begin], n_tables = plan->table_s[begin + count - 1] + 1 - table;
+    hipLaunchKernelGGL((gather_weights32_kernel<G>), dim3(n_tables * GATHER32_BLOCKS), dim3(256), 0, s, plan->tiles_s_dev, plan->wbase_s_dev,
+                       plan->owners_dev + table, n_tables, limbs, plan->off_dev, plan->term_pt_dev, pt, wtab, plan->wtab_elems);
+    const dim3 grid((u32)((u64)count * limbs * 2 * (ctx->N / MAC32_SLICE)));
+    if constexpr (G == 1)
+        hipLaunchKernelGGL(mac_scalar32_single_kernel, grid, dim3(MAC32_THREADS), 0, s, ctx->limbs32, limbs, ctx->N, tiles, count, wbase,
+                           plan->term_ct_dev, wtab, plan->wtab_elems, ct_in, bias, out, accumulate);
+    else
+        hipLaunchKernelGGL((mac_scalar32_kernel<G>), grid, dim3(MAC32_THREADS), 0, s, ctx->limbs32, limbs, ctx->N, tiles, count, wbase,
+                           plan->term_ct_dev, wtab, plan->wtab_elems, ct_in, bias, out, accumulate);
+}
+
+// Whether a class of groups with several outputs runs on the vector ALU (see mac_scalar32_kernel for the figures): the matrix
+// cores take terms in chunks of 16 and outputs in tiles of 8, pay for the whole of both, and every workgroup brings a table
+// of that size into its LDS.  Measured side by side over 1 to 50 terms and 2 to 16 outputs: where at most half of the tiles'
+// outputs are in use the vector ALU is the faster one up to about 40 terms (pairs of outputs that share their plaintexts, as in
+// a convolution of two filters: 24); where at most three quarters are, up to 18; beyond that, up to 12.
+static bool on_vector_alu(const he_plan* plan, u32 cls) {
+    const u32 begin = plan->class_begin_s[cls], end = plan->class_begin_s[cls + 1], tables = plan->table_s[end - 1] + 1 - plan->table_s[begin];
+    const u32 count = plan->max_count_s[cls], tile = count <= 8 ? 8 : 16;
+    const u32 limit = 2 * count <= tile ? (count <= 2 && end - begin >= 4 * tables ? 24 : 40) : 4 * count <= 3 * tile ? 18 : 12;
+    return plan->max_terms_s[cls] <= limit;
+}
+
 static int launch_scalar32(he_ctx* ctx, const he_plan* plan, u32 limbs, const u32* ct_in, const u64* pt, const u64* bias, u32* out, u64* wtab,
                            u32 accumulate, hipStream_t s) {
-    const u32 count = plan->class_begin_s[1];
-    if (count > 0) {
-        const u32 n_tables = plan->table_s[count - 1] + 1;
-        hipLaunchKernelGGL(gather_weights32_kernel, dim3(n_tables * GATHER32_BLOCKS), dim3(256), 0, s, plan->tiles_s_dev, plan->wbase_s_dev,
-                           plan->owners_dev, n_tables, limbs, plan->off_dev, plan->term_pt_dev, pt, wtab, plan->wtab_elems);
-        const u64 blocks = (u64)count * limbs * 2 * (ctx->N / MAC32_SLICE);
-        hipLaunchKernelGGL(mac_scalar32_single_kernel, dim3((u32)blocks), dim3(MAC32_THREADS), 0, s, ctx->limbs32, limbs, ctx->N, plan->tiles_s_dev,
-                           count, plan->wbase_s_dev, plan->term_ct_dev, wtab, plan->wtab_elems, ct_in, bias, out, accumulate);
-        HE_HIP(hipGetLastError());
-    }
+    launch_scalar32_class<1>(ctx, plan, 0, limbs, ct_in, pt, bias, out, wtab, accumulate, s);
     ScalarSlice sl;
-    for (u32 cls = 0; cls < SCALAR_CLASSES; cls++) {
-        sl.begin[cls] = cls == 0 ? 0 : plan->class_begin_s[cls];
-        sl.end[cls] = cls == 0 ? 0 : plan->class_begin_s[cls + 1];
-    }
-    sl.table_begin = 0;
-    sl.table_end = (u32)plan->table_end.size();
+    sl.begin[0] = sl.end[0] = 0;
+    sl.table_begin = sl.table_end = 0;
     sl.tab_skip = 0;
     sl.tab_words = plan->wtab_elems;
-    for (u64 t = 0; t == 0 || t < plan->max_terms; t += DIGIT_MAX_TERMS) {  // (sums beyond the range of the matrix cores')
+    u32 n_terms = 0;
+    for (u32 cls = 1; cls < SCALAR_CLASSES; cls++) {
+        sl.begin[cls] = sl.end[cls] = 0;
+        if (plan->class_begin_s[cls] == plan->class_begin_s[cls + 1]) continue;
+        if (on_vector_alu(plan, cls)) {
+            if (cls == 1) launch_scalar32_class<4>(ctx, plan, 1, limbs, ct_in, pt, bias, out, wtab, accumulate, s);
+            if (cls == 2) launch_scalar32_class<8>(ctx, plan, 2, limbs, ct_in, pt, bias, out, wtab, accumulate, s);
+            if (cls == 3) launch_scalar32_class<16>(ctx, plan, 3, limbs, ct_in, pt, bias, out, wtab, accumulate, s);
+            continue;
+        }
+        sl.begin[cls] = plan->class_begin_s[cls];
+        sl.end[cls] = plan->class_begin_s[cls + 1];
+        sl.table_end = plan->table_s[sl.end[cls] - 1] + 1;
+        n_terms = std::max(n_terms, plan->max_terms_s[cls]);
+    }
+    HE_HIP(hipGetLastError());
+    for (u64 t = 0; t < n_terms; t += DIGIT_MAX_TERMS) {  // (sums beyond the range of the matrix cores')
         sl.t_begin = (u32)t;
         sl.t_end = (u32)std::min<u64>(t + DIGIT_MAX_TERMS, ~0u);
         if (int rc = launch_mac_digits32(ctx, plan, sl, limbs, ct_in, pt, t == 0 ? bias : nullptr, out, wtab, t == 0 ? accumulate : 1u, s)) return rc;
@@ -501,8 +627,8 @@ static int launch_poly32_class(he_ctx* ctx, const he_plan* plan, int cls, u32 li
 // the grid sizes launch_mac32 would use, checked without launching anything
 int check_mac32_launch(he_ctx* ctx, const he_plan* plan, u32 limbs, int pt_kind) {
     if (pt_kind == HE_PT_SCALAR) {
-        const u64 singles = plan->class_begin_s[1];
-        if (singles * limbs * 2 * (ctx->N / MAC32_SLICE) > 0x7FFFFFFFull || singles * GATHER32_BLOCKS > 0x7FFFFFFFull) return HE_ERR_RANGE;
+        const u64 groups = plan->n_tiles_s;  // (as if all were in one launch)
+        if (groups * limbs * 2 * (ctx->N / MAC32_SLICE) > 0x7FFFFFFFull || groups * GATHER32_BLOCKS > 0x7FFFFFFFull) return HE_ERR_RANGE;
         return mac_digits_blocks(ctx, plan, limbs) > 0x7FFFFFFFull ? HE_ERR_RANGE : HE_OK;
     }
     for (u32 cls = 0; cls < 3; cls++) {

@@ -100,7 +100,12 @@ def host32(t):
 @pytest.mark.parametrize("bits,groups", [
     ([17, 24, 29, 30], [(c, t) for c in (2, 4, 5, 8, 9, 16) for t in (1, 16, 17)] + [(3, 15), (7, 64), (16, 65), (2, 129), (1, 20)]),
     ([30, 30], [(16, 4080), (16, 4081), (3, 8161), (8, 7), (1, 4097)]),
-], ids=["sizes", "long"])
+    # classes of few terms run on the vector ALU: the most that it takes, one more, and one class of three
+    ([30, 29, 20], [(c, t) for c in (2, 3, 4) for t in (1, 3, 15, 16, 39, 40)] + [(c, t) for c in (5, 6) for t in (1, 4, 17, 18)]
+     + [(c, t) for c in (9, 12) for t in (2, 5, 13, 18)] + [(1, 30)]),
+    ([30, 30], [(4, 41), (2, 5), (8, 12), (7, 1), (5, 11), (16, 13), (9, 2)]),
+    ([17, 30], [(4, 40), (6, 19), (5, 2), (16, 12), (13, 1), (10, 12), (3, 0), (2, 0)]),
+], ids=["sizes", "long", "few terms", "one class of few terms", "two classes of few terms"])
 @pytest.mark.parametrize("extreme", [False, True])
 def test_packed_group_sizes_and_term_counts(he, bits, groups, extreme):
     N = 1 << 10
