@@ -676,7 +676,8 @@ int he_plan_create(he_ctx* ctx, uint32_t n_in, uint32_t n_out, uint32_t n_pt, co
     std::vector<u32> owners, lists;
     std::vector<DigitTile> dts(ts.size());
     u64 elems = 0;
-    p->max_terms = 0;
+    p->max_terms = p->max_group_terms = 0;
+    for (u32 i = p->class_begin_s[1]; i < p->n_tiles_s; ++i) p->max_group_terms = std::max(p->max_group_terms, ts[i].n_terms);
     p->wbase_s.resize(ts.size());
     p->table_s.resize(ts.size());
     for (u32 cls = 0; cls < SCALAR_CLASSES; ++cls) {
@@ -704,8 +705,9 @@ int he_plan_create(he_ctx* ctx, uint32_t n_in, uint32_t n_out, uint32_t n_pt, co
             ts[begin + i] = t;
             if (i == 0 || table[order[i]] != table[order[i - 1]]) {
                 owners.push_back(begin + i);
-                // per 16 terms: one word per term (single outputs), else four tiles of 128 words per four outputs
-                p->table_end.push_back(elems + (u64)((t.n_terms + 15) / 16) * (cls == 0 ? 16 : 512 * output_tiles(t.count)));
+                // one word per term (single outputs), else per four terms and four outputs a tile of 128 words
+                const u32 pad = cls == 0 || p->short_sums() ? BLOCK_TERMS : LIST_CHUNK, padded = (t.n_terms + pad - 1) / pad * pad;
+                p->table_end.push_back(elems + (cls == 0 ? padded : (u64)padded / BLOCK_TERMS * 128 * output_tiles(t.count)));
             }
             p->wbase_s[begin + i] = elems;
             p->table_s[begin + i] = (u32)owners.size() - 1;

@@ -107,6 +107,7 @@ struct DigitTile {
     u32 pad;
 };
 constexpr u32 LIST_CHUNK = 16;  // terms per chunk of a list (and of a table's padding)
+constexpr u32 BLOCK_TERMS = 4;  // ... of a block, the terms of one matrix instruction on 64-bit residues
 
 struct he_plan {
     he_ctx* ctx;
@@ -120,6 +121,8 @@ struct he_plan {
     u32 max_terms_s[SCALAR_CLASSES];  // most terms of any scalar tile of the class
     u32 max_count_s[SCALAR_CLASSES];  // most outputs of any scalar tile of the class
     u32 max_terms;         // most terms of any tile
+    u32 max_group_terms;   // ... of any tile with several outputs
+    bool short_sums() const { return max_group_terms <= BLOCK_TERMS; }  // (tables of one block per group)
     Tile* tiles_s_dev;
     Tile* tiles_p_dev;
     // Tables of gathered weights (scalar plaintexts): tiles with equal plaintexts share one.  Within a class the tiles

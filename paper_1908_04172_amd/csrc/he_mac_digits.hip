@@ -41,6 +41,7 @@ constexpr u32 TILE_WORDS = 128;                             // 64-bit words of a
 constexpr u32 GROUPS_PER_WG = 16;                           // groups a workgroup runs through, at most
 constexpr u64 MIN_WORKGROUPS = 2048;                        // ... while the launch keeps at least this many workgroups
 static_assert(DIGIT_MAX_TERMS % CHUNK_TERMS == 0, "the parts of a long sum are whole chunks");
+static_assert(BLOCK_TERMS == 32 / sizeof(u64), "the terms that one instruction contracts");
 
 // What the storage form of a residue sets (V = u64 or u32): its digits D fill sizeof(V) bytes of the contraction, an
 // output has D sums.
@@ -71,18 +72,18 @@ __device__ __forceinline__ void lds_barrier() { asm volatile("s_waitcnt lgkmcnt(
 // the matrix instruction's operand as the lanes read it.  Lane (row r, half h) holds row r's elements of half h's terms of
 // the block: positions h * LANE_TERMS .. of the order in which the term lists are stored (he_plan::lists_dev).  Row r
 // belongs to half (r >> 2) & 1 of the tile's outputs and there to sum (r & 3) + 4 * (r >> 3) of the 16 of that half's lanes.
-// Terms beyond the group's (up to whole chunks) and outputs beyond its count are zeros.  One thread: one (term, output,
-// limb).
+// Terms beyond the group's (up to a multiple of `pad`: whole chunks, or one block for a plan of short sums, see SHORT) and
+// outputs beyond its count are zeros.  One thread: one (term, output, limb).
 template <typename V>
 __global__ void __launch_bounds__(256) gather_digits_kernel(DigitTable dt, const Tile* tiles, const u64* wbase, const u32* owners, u32 limbs,
                                                             const u32* off, const u32* term_pt, const u64* pt, u64* tab, u64 tab_words,
-                                                            u64 tab_skip, u32 t_begin, u32 t_end) {
+                                                            u64 tab_skip, u32 t_begin, u32 t_end, u32 pad) {
     using F = Form<V>;
     const u32 tile_i = uniform_load(owners + blockIdx.y);
     const Tile tile = tiles[tile_i];
     const u32 first = min(t_begin, tile.n_terms), K = min(t_end, tile.n_terms) - first;
     const u32 ot = F::tiles(tile.count), G = F::TILE_OUTPUTS * ot;
-    const u32 Kp = (K + CHUNK_TERMS - 1) / CHUNK_TERMS * CHUNK_TERMS;
+    const u32 Kp = (K + pad - 1) / pad * pad;
     const u64 total = (u64)Kp * G * limbs;
     u64* dst = tab + (wbase[tile_i] - tab_skip);
     for (u64 i = (u64)blockIdx.x * 256 + threadIdx.x; i < total; i += (u64)gridDim.x * 256) {
@@ -300,10 +301,15 @@ __device__ __forceinline__ v4i operand(const u32x4 (&x)[4], int k) {
 // for the loads it needs and no others.
 // RESIDENT: the groups share one table, which the workgroup has put into the LDS; the wavefronts do not meet.
 // Otherwise the workgroup brings the next chunk's table tiles into the other half of the LDS meanwhile.
-template <typename V, int OT, bool RESIDENT>
+// SHORT: no group of the plan has more terms than one block takes (1x1 convolutions over few channels), and a chunk is that
+// one block: with the other three as padding a quarter of the loads and products were of use.  (N = 2^13, L = 4: 256 groups of
+// 16 outputs and one term with plaintexts of their own 1000 -> 785 us, 935 on the vector ALU; of two outputs that share their
+// plaintexts 197 -> 135.)
+template <typename V, int OT, bool RESIDENT, bool SHORT>
 __device__ __forceinline__ void mac_stream(const MacArgs<V>& a, const Slice<V>& w, const DigitConst& c, u32 tile_first, u32 tile_end, v4i* lds) {
     using F = Form<V>;
-    constexpr u32 CHUNK_BLOCKS = F::CHUNK_BLOCKS, LANE_TERMS = F::LANE_TERMS;
+    static_assert(!SHORT || (RESIDENT && F::LANE_TERMS <= 4), "one chunk, its list in one piece");
+    constexpr u32 CHUNK_BLOCKS = SHORT ? 1 : F::CHUNK_BLOCKS, LANE_TERMS = F::LANE_TERMS;
     constexpr int CT = F::CT;
     constexpr u32 CHUNK_PIECES = CHUNK_BLOCKS * OT * 64;  // 16-byte pieces of a chunk's tiles
     constexpr u32 PER_THREAD = CHUNK_PIECES < THREADS ? 1 : CHUNK_PIECES / THREADS;
@@ -340,11 +346,11 @@ __device__ __forceinline__ void mac_stream(const MacArgs<V>& a, const Slice<V>& 
     u32 buf = 0;
     if constexpr (!RESIDENT) request_tiles(cur);
     request_idx(cur, 0);
-    request_idx(cur, 1);
+    if constexpr (!SHORT) request_idx(cur, 1);
 #pragma unroll
     for (u32 b = 0; b < CHUNK_BLOCKS; b++) request_x(b);
     request_idx(nxt, 0);
-    request_idx(nxt, 1);
+    if constexpr (!SHORT) request_idx(nxt, 1);
     if constexpr (!RESIDENT) write_tiles(0);
     while (true) {
         const u32 tile = cur.tile, chunks = cur.n_chunks;
@@ -363,7 +369,7 @@ __device__ __forceinline__ void mac_stream(const MacArgs<V>& a, const Slice<V>& 
 #pragma unroll
                 for (int k = 0; k < CT; k++) in[k] = operand(x[b], k);
                 request_x(b);
-                if ((b + 1) * LANE_TERMS == 4) request_idx(after, 0);
+                if (SHORT || (b + 1) * LANE_TERMS == 4) request_idx(after, 0);
                 if ((b + 1) * LANE_TERMS == 8) request_idx(after, 1);
 #pragma unroll
                 for (int o = 0; o < OT; o++) {
@@ -395,11 +401,15 @@ __device__ __forceinline__ void mac_stream(const MacArgs<V>& a, const Slice<V>& 
     }
 }
 
+// 16-byte pieces of table tiles that a workgroup keeps in its LDS
+template <typename V, bool SHORT>
+constexpr u32 lds_pieces(int ot) { return (SHORT ? 1 : RESIDENT_CHUNKS * Form<V>::CHUNK_BLOCKS) * ot * 64; }
+
 struct MacClass {
     u32 first, end, per_wg, blocks;  // the class's groups among the plan's tiles, groups per workgroup and workgroups
 };
 
-template <typename V, int OT>
+template <typename V, int OT, bool SHORT>
 __device__ __forceinline__ void mac_class(u32 b, const MacArgs<V>& a, const DigitTable& dt, const MacClass& m, v4i* lds) {
     using F = Form<V>;
     const u32 parts = a.N / F::SLOTS;
@@ -433,19 +443,21 @@ __device__ __forceinline__ void mac_class(u32 b, const MacArgs<V>& a, const Digi
             zero.clear();
             store_group<V, OT>(zero, a, w, c, t.out0, t.count);
             tile++;
-        } else if (p.n_chunks <= RESIDENT_CHUNKS) {
+        } else if (SHORT || p.n_chunks <= RESIDENT_CHUNKS) {
             const u32 end = min(tile_end, t.same_until);
-            const u32 pieces = p.n_chunks * F::CHUNK_BLOCKS * OT * 64;
+            const u32 pieces = SHORT ? OT * 64 : p.n_chunks * F::CHUNK_BLOCKS * OT * 64;
             lds_barrier();  // (the table of the groups before is no longer read)
             for (u32 i = threadIdx.x; i < pieces; i += THREADS) lds[i] = w.tab[p.piece + i];
             lds_barrier();
-            mac_stream<V, OT, true>(a, w, c, tile, end, lds);
+            mac_stream<V, OT, true, SHORT>(a, w, c, tile, end, lds);
             tile = end;
         } else {
             // the rest of the run: groups with long sums follow one another (tables of a class are in the order of
             // their first use, so a shorter one may still come and takes the same path)
-            lds_barrier();
-            mac_stream<V, OT, false>(a, w, c, tile, tile_end, lds);
+            if constexpr (!SHORT) {
+                lds_barrier();
+                mac_stream<V, OT, false, false>(a, w, c, tile, tile_end, lds);
+            }
             tile = tile_end;
         }
     }
@@ -453,22 +465,22 @@ __device__ __forceinline__ void mac_class(u32 b, const MacArgs<V>& a, const Digi
 
 // 64-bit residues: groups of 9..16 (OT = 4), 5..8 (2) and 2..4 (1) outputs; packed ones: of 9..16 (2) and up to 8 (1).
 // The accumulators, OT x CT x 16 registers, set how many wavefronts a SIMD holds.
-template <typename V, int OT>
+template <typename V, int OT, bool SHORT>
 __global__ void __launch_bounds__(THREADS, OT * Form<V>::CT == 8 ? 2 : OT * Form<V>::CT == 4 ? 3 : 4)
 mac_digits_kernel(DigitTable dt, MacArgs<V> a, MacClass m) {
-    __shared__ v4i lds[RESIDENT_CHUNKS * Form<V>::CHUNK_BLOCKS * OT * 64];
-    mac_class<V, OT>(blockIdx.x, a, dt, m, lds);
+    __shared__ v4i lds[lds_pieces<V, SHORT>(OT)];
+    mac_class<V, OT, SHORT>(blockIdx.x, a, dt, m, lds);
 }
 
 // A plan with groups of several classes in one launch: the first workgroups take the largest class, and the smaller
 // ones (often the ragged end of a layer) fill in while it drains.
-template <typename V>
+template <typename V, bool SHORT>
 __global__ void __launch_bounds__(THREADS, 2) mac_digits_mixed_kernel(DigitTable dt, MacArgs<V> a, MacClass c16, MacClass c8, MacClass c4) {
     constexpr int OT16 = Form<V>::tiles(16), OT8 = Form<V>::tiles(8), OT4 = Form<V>::tiles(4);
-    __shared__ v4i lds[RESIDENT_CHUNKS * Form<V>::CHUNK_BLOCKS * OT16 * 64];
-    if (blockIdx.x < c16.blocks) mac_class<V, OT16>(blockIdx.x, a, dt, c16, lds);
-    else if (blockIdx.x < c16.blocks + c8.blocks) mac_class<V, OT8>(blockIdx.x - c16.blocks, a, dt, c8, lds);
-    else mac_class<V, OT4>(blockIdx.x - c16.blocks - c8.blocks, a, dt, c4, lds);
+    __shared__ v4i lds[lds_pieces<V, SHORT>(OT16)];
+    if (blockIdx.x < c16.blocks) mac_class<V, OT16, SHORT>(blockIdx.x, a, dt, c16, lds);
+    else if (blockIdx.x < c16.blocks + c8.blocks) mac_class<V, OT8, SHORT>(blockIdx.x - c16.blocks, a, dt, c8, lds);
+    else mac_class<V, OT4, SHORT>(blockIdx.x - c16.blocks - c8.blocks, a, dt, c4, lds);
 }
 
 // Groups per workgroup and workgroups of one class over the tiles [first, end).  Several groups per workgroup pay the
@@ -481,6 +493,16 @@ MacClass mac_class_of(const he_ctx* ctx, const he_plan* plan, u32 limbs, u32 cls
     while (per_wg > 1 && (u64)((count + per_wg - 1) / per_wg) * per_run < MIN_WORKGROUPS) per_wg /= 2;
     const u64 blocks = (u64)((count + per_wg - 1) / per_wg) * per_run;
     return MacClass{first, end, per_wg, (u32)std::min<u64>(blocks, 0x7FFFFFFFull)};
+}
+
+template <typename V, bool SHORT>
+void launch_classes(he_ctx* ctx, const MacArgs<V>& a, const MacClass (&c)[SCALAR_CLASSES], u64 blocks, hipStream_t s) {
+    const dim3 grid((u32)blocks), block(THREADS);
+    constexpr int OT16 = Form<V>::tiles(16), OT8 = Form<V>::tiles(8), OT4 = Form<V>::tiles(4);
+    if (c[3].blocks == blocks) hipLaunchKernelGGL((mac_digits_kernel<V, OT16, SHORT>), grid, block, 0, s, ctx->digits, a, c[3]);
+    else if (c[2].blocks == blocks) hipLaunchKernelGGL((mac_digits_kernel<V, OT8, SHORT>), grid, block, 0, s, ctx->digits, a, c[2]);
+    else if (c[1].blocks == blocks) hipLaunchKernelGGL((mac_digits_kernel<V, OT4, SHORT>), grid, block, 0, s, ctx->digits, a, c[1]);
+    else hipLaunchKernelGGL((mac_digits_mixed_kernel<V, SHORT>), grid, block, 0, s, ctx->digits, a, c[3], c[2], c[1]);
 }
 
 template <typename V>
@@ -496,6 +518,7 @@ int launch_mac_digits_t(he_ctx* ctx, const he_plan* plan, const ScalarSlice& sl,
     }
     if (blocks == 0) return HE_OK;
     const u32 table0 = plan->table_s[first];
+    const bool short_sums = sizeof(V) == sizeof(u64) && plan->short_sums();  // (packed sums that short run on the vector ALU)
     // about one entry per thread, but no more workgroups than fill the chip a few times
     const u64 entries = (u64)std::min(plan->max_terms, sl.t_end - sl.t_begin) * 16 * limbs;
     const u32 n_tables = sl.table_end - table0;
@@ -503,16 +526,14 @@ int launch_mac_digits_t(he_ctx* ctx, const he_plan* plan, const ScalarSlice& sl,
     for (u32 t = 0; t < n_tables; t += 32768) {  // (the grid's second dimension is limited to 65535)
         hipLaunchKernelGGL(gather_digits_kernel<V>, dim3(per_table, std::min<u32>(n_tables - t, 32768)), dim3(256), 0, s, ctx->digits,
                            plan->tiles_s_dev, plan->wbase_s_dev, plan->owners_dev + table0 + t, limbs, plan->off_dev, plan->term_pt_dev, pt, wtab,
-                           sl.tab_words, sl.tab_skip, sl.t_begin, sl.t_end);
+                           sl.tab_words, sl.tab_skip, sl.t_begin, sl.t_end, short_sums ? BLOCK_TERMS : CHUNK_TERMS);
     }
     const MacArgs<V> a{plan->digit_tiles_dev, plan->lists_dev, wtab, sl.tab_words, sl.tab_skip, ct_in, bias, out, limbs, ctx->N, sl.t_begin,
                        sl.t_end, mode};
-    const dim3 grid((u32)blocks), block(THREADS);
-    constexpr int OT16 = Form<V>::tiles(16), OT8 = Form<V>::tiles(8), OT4 = Form<V>::tiles(4);
-    if (c[3].blocks == blocks) hipLaunchKernelGGL((mac_digits_kernel<V, OT16>), grid, block, 0, s, ctx->digits, a, c[3]);
-    else if (c[2].blocks == blocks) hipLaunchKernelGGL((mac_digits_kernel<V, OT8>), grid, block, 0, s, ctx->digits, a, c[2]);
-    else if (c[1].blocks == blocks) hipLaunchKernelGGL((mac_digits_kernel<V, OT4>), grid, block, 0, s, ctx->digits, a, c[1]);
-    else hipLaunchKernelGGL(mac_digits_mixed_kernel<V>, grid, block, 0, s, ctx->digits, a, c[3], c[2], c[1]);
+    if constexpr (sizeof(V) == sizeof(u64)) {
+        if (short_sums) launch_classes<V, true>(ctx, a, c, blocks, s);
+    }
+    if (!short_sums) launch_classes<V, false>(ctx, a, c, blocks, s);
     HE_HIP(hipGetLastError());
     return HE_OK;
 }

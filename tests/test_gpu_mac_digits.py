@@ -76,6 +76,27 @@ def test_group_sizes_and_term_counts_on_moduli_of_every_width(he, bits, extreme)
     assert np.array_equal(run(he, ctx, plan, ct, w, b, flags=he.RESCALE), layer)
 
 
+@pytest.mark.parametrize("groups", [[(16, 1)], [(8, 4)], [(2, 3), (4, 4)], [(16, 4), (9, 2), (5, 1), (8, 3), (2, 4), (3, 0), (12, 0), (1, 7)],
+                                    [(c, 1 + k % 4) for k, c in enumerate([2, 3, 7, 16, 13, 4, 1] * 40)]], ids=lambda g: f"{len(g)}-{g[0]}")
+@pytest.mark.parametrize("extreme", [False, True])
+def test_plans_of_short_sums(he, groups, extreme):
+    """No group of outputs with more than four terms: tables of one block.  (The longest plan chains groups in a workgroup.)"""
+    N = 1 << 11
+    q = wl.modulus_chain([60, 50, 40, 61], N)
+    ctx = he.Context(11, q)
+    plan = groups_plan(groups, 40, 50, len(groups))
+    ct, w, b = operands(plan, q, N, 9, extreme)
+    want = oracle.mac(ct, q, plan.off, plan.term_ct, plan.term_pt, w, oracle.PT_SCALAR, b)
+    out = dev(want)
+    got = run(he, ctx, plan, ct, w, b)
+    assert np.array_equal(got, want)
+    run(he, ctx, plan, ct, w, b, flags=he.ACCUMULATE, out=out)
+    assert np.array_equal(host(out), (2 * want.astype(object) % np.asarray(q, object)[:, None]).astype(np.uint64))
+    if plan.n_out < 500:
+        layer, _ = oracle.layer(ct, q, ctx.psi, plan.off, plan.term_ct, plan.term_pt, w, oracle.PT_SCALAR, b)
+        assert np.array_equal(run(he, ctx, plan, ct, w, b, flags=he.RESCALE), layer)
+
+
 @pytest.mark.parametrize("terms", [4079, 4080, 4081, 8161])
 def test_sums_beyond_the_range_of_the_32_bit_accumulators(he, terms):
     N = 1 << 10
