@@ -67,8 +67,11 @@ __device__ __forceinline__ void housekeeping(MacAcc (&acc)[A], u32& f, u32& r, u
 // case: a plain Alg. 8 call over a tensor).  There is little arithmetic per byte here, so the kernel
 // is shaped for the memory system instead: a thread handles SL pairs of adjacent residues (16-byte
 // accesses, SL independent loads in flight), a workgroup 512*SL residues of one row.
-template <int SL>
-__global__ void __launch_bounds__(MAC_THREADS)
+// WAVES: the wavefronts per SIMD, no more and no fewer.  The registers allow five, which longer sums want; up to two terms the
+// fifth only adds rows to what the memory is working on at once.  N = 2^14, L = 4, four and five (the launch): one term
+// of 500 ciphertexts 196 and 204 us, two terms of 300 149 and 151, four 210 and 200, nine 285 and 252.
+template <int SL, int WAVES>
+__global__ void __launch_bounds__(MAC_THREADS) __attribute__((amdgpu_waves_per_eu(WAVES, WAVES)))
 mac_scalar_single_kernel(LimbTable lt, u32 limbs, u32 N, const Tile* tiles, u32 n_tiles, const u64* wbase, const u32* term_ct,
                          const u64* wtab, u64 tab_words, u64 tab_skip, u32 t_begin, u32 t_end, const u64* ct_in, const u64* bias, u64* out,
                          u32 accumulate) {
@@ -252,14 +255,13 @@ static int launch_scalar_single(he_ctx* ctx, const he_plan* plan, const ScalarSl
     HE_HIP(hipGetLastError());
     const u32 per_thread = ctx->N >= 2048 ? 4 : 2;
     const u64 blocks = (u64)count * limbs * 2 * (ctx->N / (MAC_THREADS * 2 * per_thread));
-    if (per_thread == 4)
-        hipLaunchKernelGGL((mac_scalar_single_kernel<4>), dim3((u32)blocks), dim3(MAC_THREADS), 0, s, ctx->limbs, limbs, ctx->N, tiles + begin,
-                           count, plan->wbase_s_dev + begin, plan->term_ct_dev, wtab, sl.tab_words, sl.tab_skip, sl.t_begin, sl.t_end, ct_in,
-                           bias, out, accumulate);
-    else
-        hipLaunchKernelGGL((mac_scalar_single_kernel<2>), dim3((u32)blocks), dim3(MAC_THREADS), 0, s, ctx->limbs, limbs, ctx->N, tiles + begin,
-                           count, plan->wbase_s_dev + begin, plan->term_ct_dev, wtab, sl.tab_words, sl.tab_skip, sl.t_begin, sl.t_end, ct_in,
-                           bias, out, accumulate);
+    auto launch = [&](auto kernel) {
+        hipLaunchKernelGGL(kernel, dim3((u32)blocks), dim3(MAC_THREADS), 0, s, ctx->limbs, limbs, ctx->N, tiles + begin, count, plan->wbase_s_dev + begin,
+                           plan->term_ct_dev, wtab, sl.tab_words, sl.tab_skip, sl.t_begin, sl.t_end, ct_in, bias, out, accumulate);
+    };
+    if (per_thread == 2) launch(mac_scalar_single_kernel<2, 8>);
+    else if (plan->max_terms_s[0] <= 2) launch(mac_scalar_single_kernel<4, 4>);
+    else launch(mac_scalar_single_kernel<4, 5>);
     HE_HIP(hipGetLastError());
     return HE_OK;
 }

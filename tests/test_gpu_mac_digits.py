@@ -97,6 +97,21 @@ def test_plans_of_short_sums(he, groups, extreme):
         assert np.array_equal(run(he, ctx, plan, ct, w, b, flags=he.RESCALE), layer)
 
 
+@pytest.mark.parametrize("log2N", [10, 11, 13])
+@pytest.mark.parametrize("terms", [[1], [2, 1, 0], [3, 1, 2]], ids=str)
+def test_single_outputs_of_few_terms(he, log2N, terms):
+    """Outputs that share their inputs with no other: the forms of the streaming kernel."""
+    N = 1 << log2N
+    q = wl.modulus_chain([60, 50, 30], N)
+    ctx = he.Context(log2N, q)
+    plan = groups_plan([(1, t) for t in terms * 5], 7, 9, log2N)
+    ct, w, b = operands(plan, q, N, 70 + log2N, True)
+    want = oracle.mac(ct, q, plan.off, plan.term_ct, plan.term_pt, w, oracle.PT_SCALAR, b)
+    assert np.array_equal(run(he, ctx, plan, ct, w, b), want)
+    layer, _ = oracle.layer(ct, q, ctx.psi, plan.off, plan.term_ct, plan.term_pt, w, oracle.PT_SCALAR, b)
+    assert np.array_equal(run(he, ctx, plan, ct, w, b, flags=he.RESCALE), layer)
+
+
 @pytest.mark.parametrize("terms", [4079, 4080, 4081, 8161])
 def test_sums_beyond_the_range_of_the_32_bit_accumulators(he, terms):
     N = 1 << 10
