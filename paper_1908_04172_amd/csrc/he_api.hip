@@ -260,8 +260,8 @@ __global__ void __launch_bounds__(256) add_kernel(LimbTable lt, u32 limbs, u32 N
     const size_t half = N / 2;
     const size_t total = n_ct * limbs * half;
     const size_t first = (size_t)blockIdx.x * (256 * ADD_UNROLL) + threadIdx.x;
-    ulonglong2* p[ADD_UNROLL];
-    ulonglong2 v[ADD_UNROLL], a[ADD_UNROLL];
+    u64x2* p[ADD_UNROLL];
+    u64x2 v[ADD_UNROLL], a[ADD_UNROLL];
     u64 q[ADD_UNROLL];
 #pragma unroll
     for (u32 u = 0; u < ADD_UNROLL; u++) {
@@ -273,10 +273,10 @@ __global__ void __launch_bounds__(256) add_kernel(LimbTable lt, u32 limbs, u32 N
         const u32 limb = (u32)(row % limbs);
         const size_t c_idx = row / limbs;
         q[u] = lt.c[limb].q;
-        p[u] = reinterpret_cast<ulonglong2*>(ct + ((c_idx * 2) * limbs + limb) * N) + k2;
+        p[u] = reinterpret_cast<u64x2*>(ct + ((c_idx * 2) * limbs + limb) * N) + k2;
         v[u] = *p[u];
         if constexpr (POLY) {
-            a[u] = reinterpret_cast<const ulonglong2*>(pt + row * N)[k2];
+            a[u] = reinterpret_cast<const u64x2*>(pt + row * N)[k2];
         } else {
             a[u].x = a[u].y = pt[row];
         }

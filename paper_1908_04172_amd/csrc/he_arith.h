@@ -10,6 +10,12 @@ typedef uint64_t u64;
 typedef uint32_t u32;
 typedef unsigned __int128 u128;
 
+// 16 bytes of a caller's tensor or workspace: two residues, or four packed ones.  Device pointers of the ABI are 8-byte
+// aligned and no more, so the types say that much: the compiler still makes one 16-byte access of it, which global memory
+// takes at any multiple of four bytes, and assumes nothing else about the address.
+typedef u64 u64x2 __attribute__((ext_vector_type(2), aligned(8)));
+typedef u32 u32x4 __attribute__((ext_vector_type(4), aligned(8)));
+
 #define HE_HD __host__ __device__ __forceinline__
 
 // Per-limb constants, computed once per context on the host.

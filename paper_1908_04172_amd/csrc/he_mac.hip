@@ -95,9 +95,9 @@ mac_scalar_single_kernel(LimbTable lt, u32 limbs, u32 N, const Tile* tiles, u32 
     for (int s = 0; s < SL; s++) { acc_clear(acc[s][0]); acc_clear(acc[s][1]); }
     u32 f = 0, r = 0;
     for (u32 t = 0; t < K; ++t) {
-        const ulonglong2* row = reinterpret_cast<const ulonglong2*>(ct_in + (size_t)tc[t] * ct_stride + row_off);
+        const u64x2* row = reinterpret_cast<const u64x2*>(ct_in + (size_t)tc[t] * ct_stride + row_off);
         const u64 wv = w[t];
-        ulonglong2 x[SL];
+        u64x2 x[SL];
 #pragma unroll
         for (int s = 0; s < SL; s++) x[s] = row[s * MAC_THREADS + threadIdx.x];
 #pragma unroll
@@ -125,14 +125,14 @@ mac_scalar_single_kernel(LimbTable lt, u32 limbs, u32 N, const Tile* tiles, u32 
     }
     const u32 o = tile.out0;
     const u64 bv = (bias != nullptr && comp == 0) ? bias[(size_t)o * limbs + limb] : 0;
-    ulonglong2* dst = reinterpret_cast<ulonglong2*>(out + (size_t)o * ct_stride + row_off);
+    u64x2* dst = reinterpret_cast<u64x2*>(out + (size_t)o * ct_stride + row_off);
 #pragma unroll
     for (int s = 0; s < SL; s++) {
-        ulonglong2 v;
+        u64x2 v;
         v.x = add_mod(acc_reduce(acc[s][0], c), bv, c.q);
         v.y = add_mod(acc_reduce(acc[s][1], c), bv, c.q);
         if (accumulate & MAC_ACCUMULATE) {
-            const ulonglong2 old = dst[s * MAC_THREADS + threadIdx.x];
+            const u64x2 old = dst[s * MAC_THREADS + threadIdx.x];
             v.x = add_mod(v.x, old.x, c.q);
             v.y = add_mod(v.y, old.y, c.q);
         }
@@ -173,11 +173,11 @@ mac_poly_kernel(LimbTable lt, u32 limbs, u32 N, const Tile* tiles, u32 n_tiles, 
     // The operands of term t + 1 are requested before term t is multiplied: twice the bytes in flight per wave
     // (the kernel is bound by HBM latency times the bytes outstanding).  Outputs beyond the group's count read the
     // first output's plaintexts again (tp[g] points there) and are not stored.
-    ulonglong2 x0, x1, p[G];
-    auto request = [&](u32 t, ulonglong2& a0, ulonglong2& a1, ulonglong2 (&w)[G]) {
+    u64x2 x0, x1, p[G];
+    auto request = [&](u32 t, u64x2& a0, u64x2& a1, u64x2 (&w)[G]) {
         const u64* xp = x_base + (size_t)tc[t] * ct_stride;
-        a0 = *reinterpret_cast<const ulonglong2*>(xp);
-        a1 = *reinterpret_cast<const ulonglong2*>(xp + comp_stride);
+        a0 = *reinterpret_cast<const u64x2*>(xp);
+        a1 = *reinterpret_cast<const u64x2*>(xp + comp_stride);
 #pragma unroll
         for (int g = 0; g < G; g++) {
             // read once: a non-temporal load keeps it from displacing the reused ciphertext rows in L2
@@ -188,7 +188,7 @@ mac_poly_kernel(LimbTable lt, u32 limbs, u32 N, const Tile* tiles, u32 n_tiles, 
     };
     if (K > 0) request(0, x0, x1, p);
     for (u32 t = 0; t < K; t++) {
-        ulonglong2 x0n = x0, x1n = x1, pn[G];
+        u64x2 x0n = x0, x1n = x1, pn[G];
 #pragma unroll
         for (int g = 0; g < G; g++) pn[g] = p[g];
         if (t + 1 < K) request(t + 1, x0n, x1n, pn);
@@ -220,21 +220,21 @@ mac_poly_kernel(LimbTable lt, u32 limbs, u32 N, const Tile* tiles, u32 n_tiles, 
         if ((u32)g < tile.count) {
             const u32 o = tile.out0 + g;
             const u64 bv = bias != nullptr ? bias[(size_t)o * limbs + limb] : 0;
-            ulonglong2 v0, v1;
+            u64x2 v0, v1;
             v0.x = add_mod(acc_reduce(acc[4 * g + 0], c), bv, c.q);
             v0.y = add_mod(acc_reduce(acc[4 * g + 1], c), bv, c.q);
             v1.x = acc_reduce(acc[4 * g + 2], c);
             v1.y = acc_reduce(acc[4 * g + 3], c);
             u64* dst = out + ((size_t)o * 2 * limbs + limb) * N + n;
             if (accumulate & MAC_ACCUMULATE) {
-                const ulonglong2 o0 = *reinterpret_cast<const ulonglong2*>(dst), o1 = *reinterpret_cast<const ulonglong2*>(dst + comp_stride);
+                const u64x2 o0 = *reinterpret_cast<const u64x2*>(dst), o1 = *reinterpret_cast<const u64x2*>(dst + comp_stride);
                 v0.x = add_mod(v0.x, o0.x, c.q);
                 v0.y = add_mod(v0.y, o0.y, c.q);
                 v1.x = add_mod(v1.x, o1.x, c.q);
                 v1.y = add_mod(v1.y, o1.y, c.q);
             }
-            *reinterpret_cast<ulonglong2*>(dst) = v0;
-            *reinterpret_cast<ulonglong2*>(dst + comp_stride) = v1;
+            *reinterpret_cast<u64x2*>(dst) = v0;
+            *reinterpret_cast<u64x2*>(dst + comp_stride) = v1;
             __builtin_amdgcn_sched_barrier(0);
         }
     }

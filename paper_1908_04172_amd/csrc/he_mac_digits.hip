@@ -31,7 +31,7 @@
 namespace {
 
 typedef int v4i __attribute__((ext_vector_type(4)));
-typedef u32 u32x4 __attribute__((ext_vector_type(4)));
+typedef v4i v4i_mem __attribute__((aligned(8)));  // ... in the workspace (see u32x4)
 typedef int v16i __attribute__((ext_vector_type(16)));
 
 constexpr u32 THREADS = 256, WAVES = THREADS / 64;
@@ -202,7 +202,7 @@ struct Slice {
     u32 comp, limb, lane, half;
     u32 ct_stride;       // bytes (below 2^32 for 16 limbs of 2^15 residues)
     const char* x_base;  // this lane's slots of ciphertext 0
-    const v4i* tab;      // the limb's tables
+    const v4i_mem* tab;  // the limb's tables
     V* dst;              // this lane's slots of output 0
 };
 
@@ -259,7 +259,7 @@ __device__ __forceinline__ void store_group(const Sums<V, OT>& sums, const MacAr
                     v[k] = reduce(r, st);
                 }
                 if (mine) {
-                    typedef V row_piece __attribute__((ext_vector_type(CT)));  // 16 bytes
+                    typedef V row_piece __attribute__((ext_vector_type(CT), aligned(8)));  // 16 bytes (see u64x2)
                     if (accumulate) {
                         const row_piece old = *reinterpret_cast<const row_piece*>(at);
 #pragma unroll
@@ -335,7 +335,7 @@ __device__ __forceinline__ void mac_stream(const MacArgs<V>& a, const Slice<V>& 
     // (with fewer pieces than threads some pieces are brought twice)
     v4i stage[PER_THREAD];
     auto request_tiles = [&](const Cursor& p) {
-        const v4i* src = w.tab + (p.piece + (u64)p.chunk * CHUNK_PIECES);
+        const v4i_mem* src = w.tab + (p.piece + (u64)p.chunk * CHUNK_PIECES);
 #pragma unroll
         for (u32 i = 0; i < PER_THREAD; i++) stage[i] = src[(i * THREADS + threadIdx.x) % CHUNK_PIECES];
     };
@@ -429,7 +429,7 @@ __device__ __forceinline__ void mac_class(u32 b, const MacArgs<V>& a, const Digi
     const size_t at = ((size_t)w.comp * a.limbs + w.limb) * a.N + part * F::SLOTS + threadIdx.x / 64 * (32 * F::CT) + F::CT * (w.lane % 32);
     w.x_base = reinterpret_cast<const char*>(a.ct_in + at);
     w.dst = a.out + at;
-    w.tab = reinterpret_cast<const v4i*>(a.tab + (u64)w.limb * a.tab_words);
+    w.tab = reinterpret_cast<const v4i_mem*>(a.tab + (u64)w.limb * a.tab_words);
     // the constants of the reduction, fetched once and held in scalar registers (left to itself the compiler fetches
     // them again for every output, and waits each time)
     DigitConst c = dt.c[w.limb];

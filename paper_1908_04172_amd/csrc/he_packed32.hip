@@ -39,7 +39,7 @@ __device__ __forceinline__ T uniform_load(const T* p) {  // read-only, workgroup
 __global__ void __launch_bounds__(256) pack32_kernel(const u64* in, u32* out, size_t count) {
     const size_t i = ((size_t)blockIdx.x * 256 + threadIdx.x) * 2;
     if (i + 1 < count) {
-        const ulonglong2 v = *reinterpret_cast<const ulonglong2*>(in + i);
+        const u64x2 v = *reinterpret_cast<const u64x2*>(in + i);
         *reinterpret_cast<uint2*>(out + i) = make_uint2((u32)v.x, (u32)v.y);
     } else if (i < count) {
         out[i] = (u32)in[i];
@@ -50,7 +50,7 @@ __global__ void __launch_bounds__(256) unpack32_kernel(const u32* in, u64* out, 
     const size_t i = ((size_t)blockIdx.x * 256 + threadIdx.x) * 2;
     if (i + 1 < count) {
         const uint2 v = *reinterpret_cast<const uint2*>(in + i);
-        *reinterpret_cast<ulonglong2*>(out + i) = make_ulonglong2(v.x, v.y);
+        *reinterpret_cast<u64x2*>(out + i) = u64x2{v.x, v.y};
     } else if (i < count) {
         out[i] = in[i];
     }
@@ -299,10 +299,10 @@ __global__ void __launch_bounds__(256) add32_kernel(Limb32Table lt, u32 limbs, u
     const u32 limb = (u32)(row % limbs);
     const size_t c_idx = row / limbs;
     const u32 q = lt.c[limb].q;
-    uint4* p = reinterpret_cast<uint4*>(ct + ((c_idx * 2) * limbs + limb) * N) + k4;
-    uint4 v = *p, a;
+    u32x4* p = reinterpret_cast<u32x4*>(ct + ((c_idx * 2) * limbs + limb) * N) + k4;
+    u32x4 v = *p, a;
     if constexpr (POLY) {
-        a = reinterpret_cast<const uint4*>(static_cast<const u32*>(pt) + row * N)[k4];
+        a = reinterpret_cast<const u32x4*>(static_cast<const u32*>(pt) + row * N)[k4];
     } else {
         a.x = a.y = a.z = a.w = (u32) static_cast<const u64*>(pt)[row];
     }
