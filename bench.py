@@ -241,18 +241,15 @@ def main() -> int:
             fwd = he.RATE_BUTTERFLY_FP64 if fp[i] and q[last] <= 2 * q[i] else fwd_kind[mode[i]]
             per_poly += bf / rate(fwd, i) + N / rate(he.RATE_SHOUP_EXACT, i)
         return 2 * n_ct * per_poly
-    # the scalar MAC runs the three-product form of a term on the limbs that leave room for it
-    three = [he.host_mac_three_product_terms(qi) >= max(int(x) for x in np.diff(p4.off.astype(np.int64))) for qi in q]
-    def mac_ideal_s(plan, scalar):
-        return sum(plan.n_terms * 2 * N / rate(he.RATE_MAC_TERM3 if scalar and three[i] else he.RATE_MAC_TERM, i) for i in range(L))
-    ideal = {"mac_scalar_cfg4": mac_ideal_s(p4, True), "rescale_cfg4": rescale_ideal_s(p4.n_out),
-             "mac_poly_cfg5": mac_ideal_s(p5, False), "rescale_cfg5": rescale_ideal_s(p5.n_out)}
+    # (the scalar MAC runs on the matrix cores, for which there is no such rate)
+    ideal = {"rescale_cfg4": rescale_ideal_s(p4.n_out), "rescale_cfg5": rescale_ideal_s(p5.n_out),
+             "mac_poly_cfg5": sum(p5.n_terms * 2 * N / rate(he.RATE_MAC_TERM, i) for i in range(L))}
     for name, r in rooflines.items():
-        if args.rates and not only:
+        if args.rates and not only and name in ideal:
             r["arithmetic_ms_at_measured_rate"] = ideal[name] * 1e3
             r["frac_of_measured_rate"] = ideal[name] * 1e3 / phase_ms[name]
     names = ["mad32", "mac_term", "shoup_exact", "shoup_cheap", "butterfly_mode0", "butterfly_mode1",
-             "butterfly_mode2", "butterfly_inverse", "mac_term_three_products", "butterfly_fp64", "butterfly_fp64_inverse"]
+             "butterfly_mode2", "butterfly_inverse", None, "butterfly_fp64", "butterfly_fp64_inverse"]
     measured_rates = {"unit": "G operations/s, register-resident, whole GPU",
                       "rates": {"%s@%dbit" % (names[k], q[limb].bit_length()): v / 1e9
                                 for (k, limb), v in sorted(rate_cache.items(), reverse=True)}}

@@ -1,8 +1,8 @@
 /*
  * he_test.h -- test and measurement hooks of the library, kept apart from the product ABI of he.h:
  * the device arithmetic compiled for the host (for CPU-only tests of Alg. 5 / Alg. 6, the Shoup
- * products and the MAC accumulator), and the register-resident rate probes against which the
- * benchmark quotes the MAC and NTT kernels.  Nothing on the compute path calls these.
+ * products, the MAC accumulators and the double-precision transforms), and the register-resident rate
+ * probes against which the benchmark quotes the polynomial MAC and NTT kernels.  Nothing on the compute path calls these.
  */
 #ifndef HE_TEST_H
 #define HE_TEST_H
@@ -24,18 +24,25 @@ uint64_t he_host_shoup_mulmod(uint64_t y, uint64_t w, uint64_t q);
 /* The unreduced Shoup product of the butterflies: congruent to y*w mod q for any 64-bit y, in [0, 2q)
  * with the exact quotient estimate (cheap_quotient = 0), in [0, 4q) with the cheap one (= 1). */
 uint64_t he_host_shoup_lazy(uint64_t y, uint64_t w, uint64_t q, int cheap_quotient);
-/* The accumulator the MAC kernels use, run on the host: sum of x[t]*w[t] (n terms) mod q. */
+/* The accumulator of the MAC kernels on the vector ALU (full-polynomial plaintexts, single outputs, the key product), run on
+ * the host: sum of x[t]*w[t] (n terms) mod q. */
 uint64_t he_host_mac_accumulate(const uint64_t* x, const uint64_t* w, size_t n, uint64_t q);
 /* The same with the kernels' final step: (sum + addend) mod q for an addend below q (the bias of Alg. 4). */
 uint64_t he_host_mac_accumulate_add(const uint64_t* x, const uint64_t* w, size_t n, uint64_t q, uint64_t addend);
-/* The unreduced result that the MAC of a fused layer (he_ct_pt_mac with HE_RESCALE) leaves for the rescale kernel:
- * congruent to (sum of x[t]*w[t] + addend) modulo q and below 12q, for an addend below 2q. */
+/* The MAC of groups of outputs on the int8 matrix cores, run on the host: the balanced digits of both operands, the integer
+ * sums of their products and the final reduction, (sum of x[t]*w[t] + addend) in the form asked for (n <= 4080, else
+ * UINT64_MAX; addend < q); and that reduction alone, of the sums [8] (packed: [4]) in the order of the kernels' registers. */
+enum {
+    HE_DIGITS_CANONICAL = 0, /* below q */
+    HE_DIGITS_BELOW_6Q = 1,  /* congruent and below 6q (3.2q for q >= 2^60): kept limbs of a fused layer on integer butterflies */
+    HE_DIGITS_BELOW_4Q = 2,  /* congruent and below 4q, q < 2^61: those whose combine step runs on doubles */
+    HE_DIGITS_PACKED = 3     /* q < 2^30: four digits, four sums; below q */
+};
+uint64_t he_host_mac_digits(const uint64_t* x, const uint64_t* w, size_t n, uint64_t q, uint64_t addend, int form);
+uint64_t he_host_digit_reduce(const int32_t* sums, uint64_t q, uint64_t addend, int form);
+/* What the MAC of a fused layer (he_ct_pt_mac with HE_RESCALE) leaves on a kept limb for the rescale kernel: congruent to
+ * (sum of x[t]*w[t] + addend) modulo q and below 4q for q < 2^50, else below 6q. */
 uint64_t he_host_mac_accumulate_lazy(const uint64_t* x, const uint64_t* w, size_t n, uint64_t q, uint64_t addend);
-/* The three-product (Karatsuba) form of the MAC terms that the 16-output kernel uses on limbs that leave room
- * for it: the number of terms such sums can take for modulus q (0: the form is not used for q), and
- * (sum of x[t]*w[t] + addend) mod q computed that way for n terms (UINT64_MAX if n exceeds that number). */
-uint32_t he_host_mac_three_product_terms(uint64_t q);
-uint64_t he_host_mac_accumulate_three_products(const uint64_t* x, const uint64_t* w, size_t n, uint64_t q, uint64_t addend);
 /* The forward negacyclic transform as the kernels run it on double-precision FMAs for moduli below 2^50 (the same
  * inline butterfly and reductions, compiled for the host; works on a host-only context): in host [N], integers of
  * magnitude at most q standing for residues of limb `limb`; out host [N], the canonical residues of the transform
@@ -43,6 +50,8 @@ uint64_t he_host_mac_accumulate_three_products(const uint64_t* x, const uint64_t
  * HE_ERR_MODULUS if the limb's modulus is 2^50 or more, HE_ERR_RANGE if an input exceeds q in magnitude or an
  * intermediate value was not an integer below 2^53 (which the bounds the kernels rely on exclude). */
 int he_host_ntt_forward_fp64(he_ctx* ctx, uint32_t limb, const int64_t* in, uint64_t* out, double* max_over_q);
+/* The same for inputs of magnitude up to 2q, which the digit expansion of a key switch feeds to it unreduced. */
+int he_host_ntt_expand_fp64(he_ctx* ctx, uint32_t limb, const int64_t* in, uint64_t* out, double* max_over_q);
 /* The inverse transform the same way: in host [N], canonical residues in the order of he_ntt_fwd's output; out host [N],
  * the canonical coefficients (multiplied by N^-1).  *max_over_q: the largest |value| / q among the sums, differences
  * and products.  Errors as above (HE_ERR_RANGE also for an input that is not below q). */
@@ -57,7 +66,7 @@ uint32_t he_host_shoup32(uint32_t y, uint32_t w, uint32_t q);
  * The first kernel launches of he_ct_pt_mac(..., HE_RESCALE) on their own, for timing the two halves of a fused layer
  * separately: acc_out dev [n_out][2][limbs][N] receives the accumulators (sums + bias) as the fused call leaves them in
  * its workspace, where the kept limbs of scalar-plaintext sums are congruent to the result but not reduced below
- * the modulus; he_rescale(limbs, acc_out, ...) then yields what the fused call yields.  workspace: as for
+ * the modulus (below 4q for q < 2^50, below 6q for others); he_rescale(limbs, acc_out, ...) then yields what the fused call yields.  workspace: as for
  * he_ct_pt_mac with flags = 0.
  */
 int he_test_mac_for_rescale(he_ctx* ctx, const he_plan* plan, uint32_t limbs, const uint64_t* ct_in, const uint64_t* pt, int pt_kind,
@@ -89,7 +98,6 @@ enum {
     HE_RATE_BUTTERFLY_MODE1 = 5, /* forward butterfly for moduli below 2^61 */
     HE_RATE_BUTTERFLY_MODE2 = 6, /* forward butterfly for moduli below 2^58 */
     HE_RATE_BUTTERFLY_INV = 7,   /* inverse butterfly for moduli below 2^61 */
-    HE_RATE_MAC_TERM3 = 8,       /* the three multiply-adds of one MAC term in the three-product form */
     HE_RATE_BUTTERFLY_FP64 = 9,  /* forward butterfly on double-precision FMAs for moduli below 2^50, with the transform's
                                     share of reductions (both values once per four butterflies) */
     HE_RATE_BUTTERFLY_FP64_INV = 10 /* inverse butterfly the same way (both values once per four butterflies, the sum

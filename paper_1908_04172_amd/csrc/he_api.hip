@@ -166,26 +166,16 @@ void fill_limb_const(LimbConst& c, u64 q, u64 psi, u32 N) {
     c.fp_ok = q < (1ull << 50);
     c.fp_free = q < (1ull << 46);
     c.q_inv_f = 1.0 / (double)q;  // (a double holds q exactly; the division rounds to nearest)
-    c.pow64 = (u64)((((u128)1) << 64) % q);
-    c.pow64_shoup = h_shoup(c.pow64, q);
-    // three products per MAC term: the sum of (xa+xb)*(wa+wb) must fit 64 bits with xa+xb, wa+wb below 2^32,
-    // and the total must stay within the one-word Barrett of acc_reduce_add (narrow limbs below 2^61)
-    c.kara_terms = 0;
-    const u128 all_ones64 = (((u128)1) << 64) - 1;
-    if (c.narrow && q < (1ull << 61)) {
-        const u128 ab = (u128)c.split_mask + ((q - 1) >> c.split_bits);
-        if (ab < ((u128)1 << 32)) {
-            const u128 sq = (u128)(q - 1) * (q - 1);
-            u128 lim = std::min<u128>(all_ones64 / (ab * ab), ((((u128)1) << (63 + bits)) - 1 - q) / sq);
-            // the kernel runs such a group's padded terms (up to 3 more, zero weights) in one go, with no
-            // fold or reduction on the way: stay within those periods too
-            lim = std::min<u128>(lim, std::min(c.fold_every, c.reduce_every));
-            c.kara_terms = lim > 3 ? (u32)std::min<u128>(lim - 3, 0x7FFFFFFFull) : 0;
-        }
-    }
     c.neg_two_q = 0 - 2 * q;
     c.four_q = 4 * q;
     c.neg_four_q = 0 - 4 * q;
+}
+
+// x + cap - correction in the rescale's combine step must fit 64 bits for x below 12q, where cap bounds the transformed
+// correction: (3 + 4 log2 N) q in butterfly mode 2, 4q in mode 1, 2q in mode 0
+u32 mac_lazy(const LimbConst& c, u32 log2N) {
+    const u128 cap_q = c.ntt_mode == 2 ? 3 + 4 * log2N : c.ntt_mode == 1 ? 4 : 2;
+    return (12 + cap_q) * (u128)c.q < ((u128)1 << 64);
 }
 
 void fill_digit_const(DigitConst& d, const LimbConst& c) {  // (see DigitConst)
@@ -381,13 +371,8 @@ int he_ctx_create(he_ctx** out, uint32_t log2N, uint32_t L, const uint64_t* modu
         ctx->psi[i] = h_min_psi(moduli[i], N);
         if (!ctx->psi[i]) { delete ctx; return HE_ERR_MODULUS; }
         fill_limb_const(ctx->limbs.c[i], ctx->q[i], ctx->psi[i], N);
-        {   // x + cap - correction in the rescale's combine step must fit 64 bits for x below 12q, where cap bounds the
-            // transformed correction: (3 + 4 log2 N) q in butterfly mode 2, 4q in mode 1, 2q in mode 0
-            LimbConst& c = ctx->limbs.c[i];
-            const u128 cap_q = c.ntt_mode == 2 ? 3 + 4 * log2N : c.ntt_mode == 1 ? 4 : 2;
-            c.mac_lazy = (12 + cap_q) * (u128)c.q < ((u128)1 << 64);
-            fill_digit_const(ctx->digits.c[i], c);
-        }
+        ctx->limbs.c[i].mac_lazy = mac_lazy(ctx->limbs.c[i], log2N);
+        fill_digit_const(ctx->digits.c[i], ctx->limbs.c[i]);
         if (ctx->q[i] < (1ull << 30)) {  // the limb has a packed 32-bit form
             Limb32& c = ctx->limbs32.c[i];
             const u64 q = ctx->q[i], n_inv = ctx->limbs.c[i].n_inv;
@@ -1090,9 +1075,8 @@ uint32_t he_host_shoup32(uint32_t y, uint32_t w, uint32_t q) { return shoup32(y,
 
 int he_measure_rate(he_ctx* ctx, int kind, uint32_t limb, uint32_t iters, double* ops_per_s) {
     if (!ctx || !ops_per_s || limb >= ctx->L || iters == 0 || iters > (1u << 20)) return HE_ERR_ARG;
-    if (kind < HE_RATE_MAD32 || kind > HE_RATE_BUTTERFLY_FP64_INV) return HE_ERR_ARG;
+    if (kind < HE_RATE_MAD32 || kind > HE_RATE_BUTTERFLY_FP64_INV || kind == 8) return HE_ERR_ARG;  // (8: not in use)
     if ((kind == HE_RATE_BUTTERFLY_FP64 || kind == HE_RATE_BUTTERFLY_FP64_INV) && !ctx->limbs.c[limb].fp_ok) return HE_ERR_MODULUS;
-    if (kind == HE_RATE_MAC_TERM3 && ctx->limbs.c[limb].kara_terms == 0) return HE_ERR_MODULUS;  // the limb never takes that form
     // the lazier butterflies assume the room their modes are chosen by
     const u32 mode = ctx->limbs.c[limb].ntt_mode;
     if ((kind == HE_RATE_BUTTERFLY_MODE2 && mode < 2) || ((kind == HE_RATE_BUTTERFLY_MODE1 || kind == HE_RATE_BUTTERFLY_INV) && mode < 1))
@@ -1102,30 +1086,7 @@ int he_measure_rate(he_ctx* ctx, int kind, uint32_t limb, uint32_t iters, double
     return launch_rate(ctx, kind, limb, iters, ops_per_s);
 }
 
-uint64_t he_host_mac_accumulate(const uint64_t* x, const uint64_t* w, size_t n, uint64_t q) {
-    return he_host_mac_accumulate_add(x, w, n, q, 0);
-}
-
-// The unreduced result that a fused layer's MAC hands to its rescale kernel: congruent to sum + addend, below 12q.
-uint64_t he_host_mac_accumulate_lazy(const uint64_t* x, const uint64_t* w, size_t n, uint64_t q, uint64_t addend) {
-    const LimbConst c = host_const(q);
-    MacAcc a;
-    acc_clear(a);
-    u32 f = 0, r = 0;
-    for (size_t t = 0; t < n; ++t) {
-        u32 xa, xb, wa, wb;
-        split_operand(x[t], c, xa, xb);
-        split_operand(w[t], c, wa, wb);
-        acc_mac(a, xa, xb, wa, wb);
-        ++f;
-        ++r;
-        if (r + 1 > c.reduce_every) { acc_restart(a, c); r = 0; f = 0; }
-        else if (f + 1 > c.fold_every) { acc_fold(a, c); f = 0; }
-    }
-    if (c.narrow && c.ntt_mode >= 1) return acc_reduce_add_lazy(a, addend, c);
-    return acc_reduce_lazy(a, addend, c);
-}
-
+// The accumulator of the vector-ALU MAC kernels (MacAcc) with their final step: (sum + addend) mod q.
 uint64_t he_host_mac_accumulate_add(const uint64_t* x, const uint64_t* w, size_t n, uint64_t q, uint64_t addend) {
     const LimbConst c = host_const(q);
     MacAcc a;
@@ -1141,32 +1102,65 @@ uint64_t he_host_mac_accumulate_add(const uint64_t* x, const uint64_t* w, size_t
         if (r + 1 > c.reduce_every) { acc_restart(a, c); r = 0; f = 0; }
         else if (f + 1 > c.fold_every) { acc_fold(a, c); f = 0; }
     }
-    // the final step as the kernels take it
-    if (c.narrow && c.ntt_mode >= 1) return acc_reduce_add(a, addend, c);
     return add_mod(acc_reduce(a, c), addend, c.q);
 }
 
-// The three-product form of the MAC terms, as the 16-output kernel takes it where the limb allows:
-// (sum of x[t]*w[t] + addend) mod q for n <= he_host_mac_three_product_terms(q) terms.  Returns UINT64_MAX if
-// n exceeds that.
-uint64_t he_host_mac_accumulate_three_products(const uint64_t* x, const uint64_t* w, size_t n, uint64_t q, uint64_t addend) {
-    const LimbConst c = host_const(q);
-    if (n > c.kara_terms) return ~0ull;
-    MacAcc a;
-    acc_clear(a);
-    for (size_t t = 0; t < n; ++t) {
-        u32 xa, xb, wa, wb;
-        split_operand(x[t], c, xa, xb);
-        split_operand(w[t], c, wa, wb);
-        a.lo += (u64)xa * wa;
-        a.mid += (u64)(xa + xb) * (wa + wb);
-        a.hi += (u64)xb * wb;
-    }
-    acc_uncross(a);
-    return acc_reduce_add(a, addend, c);
+uint64_t he_host_mac_accumulate(const uint64_t* x, const uint64_t* w, size_t n, uint64_t q) {
+    return he_host_mac_accumulate_add(x, w, n, q, 0);
 }
 
-uint32_t he_host_mac_three_product_terms(uint64_t q) { return host_const(q).kara_terms; }
+// The final reduction of the matrix-core MAC, of sums [8] (packed: [4]).
+uint64_t he_host_digit_reduce(const int32_t* sums, uint64_t q, uint64_t addend, int form) {
+    const LimbConst c = host_const(q);
+    DigitConst d;
+    fill_digit_const(d, c);
+    if (form == HE_DIGITS_PACKED) {
+        const int32_t r[4] = {sums[0], sums[1], sums[2], sums[3]};
+        return digit_reduce32(r, (u32)add_mod(d.start, addend, q), d);
+    }
+    const int32_t r[8] = {sums[0], sums[1], sums[2], sums[3], sums[4], sums[5], sums[6], sums[7]};
+    if (form == HE_DIGITS_BELOW_6Q) return digit_reduce_lazy(r, d.start + addend, d);
+    if (form == HE_DIGITS_BELOW_4Q) return digit_reduce_lazy4(r, d.start + addend, d);
+    return digit_reduce(r, d.start + addend, d);
+}
+
+// A sum of at most DIGIT_MAX_TERMS terms: the digits of both operands, their products, the final reduction.
+uint64_t he_host_mac_digits(const uint64_t* x, const uint64_t* w, size_t n, uint64_t q, uint64_t addend, int form) {
+    if (n > DIGIT_MAX_TERMS) return ~0ull;
+    const LimbConst c = host_const(q);
+    DigitConst d;
+    fill_digit_const(d, c);
+    int32_t sums[8] = {};
+    for (size_t t = 0; t < n; ++t) {
+        if (form == HE_DIGITS_PACKED) {
+            u32 row[4] = {};
+            plaintext_digits(w[t], d, row);
+            const u32 digits = balanced_digits32((u32)x[t]);
+            for (u32 m = 0; m < 4; ++m)
+                for (u32 j = 0; j < 4; ++j) sums[m] += (int32_t)(int8_t)(digits >> (8 * j)) * (int8_t)(row[m] >> (8 * j));
+        } else {
+            u64 row[8] = {};
+            plaintext_digits(w[t], d, row);
+            const u64 digits = balanced_digits(x[t]);
+            for (u32 m = 0; m < 8; ++m)
+                for (u32 j = 0; j < 8; ++j) sums[m] += (int32_t)(int8_t)(digits >> (8 * j)) * (int8_t)(row[m] >> (8 * j));
+        }
+    }
+    return he_host_digit_reduce(sums, q, addend, form);
+}
+
+// What a fused layer's MAC hands to its rescale kernel on a kept limb: unreduced where the limb takes that and the sum is taken
+// in one part, else canonical (longer sums are added up part by part).
+uint64_t he_host_mac_accumulate_lazy(const uint64_t* x, const uint64_t* w, size_t n, uint64_t q, uint64_t addend) {
+    const LimbConst c = host_const(q);
+    const u32 lazy = c.fp_ok ? 2 : mac_lazy(c, HE_MAX_LOG2N - 1);
+    if (n <= DIGIT_MAX_TERMS)
+        return he_host_mac_digits(x, w, n, q, addend % q, lazy == 2 ? HE_DIGITS_BELOW_4Q : lazy == 1 ? HE_DIGITS_BELOW_6Q : HE_DIGITS_CANONICAL);
+    u64 sum = addend % q;
+    for (size_t t = 0; t < n; t += DIGIT_MAX_TERMS)
+        sum = add_mod(sum, he_host_mac_digits(x + t, w + t, std::min<size_t>(n - t, DIGIT_MAX_TERMS), q, 0, HE_DIGITS_CANONICAL), q);
+    return sum;
+}
 
 // Which arithmetic the transforms of limbs below 2^50 use from now on: integer butterflies only (1), or the
 // double-precision ones (0, the state a context is created in).
@@ -1181,7 +1175,7 @@ int he_test_integer_transforms(he_ctx* ctx, int integer_only) {
 
 // The double-precision forward transform (bfly_fwd_f, fp_reduce, the reduction points of ntt_forward_f) run on the
 // host, stage by stage in the textbook loop order.
-int he_host_ntt_forward_fp64(he_ctx* ctx, uint32_t limb, const int64_t* in, uint64_t* out, double* max_over_q) {
+static int host_ntt_forward_fp64(he_ctx* ctx, uint32_t limb, const int64_t* in, uint64_t* out, double* max_over_q, u64 max_in_q) {
     if (!ctx || !in || !out || limb >= ctx->L || ctx->log2N > 14) return HE_ERR_ARG;
     const LimbConst& c = ctx->limbs.c[limb];
     if (!c.fp_ok) return HE_ERR_MODULUS;
@@ -1203,7 +1197,7 @@ int he_host_ntt_forward_fp64(he_ctx* ctx, uint32_t limb, const int64_t* in, uint
         exact = exact && std::fabs(v) < 9007199254740992.0 && v == std::nearbyint(v);
     };
     for (u32 j = 0; j < N; ++j) {
-        if ((u64)std::llabs(in[j]) > q) return HE_ERR_RANGE;
+        if ((u64)std::llabs(in[j]) > max_in_q * q) return HE_ERR_RANGE;
         a[j] = (double)in[j];
     }
     const u32 npass = (log2N + 3) / 4, rem = log2N - 4 * (npass - 1);
@@ -1222,6 +1216,14 @@ int he_host_ntt_forward_fp64(he_ctx* ctx, uint32_t limb, const int64_t* in, uint
     for (u32 j = 0; j < N; ++j) out[j] = fp_to_canonical(fp_reduce(a[j], qf, q_inv), qf);
     if (max_over_q) *max_over_q = worst;
     return exact ? HE_OK : HE_ERR_RANGE;
+}
+
+int he_host_ntt_forward_fp64(he_ctx* ctx, uint32_t limb, const int64_t* in, uint64_t* out, double* max_over_q) {
+    return host_ntt_forward_fp64(ctx, limb, in, out, max_over_q, 1);
+}
+
+int he_host_ntt_expand_fp64(he_ctx* ctx, uint32_t limb, const int64_t* in, uint64_t* out, double* max_over_q) {
+    return host_ntt_forward_fp64(ctx, limb, in, out, max_over_q, 2);
 }
 
 // The inverse transform the same way (bfly_inv_f, the reduction points of ntt_inverse_f).

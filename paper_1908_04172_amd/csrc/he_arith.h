@@ -1,5 +1,6 @@
 // Modular arithmetic on 64-bit residues for gfx950's vector ALU: 32-bit integer multiply-adds, and for moduli
-// below 2^50 the double-precision FMAs of the transforms (last section).  Every function is
+// below 2^50 the double-precision FMAs of the transforms (last section); and the digits and the final reduction of the MAC
+// sums that the int8 matrix cores form.  Every function is
 // __host__ __device__ so that the host-side check entry points run exactly the code the
 // kernels run.  Moduli are primes below 2^62.
 #pragma once
@@ -34,13 +35,12 @@ struct LimbConst {
     u32 mu_shift;     // bit length of q, minus 1
     u32 ntt_mode;     // how lazily the butterflies reduce: 0 for q >= 2^61, 1 for q >= 2^58, else 2 (see the butterflies at the end of this file)
     u64 neg_two_q, four_q, neg_four_q;  // 2^64 - 2q, 4q mod 2^64, 2^64 - 4q (4q is used only when it fits)
-    u32 kara_terms;   // MAC terms whose three-product sums (see acc_uncross) fit 64 bits and the one-word Barrett; 0: never
-    u32 mac_lazy;     // 1: the rescale kernel can combine a MAC result that is only congruent to the sum and below 12q
-                      // with its transformed correction without leaving 64 bits (depends on q, the butterfly mode and N)
+    u32 mac_lazy;     // 1: the rescale kernel can combine a MAC result that is only congruent to the sum and below 12q (the
+                      // MAC leaves it below 6q, see DigitConst) with its transformed correction on integers without leaving
+                      // 64 bits (depends on q, the butterfly mode and N)
     u32 fp_ok;        // 1: q < 2^50, the forward transform can run on double-precision FMAs (see bfly_fwd_f)
     u32 fp_free;      // 1: q < 2^46, that transform needs no reduction between its stages (see bfly_fwd_f)
     double q_inv_f;   // 1 / q, rounded to nearest
-    u64 pow64, pow64_shoup;  // 2^64 mod q and its Shoup companion (acc_reduce_lazy)
 };
 
 HE_HD u64 mul_hi64(u64 a, u64 b) {
@@ -232,10 +232,6 @@ HE_HD void acc_mac(MacAcc& a, u32 xa, u32 xb, u32 wa, u32 wb) {
     a.hi += (u64)xb * wb;
 }
 
-// The three-product form of a term (Karatsuba) adds xa*wa to lo, xb*wb to hi and (xa+xb)*(wa+wb) to mid;
-// this turns such sums into the plain ones (mid = the cross terms xa*wb + xb*wa), once, when they are read out.
-HE_HD void acc_uncross(MacAcc& a) { a.mid -= a.lo + a.hi; }
-
 HE_HD void acc_fold(MacAcc& a, const LimbConst& c) {  // push the high parts of lo and mid upwards
     a.mid += a.lo >> c.split_bits;
     a.lo &= c.split_mask;
@@ -260,76 +256,6 @@ HE_HD u64 acc_reduce(MacAcc a, const LimbConst& c) {
         return r >= c.q ? r - c.q : r;
     }
     return reduce128(hi, lo, c);
-}
-
-// (accumulated value + addend) mod q for an addend below q (the bias of Alg. 4, or 0), for limbs with
-// LimbConst::narrow set and q < 2^61.  The one-word Barrett step of acc_reduce with the high product
-// x1*mu / 2^64 taken from three 32-bit products only (x1h*muh + hi32(x1l*muh) + hi32(x1h*mul)), which
-// is short of the full product by at most 2 more: the remainder lies in [0, 6q), the addend brings it
-// below 7q, and three conditional subtractions (4q, 2q, q) finish.  8q fits 64 bits and 4q is below
-// 2^63, as sub_if_ge needs.
-HE_HD u64 acc_reduce_add(MacAcc a, u64 addend, const LimbConst& c) {
-    acc_fold(a, c);
-    const u32 s2 = 2 * c.split_bits;
-    const u64 lo = a.lo | (a.mid << c.split_bits) | (a.hi << s2);
-    const u64 hi = a.hi >> (64 - s2);
-    const u64 x1 = (hi << (64 - c.mu_shift)) | (lo >> c.mu_shift);
-    const u32 xl = (u32)x1, xh = (u32)(x1 >> 32), ml = (u32)c.mu, mh = (u32)(c.mu >> 32);
-    const u64 qe = (u64)xh * mh + mul_hi32(xl, mh) + mul_hi32(xh, ml);
-    // lo - qe*q modulo 2^64, as lo + qe*(2^64 - q) on 32-bit pieces
-    const u64 nq = 0 - c.q;
-    const u32 n0 = (u32)nq, n1 = (u32)(nq >> 32), e0 = (u32)qe, e1 = (u32)(qe >> 32);
-    u64 cross = mad_wide(e0, n1, 0);
-    cross = mad_wide(e1, n0, cross);
-    const u64 low = (u64)e0 * n0 + lo;
-    u32 top = (u32)(low >> 32) + (u32)cross;
-#if defined(__HIP_DEVICE_COMPILE__)
-    asm("" : "+v"(top));
-#endif
-    u64 r = (((u64)top << 32) | (u32)low) + addend;
-    r = sub_if_ge(r, c.neg_four_q);
-    r = sub_if_ge(r, c.neg_two_q);
-    return sub_if_ge(r, 0 - c.q);
-}
-
-// The sums taken to a value that is only CONGRUENT to (accumulated value + addend) modulo q and lies below 12q,
-// for limbs with LimbConst::narrow set and an addend below 2q: what the MAC leaves for the rescale kernel, which
-// takes any representative that small (see LimbConst::mac_lazy).  The sums are used as they are, not folded:
-// with b the bit length of q and s the cut, x1 = (hi << (2s-b+1)) + (mid >> (b-1-s)) + (lo >> (b-1)) is
-// floor(value / 2^(b-1)) or up to 2 less and fits 64 bits; the one-word Barrett quotient of acc_reduce_add from
-// it is short of the true quotient by at most 3 + 3 + 2, so the remainder, taken modulo 2^64 from the low word
-// lo + (mid << s) + (hi << 2s) with the addend as the start of the multiply-add chain, is below 9q + 2q.
-HE_HD u64 acc_reduce_add_lazy(const MacAcc& a, u64 addend, const LimbConst& c) {
-    const u32 s = c.split_bits, sh = c.mu_shift;
-    const u64 x1 = (a.hi << (2 * s - sh)) + (a.mid >> (sh - s)) + (a.lo >> sh);
-    const u32 xl = (u32)x1, xh = (u32)(x1 >> 32), ml = (u32)c.mu, mh = (u32)(c.mu >> 32);
-    const u64 qe = (u64)xh * mh + mul_hi32(xl, mh) + mul_hi32(xh, ml);
-    const u64 low_word = a.lo + (a.mid << s) + (a.hi << (2 * s)) + addend;
-    const u64 nq = 0 - c.q;
-    const u32 n0 = (u32)nq, n1 = (u32)(nq >> 32), e0 = (u32)qe, e1 = (u32)(qe >> 32);
-    u64 cross = mad_wide(e0, n1, 0);
-    cross = mad_wide(e1, n0, cross);
-    const u64 low = (u64)e0 * n0 + low_word;
-    u32 top = (u32)(low >> 32) + (u32)cross;
-#if defined(__HIP_DEVICE_COMPILE__)
-    asm("" : "+v"(top));
-#endif
-    return ((u64)top << 32) | (u32)low;
-}
-
-// The same for the other limbs (moduli below 2^62): two lazy Shoup products, below 4q each, plus the addend
-// (below 2q): below 10q.
-HE_HD u64 acc_reduce_lazy(const MacAcc& a, u64 addend, const LimbConst& c) {
-    // the value lo + mid * 2^s + hi * 2^(2s) as two words (it is below 2^128; the sums are used as they are)
-    const u32 s = c.split_bits;
-    const u64 mid_lo = a.mid << s, hi_lo = a.hi << (2 * s);
-    const u64 t = a.lo + mid_lo;
-    const u64 low = t + hi_lo;
-    const u64 high = (a.mid >> (64 - s)) + (a.hi >> (64 - 2 * s)) + (u64)(t < mid_lo) + (u64)(low < hi_lo);
-    // low + high * 2^64 = low * 1 + high * (2^64 mod q), each as a lazy Shoup product (below 4q; the companion of 1
-    // is floor(2^64 / q)), the addend and the first product being the starting values of the multiply-add chains
-    const u64 r0 = shoup_remainder_add(low, 1, shoup_quotient_cheap(low, c.ratio_hi), c.q, addend);
-    return shoup_remainder_add(high, c.pow64, shoup_quotient_cheap(high, c.pow64_shoup), c.q, r0);
 }
 
 HE_HD void acc_restart(MacAcc& a, const LimbConst& c) {  // reduce in place and keep accumulating
@@ -379,6 +305,24 @@ constexpr u32 DIGIT_MAX_TERMS = 4080;
 
 // the balanced digits of x < 2^62 (or of a centred residue, as a two's complement word), one per byte
 HE_HD u64 balanced_digits(u64 x) { return (x + HE_DIGIT_BIAS) ^ HE_DIGIT_BIAS; }
+
+// A plaintext w < q as the table holds it: byte j of row[m] is the digit of w * 256^j mod q that goes to R_m (see above; on
+// packed residues there are four digits, and R_m stands for R_(4 + m)).
+template <typename V>
+HE_HD void plaintext_digits(u64 w, const DigitConst& c, V (&row)[sizeof(V)]) {
+    constexpr u32 D = sizeof(V);
+#pragma unroll
+    for (u32 j = 0; j < D; j++) {
+        const u64 d = balanced_digits(w > c.q / 2 ? w - c.q : w);
+        const u64 low = c.kappa8 ? d & (~0ull >> (64 - c.kappa8)) : 0, high = d >> c.kappa8;
+#pragma unroll
+        for (u32 m = 0; m < 4; m++) {
+            if constexpr (D == 8) row[m] |= ((low >> (8 * m)) & 255) << (8 * j);
+            row[D - 4 + m] |= (V)((high >> (8 * m)) & 255) << (8 * j);
+        }
+        w = shoup_mul(w, 256, c.pow8_shoup, c.q);
+    }
+}
 
 // lo or hi of an output's eight sums, plus `start`: four signed 32x32+64-bit multiply-adds
 HE_HD u64 digit_sum4(int32_t r0, int32_t r1, int32_t r2, int32_t r3, u64 start, const DigitConst& c) {

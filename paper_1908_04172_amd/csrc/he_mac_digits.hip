@@ -93,18 +93,7 @@ __global__ void __launch_bounds__(256) gather_digits_kernel(DigitTable dt, const
         const DigitConst& c = dt.c[limb];
         V row[F::D] = {};
         if (o < tile.count && t < K) {
-            u64 v = pt[(size_t)term_pt[off[tile.out0 + o] + first + t] * limbs + limb];
-#pragma unroll
-            for (u32 j = 0; j < F::D; j++) {
-                const u64 d = balanced_digits(v > c.q / 2 ? v - c.q : v);
-                const u64 low = c.kappa8 ? d & (~0ull >> (64 - c.kappa8)) : 0, high = d >> c.kappa8;
-#pragma unroll
-                for (u32 m = 0; m < 4; m++) {
-                    if constexpr (F::D == 8) row[m] |= ((low >> (8 * m)) & 255) << (8 * j);
-                    row[F::D - 4 + m] |= (V)((high >> (8 * m)) & 255) << (8 * j);
-                }
-                v = shoup_mul(v, 256, c.pow8_shoup, c.q);
-            }
+            plaintext_digits(pt[(size_t)term_pt[off[tile.out0 + o] + first + t] * limbs + limb], c, row);
         }
         // where the term is in its chunk's list order [half][block of 4][2], and so in the table
         const u32 half = (t >> 1) & 1, at = ((t >> 2) & 3) * 2 + (t & 1);

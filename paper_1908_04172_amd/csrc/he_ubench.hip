@@ -38,13 +38,11 @@ __global__ void __launch_bounds__(THREADS) rate_kernel(LimbTable lt, u32 limb, u
     const u64 below_q = (1ull << c.mu_shift) - 1;  // mu_shift = bit length of q, minus 1
     u32 wa, wb;
     split_operand(w, c, wa, wb);
-    const u32 ws = wa + wb;
-    u32 ta = xa[0], tb = xb[0], ts = ta + tb;
+    u32 ta = xa[0], tb = xb[0];
     for (u32 it = 0; it < iters; it++) {
-        if constexpr (KIND == HE_RATE_MAC_TERM || KIND == HE_RATE_MAC_TERM3) {  // the next term's input residue
+        if constexpr (KIND == HE_RATE_MAC_TERM) {  // the next term's input residue
             ta = ta * 0x9E3779B1u + 1u;
             tb ^= ta >> 7;
-            ts = ta + tb;
         }
 #pragma unroll
         for (int i = 0; i < CHAINS; i++) {
@@ -57,12 +55,6 @@ __global__ void __launch_bounds__(THREADS) rate_kernel(LimbTable lt, u32 limb, u
                 // are outputs that share the input residue of the term (ta, tb: renewed once per
                 // iteration, below) and have a plaintext residue each.
                 acc_mac(acc[i], ta, tb, wa + i, wb + i);
-            } else if constexpr (KIND == HE_RATE_MAC_TERM3) {
-                // the three-product form of a term (lo += xa*wa, mid += (xa+xb)*(wa+wb), hi += xb*wb): the sum
-                // wa + wb comes with the weights, xa + xb is formed once per term for all outputs
-                acc[i].lo += (u64)ta * (wa + i);
-                acc[i].mid += (u64)ts * (ws + 2 * i);
-                acc[i].hi += (u64)tb * (wb + i);
             } else if constexpr (KIND == HE_RATE_SHOUP_EXACT) {
                 x[i] = shoup_mul_lazy(x[i], w, w_shoup, c.q);
             } else if constexpr (KIND == HE_RATE_SHOUP_CHEAP) {
@@ -159,7 +151,6 @@ int launch_rate(he_ctx* ctx, int kind, u32 limb, u32 iters, double* ops_per_s) {
         case HE_RATE_BUTTERFLY_MODE1: return run_rate<HE_RATE_BUTTERFLY_MODE1>(ctx, limb, iters, ops_per_s);
         case HE_RATE_BUTTERFLY_MODE2: return run_rate<HE_RATE_BUTTERFLY_MODE2>(ctx, limb, iters, ops_per_s);
         case HE_RATE_BUTTERFLY_INV: return run_rate<HE_RATE_BUTTERFLY_INV>(ctx, limb, iters, ops_per_s);
-        case HE_RATE_MAC_TERM3: return run_rate<HE_RATE_MAC_TERM3>(ctx, limb, iters, ops_per_s);
         case HE_RATE_BUTTERFLY_FP64: return run_rate<HE_RATE_BUTTERFLY_FP64>(ctx, limb, iters, ops_per_s);
         case HE_RATE_BUTTERFLY_FP64_INV: return run_rate<HE_RATE_BUTTERFLY_FP64_INV>(ctx, limb, iters, ops_per_s);
     }

@@ -15,8 +15,8 @@ import numpy as np
 
 RATE_MAD32, RATE_MAC_TERM, RATE_SHOUP_EXACT, RATE_SHOUP_CHEAP = 0, 1, 2, 3
 RATE_BUTTERFLY_MODE0, RATE_BUTTERFLY_MODE1, RATE_BUTTERFLY_MODE2, RATE_BUTTERFLY_INV = 4, 5, 6, 7
-RATE_MAC_TERM3 = 8
 RATE_BUTTERFLY_FP64, RATE_BUTTERFLY_FP64_INV = 9, 10
+DIGITS_CANONICAL, DIGITS_BELOW_6Q, DIGITS_BELOW_4Q, DIGITS_PACKED = 0, 1, 2, 3
 PT_SCALAR = 0
 PT_POLY = 1
 RESCALE = 1
@@ -32,7 +32,7 @@ EXPORTS = [
     "he_plan_create", "he_plan_destroy", "he_plan_workspace_bytes", "he_ct_pt_mac", "he_ct_pt_mac_static", "he_ct_pt_add", "he_rescale",
     "he_ntt_fwd", "he_ntt_inv", "he_check_reduced", "he_host_mulmod", "he_host_reduce128", "he_host_shoup_mulmod", "he_host_shoup_lazy",
     "he_host_mac_accumulate", "he_host_mac_accumulate_add", "he_host_mac_accumulate_lazy", "he_test_mac_for_rescale", "he_measure_rate",
-    "he_host_barrett64", "he_host_shoup32", "he_host_mac_three_product_terms", "he_host_mac_accumulate_three_products", "he_host_ntt_forward_fp64", "he_host_ntt_inverse_fp64", "he_test_integer_transforms", "he_square_relin_workspace_bytes", "he_ct_square_relin", "he_pack32", "he_unpack32", "he_ct_pt_mac32", "he_ct_pt_add32", "he_rescale32", "he_ntt_fwd32", "he_ntt_inv32",
+    "he_host_barrett64", "he_host_shoup32", "he_host_mac_digits", "he_host_digit_reduce", "he_host_ntt_forward_fp64", "he_host_ntt_expand_fp64", "he_host_ntt_inverse_fp64", "he_test_integer_transforms", "he_square_relin_workspace_bytes", "he_ct_square_relin", "he_pack32", "he_unpack32", "he_ct_pt_mac32", "he_ct_pt_add32", "he_rescale32", "he_ntt_fwd32", "he_ntt_inv32",
 ]
 
 _lib = None
@@ -84,8 +84,9 @@ def lib():
         "he_host_mac_accumulate": (u64, [vp, vp, sz, u64]),
         "he_square_relin_workspace_bytes": (i32, [vp, u32, u32, ctypes.POINTER(sz)]),
         "he_ct_square_relin": (i32, [vp, u32, vp, u32, vp, vp, vp, sz, vp]),
-        "he_host_mac_three_product_terms": (u32, [u64]),
-        "he_host_mac_accumulate_three_products": (u64, [vp, vp, sz, u64, u64]),
+        "he_host_mac_digits": (u64, [vp, vp, sz, u64, u64, i32]),
+        "he_host_digit_reduce": (u64, [vp, u64, u64, i32]),
+        "he_host_ntt_expand_fp64": (i32, [vp, u32, vp, vp, ctypes.POINTER(ctypes.c_double)]),
         "he_host_ntt_forward_fp64": (i32, [vp, u32, vp, vp, ctypes.POINTER(ctypes.c_double)]),
         "he_host_ntt_inverse_fp64": (i32, [vp, u32, vp, vp, ctypes.POINTER(ctypes.c_double)]),
         "he_test_integer_transforms": (i32, [vp, i32]),
@@ -167,15 +168,16 @@ class Context:
         """he_test_integer_transforms: integer butterflies for every limb (True), or the default (False)."""
         _check(lib().he_test_integer_transforms(self._h, int(bool(integer_only))), "he_test_integer_transforms")
 
-    def host_ntt_forward_fp64(self, limb: int, values) -> "tuple[np.ndarray, float]":
+    def host_ntt_forward_fp64(self, limb: int, values, expand: bool = False) -> "tuple[np.ndarray, float]":
         """he_host_ntt_forward_fp64: the double-precision forward transform run on the host.  values: N integers of
-        magnitude at most q; returns (canonical residues of the transform, largest |intermediate| / q)."""
+        magnitude at most q (expand: 2q, he_host_ntt_expand_fp64); returns (canonical residues of the transform,
+        largest |intermediate| / q)."""
         v = np.ascontiguousarray(values, dtype=np.int64)
         assert v.shape == (self.N,)
         out = np.zeros(self.N, dtype=np.uint64)
         worst = ctypes.c_double()
-        _check(lib().he_host_ntt_forward_fp64(self._h, limb, v.ctypes.data, out.ctypes.data, ctypes.byref(worst)),
-               "he_host_ntt_forward_fp64")
+        name = "he_host_ntt_expand_fp64" if expand else "he_host_ntt_forward_fp64"
+        _check(getattr(lib(), name)(self._h, limb, v.ctypes.data, out.ctypes.data, ctypes.byref(worst)), name)
         return out, float(worst.value)
 
     def host_ntt_inverse_fp64(self, limb: int, values) -> "tuple[np.ndarray, float]":
@@ -314,7 +316,6 @@ class Context:
                                   _dev_ptr(bias, "bias"), _dev_ptr(out, "ct_out"), flags, _dev_ptr(workspace, "workspace"),
                                   ws_bytes, _stream()), "he_ct_pt_mac")
         return out
-
 
     def mac_for_rescale(self, plan: "Plan", ct_in, pt, pt_kind: int, out, bias=None, workspace=None):
         """he_test_mac_for_rescale: the accumulators of a fused layer, as its rescale kernel receives them."""
@@ -485,14 +486,17 @@ def host_shoup_lazy(y: int, w: int, q: int, cheap_quotient: bool) -> int:
     return int(lib().he_host_shoup_lazy(y, w, q, int(cheap_quotient)))
 
 
-def host_mac_three_product_terms(q: int) -> int:
-    return int(lib().he_host_mac_three_product_terms(q))
-
-
-def host_mac_accumulate_three_products(x, w, q: int, addend: int = 0) -> int:
+def host_mac_digits(x, w, q: int, addend: int = 0, form: int = 0) -> int:
+    """he_host_mac_digits: the matrix-core MAC of one output and slot on the host."""
     x, w = _np64(x), _np64(w)
-    assert x.shape == w.shape and x.ndim == 1
-    return int(lib().he_host_mac_accumulate_three_products(x.ctypes.data, w.ctypes.data, x.size, q, addend))
+    assert x.size == w.size
+    return int(lib().he_host_mac_digits(x.ctypes.data, w.ctypes.data, x.size, q, addend, form))
+
+
+def host_digit_reduce(sums, q: int, addend: int = 0, form: int = 0) -> int:
+    s = np.ascontiguousarray(sums, dtype=np.int32)
+    assert s.size == (4 if form == DIGITS_PACKED else 8)
+    return int(lib().he_host_digit_reduce(s.ctypes.data, q, addend, form))
 
 
 def host_barrett64(z: int, q: int) -> int:

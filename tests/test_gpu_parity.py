@@ -347,7 +347,7 @@ def test_mac_scalar_chains_groups_with_changing_term_counts(he, bits, shared, la
     log2N, N = 11, 1 << 11
     q = wl.modulus_chain(bits, N)
     ctx = he.Context(log2N, q)
-    plan, first = chained_groups_plan(37, 77, shared, largest)         # shared tables: the three-product form of the terms
+    plan, first = chained_groups_plan(37, 77, shared, largest)         # shared: groups with the same plaintexts, one table
     hp = ctx.plan(plan.n_in, plan.n_out, plan.n_pt, plan.off, plan.term_ct, plan.term_pt)
     ct = wl.uniform_residues((plan.n_in, 2), q, N, 78)
     w = dev(wl.uniform_residues((plan.n_pt,), q, 1, 79)[..., 0])
@@ -510,8 +510,10 @@ def test_measured_rates_are_plausible(he):
     b0, b1, b2 = (ctx.measure_rate(k, 2, 512) for k in (he.RATE_BUTTERFLY_MODE0, he.RATE_BUTTERFLY_MODE1,
                                                          he.RATE_BUTTERFLY_MODE2))
     assert b0 < b1 < b2 < mad / 4
-    t4, t3 = ctx.measure_rate(he.RATE_MAC_TERM, 2, 512), ctx.measure_rate(he.RATE_MAC_TERM3, 2, 512)
-    assert mad / 6 < t4 < t3 < mad / 2                                              # four and three multiply-adds per term
+    assert mad / 6 < ctx.measure_rate(he.RATE_MAC_TERM, 2, 512) < mad / 2           # four multiply-adds per term
+    with pytest.raises(he.HeError) as e:
+        ctx.measure_rate(8, 2, 512)                                                 # a number that stands for no primitive
+    assert e.value.status == -1
     f_fwd, f_inv = ctx.measure_rate(he.RATE_BUTTERFLY_FP64, 2, 512), ctx.measure_rate(he.RATE_BUTTERFLY_FP64_INV, 2, 512)
     assert b2 < f_inv < f_fwd < mad / 4                                             # the double-precision butterflies of a 50-bit limb
     for kind in (he.RATE_BUTTERFLY_MODE2, he.RATE_BUTTERFLY_FP64, he.RATE_BUTTERFLY_FP64_INV):
