@@ -93,6 +93,25 @@ def test_rescale_around_the_limits_of_the_transforms(he, log2N, bits):
 
 
 @pytest.mark.gpu
+@pytest.mark.parametrize("log2N", [10, 12, 14])
+@pytest.mark.parametrize("bits,drop", [([50, 49, 46, 47], 50), ([60, 57, 50, 46], 45), ([50, 40, 30], 60)])
+def test_rescale_of_the_largest_unreduced_accumulators(he, log2N, bits, drop):
+    """What a fused layer may leave for the rescale at most: 4q - 1 on kept limbs below 2^50, 6q - 1 on those below 2^60."""
+    N = 1 << log2N
+    q = wl.modulus_chain(bits + [drop], N)
+    ctx = he.Context(log2N, q)
+    ct = wl.uniform_residues((4, 2), q, N, 600 + log2N)
+    acc = ct.copy()
+    for i, qi in enumerate(q[:-1]):
+        times = 4 if qi < 1 << 50 else 6
+        acc[0, :, i] = times * qi - 1                               # the largest everywhere
+        acc[1, :, i] += np.uint64((times - 1) * qi)                 # any residue, as far up as it goes
+        acc[2, :, i, ::2] += np.uint64((times - 1) * qi)
+    canonical = acc % np.array(q, dtype=np.uint64)[:, None]
+    assert np.array_equal(host(ctx.rescale(dev(acc))), oracle.rescale(canonical, q, ctx.psi))
+
+
+@pytest.mark.gpu
 @pytest.mark.parametrize("n", [1, 103, 120, 200, 400, 511, 700, 769, 1537])
 def test_rescale_of_few_polynomials_split_over_workgroups(he, n):
     """Fifteen kept limbs, shared by fifteen workgroups per polynomial down to one: even and uneven shares."""
