@@ -2,7 +2,8 @@
  * he_test.h -- test and measurement hooks of the library, kept apart from the product ABI of he.h:
  * the device arithmetic compiled for the host (for CPU-only tests of Alg. 5 / Alg. 6, the Shoup
  * products, the MAC accumulators and the double-precision transforms), and the register-resident rate
- * probes against which the benchmark quotes the polynomial MAC and NTT kernels.  Nothing on the compute path calls these.
+ * probes against which the benchmark quotes the polynomial MAC and NTT kernels.  Nothing on the compute
+ * path calls these.
  */
 #ifndef HE_TEST_H
 #define HE_TEST_H
@@ -66,11 +67,17 @@ uint32_t he_host_shoup32(uint32_t y, uint32_t w, uint32_t q);
  * The first kernel launches of he_ct_pt_mac(..., HE_RESCALE) on their own, for timing the two halves of a fused layer
  * separately: acc_out dev [n_out][2][limbs][N] receives the accumulators (sums + bias) as the fused call leaves them in
  * its workspace, where the kept limbs of scalar-plaintext sums are congruent to the result but not reduced below
- * the modulus (below 4q for q < 2^50, below 6q for others); he_rescale(limbs, acc_out, ...) then yields what the fused call yields.  workspace: as for
- * he_ct_pt_mac with flags = 0.
+ * the modulus (below 4q for q < 2^50, below 6q for others); he_rescale(limbs, acc_out, ...) then yields what the
+ * fused call yields.  workspace: as for he_ct_pt_mac with flags = 0.
  */
 int he_test_mac_for_rescale(he_ctx* ctx, const he_plan* plan, uint32_t limbs, const uint64_t* ct_in, const uint64_t* pt, int pt_kind,
                             const uint64_t* bias, uint64_t* acc_out, void* workspace, size_t workspace_bytes, void* stream);
+
+/*
+ * How many groups of `outputs` outputs (2 to 16: groups of 2..4, 5..8 and 9..16 go together) a workgroup of the matrix-core
+ * MAC runs through for this plan and level, packed or not: what a test of the transitions between groups has to know.
+ */
+int he_test_mac_groups_per_workgroup(const he_plan* plan, uint32_t limbs, uint32_t outputs, int packed, uint32_t* groups);
 
 /*
  * The transforms of limbs below 2^50 run on double-precision FMAs, those of larger limbs on integer butterflies; both

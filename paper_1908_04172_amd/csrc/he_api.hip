@@ -1162,6 +1162,15 @@ uint64_t he_host_mac_accumulate_lazy(const uint64_t* x, const uint64_t* w, size_
     return sum;
 }
 
+int he_test_mac_groups_per_workgroup(const he_plan* plan, uint32_t limbs, uint32_t outputs, int packed, uint32_t* groups) {
+    if (!plan || !groups || outputs < 2 || outputs > CAPS_S[SCALAR_CLASSES - 1]) return HE_ERR_ARG;
+    if (int rc = check_level(plan->ctx, limbs, 1)) return rc;
+    u32 cls = 1;
+    while (outputs > CAPS_S[cls]) ++cls;
+    *groups = mac_digits_groups_per_workgroup(plan->ctx, plan, limbs, cls, packed != 0);
+    return HE_OK;
+}
+
 // Which arithmetic the transforms of limbs below 2^50 use from now on: integer butterflies only (1), or the
 // double-precision ones (0, the state a context is created in).
 int he_test_integer_transforms(he_ctx* ctx, int integer_only) {

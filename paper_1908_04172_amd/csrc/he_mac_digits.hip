@@ -537,6 +537,12 @@ u64 mac_digits_blocks(const he_ctx* ctx, const he_plan* plan, u32 limbs) {
     return blocks;
 }
 
+// groups of a class that a workgroup runs through, in a pass from the first term on
+u32 mac_digits_groups_per_workgroup(const he_ctx* ctx, const he_plan* plan, u32 limbs, u32 cls, bool packed) {
+    const u32 first = plan->class_begin_s[cls], end = plan->class_begin_s[cls + 1];
+    return packed ? mac_class_of<u32>(ctx, plan, limbs, cls, first, end, 0).per_wg : mac_class_of<u64>(ctx, plan, limbs, cls, first, end, 0).per_wg;
+}
+
 int launch_mac_digits(he_ctx* ctx, const he_plan* plan, const ScalarSlice& sl, u32 limbs, const u64* ct_in, const u64* pt, const u64* bias,
                       u64* out, u64* wtab, u32 mode, hipStream_t s) {
     return launch_mac_digits_t<u64>(ctx, plan, sl, limbs, ct_in, pt, bias, out, wtab, mode, s);

@@ -32,7 +32,7 @@ EXPORTS = [
     "he_plan_create", "he_plan_destroy", "he_plan_workspace_bytes", "he_ct_pt_mac", "he_ct_pt_mac_static", "he_ct_pt_add", "he_rescale",
     "he_ntt_fwd", "he_ntt_inv", "he_check_reduced", "he_host_mulmod", "he_host_reduce128", "he_host_shoup_mulmod", "he_host_shoup_lazy",
     "he_host_mac_accumulate", "he_host_mac_accumulate_add", "he_host_mac_accumulate_lazy", "he_test_mac_for_rescale", "he_measure_rate",
-    "he_host_barrett64", "he_host_shoup32", "he_host_mac_digits", "he_host_digit_reduce", "he_host_ntt_forward_fp64", "he_host_ntt_expand_fp64", "he_host_ntt_inverse_fp64", "he_test_integer_transforms", "he_square_relin_workspace_bytes", "he_ct_square_relin", "he_pack32", "he_unpack32", "he_ct_pt_mac32", "he_ct_pt_add32", "he_rescale32", "he_ntt_fwd32", "he_ntt_inv32",
+    "he_host_barrett64", "he_host_shoup32", "he_host_mac_digits", "he_host_digit_reduce", "he_test_mac_groups_per_workgroup", "he_host_ntt_forward_fp64", "he_host_ntt_expand_fp64", "he_host_ntt_inverse_fp64", "he_test_integer_transforms", "he_square_relin_workspace_bytes", "he_ct_square_relin", "he_pack32", "he_unpack32", "he_ct_pt_mac32", "he_ct_pt_add32", "he_rescale32", "he_ntt_fwd32", "he_ntt_inv32",
 ]
 
 _lib = None
@@ -90,6 +90,7 @@ def lib():
         "he_host_ntt_forward_fp64": (i32, [vp, u32, vp, vp, ctypes.POINTER(ctypes.c_double)]),
         "he_host_ntt_inverse_fp64": (i32, [vp, u32, vp, vp, ctypes.POINTER(ctypes.c_double)]),
         "he_test_integer_transforms": (i32, [vp, i32]),
+        "he_test_mac_groups_per_workgroup": (i32, [vp, u32, u32, i32, ctypes.POINTER(u32)]),
         "he_host_barrett64": (u32, [u64, u32]),
         "he_host_shoup32": (u32, [u32, u32, u32]),
         "he_pack32": (i32, [vp, vp, vp, sz, vp]),
@@ -455,6 +456,12 @@ class Plan:
         b = ctypes.c_size_t()
         _check(lib().he_plan_workspace_bytes(self._h, limbs, pt_kind, flags, ctypes.byref(b)), "he_plan_workspace_bytes")
         return int(b.value)
+
+    def groups_per_workgroup(self, limbs: int, outputs: int, packed: bool = False) -> int:
+        """he_test_mac_groups_per_workgroup."""
+        n = ctypes.c_uint32()
+        _check(lib().he_test_mac_groups_per_workgroup(self._h, limbs, outputs, int(packed), ctypes.byref(n)), "he_test_mac_groups_per_workgroup")
+        return int(n.value)
 
     def close(self):
         if getattr(self, "_h", None):

@@ -160,6 +160,66 @@ def test_packed_group_sizes_and_term_counts(he, bits, groups, extreme):
     assert np.array_equal(host32(ctx.ct_pt_mac32(hp, dev32(ct), dev(w), he.PT_SCALAR, bias=dev(b), flags=he.RESCALE)), layer)
 
 
+def runs_of_long_sums(classes, groups, seed):
+    """`groups` groups of each of the output counts, most with sums beyond the 64 terms whose tables stay in the LDS, shorter
+    ones among them and, at the front of the first class, a whole run of those."""
+    rng = np.random.default_rng(seed)
+    terms = [int(t) for t in rng.choice([65, 66, 80, 96, 129, 160, 1, 16, 40, 64], groups, p=[.15, .1, .15, .1, .1, .1, .05, .1, .05, .1])]
+    terms[:2], terms[2:5], terms[-3:] = [30, 64], [65, 7, 81], [70, 12, 90]
+    return [(c, t + (k if t > 64 else 0)) for t in terms for k, c in enumerate(classes)]
+
+
+@pytest.mark.parametrize("log2N,bits,classes,groups,per_wg", [(11, [60, 50, 40, 55], (16, 7, 3), 97, 2), (11, [62, 30], (9, 2), 131, 2),
+                                                              (12, [60, 60, 50, 50, 50, 50, 46, 50], (4, 16), 69, 8)])
+@pytest.mark.parametrize("extreme", [False, True])
+def test_long_sums_of_several_groups_in_one_workgroup(he, log2N, bits, classes, groups, per_wg, extreme):
+    """The stream of chunks that brings its tables along runs on from one group into the next (lists, inputs and tables of the
+    next group are requested during the last chunk of the one before), past shorter groups too and into a ragged last run."""
+    N = 1 << log2N
+    q = wl.modulus_chain(bits, N)
+    ctx = he.Context(log2N, q)
+    plan = groups_plan(runs_of_long_sums(classes, groups, log2N), 11, 13, groups)
+    hp = ctx.plan(plan.n_in, plan.n_out, plan.n_pt, plan.off, plan.term_ct, plan.term_pt)
+    assert [hp.groups_per_workgroup(len(q), c) for c in classes] == [per_wg] * len(classes)
+    ct, w, b = operands(plan, q, N, groups, extreme)
+    first = np.cumsum([0] + [c for _ in range(groups) for c in classes])[:-1]        # a group's first output, and of some all
+    some = sorted(set(first.tolist()) | set(range(40)) | set(range(plan.n_out - 40, plan.n_out)))[::1 if groups > 90 else 3]
+    sub = plan.subset(some)
+    want = oracle.mac(ct, q, sub.off, sub.term_ct, sub.term_pt, w, oracle.PT_SCALAR, b[some])
+    out = run(he, ctx, plan, ct, w, b)
+    assert np.array_equal(out[some], want)
+    twice = dev(out)
+    run(he, ctx, plan, ct, w, b, flags=he.ACCUMULATE, out=twice)
+    qa = np.asarray(q, np.uint64)[:, None]
+    assert np.array_equal(host(twice), (out + out) % qa)             # (below 2^63)
+    few = some[::7]
+    layer, _ = oracle.layer(ct, q, ctx.psi, *(lambda s: (s.off, s.term_ct, s.term_pt))(plan.subset(few)), w, oracle.PT_SCALAR, b[few])
+    assert np.array_equal(run(he, ctx, plan, ct, w, b, flags=he.RESCALE)[few], layer)
+
+
+@pytest.mark.parametrize("classes,groups,per_wg", [((16, 11), 200, 4), ((8, 7), 131, 4), ((3,), 150, 2), ((16, 6, 2), 129, 2)])
+def test_packed_long_sums_of_several_groups_in_one_workgroup(he, classes, groups, per_wg):
+    N = 1 << 11
+    q = wl.modulus_chain([30, 29, 30, 24], N)
+    ctx = he.Context(11, q)
+    plan = groups_plan(runs_of_long_sums(classes, groups, 5), 11, 13, groups)
+    hp = ctx.plan(plan.n_in, plan.n_out, plan.n_pt, plan.off, plan.term_ct, plan.term_pt)
+    assert [hp.groups_per_workgroup(len(q), c, packed=True) for c in classes] == [per_wg] * len(classes)
+    ct, w, b = operands(plan, q, N, groups, True)
+    first = np.cumsum([0] + [c for _ in range(groups) for c in classes])[:-1]
+    some = sorted(set(first.tolist()) | set(range(40)) | set(range(plan.n_out - 40, plan.n_out)))
+    sub = plan.subset(some)
+    want = oracle.mac(ct, q, sub.off, sub.term_ct, sub.term_pt, w, oracle.PT_SCALAR, b[some])
+    out = ctx.ct_pt_mac32(hp, dev32(ct), dev(w), he.PT_SCALAR, bias=dev(b))
+    once = host32(out)
+    assert np.array_equal(once[some], want)
+    ctx.ct_pt_mac32(hp, dev32(ct), dev(w), he.PT_SCALAR, bias=dev(b), flags=he.ACCUMULATE, out=out)
+    assert np.array_equal(host32(out), 2 * once % np.asarray(q, np.uint64)[:, None])
+    few = some[::7]
+    layer, _ = oracle.layer(ct, q, ctx.psi, *(lambda s: (s.off, s.term_ct, s.term_pt))(plan.subset(few)), w, oracle.PT_SCALAR, b[few])
+    assert np.array_equal(host32(ctx.ct_pt_mac32(hp, dev32(ct), dev(w), he.PT_SCALAR, bias=dev(b), flags=he.RESCALE))[few], layer)
+
+
 @pytest.mark.parametrize("K,M,rescale", [(9000, 16, True), (600, 528, False)])
 def test_tables_larger_than_the_fixed_scratch_are_worked_off_in_slices(he, K, M, rescale):
     """One table that does not fit (passes over its terms), and many (ranges of groups)."""
