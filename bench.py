@@ -24,7 +24,9 @@ sys.path.insert(0, ROOT)
 HBM_PEAK_GBS = 8000.0
 # 256 CUs x 64 lanes x 2.4 GHz: one 32x32(+64)-bit integer multiply(-add) per lane per clock
 INT_MUL32_PEAK_TOPS = 256 * 64 * 2.4e9 / 1e12
-MUL32_PER_MAC = 4          # a 64x64 -> 128-bit product is four 32x32 -> 64 multiply-adds
+# 256 CUs x 4 SIMDs x 1024 int8 multiply-adds per clock (a 32x32x32 tile in 32 clocks) x 2.4 GHz
+INT8_MAD_PEAK_TOPS = 256 * 4 * 1024 * 2.4e9 / 1e12
+INT8_MAD_PER_MAC = 64      # eight digits of a residue times the eight sums of an output
 MUL32_PER_SHOUP = 10       # hi64(y*w') 4, lo64(y*w) 3, lo64(qh*q) 3
 # HBM-side bytes per launch (read + written) of the main kernels come from rocprofv3 --pmc FETCH_SIZE / WRITE_SIZE
 # runs of this benchmark, scaled by a plain kernel of known size: counters cannot be read from inside this
@@ -213,7 +215,10 @@ def main() -> int:
         a = nbytes / (phase_ms[name] * 1e-3) / 1e9
         return {"kernel": name, "bound": "hbm", "achieved": a, "peak": HBM_PEAK_GBS, "unit": "GB/s",
                 "frac": a / HBM_PEAK_GBS, "traffic": traffic.get(name)}
-    rooflines["mac_scalar_cfg4"] = alu("mac_scalar_cfg4", macs4 * MUL32_PER_MAC)   # the four-product definition of a term
+    # the scalar MAC on the matrix cores: short sums (27 terms), so the memory is what bounds it
+    rooflines["mac_scalar_cfg4"] = hbm("mac_scalar_cfg4", p4.n_in * ct_bytes + p4.n_out * ct_bytes)
+    int8 = macs4 * INT8_MAD_PER_MAC / (phase_ms["mac_scalar_cfg4"] * 1e-3) / 1e12
+    rooflines["mac_scalar_cfg4"]["int8"] = {"achieved": int8, "peak": INT8_MAD_PEAK_TOPS, "unit": "Tmultiply-adds/s", "frac": int8 / INT8_MAD_PEAK_TOPS}
     rooflines["rescale_cfg4"] = alu("rescale_cfg4", rescale_mul32(p4.n_out))
     # the full-polynomial MAC streams every plaintext residue once: HBM-bound
     mac5_bytes = p5.n_pt * L * N * 8 + p5.n_in * ct_bytes + p5.n_out * ct_bytes
@@ -263,9 +268,10 @@ def main() -> int:
                                "4096 outputs) + cfg5 (dense 256->64, full-poly pt: MAC+lazy rescale, 64 outputs), "
                                "N=2^14, L=8 (2x60-bit + 6x50-bit)",
                    "value_definition": "algorithmic bytes of the step (inputs once + outputs once) / step time",
-                   "arithmetic": "residues are uint64; MAC, bias add and the rescale's combine step on 32-bit integer multiply-adds; "
-                                 "the transforms of the 50-bit limbs on double-precision FMAs, those of the 60-bit limbs on integer "
-                                 "Shoup butterflies (identical residues either way)",
+                   "arithmetic": "residues are uint64; the scalar-plaintext MAC on the int8 matrix cores (balanced base-256 digits, exact "
+                                 "32-bit sums), the full-polynomial MAC on 32-bit integer multiply-adds; transforms and combine step "
+                                 "of the rescale on double-precision FMAs for the 50-bit limbs, on integer Shoup butterflies and "
+                                 "products for the 60-bit limbs (identical residues either way)",
                    "algorithmic_bytes_per_step": total_bytes},
         "pct_hbm_peak": 100.0 * value / HBM_PEAK_GBS,
         "rescaled_ct_per_s": n_rescaled / (ms_per_step * 1e-3),
