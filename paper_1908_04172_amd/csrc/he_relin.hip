@@ -25,28 +25,76 @@ namespace {
 // for the whole run of ciphertexts (read for every one of them they were as many bytes again as digits and sums
 // together, out of the caches), and the sums are MacAcc ones, of which P * d_k is one more term: four multiply-adds per
 // product and one reduction per sum.  256 ciphertexts, seven limbs and P, N = 2^14 (2.9 GB): 767 -> 574 us.
+// A run of one ciphertext has nothing to keep the key for, and holding it only costs wavefronts (186 registers at l = 15):
+// such launches read it term by term (eight ciphertexts at N = 2^13, l = 15: 52 -> 34 us; l = 10: 24 -> 20).
 struct SpecialPrimeResidues {
     u64 r[HE_MAX_LIMBS], r_shoup[HE_MAX_LIMBS];
 };
 constexpr u32 KEY_WORKGROUPS = 8192;  // a launch is cut into at least so many workgroups while there are ciphertexts to cut
 
+// the two sums of a slot
+struct KeySums {
+    MacAcc a0, a1;
+    u32 f = 0, r = 0;
+    __device__ __forceinline__ KeySums() {
+        acc_clear(a0);
+        acc_clear(a1);
+    }
+    // += x * (w0, w1), all in two pieces
+    __device__ __forceinline__ void add(u64 x, u32 w0a, u32 w0b, u32 w1a, u32 w1b, const LimbConst& c) {
+        if (r >= c.reduce_every) {
+            acc_restart(a0, c);
+            acc_restart(a1, c);
+            f = r = 0;
+        } else if (f >= c.fold_every) {
+            acc_fold(a0, c);
+            acc_fold(a1, c);
+            f = 0;
+        }
+        ++f;
+        ++r;
+        u32 xa, xb;
+        split_operand(x, c, xa, xb);
+        acc_mac(a0, xa, xb, w0a, w0b);
+        acc_mac(a1, xa, xb, w1a, w1b);
+    }
+    __device__ __forceinline__ void add(u64 x, u64 w0, u64 w1, const LimbConst& c) {
+        u32 w0a, w0b, w1a, w1b;
+        split_operand(w0, c, w0a, w0b);
+        split_operand(w1, c, w1a, w1b);
+        add(x, w0a, w0b, w1a, w1b, c);
+    }
+};
+
+// where a thread is: its slot, its limb position and the run of ciphertexts
+struct KeyPlace {
+    size_t k;
+    u32 limb, first, end, key_limb;
+    __device__ __forceinline__ KeyPlace(u32 l, u32 key_limbs, u32 N, u32 n, u32 per_wg) {
+        u32 b = blockIdx.x;
+        k = (size_t)(b % (N / 256)) * 256 + threadIdx.x;
+        b /= N / 256;
+        limb = b % (l + 1);
+        first = b / (l + 1) * per_wg;
+        end = min(n, first + per_wg);
+        key_limb = limb == l ? key_limbs - 1 : limb;
+    }
+};
+
 template <int l>
 __global__ void __launch_bounds__(256) key_product_kernel(LimbTable lt, SpecialPrimeResidues p_mod, u32 key_limbs, u32 N, const u64* digits,
                                                           u32 n, u32 per_wg, const u64* evk, const u64* ct, u64* acc) {
     constexpr u32 L = l + 1;
-    const u32 chunks = N / 256;
-    u32 b = blockIdx.x;
-    const size_t k = (size_t)(b % chunks) * 256 + threadIdx.x; b /= chunks;
-    const u32 limb = b % L;
-    const u32 first = b / L * per_wg, end = min(n, first + per_wg);
-    const u32 key_limb = limb == l ? key_limbs - 1 : limb;
+    const KeyPlace at0(l, key_limbs, N, n, per_wg);
+    const size_t k = at0.k;
+    const u32 limb = at0.limb, key_limb = at0.key_limb;
     const LimbConst& c = lt.c[limb];
     u32 ka[2][l], kb[2][l];
 #pragma unroll
     for (u32 j = 0; j < l; j++)
 #pragma unroll
         for (u32 i = 0; i < 2; i++) split_operand(evk[((size_t)(j * 2 + i) * key_limbs + key_limb) * N + k], c, ka[i][j], kb[i][j]);
-    for (u32 at = first; at < end; at++) {
+    for (u32 at = at0.first; at < at0.end; at++) {
         u64 d[l], c0 = 0, c1 = 0;
 #pragma unroll
         for (u32 j = 0; j < l; j++) d[j] = digits[(((size_t)at * l + j) * L + limb) * N + k];
@@ -54,43 +102,34 @@ __global__ void __launch_bounds__(256) key_product_kernel(LimbTable lt, SpecialP
             c0 = ct[(((size_t)at * 2) * l + limb) * N + k];
             c1 = ct[(((size_t)at * 2 + 1) * l + limb) * N + k];
         }
-        MacAcc a0, a1;
-        acc_clear(a0);
-        acc_clear(a1);
-        u32 f = 0, r = 0;
-        auto room = [&] {  // for one more term
-            if (r >= c.reduce_every) {
-                acc_restart(a0, c);
-                acc_restart(a1, c);
-                f = r = 0;
-            } else if (f >= c.fold_every) {
-                acc_fold(a0, c);
-                acc_fold(a1, c);
-                f = 0;
-            }
-            ++f;
-            ++r;
-        };
+        KeySums s;
 #pragma unroll
-        for (u32 j = 0; j < l; j++) {
-            u32 xa, xb;
-            split_operand(d[j], c, xa, xb);
-            room();
-            acc_mac(a0, xa, xb, ka[0][j], kb[0][j]);
-            acc_mac(a1, xa, xb, ka[1][j], kb[1][j]);
-        }
-        if (limb < l) {  // + P * (c0^2, 2 c0 c1); modulo P itself that is zero
-            u32 xa, xb, wa, wb;
-            split_operand(shoup_mul(c0, p_mod.r[limb], p_mod.r_shoup[limb], c.q), c, xa, xb);
-            room();
-            split_operand(c0, c, wa, wb);
-            acc_mac(a0, xa, xb, wa, wb);
-            split_operand(add_mod(c1, c1, c.q), c, wa, wb);
-            acc_mac(a1, xa, xb, wa, wb);
-        }
-        acc[(((size_t)at * 2) * L + limb) * N + k] = acc_reduce(a0, c);
-        acc[(((size_t)at * 2 + 1) * L + limb) * N + k] = acc_reduce(a1, c);
+        for (u32 j = 0; j < l; j++) s.add(d[j], ka[0][j], kb[0][j], ka[1][j], kb[1][j], c);
+        // + P * (c0^2, 2 c0 c1); modulo P itself that is zero
+        if (limb < l) s.add(shoup_mul(c0, p_mod.r[limb], p_mod.r_shoup[limb], c.q), c0, add_mod(c1, c1, c.q), c);
+        acc[(((size_t)at * 2) * L + limb) * N + k] = acc_reduce(s.a0, c);
+        acc[(((size_t)at * 2 + 1) * L + limb) * N + k] = acc_reduce(s.a1, c);
     }
+}
+
+// runs of one ciphertext, any l
+__global__ void __launch_bounds__(256) key_product_single_kernel(LimbTable lt, SpecialPrimeResidues p_mod, u32 l, u32 key_limbs, u32 N,
+                                                                 const u64* digits, u32 n, const u64* evk, const u64* ct, u64* acc) {
+    const KeyPlace at0(l, key_limbs, N, n, 1);
+    const size_t k = at0.k, at = at0.first;
+    const u32 limb = at0.limb, key_limb = at0.key_limb, L = l + 1;
+    const LimbConst& c = lt.c[limb];
+    KeySums s;
+    for (u32 j = 0; j < l; j++) {
+        const u64* key = evk + ((size_t)j * 2 * key_limbs + key_limb) * N + k;
+        s.add(digits[((at * l + j) * L + limb) * N + k], key[0], key[(size_t)key_limbs * N], c);
+    }
+    if (limb < l) {
+        const u64 c0 = ct[(at * 2 * l + limb) * N + k], c1 = ct[((at * 2 + 1) * l + limb) * N + k];
+        s.add(shoup_mul(c0, p_mod.r[limb], p_mod.r_shoup[limb], c.q), c0, add_mod(c1, c1, c.q), c);
+    }
+    acc[(at * 2 * L + limb) * N + k] = acc_reduce(s.a0, c);
+    acc[((at * 2 + 1) * L + limb) * N + k] = acc_reduce(s.a1, c);
 }
 
 template <int l>
@@ -100,8 +139,11 @@ void launch_key_product(u32 l_wanted, const LimbTable& lt, const SpecialPrimeRes
         if (l != l_wanted) return launch_key_product<l + 1>(l_wanted, lt, p_mod, key_limbs, N, digits, n, evk, ct, acc, s);
         const u32 rows = N / 256 * (l + 1);
         const u32 runs = std::min(n, (KEY_WORKGROUPS + rows - 1) / rows), per_wg = (n + runs - 1) / runs;
-        hipLaunchKernelGGL((key_product_kernel<l>), dim3(rows * ((n + per_wg - 1) / per_wg)), dim3(256), 0, s, lt, p_mod, key_limbs, N, digits, n,
-                           per_wg, evk, ct, acc);
+        const dim3 grid(rows * ((n + per_wg - 1) / per_wg)), block(256);
+        if (per_wg == 1)
+            hipLaunchKernelGGL(key_product_single_kernel, grid, block, 0, s, lt, p_mod, l, key_limbs, N, digits, n, evk, ct, acc);
+        else
+            hipLaunchKernelGGL((key_product_kernel<l>), grid, block, 0, s, lt, p_mod, key_limbs, N, digits, n, per_wg, evk, ct, acc);
     }
 }
 

@@ -129,10 +129,12 @@ def test_rescale_of_few_polynomials_split_over_workgroups(he, n):
 
 @pytest.mark.gpu
 @pytest.mark.parametrize("log2N,bits,n", [(10, [30, 62, 50, 49, 51, 46, 60], 3), (12, [60, 59, 50, 30, 31, 46, 47, 62], 2),
-                                          (10, [50] * 15 + [60], 2), (14, [50, 40, 60], 45)])
+                                          (10, [50] * 15 + [60], 2), (14, [50, 40, 60], 45),
+                                          (14, [50] * 15 + [60], 9), (13, [60, 50, 50, 50, 50, 50, 50, 60], 70),
+                                          (13, [62, 60, 61, 30, 62], 120)])
 def test_key_switch_of_mixed_widths_and_runs(he, log2N, bits, n):
-    """Digits wider and narrower than the limb they are expanded to; fifteen digits; and more ciphertexts than runs (45 in
-    runs of two, the last one shorter)."""
+    """Digits wider and narrower than the limb they are expanded to; fifteen digits; runs of one ciphertext and, from two, seven,
+    four and fifteen key residues held in registers, of two and three (the last one shorter)."""
     N = 1 << log2N
     q = wl.modulus_chain(bits, N)
     ctx = he.Context(log2N, q)
