@@ -133,7 +133,11 @@ int he_plan_create(he_ctx* ctx, uint32_t n_in, uint32_t n_out, uint32_t n_pt, co
 /* Frees the plan's device arrays.  Valid also after the plan's context was destroyed; every other
  * call on a plan needs its context alive. */
 int he_plan_destroy(he_plan* plan);
-/* Device bytes he_ct_pt_mac needs in `workspace` for this plan, level and flags. */
+/* Device bytes he_ct_pt_mac needs in `workspace` for this plan, level and flags: with HE_RESCALE the accumulators of all
+ * outputs, and with HE_PT_SCALAR the plaintexts as the kernels read them, once for all groups that multiply by the same
+ * ones.  The latter are, per limb, 8 bytes a term for an output that shares its ciphertexts with no other, and 256, 512 or
+ * 1024 bytes a term for a group of 2..4, 5..8 or 9..16 outputs, the terms of a group rounded up to a multiple of 16 (of 4
+ * if no group of the plan has more than 4). */
 int he_plan_workspace_bytes(const he_plan* plan, uint32_t limbs, int pt_kind, uint32_t flags,
                             size_t* bytes);
 

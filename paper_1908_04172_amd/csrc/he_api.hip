@@ -171,7 +171,7 @@ void fill_limb_const(LimbConst& c, u64 q, u64 psi, u32 N) {
     c.neg_four_q = 0 - 4 * q;
 }
 
-// x + cap - correction in the rescale's combine step must fit 64 bits for x below 12q, where cap bounds the transformed
+// x + cap - correction in the rescale's combine step must fit 64 bits for x below 12q (twice what the MAC leaves), where cap bounds the transformed
 // correction: (3 + 4 log2 N) q in butterfly mode 2, 4q in mode 1, 2q in mode 0
 u32 mac_lazy(const LimbConst& c, u32 log2N) {
     const u128 cap_q = c.ntt_mode == 2 ? 3 + 4 * log2N : c.ntt_mode == 1 ? 4 : 2;

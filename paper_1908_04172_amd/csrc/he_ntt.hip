@@ -701,7 +701,7 @@ __global__ void __launch_bounds__(256) split_combine_kernel(LimbTable lt, DropRo
         const size_t p = row / (limbs - 1);
         const u32 i = (u32)(row % (limbs - 1));
         const LimbConst& c = lt.c[i];
-        // x may be the unreduced accumulator of a fused layer (below 12q where LimbConst::mac_lazy allows it)
+        // x may be the unreduced accumulator of a fused layer (below 6q, or 4q for limbs below 2^50: see DigitConst)
         const u64 x = in[(p * limbs + i) * 2 * HALF_N + j];
         out[k] = shoup_mul(x + c.q - out[k], drop.d[i].p_inv, drop.d[i].p_inv_shoup, c.q);
     }
