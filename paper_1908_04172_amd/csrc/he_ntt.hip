@@ -98,11 +98,14 @@ __device__ __forceinline__ void pass_int(u64 (&a)[16], const u64* tw, u64* lds, 
 template <int LOGN, int MODE, bool WHOLE>
 __device__ __forceinline__ void ntt_forward(u64 (&a)[16], const u64* tw, u64* lds, u32 tid, const LimbConst& c) {
     using G = Geo<LOGN>;
-    static_assert(G::NPASS >= 2 && G::NPASS <= 4, "two to four passes");
+    static_assert(G::NPASS >= 3 && G::NPASS <= 4, "three or four passes");
     pass_int<LOGN, 0, false, MODE, 0, WHOLE>(a, tw, lds, tid, c);
     pass_int<LOGN, 1, false, MODE, 0, WHOLE>(a, tw, lds, tid, c);
-    if constexpr (G::NPASS > 2) pass_int<LOGN, 2, false, MODE, 1, WHOLE>(a, tw, lds, tid, c);
-    if constexpr (G::NPASS > 3) pass_int<LOGN, 3, false, MODE, 2, WHOLE>(a, tw, lds, tid, c);
+    if constexpr (G::NPASS == 3) pass_int<LOGN, 2, false, MODE, 1, WHOLE>(a, tw, lds, tid, c);
+    if constexpr (G::NPASS > 3) {
+        pass_int<LOGN, 2, false, MODE, 1, WHOLE>(a, tw, lds, tid, c);
+        pass_int<LOGN, 3, false, MODE, 2, WHOLE>(a, tw, lds, tid, c);
+    }
 }
 
 // The forward transform in the limb's mode, of inputs below IN_Q * q (IN_Q <= 3: every mode takes them),
@@ -172,8 +175,11 @@ __device__ __forceinline__ void ntt_forward_f(double (&a)[16], const double* tw,
     const TwiddleF* t = reinterpret_cast<const TwiddleF*>(tw);
     pass_f<LOGN, 0>(a, t, lds, tid, c, q, q_inv);
     pass_f<LOGN, 1>(a, t, lds, tid, c, q, q_inv);
-    if constexpr (G::NPASS > 2) pass_f<LOGN, 2>(a, t, lds, tid, c, q, q_inv);
-    if constexpr (G::NPASS > 3) pass_f<LOGN, 3>(a, t, lds, tid, c, q, q_inv);
+    if constexpr (G::NPASS == 3) pass_f<LOGN, 2>(a, t, lds, tid, c, q, q_inv);
+    if constexpr (G::NPASS > 3) {
+        pass_f<LOGN, 2>(a, t, lds, tid, c, q, q_inv);
+        pass_f<LOGN, 3>(a, t, lds, tid, c, q, q_inv);
+    }
 }
 
 // Registers in last-pass order, canonical -> registers in pass-0 order, below 2q, multiplied by N^-1.
@@ -286,8 +292,11 @@ enum { ROWS_PLAIN = 0, ROWS_SPREAD = 1, ROWS_SQUARE = 2, ROWS_HALVES = 3 };
 struct RowMap {
     u32 stride, first, limb_fixed;  // limb_fixed = NO_LIMB: none
     u32 rotate = 0;                 // 1: workgroups change their place from slab to slab (see the loop of ntt_rows_kernel)
+    u32 stream = 0;                 // 1: the results are not to be kept in the caches
 };
 constexpr u32 NO_LIMB = 0xFFFFFFFFu;
+enum : u32 { STREAM_LOADS = 1, STREAM_STORES = 2 };
+constexpr size_t L2_BYTES = 32u << 20, MEMORY_CACHE_BYTES = 256u << 20;  // all eight L2s, the memory-side cache
 template <int LOGN, bool INVERSE, int KIND = ROWS_PLAIN>
 __global__ void __launch_bounds__(Geo<LOGN>::T, 4)
 ntt_rows_kernel(LimbTable lt, u32 limbs, u64* data, const u64* tw_all, const double* tw_f_all, u32 rows,
@@ -297,7 +306,7 @@ ntt_rows_kernel(LimbTable lt, u32 limbs, u64* data, const u64* tw_all, const dou
     constexpr bool SPREAD = KIND == ROWS_SPREAD, SQUARE = KIND == ROWS_SQUARE, HALVES = KIND == ROWS_HALVES;
     static_assert(!(SPREAD && INVERSE), "the digit expansion is a forward transform");
     static_assert(!SQUARE || INVERSE, "the squares are taken back to coefficients");
-    constexpr int PIN = INVERSE ? G::NPASS - 1 : 0, POUT = INVERSE ? 0 : G::NPASS - 1;
+    constexpr int PIN = INVERSE ? G::LOAD : 0, POUT = INVERSE ? 0 : G::STORE;  // the orders of the accesses
     extern __shared__ u64 lds[];
     u64 a[16];
     // SPREAD: `rows` counts the rows to transform, limbs - 1 per digit row: digit j under every limb position but
@@ -389,7 +398,9 @@ ntt_rows_kernel(LimbTable lt, u32 limbs, u64* data, const u64* tw_all, const dou
                 for (u32 e = 0; e < 16; e++) a[e] = __builtin_bit_cast(u64, f[e]);
             }
             if (!choice(fp)) ntt_forward_any<LOGN, SPREAD ? 2 : 1>(a, tw, lds, tid, c);
+            reorder<LOGN, G::LAST, POUT>(a, lds, tid);
         } else {
+            reorder<LOGN, PIN, G::LAST>(a, lds, tid);
             ntt_inverse_any<LOGN>(a, tw, tw_f_all + (size_t)tw_limb * G::N, lds, tid, c);
         }
         // The next row is requested first, the last reductions of this row run while it travels, and it is
@@ -430,8 +441,7 @@ ntt_rows_kernel(LimbTable lt, u32 limbs, u64* data, const u64* tw_all, const dou
             for (u32 e = 0; e < 16; e++) asm volatile("" : "+v"(next[e]) :: "memory");
         }
         u64* p = HALVES ? const_cast<u64*>(source(work)) : data + (size_t)row * G::N;
-#pragma unroll
-        for (u32 e = 0; e < 16; e++) row_at<LOGN, POUT>(p, tid_s, e) = a[e];
+        store_row<LOGN, POUT>(a, p, tid_s, map.stream);
 #pragma unroll
         for (u32 e = 0; e < 16; e++) a[e] = next[e];
         if (next_work >= rows) break;
@@ -453,16 +463,24 @@ ntt_rows_kernel(LimbTable lt, u32 limbs, u64* data, const u64* tw_all, const dou
 // the first kept limb takes t straight from the registers; for the others t is parked in memory.
 //
 // The parked t for limb i+1 is requested, and waited for, before the outputs of limb i are stored.
-// Wavefronts per SIMD that the register allocation leaves room for.  Up to N = 2^12 three: the kernel takes 134 to 140
-// registers, and under 128 up to 16 of them were spilled (8192 ciphertexts of N = 2^12 at L = 2: 444 us at three, 476 at
-// four; 128 at L = 4: 28.4 and 33.5).  Above that four: it takes 127 or 128 anyway (at 2^14, 4 spilled), and at 2^13 the LDS
-// has room for two workgroups.
-template <int LOGN>
-constexpr int rescale_waves() { return LOGN <= 12 ? 3 : 4; }
+// Three things keep its traffic low, which bounds it as much as the arithmetic (with every butterfly left out it took 86 % of
+// its time): full cache lines (Geo::STORE), the first values of t in the LDS instead of in memory (as many as the workgroups
+// of a compute unit leave room for beside their rows: three at every ring degree), and rows that pass by the caches when a call
+// is larger than they are (launch_rescale_t).  Before and with all three: 1024 ciphertexts of N = 2^14 at L = 8 1360 -> 1231 us,
+// 768 of 2^13 at L = 4 226 -> 213, 2048 of 2^12 at L = 4 327 -> 260, 128 of 2^12 at L = 4 27.9 -> 23.0.
+// Four wavefronts per SIMD: 108 to 122 registers, no spills.
+constexpr u32 LDS_BYTES = 160u << 10;  // of a compute unit
+constexpr u32 RESCALE_WAVES = 4;
 
 template <int LOGN>
-__global__ void __launch_bounds__(Geo<LOGN>::T, rescale_waves<LOGN>())
-rescale_kernel(LimbTable lt, DropRow drop, u32 limbs, u64 shares, const u64* in, u64* out, const u64* tw_fwd,
+constexpr u32 rescale_kept() {
+    constexpr u32 workgroups = 256 * RESCALE_WAVES / Geo<LOGN>::T;  // of a compute unit
+    return (LDS_BYTES / workgroups - lds_row_bytes<LOGN, u64>()) / (Geo<LOGN>::T * (u32)sizeof(u64));
+}
+
+template <int LOGN>
+__global__ void __launch_bounds__(Geo<LOGN>::T, RESCALE_WAVES)
+rescale_kernel(LimbTable lt, DropRow drop, u32 limbs, u64 shares, u32 stream, const u64* in, u64* out, const u64* tw_fwd,
                const u64* tw_inv, const double* tw_fwd_f, const double* tw_inv_f) {
     using G = Geo<LOGN>;
     extern __shared__ __align__(16) u64 lds[];
@@ -481,14 +499,17 @@ rescale_kernel(LimbTable lt, DropRow drop, u32 limbs, u64 shares, const u64* in,
     // t is parked in the output row of this workgroup's last limb: every thread re-reads only what it
     // wrote itself, and that row is overwritten only in the last iteration, after all its threads have
     // taken their t back (they use it before the first regrouping barrier of that iteration).
+    // Its first KEPT values stay in the LDS beside the row, as many as fit.
     u64* park = dst + (size_t)(end - 1) * G::N;
+    constexpr u32 KEPT = rescale_kept<LOGN>();
+    auto kept = [&](u32 tid, u32 e) -> u64& { return lds[lds_slot(G::N) + e * G::T + tid]; };
     u64 a[16];
     {
         const u32 tid = threadIdx.x;
         const LimbConst& c = lt.c[last];
         const u64* row = src + (size_t)last * G::N;
-#pragma unroll
-        for (u32 e = 0; e < 16; e++) a[e] = row_at<LOGN, G::NPASS - 1>(row, tid, e);
+        load_row<LOGN, G::LOAD>(a, row, tid, stream & STREAM_LOADS);
+        reorder<LOGN, G::LOAD, G::LAST>(a, lds, tid);
         ntt_inverse_any<LOGN, true>(a, tw_inv + (size_t)last * G::N * 2, tw_inv_f + (size_t)last * G::N, lds, tid, c);
         const u64 half = c.q >> 1;
         const u32 tid_s = fresh(tid);
@@ -500,7 +521,9 @@ rescale_kernel(LimbTable lt, DropRow drop, u32 limbs, u64 shares, const u64* in,
         }
         if (end - first > 1) {
 #pragma unroll
-            for (u32 e = 0; e < 16; e++) row_at<LOGN, 0>(park, tid_s, e) = a[e];
+            for (u32 e = 0; e < KEPT; e++) kept(tid_s, e) = a[e];
+#pragma unroll
+            for (u32 e = KEPT; e < 16; e++) row_at<LOGN, 0>(park, tid_s, e) = a[e];
         }
     }
     for (u32 i = first; i < end; i++) {
@@ -520,28 +543,29 @@ rescale_kernel(LimbTable lt, DropRow drop, u32 limbs, u64 shares, const u64* in,
         // loads (its first two passes' twiddles), with nothing to wait for behind the stores.
         // (The two forms of a limb's iteration are separate code from the transform to the stores, see choice().)
         auto finish = [&](auto combine) {
+            reorder<LOGN, G::LAST, G::STORE>(a, lds, tid);
             __builtin_amdgcn_sched_barrier(0);  // the loads not before the last stage: their registers are in use
             const u32 tid_s = fresh(tid);
             u64 x[16], next[16];
+            load_row<LOGN, G::STORE>(x, xrow, tid_s, stream & STREAM_LOADS);
 #pragma unroll
-            for (u32 e = 0; e < 16; e++) x[e] = row_at<LOGN, G::NPASS - 1>(xrow, tid_s, e);
-#pragma unroll
-            for (u32 e = 0; e < 16; e++) next[e] = 0;
+            for (u32 e = KEPT; e < 16; e++) next[e] = 0;
             if (i + 1 < end) {
 #pragma unroll
-                for (u32 e = 0; e < 16; e++) next[e] = row_at<LOGN, 0>(park, tid_s, e);
+                for (u32 e = KEPT; e < 16; e++) next[e] = row_at<LOGN, 0>(park, tid_s, e);
             }
 #pragma unroll
-            for (u32 e = 0; e < 16; e++) {
-                x[e] = combine(x[e], a[e]);
-            }
+            for (u32 e = 0; e < 16; e++) x[e] = combine(x[e], a[e]);
 #pragma unroll
-            for (u32 e = 0; e < 16; e++) {
+            for (u32 e = KEPT; e < 16; e++) {
                 a[e] = next[e];
                 asm volatile("" : "+v"(a[e]) :: "memory");  // t for the next limb has arrived: nothing is left to wait for
             }
+            store_row<LOGN, G::STORE>(x, orow, tid_s, stream & STREAM_STORES);
+            if (i + 1 < end) {
 #pragma unroll
-            for (u32 e = 0; e < 16; e++) row_at<LOGN, G::NPASS - 1>(orow, tid_s, e) = x[e];
+                for (u32 e = 0; e < KEPT; e++) a[e] = kept(tid_s, e);
+            }
         };
         if (choice(d.fp64)) {
             // q_i < 2^50 and p <= 2*q_i: the transform runs on doubles.  t - h as an integer lies in [-h, h],
@@ -635,20 +659,21 @@ u32 elementwise_grid(size_t total) { return (u32)std::min<size_t>((total + 255) 
 int launch_split_transform(he_ctx* ctx, const LimbTable& lt, u32 limbs, u64* data, u32 rows, bool inverse, const u64* tw,
                            const double* tw_f, RowMap map, hipStream_t s, bool top_done = false) {
     using G = Geo<14>;
-    const size_t lds = (size_t)G::N * sizeof(u64);
+    const size_t lds = lds_row_bytes<14, u64>();
     const u32 halves = rows * 2;
     const u32 grid = std::min<u32>(halves, 256);
     if (map.limb_fixed == NO_LIMB) map.rotate = limbs_differ(lt, limbs);
+    map.stream = (size_t)halves * G::N * sizeof(u64) > MEMORY_CACHE_BYTES;
     if (inverse) {
         static std::atomic<uint32_t> lds_allowed{0};
-        if (int rc = allow_dynamic_lds((const void*)ntt_rows_kernel<14, true, ROWS_HALVES>, lds, ctx->device, lds_allowed, true)) return rc;
+        if (int rc = allow_dynamic_lds((const void*)ntt_rows_kernel<14, true, ROWS_HALVES>, lds, ctx->device, lds_allowed)) return rc;
         hipLaunchKernelGGL((ntt_rows_kernel<14, true, ROWS_HALVES>), dim3(grid), dim3(G::T), lds, s, lt, limbs, data, tw, tw_f, halves,
                            (const u64*)nullptr, 1u, 0u, (u64*)nullptr, map);
         hipLaunchKernelGGL((split_top_kernel<true>), dim3(elementwise_grid((size_t)rows * HALF_N)), dim3(256), 0, s, lt, limbs, data, tw,
                            rows, map);
     } else {
         static std::atomic<uint32_t> lds_allowed{0};
-        if (int rc = allow_dynamic_lds((const void*)ntt_rows_kernel<14, false, ROWS_HALVES>, lds, ctx->device, lds_allowed, true)) return rc;
+        if (int rc = allow_dynamic_lds((const void*)ntt_rows_kernel<14, false, ROWS_HALVES>, lds, ctx->device, lds_allowed)) return rc;
         if (!top_done)
             hipLaunchKernelGGL((split_top_kernel<false>), dim3(elementwise_grid((size_t)rows * HALF_N)), dim3(256), 0, s, lt, limbs, data,
                                tw, rows, map);
@@ -732,28 +757,28 @@ int launch_rescale_split(he_ctx* ctx, u32 limbs, u32 drop_id, const u64* in, u64
 
 // workgroups that a compute unit holds at once: its LDS, and the wavefronts per SIMD of the kernel's register limit
 template <int LOGN>
-constexpr u32 resident_per_cu(int waves = 4) {
+constexpr u32 resident_per_cu() {
     using G = Geo<LOGN>;
-    const u32 by_lds = (160u << 10) / (G::N * (u32)sizeof(u64)), by_waves = 256 * waves / G::T;
+    const u32 by_lds = LDS_BYTES / lds_row_bytes<LOGN, u64>(), by_waves = 256 * 4 / G::T;
     return by_lds < by_waves ? by_lds : by_waves;
 }
 
 template <int LOGN>
 int launch_ntt_t(he_ctx* ctx, u32 limbs, u64* data, u32 rows, bool inverse, const u64* src, hipStream_t s) {
     using G = Geo<LOGN>;
-    const RowMap map{1, 0, NO_LIMB, limbs_differ(ctx->limbs, limbs)};
-    const size_t lds = (size_t)G::N * sizeof(u64);
+    const RowMap map{1, 0, NO_LIMB, limbs_differ(ctx->limbs, limbs), (size_t)rows * G::N * sizeof(u64) > MEMORY_CACHE_BYTES};
+    const size_t lds = lds_row_bytes<LOGN, u64>();
     // as many workgroups as stay resident at once (LDS and the 2048 threads of a compute unit bound
     // that), each looping over its share of the rows
     const u32 per_cu = resident_per_cu<LOGN>();
     const u32 grid = std::min<u32>(rows, 256 * per_cu);
     if (inverse) {
         static std::atomic<uint32_t> lds_allowed{0};
-        if (int rc = allow_dynamic_lds((const void*)ntt_rows_kernel<LOGN, true>, lds, ctx->device, lds_allowed, true)) return rc;
+        if (int rc = allow_dynamic_lds((const void*)ntt_rows_kernel<LOGN, true>, lds, ctx->device, lds_allowed)) return rc;
         hipLaunchKernelGGL((ntt_rows_kernel<LOGN, true>), dim3(grid), dim3(G::T), lds, s, ctx->limbs, limbs, data, ctx->tw_inv, ctx->tw_inv_f, rows, src, 1u, 0u, (u64*)nullptr, map);
     } else {
         static std::atomic<uint32_t> lds_allowed{0};
-        if (int rc = allow_dynamic_lds((const void*)ntt_rows_kernel<LOGN, false>, lds, ctx->device, lds_allowed, true)) return rc;
+        if (int rc = allow_dynamic_lds((const void*)ntt_rows_kernel<LOGN, false>, lds, ctx->device, lds_allowed)) return rc;
         hipLaunchKernelGGL((ntt_rows_kernel<LOGN, false>), dim3(grid), dim3(G::T), lds, s, ctx->limbs, limbs, data, ctx->tw_fwd, ctx->tw_fwd_f, rows, src, 1u, 0u, (u64*)nullptr, map);
     }
     HE_HIP(hipGetLastError());
@@ -765,13 +790,14 @@ int launch_ntt_spread_t(he_ctx* ctx, u32 limbs, const u64* src, u64* out, u32 ro
     LimbTable lt = ctx->limbs;
     lt.c[limbs - 1] = ctx->limbs.c[ctx->L - 1];
     using G = Geo<LOGN>;
-    const size_t lds = (size_t)G::N * sizeof(u64);
+    const size_t lds = lds_row_bytes<LOGN, u64>();
     const u32 per_cu = resident_per_cu<LOGN>();
     const u32 grid = std::min<u32>(rows, 256 * per_cu);
     static std::atomic<uint32_t> lds_allowed{0};
-    if (int rc = allow_dynamic_lds((const void*)ntt_rows_kernel<LOGN, false, ROWS_SPREAD>, lds, ctx->device, lds_allowed, true)) return rc;
+    if (int rc = allow_dynamic_lds((const void*)ntt_rows_kernel<LOGN, false, ROWS_SPREAD>, lds, ctx->device, lds_allowed)) return rc;
+    const RowMap map{1, 0, NO_LIMB, 0, (size_t)rows * G::N * sizeof(u64) > MEMORY_CACHE_BYTES};
     hipLaunchKernelGGL((ntt_rows_kernel<LOGN, false, ROWS_SPREAD>), dim3(grid), dim3(G::T), lds, s, lt, limbs, out, ctx->tw_fwd, ctx->tw_fwd_f,
-                       rows, src, digits, ctx->L - 1);
+                       rows, src, digits, ctx->L - 1, (u64*)nullptr, map);
     HE_HIP(hipGetLastError());
     return HE_OK;
 }
@@ -781,13 +807,14 @@ int launch_ntt_spread_t(he_ctx* ctx, u32 limbs, const u64* src, u64* out, u32 ro
 template <int LOGN>
 int launch_ntt_square_t(he_ctx* ctx, u32 limbs, const u64* ct, u64* d2, u64* digits, u32 rows, hipStream_t s) {
     using G = Geo<LOGN>;
-    const size_t lds = (size_t)G::N * sizeof(u64);
+    const size_t lds = lds_row_bytes<LOGN, u64>();
     const u32 per_cu = resident_per_cu<LOGN>();
     const u32 grid = std::min<u32>(rows, 256 * per_cu);
     static std::atomic<uint32_t> lds_allowed{0};
-    if (int rc = allow_dynamic_lds((const void*)ntt_rows_kernel<LOGN, true, ROWS_SQUARE>, lds, ctx->device, lds_allowed, true)) return rc;
+    if (int rc = allow_dynamic_lds((const void*)ntt_rows_kernel<LOGN, true, ROWS_SQUARE>, lds, ctx->device, lds_allowed)) return rc;
+    const RowMap map{1, 0, NO_LIMB, 0, (size_t)rows * G::N * sizeof(u64) > MEMORY_CACHE_BYTES};
     hipLaunchKernelGGL((ntt_rows_kernel<LOGN, true, ROWS_SQUARE>), dim3(grid), dim3(G::T), lds, s, ctx->limbs, limbs, d2, ctx->tw_inv,
-                       ctx->tw_inv_f, rows, ct, 1u, 0u, digits);
+                       ctx->tw_inv_f, rows, ct, 1u, 0u, digits, map);
     HE_HIP(hipGetLastError());
     return HE_OK;
 }
@@ -803,18 +830,23 @@ int launch_rescale_t(he_ctx* ctx, u32 limbs, u32 drop_id, const u64* in, u64* ou
     lt.c[limbs - 1] = ctx->limbs.c[drop_id];
     const u64* tw_inv = ctx->tw_inv + (size_t)(drop_id - (limbs - 1)) * G::N * 2;
     const double* tw_inv_f = ctx->tw_inv_f + (size_t)(drop_id - (limbs - 1)) * G::N;
-    const size_t lds = (size_t)G::N * sizeof(u64);
+    const size_t lds = lds_row_bytes<LOGN, u64>() + rescale_kept<LOGN>() * G::T * sizeof(u64);
     static std::atomic<uint32_t> lds_allowed{0};
-    if (int rc = allow_dynamic_lds((const void*)rescale_kernel<LOGN>, lds, ctx->device, lds_allowed, true)) return rc;
+    if (int rc = allow_dynamic_lds((const void*)rescale_kernel<LOGN>, lds, ctx->device, lds_allowed)) return rc;
     DropRow row;
     for (u32 i = 0; i < HE_MAX_LIMBS; i++) row.d[i] = ctx->drop[drop_id][i];
     // with fewer polynomials than workgroups the chip holds at once, split each over several workgroups
     // (at most one per kept limb), as far as they still all run at the same time
-    const u32 resident = 256 * resident_per_cu<LOGN>(rescale_waves<LOGN>());
+    const u32 resident = 256 * resident_per_cu<LOGN>();
     const u32 parts = std::max(1u, std::min(limbs - 1, resident / (2 * n)));
     u64 shares = 0;
     for (u32 k = 0; k <= parts; k++) shares |= (u64)(k * (limbs - 1) / parts) << (4 * k);
-    hipLaunchKernelGGL((rescale_kernel<LOGN>), dim3(2 * n, parts), dim3(G::T), lds, s, lt, row, limbs, shares, in, out, ctx->tw_fwd, tw_inv,
+    // Accumulators that do not fit the memory-side cache (256 MiB) are read past the caches, so that the parked t stays
+    // there (845 ciphertexts of N = 2^13 at L = 3, 332 MB: 191 -> 185 us); smaller ones lie in it when a MAC has just written
+    // them (300 at L = 4, 157 MB: 93 us, 101 past the caches).  Results of calls beyond the L2s (8 x 4 MiB) are written past them.
+    const size_t row_bytes = (size_t)G::N * sizeof(u64), in_bytes = 2 * n * limbs * row_bytes, out_bytes = 2 * n * (limbs - 1) * row_bytes;
+    const u32 stream = (in_bytes > MEMORY_CACHE_BYTES ? STREAM_LOADS : 0) | (in_bytes + out_bytes > L2_BYTES ? STREAM_STORES : 0);
+    hipLaunchKernelGGL((rescale_kernel<LOGN>), dim3(2 * n, parts), dim3(G::T), lds, s, lt, row, limbs, shares, stream, in, out, ctx->tw_fwd, tw_inv,
                        ctx->tw_fwd_f, tw_inv_f);
     HE_HIP(hipGetLastError());
     return HE_OK;

@@ -25,11 +25,23 @@ struct Geo {
     static constexpr int T = N / 16;
     static constexpr int NPASS = (LOGN + 3) / 4;
     static constexpr int REM = LOGN - 4 * (NPASS - 1);  // stages of the last pass, 1..4
+    static constexpr int LAST = NPASS - 1;
+    // The orders of the accesses to rows in bit-reversed order: the last pass's, or MEMORY (see reg_index) where that leaves a
+    // lane more than 16 bytes in a row; the loads of 32 bytes of 64-bit residues are not worth the regrouping (inverse
+    // transforms of 4096 rows of 2^14: 336 us without, 340 with it; stores of forward ones 305 without, 298 with it).
+    static constexpr int MEMORY = NPASS;
+    static constexpr int STORE = REM > 1 ? MEMORY : LAST, LOAD = REM > 2 ? MEMORY : LAST;
+    static constexpr int PACKED = REM > 2 ? MEMORY : LAST;  // 32-bit residues
 };
 
 // Index of register e of thread tid while pass P is being computed.  In the last pass the registers
 // own the lowest REM index bits (the stages left) and, to fill 16 registers, the 4-REM bits just above
 // the six bits that the lane number owns, so that a wavefront holds one aligned block of 1024.
+// In the order MEMORY, in which rows in bit-reversed order are read and written, a lane holds two consecutive residues and
+// its neighbours the next ones: an access of 16 bytes per lane is 1 KiB in one piece.  It is the last pass's own order when
+// that has one stage; otherwise a regrouping within the wavefront lies between the two.  (In the last pass's order a lane
+// holds 2^REM consecutive residues, and an instruction touches a part of every one of up to 64 cache lines: a rescale of 2048
+// ciphertexts of N = 2^12 at L = 4 315 us, 268 in this order.)
 template <int LOGN, int P>
 __host__ __device__ constexpr u32 reg_index(u32 tid, u32 e) {
     using G = Geo<LOGN>;
@@ -37,6 +49,8 @@ __host__ __device__ constexpr u32 reg_index(u32 tid, u32 e) {
         constexpr int low = LOGN - 4 * (P + 1);
         u32 hi = tid >> low, lo = tid & ((1u << low) - 1);
         return (hi << (low + 4)) | (e << low) | lo;
+    } else if constexpr (P == G::MEMORY) {
+        return ((tid >> 6) << 10) | ((e >> 1) << 7) | ((tid & 63u) << 1) | (e & 1u);
     } else if constexpr (G::REM == 4) {
         return (tid << 4) | e;
     } else {
@@ -56,6 +70,33 @@ __device__ __forceinline__ V& row_at(V* row, u32 tid, u32 e) {
     return *reinterpret_cast<V*>(reinterpret_cast<byte*>(row + reg_index<LOGN, P>(0, e)) + reg_index<LOGN, P>(tid, 0) * (u32)sizeof(V));
 }
 
+// All sixteen registers of a thread from or to a row, in the order of pass P.  STREAM accesses (a choice that is the same for
+// the whole launch) are marked as not to be kept in the caches: see the launchers for when.
+template <int LOGN, int P>
+__device__ __forceinline__ void load_row(u64 (&a)[16], const u64* row, u32 tid, bool stream) {
+    if (stream) {
+        asm volatile("; streamed loads" ::: "memory");  // (left to itself the compiler makes one loop of the two, of ordinary loads)
+#pragma unroll
+        for (u32 e = 0; e < 16; e++) a[e] = __builtin_nontemporal_load(&row_at<LOGN, P>(row, tid, e));
+        asm volatile("; end" ::: "memory");
+    } else {
+#pragma unroll
+        for (u32 e = 0; e < 16; e++) a[e] = row_at<LOGN, P>(row, tid, e);
+    }
+}
+template <int LOGN, int P>
+__device__ __forceinline__ void store_row(const u64 (&a)[16], u64* row, u32 tid, bool stream) {
+    if (stream) {
+        asm volatile("; streamed stores" ::: "memory");
+#pragma unroll
+        for (u32 e = 0; e < 16; e++) __builtin_nontemporal_store(a[e], &row_at<LOGN, P>(row, tid, e));
+        asm volatile("; end" ::: "memory");
+    } else {
+#pragma unroll
+        for (u32 e = 0; e < 16; e++) row_at<LOGN, P>(row, tid, e) = a[e];
+    }
+}
+
 // True when, in pass P, every wavefront (64 consecutive threads) holds exactly the aligned block of
 // 1024 indices with its own number: a regrouping between two such passes moves data only within
 // wavefronts.  Checked over all threads and registers at compile time.
@@ -67,11 +108,16 @@ constexpr bool wave_holds_own_block() {
     return true;
 }
 
-// LDS placement: XOR the low index bits with higher ones so that the strided access patterns of
-// the regrouping steps spread over the banks.  A bijection on every aligned block of 1024 indices.
-__host__ __device__ constexpr u32 lds_slot(u32 idx) {
-    return idx ^ (((idx >> 6) & 0xFu) << 2) ^ ((idx >> 5) & 3u);
-}
+// LDS placement: one slot of padding after every sixteen, so that the strided access patterns of the regrouping steps
+// spread over the banks (64-bit residues: no conflict in any pass of any ring degree; 32-bit ones two-way conflicts in some).
+// An aligned block of 1024 indices keeps a range of slots of its own.  Of two indices without common bits the slot of the
+// sum is the sum of the slots: an access is one base per thread and a constant that goes into the instruction.  (As an
+// exclusive or of index bits the placement cost an instruction per access, 96 of about 1900 in a transform of 2^14.)
+__host__ __device__ constexpr u32 lds_slot(u32 idx) { return idx + (idx >> 4); }
+
+// bytes of a row of N residues of type V in the LDS
+template <int LOGN, typename V>
+constexpr u32 lds_row_bytes() { return lds_slot(Geo<LOGN>::N) * (u32)sizeof(V); }
 
 // Workgroup barrier that orders LDS traffic only: waits for this wave's LDS operations, then for the
 // other waves.  (A full __syncthreads() would also wait for outstanding global loads, and the
@@ -83,34 +129,51 @@ __device__ __forceinline__ void lds_barrier() { asm volatile("s_waitcnt lgkmcnt(
 // compiler); other waves are not waited for and run ahead or behind freely.
 __device__ __forceinline__ void lds_wave_order() { asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory"); }
 
+// Where a thread's registers of pass P are in the LDS.  (An instruction's constant offset reaches 64 KiB; the first pass of
+// N = 2^14 has accesses beyond that, which take an addition.)
+template <typename V, int LOGN, int P>
+struct LdsBase {
+    typedef __attribute__((address_space(3))) V lds_v;
+    static constexpr u32 offset(u32 e) { return lds_slot(reg_index<LOGN, P>(0, e)) * (u32)sizeof(V); }
+    u32 base;
+    __device__ __forceinline__ LdsBase(V* row, u32 tid) {
+        base = (u32)(uintptr_t)(lds_v*)row + lds_slot(reg_index<LOGN, P>(tid, 0)) * (u32)sizeof(V);
+        asm("" : "+v"(base));  // (else the constants are added to the row's address, one instruction and register each)
+    }
+    __device__ __forceinline__ lds_v* operator()(u32 e) const { return (lds_v*)(uintptr_t)(base + offset(e)); }
+};
+
 // (V: the residue type, u64 or u32; the row in the LDS is N of them)
 template <int LOGN, int PFROM, int PTO, typename V>
 __device__ __forceinline__ void regroup(V (&a)[16], V* lds, u32 tid) {
     constexpr bool WAVE_LOCAL = wave_holds_own_block<LOGN, PFROM>() && wave_holds_own_block<LOGN, PTO>();
-    // reg_index(tid, e) = reg_index(tid, 0) ^ reg_index(0, e) (disjoint bits) and lds_slot is linear
-    // over XOR, so each address is one XOR of a per-thread base with a compile-time constant
+    // reg_index(tid, e) = reg_index(tid, 0) + reg_index(0, e) (disjoint bits), and so are their slots: see lds_slot
     // The two bases are derived from copies of the thread index that the optimizer cannot relate to
     // each other or to other passes: a regrouping writes where the previous one read, and addresses
     // kept alive from one to the next would cost more registers than the few operations they save.
     u32 tid_w = tid, tid_r = tid;
     asm("; regroup %1 write" : "+v"(tid_w) : "n"(PFROM * 16 + PTO));
     asm("; regroup %1 read" : "+v"(tid_r) : "n"(PFROM * 16 + PTO));
-    // Addresses are formed as LDS byte addresses outright, one XOR per access: (row + from) ^ constant equals
-    // row + (from ^ constant) because the row starts at LDS address 0 -- a workgroup's LDS addresses are relative
-    // to its own allocation, and these kernels have no static LDS in front of the dynamic row (the launchers
-    // check that: lds_row_starts_at_zero).
-    typedef __attribute__((address_space(3))) V lds_v;
-    constexpr u32 W = sizeof(V);
-    const u32 row = (u32)(uintptr_t)(lds_v*)lds;
-    const u32 from = row + lds_slot(reg_index<LOGN, PFROM>(tid_w, 0)) * W, to = row + lds_slot(reg_index<LOGN, PTO>(tid_r, 0)) * W;
     // earlier readers of the slots written here are done: all waves, or (wave-local) this wave only,
     // since its block of slots is then touched by no other wave until the next workgroup-wide regrouping
     if constexpr (WAVE_LOCAL) lds_wave_order(); else lds_barrier();
+    {
+        const LdsBase<V, LOGN, PFROM> at(lds, tid_w);
 #pragma unroll
-    for (u32 e = 0; e < 16; e++) *(lds_v*)(uintptr_t)(from ^ (lds_slot(reg_index<LOGN, PFROM>(0, e)) * W)) = a[e];
+        for (u32 e = 0; e < 16; e++) *at(e) = a[e];
+    }
     if constexpr (WAVE_LOCAL) lds_wave_order(); else lds_barrier();
+    {
+        const LdsBase<V, LOGN, PTO> at(lds, tid_r);
 #pragma unroll
-    for (u32 e = 0; e < 16; e++) a[e] = *(const lds_v*)(uintptr_t)(to ^ (lds_slot(reg_index<LOGN, PTO>(0, e)) * W));
+        for (u32 e = 0; e < 16; e++) a[e] = *at(e);
+    }
+}
+
+// ... if the two orders differ (between the last pass's and that of the accesses to memory)
+template <int LOGN, int FROM, int TO, typename V>
+__device__ __forceinline__ void reorder(V (&a)[16], V* lds, u32 tid) {
+    if constexpr (FROM != TO) regroup<LOGN, FROM, TO>(a, lds, tid);
 }
 
 // Tw: the twiddle type, Twiddle (two 64-bit words), Twiddle32 (two 32-bit words) or TwiddleF (one double): a table

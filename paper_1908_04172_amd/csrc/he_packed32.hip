@@ -435,7 +435,7 @@ __device__ __forceinline__ void ntt32_inverse(u32 (&a)[16], const Twiddle32* tw,
 template <int LOGN, bool INVERSE>
 __global__ void __launch_bounds__(Geo<LOGN>::T) ntt32_rows_kernel(Limb32Table lt, u32 limbs, u32* data, const u32* tw_all, u32 rows) {
     using G = Geo<LOGN>;
-    constexpr int PIN = INVERSE ? G::NPASS - 1 : 0, POUT = INVERSE ? 0 : G::NPASS - 1;
+    constexpr int PIN = INVERSE ? G::PACKED : 0, POUT = INVERSE ? 0 : G::PACKED;
     extern __shared__ u32 lds32[];
     u32 a[16];
     {
@@ -457,11 +457,13 @@ __global__ void __launch_bounds__(Geo<LOGN>::T) ntt32_rows_kernel(Limb32Table lt
             for (u32 e = 0; e < 16; e++) next[e] = row_at<LOGN, PIN>(p, tid, e);
         }
         if constexpr (INVERSE) {
+            reorder<LOGN, PIN, G::LAST>(a, lds32, tid);
             ntt32_inverse<LOGN>(a, tw, lds32, tid, c);
 #pragma unroll
             for (u32 e = 0; e < 16; e++) a[e] = csub32(a[e], c.q);
         } else {
             ntt32_forward<LOGN>(a, tw, lds32, tid, c);
+            reorder<LOGN, G::LAST, POUT>(a, lds32, tid);
 #pragma unroll
             for (u32 e = 0; e < 16; e++) a[e] = csub32(csub32(a[e], c.two_q), c.q);
         }
@@ -486,7 +488,6 @@ template <int LOGN>
 __global__ void __launch_bounds__(Geo<LOGN>::T) rescale32_kernel(Limb32Table lt, Drop32Row drop, u32 limbs, const u32* in, u32* out,
                                                                   const u32* tw_fwd, const u32* tw_inv) {
     using G = Geo<LOGN>;
-    constexpr int LAST_PASS = G::NPASS - 1;
     extern __shared__ u32 lds32[];
     const size_t poly = blockIdx.x;
     const u32 tid = threadIdx.x;
@@ -498,7 +499,8 @@ __global__ void __launch_bounds__(Geo<LOGN>::T) rescale32_kernel(Limb32Table lt,
         const Limb32& c = lt.c[last];
         const u32* row = src + (size_t)last * G::N;
 #pragma unroll
-        for (u32 e = 0; e < 16; e++) t[e] = row_at<LOGN, LAST_PASS>(row, tid, e);
+        for (u32 e = 0; e < 16; e++) t[e] = row_at<LOGN, G::PACKED>(row, tid, e);
+        reorder<LOGN, G::PACKED, G::LAST>(t, lds32, tid);
         ntt32_inverse<LOGN>(t, reinterpret_cast<const Twiddle32*>(tw_inv) + (size_t)last * G::N, lds32, tid, c);
         const u32 half = c.q >> 1;
 #pragma unroll
@@ -510,19 +512,20 @@ __global__ void __launch_bounds__(Geo<LOGN>::T) rescale32_kernel(Limb32Table lt,
         const u32* xrow = src + (size_t)i * G::N;
         u32 x[16], a[16];
 #pragma unroll
-        for (u32 e = 0; e < 16; e++) x[e] = row_at<LOGN, LAST_PASS>(xrow, tid, e);
+        for (u32 e = 0; e < 16; e++) x[e] = row_at<LOGN, G::PACKED>(xrow, tid, e);
         // t < p is below 2*q_i unless p > 2*q_i (then Alg. 6 reduces it first); adding q_i - (h mod q_i) gives a
         // value congruent to t - h and below 3*q_i, which the forward transform takes
         const u32 minus_half = c.q - d.half_mod;
 #pragma unroll
         for (u32 e = 0; e < 16; e++) a[e] = (d.reduce ? barrett64(t[e], c) : t[e]) + minus_half;
         ntt32_forward<LOGN>(a, reinterpret_cast<const Twiddle32*>(tw_fwd) + (size_t)i * G::N, lds32, tid, c);
+        reorder<LOGN, G::LAST, G::PACKED>(a, lds32, tid);
         u32* orow = dst + (size_t)i * G::N;
 #pragma unroll
         for (u32 e = 0; e < 16; e++) {
             const u32 corr = csub32(a[e], c.two_q);  // below 2q: x + 2q - corr is positive and below 3q < 2^32
             const u32 v = shoup32_add(x[e] + c.two_q - corr, Twiddle32{d.p_inv, d.p_inv_shoup}, c.q, 0);
-            row_at<LOGN, LAST_PASS>(orow, tid, e) = csub32(v, c.q);
+            row_at<LOGN, G::PACKED>(orow, tid, e) = csub32(v, c.q);
         }
     }
 }
@@ -667,17 +670,17 @@ int launch_add32(he_ctx* ctx, u32 limbs, u32* ct, u32 n, const void* pt, int pt_
 template <int LOGN>
 static int launch_ntt32_t(he_ctx* ctx, u32 limbs, u32* data, u32 rows, bool inverse, hipStream_t s) {
     using G = Geo<LOGN>;
-    const size_t lds = (size_t)G::N * sizeof(u32);
+    const size_t lds = lds_row_bytes<LOGN, u32>();
     // as many workgroups as stay resident at once, each looping over its share of the rows
     const u32 per_cu = (u32)std::max<size_t>(1, std::min<size_t>((160u << 10) / lds, 2048 / G::T));
     const u32 grid = std::min<u32>(rows, 256 * per_cu);
     if (inverse) {
         static std::atomic<uint32_t> checked{0};
-        if (int rc = allow_dynamic_lds((const void*)ntt32_rows_kernel<LOGN, true>, lds, ctx->device, checked, true)) return rc;
+        if (int rc = allow_dynamic_lds((const void*)ntt32_rows_kernel<LOGN, true>, lds, ctx->device, checked)) return rc;
         hipLaunchKernelGGL((ntt32_rows_kernel<LOGN, true>), dim3(grid), dim3(G::T), lds, s, ctx->limbs32, limbs, data, ctx->tw32_inv, rows);
     } else {
         static std::atomic<uint32_t> checked{0};
-        if (int rc = allow_dynamic_lds((const void*)ntt32_rows_kernel<LOGN, false>, lds, ctx->device, checked, true)) return rc;
+        if (int rc = allow_dynamic_lds((const void*)ntt32_rows_kernel<LOGN, false>, lds, ctx->device, checked)) return rc;
         hipLaunchKernelGGL((ntt32_rows_kernel<LOGN, false>), dim3(grid), dim3(G::T), lds, s, ctx->limbs32, limbs, data, ctx->tw32_fwd, rows);
     }
     HE_HIP(hipGetLastError());
@@ -698,9 +701,9 @@ int launch_ntt32(he_ctx* ctx, u32 limbs, u32* data, u32 rows, bool inverse, hipS
 template <int LOGN>
 static int launch_rescale32_t(he_ctx* ctx, u32 limbs, const Drop32Row& row, const u32* in, u32* out, u32 n, hipStream_t s) {
     using G = Geo<LOGN>;
-    const size_t lds = (size_t)G::N * sizeof(u32);
+    const size_t lds = lds_row_bytes<LOGN, u32>();
     static std::atomic<uint32_t> checked{0};
-    if (int rc = allow_dynamic_lds((const void*)rescale32_kernel<LOGN>, lds, ctx->device, checked, true)) return rc;
+    if (int rc = allow_dynamic_lds((const void*)rescale32_kernel<LOGN>, lds, ctx->device, checked)) return rc;
     hipLaunchKernelGGL((rescale32_kernel<LOGN>), dim3(n * 2), dim3(G::T), lds, s, ctx->limbs32, row, limbs, in, out, ctx->tw32_fwd,
                        ctx->tw32_inv);
     HE_HIP(hipGetLastError());
