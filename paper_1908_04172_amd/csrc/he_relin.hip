@@ -24,7 +24,8 @@ namespace {
 // What bounds it: the digits, read once, and the two sums, written once.  The slot's 2 l key residues stay in registers
 // for the whole run of ciphertexts (read for every one of them they were as many bytes again as digits and sums
 // together, out of the caches), and the sums are MacAcc ones, of which P * d_k is one more term: four multiply-adds per
-// product and one reduction per sum.  256 ciphertexts, seven limbs and P, N = 2^14 (2.9 GB): 767 -> 574 us.
+// product and one reduction per sum.  256 ciphertexts, seven limbs and P, N = 2^14 (2.9 GB): 767 -> 574 us.  The digits are
+// read past the caches (the whole square of 200 ciphertexts, four limbs and P, N = 2^13: 408 -> 391 us; of 60 at 2^14 262 -> 249).
 // A run of one ciphertext has nothing to keep the key for, and holding it only costs wavefronts (186 registers at l = 15):
 // such launches read it term by term (eight ciphertexts at N = 2^13, l = 15: 52 -> 34 us; l = 10: 24 -> 20).
 struct SpecialPrimeResidues {
@@ -97,7 +98,7 @@ __global__ void __launch_bounds__(256) key_product_kernel(LimbTable lt, SpecialP
     for (u32 at = at0.first; at < at0.end; at++) {
         u64 d[l], c0 = 0, c1 = 0;
 #pragma unroll
-        for (u32 j = 0; j < l; j++) d[j] = digits[(((size_t)at * l + j) * L + limb) * N + k];
+        for (u32 j = 0; j < l; j++) d[j] = __builtin_nontemporal_load(&digits[(((size_t)at * l + j) * L + limb) * N + k]);
         if (limb < l) {
             c0 = ct[(((size_t)at * 2) * l + limb) * N + k];
             c1 = ct[(((size_t)at * 2 + 1) * l + limb) * N + k];
