@@ -710,6 +710,7 @@ int he_plan_create(he_ctx* ctx, uint32_t n_in, uint32_t n_out, uint32_t n_pt, co
         }
     }
     p->tiles_s = ts;
+    p->one_term_each = p->class_begin_s[1] == p->n_tiles_s && p->min_terms_s[0] == 1 && p->max_terms_s[0] == 1;
     p->wtab_elems = elems;
     if (upload(&p->tiles_s_dev, ts.data(), ts.size()) != HE_OK || upload(&p->tiles_p_dev, tp.data(), tp.size()) != HE_OK ||
         upload(&p->wbase_s_dev, p->wbase_s.data(), ts.size()) != HE_OK || upload(&p->owners_dev, owners.data(), owners.size()) != HE_OK ||
@@ -788,6 +789,8 @@ static int ct_pt_mac_entry(he_ctx* ctx, const he_plan* plan, uint32_t limbs, con
     hipStream_t s = (hipStream_t)stream;
     if (flags & HE_RESCALE) {
         u64* acc = (u64*)ws;
+        if (pt_kind == HE_PT_SCALAR && plan->one_term_each && ctx->log2N <= HE_MAX_LOG2N_IN_LDS)
+            return launch_rescale_scaled(ctx, plan, limbs, ct_in, pt, bias, ct_out, s);
         if ((rc = launch_mac(ctx, plan, limbs, ct_in, pt, pt_kind, bias, acc, wtab, table_bytes, MAC_FOR_RESCALE, s)) != HE_OK) return rc;
         return launch_rescale(ctx, limbs, acc, ct_out, plan->n_out, s);
     }

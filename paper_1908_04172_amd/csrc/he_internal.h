@@ -122,6 +122,7 @@ struct he_plan {
     u32 max_count_s[SCALAR_CLASSES];  // most outputs of any scalar tile of the class
     u32 max_terms;         // most terms of any tile
     u32 max_group_terms;   // ... of any tile with several outputs
+    bool one_term_each;    // every output is a group of its own with one term: output o takes term o
     bool short_sums() const { return max_group_terms <= BLOCK_TERMS; }  // (tables of one block per group)
     Tile* tiles_s_dev;
     Tile* tiles_p_dev;
@@ -197,6 +198,7 @@ u64 mac_digits_blocks(const he_ctx* ctx, const he_plan* plan, u32 limbs);
 u32 mac_digits_groups_per_workgroup(const he_ctx* ctx, const he_plan* plan, u32 limbs, u32 cls, bool packed);
 int launch_ntt(he_ctx* ctx, u32 limbs, u64* data, u32 n_polys, bool inverse, hipStream_t s, const u64* src = nullptr);
 int launch_rescale(he_ctx* ctx, u32 limbs, const u64* in, u64* out, u32 n, hipStream_t s);
+int launch_rescale_scaled(he_ctx* ctx, const he_plan* plan, u32 limbs, const u64* ct_in, const u64* pt, const u64* bias, u64* out, hipStream_t s);
 int launch_rate(he_ctx* ctx, int kind, u32 limb, u32 iters, double* ops_per_s);
 int launch_rescale_drop(he_ctx* ctx, u32 limbs, u32 drop_id, const u64* in, u64* out, u32 n, hipStream_t s);
 int launch_ntt_spread(he_ctx* ctx, u32 limbs, const u64* src, u64* out, u32 n_digit_rows, u32 digits, hipStream_t s);

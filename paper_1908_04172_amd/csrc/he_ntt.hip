@@ -478,10 +478,30 @@ constexpr u32 rescale_kept() {
     return (LDS_BYTES / workgroups - lds_row_bytes<LOGN, u64>()) / (Geo<LOGN>::T * (u32)sizeof(u64));
 }
 
-template <int LOGN>
-__global__ void __launch_bounds__(Geo<LOGN>::T, RESCALE_WAVES)
-rescale_kernel(LimbTable lt, DropRow drop, u32 limbs, u64 shares, u32 stream, const u64* in, u64* out, const u64* tw_fwd,
-               const u64* tw_inv, const double* tw_fwd_f, const double* tw_inv_f) {
+// SCALED: the polynomials are not accumulators that a MAC has left but, output by output, one input ciphertext times one
+// scalar plaintext plus a bias (a layer whose sums have one term each: an elementwise scaling), multiplied as they are read.
+// A MAC launch of its own would write and read every row once more and take one launch and the table of plaintexts with it:
+// 845 ciphertexts of N = 2^13 at L = 3 335 -> 213 us for the layer call, 500 of 2^12 at L = 2 62 -> 33, 500 of 2^14 at L = 8 1075 -> 681.
+struct ScaledInput {
+    const u32 *term_ct, *term_pt;  // per output: which input, which plaintext
+    const u64 *pt, *bias;          // [..][limbs]; bias may be null
+};
+// the factor and the bias of one limb
+struct ScaledLimb {
+    u64 w, w_shoup, b;
+    // The companion w * floor(2^128 / q) / 2^64 is short of floor(w * 2^64 / q) by at most 2, so that the product with a
+    // residue ends below 3q.
+    __device__ __forceinline__ ScaledLimb(u64 factor, u64 bias, const LimbConst& c)
+        : w(factor), w_shoup(factor * c.ratio_hi + mul_hi64(factor, c.ratio_lo)), b(bias) {}
+    __device__ __forceinline__ u64 apply(u64 x, const LimbConst& c) const {
+        return add_mod(canon4(shoup_mul_lazy(x, w, w_shoup, c.q), c.q, c.two_q), b, c.q);
+    }
+};
+
+template <int LOGN, bool SCALED>
+__device__ __forceinline__ void rescale_polynomial(const LimbTable& lt, const DropRow& drop, u32 limbs, u64 shares, u32 stream, const u64* in,
+                                                   u64* out, const u64* tw_fwd, const u64* tw_inv, const double* tw_fwd_f,
+                                                   const double* tw_inv_f, const ScaledInput& si) {
     using G = Geo<LOGN>;
     extern __shared__ __align__(16) u64 lds[];
     // A polynomial is handled by several workgroups (gridDim.y) when there are too few polynomials to fill the chip: each
@@ -494,8 +514,13 @@ rescale_kernel(LimbTable lt, DropRow drop, u32 limbs, u64 shares, u32 stream, co
     const size_t poly = blockIdx.x;  // ct*2 + component
     const u32 last = limbs - 1;
     const u32 first = (u32)(shares >> (4 * blockIdx.y)) & 15, end = (u32)(shares >> (4 * blockIdx.y + 4)) & 15;
-    const u64* src = in + poly * limbs * G::N;
+    const u32 o = (u32)(poly >> 1);
+    const u64* src = in + (SCALED ? (size_t)si.term_ct[o] * 2 + (poly & 1) : poly) * limbs * G::N;
     u64* dst = out + poly * (limbs - 1) * G::N;
+    auto scaled_limb = [&](u32 i) {
+        const bool has_bias = si.bias != nullptr && (poly & 1) == 0;
+        return ScaledLimb(si.pt[(size_t)si.term_pt[o] * limbs + i], has_bias ? si.bias[(size_t)o * limbs + i] : 0, lt.c[i]);
+    };
     // t is parked in the output row of this workgroup's last limb: every thread re-reads only what it
     // wrote itself, and that row is overwritten only in the last iteration, after all its threads have
     // taken their t back (they use it before the first regrouping barrier of that iteration).
@@ -509,6 +534,11 @@ rescale_kernel(LimbTable lt, DropRow drop, u32 limbs, u64 shares, u32 stream, co
         const LimbConst& c = lt.c[last];
         const u64* row = src + (size_t)last * G::N;
         load_row<LOGN, G::LOAD>(a, row, tid, stream & STREAM_LOADS);
+        if constexpr (SCALED) {
+            const ScaledLimb f = scaled_limb(last);
+#pragma unroll
+            for (u32 e = 0; e < 16; e++) a[e] = f.apply(a[e], c);
+        }
         reorder<LOGN, G::LOAD, G::LAST>(a, lds, tid);
         ntt_inverse_any<LOGN, true>(a, tw_inv + (size_t)last * G::N * 2, tw_inv_f + (size_t)last * G::N, lds, tid, c);
         const u64 half = c.q >> 1;
@@ -581,9 +611,17 @@ rescale_kernel(LimbTable lt, DropRow drop, u32 limbs, u64 shares, u32 stream, co
             // reduced to q/2, x - 2q - y is below 2.51q in magnitude and its product with p^-1 within 0.98q of zero: 17
             // instructions per value, where the integer form (mantissa differences, an exact Shoup product) took 31, a
             // quarter of such a limb's iteration.
+            // (SCALED: x times the factor plus the bias is below 1.19q, the difference below 1.7q and its product within 0.82q.)
             const double x_offset = 4503599627370496.0 + 2.0 * q_f;
+            double factor = 0, bias = 0;
+            if constexpr (SCALED) {
+                const ScaledLimb f = scaled_limb(i);
+                factor = fp_centred(f.w, c.q);
+                bias = fp_centred(f.b, c.q);
+            }
             finish([&](u64 x, u64 y) {
-                const double x_f = __builtin_bit_cast(double, x | 0x4330000000000000ull) - x_offset;
+                const double x_f = SCALED ? fp_mulmod(factor, fp_from_u52(x), q_f, c.q_inv_f) + bias
+                                          : __builtin_bit_cast(double, x | 0x4330000000000000ull) - x_offset;
                 const double diff = x_f - fp_reduce(__builtin_bit_cast(double, y), q_f, c.q_inv_f);
                 return fp_to_canonical(fp_mulmod(p_inv, diff, q_f, c.q_inv_f), q_f);
             });
@@ -606,9 +644,28 @@ rescale_kernel(LimbTable lt, DropRow drop, u32 limbs, u64 shares, u32 stream, co
                 for (u32 e = 0; e < 16; e++) a[e] = sub_if_ge(a[e], c.neg_two_q);
                 cap = c.two_q;
             }
-            finish([&](u64 x, u64 y) { return shoup_mul(x + cap - y, d.p_inv, d.p_inv_shoup, c.q); });
+            if constexpr (SCALED) {
+                const ScaledLimb f = scaled_limb(i);
+                finish([&](u64 x, u64 y) { return shoup_mul(f.apply(x, c) + cap - y, d.p_inv, d.p_inv_shoup, c.q); });
+            } else {
+                finish([&](u64 x, u64 y) { return shoup_mul(x + cap - y, d.p_inv, d.p_inv_shoup, c.q); });
+            }
         }
     }
+}
+
+template <int LOGN>
+__global__ void __launch_bounds__(Geo<LOGN>::T, RESCALE_WAVES)
+rescale_kernel(LimbTable lt, DropRow drop, u32 limbs, u64 shares, u32 stream, const u64* in, u64* out, const u64* tw_fwd, const u64* tw_inv,
+               const double* tw_fwd_f, const double* tw_inv_f) {
+    rescale_polynomial<LOGN, false>(lt, drop, limbs, shares, stream, in, out, tw_fwd, tw_inv, tw_fwd_f, tw_inv_f, ScaledInput{});
+}
+
+template <int LOGN>
+__global__ void __launch_bounds__(Geo<LOGN>::T, RESCALE_WAVES)
+scaled_rescale_kernel(LimbTable lt, DropRow drop, u32 limbs, u64 shares, u32 stream, const u64* in, u64* out, const u64* tw_fwd,
+                      const u64* tw_inv, const double* tw_fwd_f, const double* tw_inv_f, ScaledInput si) {
+    rescale_polynomial<LOGN, true>(lt, drop, limbs, shares, stream, in, out, tw_fwd, tw_inv, tw_fwd_f, tw_inv_f, si);
 }
 
 // ---- ring degree 2^15: a row (256 KiB) does not fit the LDS.  A transform of 2N = 2^15 points is its first stage
@@ -823,8 +880,8 @@ int launch_ntt_square_t(he_ctx* ctx, u32 limbs, const u64* ct, u64* d2, u64* dig
 // rescale; the special prime for the division that ends a key switch).  The kernel addresses limbs by
 // position: it gets a table with drop_id's constants at the last position and the inverse twiddles
 // shifted so that the last position finds drop_id's.
-template <int LOGN>
-int launch_rescale_t(he_ctx* ctx, u32 limbs, u32 drop_id, const u64* in, u64* out, u32 n, hipStream_t s) {
+template <int LOGN, bool SCALED>
+int launch_rescale_t(he_ctx* ctx, u32 limbs, u32 drop_id, const u64* in, u64* out, u32 n, const ScaledInput& si, hipStream_t s) {
     using G = Geo<LOGN>;
     LimbTable lt = ctx->limbs;
     lt.c[limbs - 1] = ctx->limbs.c[drop_id];
@@ -832,7 +889,10 @@ int launch_rescale_t(he_ctx* ctx, u32 limbs, u32 drop_id, const u64* in, u64* ou
     const double* tw_inv_f = ctx->tw_inv_f + (size_t)(drop_id - (limbs - 1)) * G::N;
     const size_t lds = lds_row_bytes<LOGN, u64>() + rescale_kept<LOGN>() * G::T * sizeof(u64);
     static std::atomic<uint32_t> lds_allowed{0};
-    if (int rc = allow_dynamic_lds((const void*)rescale_kernel<LOGN>, lds, ctx->device, lds_allowed)) return rc;
+    const void* kernel;
+    if constexpr (SCALED) kernel = (const void*)scaled_rescale_kernel<LOGN>;
+    else kernel = (const void*)rescale_kernel<LOGN>;
+    if (int rc = allow_dynamic_lds(kernel, lds, ctx->device, lds_allowed)) return rc;
     DropRow row;
     for (u32 i = 0; i < HE_MAX_LIMBS; i++) row.d[i] = ctx->drop[drop_id][i];
     // with fewer polynomials than workgroups the chip holds at once, split each over several workgroups
@@ -846,8 +906,13 @@ int launch_rescale_t(he_ctx* ctx, u32 limbs, u32 drop_id, const u64* in, u64* ou
     // them (300 at L = 4, 157 MB: 93 us, 101 past the caches).  Results of calls beyond the L2s (8 x 4 MiB) are written past them.
     const size_t row_bytes = (size_t)G::N * sizeof(u64), in_bytes = 2 * n * limbs * row_bytes, out_bytes = 2 * n * (limbs - 1) * row_bytes;
     const u32 stream = (in_bytes > MEMORY_CACHE_BYTES ? STREAM_LOADS : 0) | (in_bytes + out_bytes > L2_BYTES ? STREAM_STORES : 0);
-    hipLaunchKernelGGL((rescale_kernel<LOGN>), dim3(2 * n, parts), dim3(G::T), lds, s, lt, row, limbs, shares, stream, in, out, ctx->tw_fwd, tw_inv,
-                       ctx->tw_fwd_f, tw_inv_f);
+    const dim3 grid(2 * n, parts), block(G::T);
+    if constexpr (SCALED)
+        hipLaunchKernelGGL((scaled_rescale_kernel<LOGN>), grid, block, lds, s, lt, row, limbs, shares, stream, in, out, ctx->tw_fwd, tw_inv,
+                           ctx->tw_fwd_f, tw_inv_f, si);
+    else
+        hipLaunchKernelGGL((rescale_kernel<LOGN>), grid, block, lds, s, lt, row, limbs, shares, stream, in, out, ctx->tw_fwd, tw_inv, ctx->tw_fwd_f,
+                           tw_inv_f);
     HE_HIP(hipGetLastError());
     return HE_OK;
 }
@@ -917,15 +982,30 @@ int launch_rescale(he_ctx* ctx, u32 limbs, const u64* in, u64* out, u32 n, hipSt
 int launch_rescale_drop(he_ctx* ctx, u32 limbs, u32 drop_id, const u64* in, u64* out, u32 n, hipStream_t s) {
     if (n == 0) return HE_OK;
     if (n > 0x3FFFFFFFu) return HE_ERR_RANGE;
+    const ScaledInput none = {};
     switch (ctx->log2N) {
-        case 10: return launch_rescale_t<10>(ctx, limbs, drop_id, in, out, n, s);
-        case 11: return launch_rescale_t<11>(ctx, limbs, drop_id, in, out, n, s);
-        case 12: return launch_rescale_t<12>(ctx, limbs, drop_id, in, out, n, s);
-        case 13: return launch_rescale_t<13>(ctx, limbs, drop_id, in, out, n, s);
-        case 14: return launch_rescale_t<14>(ctx, limbs, drop_id, in, out, n, s);
+        case 10: return launch_rescale_t<10, false>(ctx, limbs, drop_id, in, out, n, none, s);
+        case 11: return launch_rescale_t<11, false>(ctx, limbs, drop_id, in, out, n, none, s);
+        case 12: return launch_rescale_t<12, false>(ctx, limbs, drop_id, in, out, n, none, s);
+        case 13: return launch_rescale_t<13, false>(ctx, limbs, drop_id, in, out, n, none, s);
+        case 14: return launch_rescale_t<14, false>(ctx, limbs, drop_id, in, out, n, none, s);
         case 15:
             if ((u64)n * 2 * (limbs - 1) > 0x3FFFFFFFull) return HE_ERR_RANGE;
             return launch_rescale_split(ctx, limbs, drop_id, in, out, n, s);
+    }
+    return HE_ERR_ARG;
+}
+
+// the layer whose sums have one term each (he_plan::one_term_each), up to the largest ring degree whose rows fit the LDS
+int launch_rescale_scaled(he_ctx* ctx, const he_plan* plan, u32 limbs, const u64* ct_in, const u64* pt, const u64* bias, u64* out, hipStream_t s) {
+    const u32 n = plan->n_out;
+    const ScaledInput si{plan->term_ct_dev, plan->term_pt_dev, pt, bias};
+    switch (ctx->log2N) {
+        case 10: return launch_rescale_t<10, true>(ctx, limbs, limbs - 1, ct_in, out, n, si, s);
+        case 11: return launch_rescale_t<11, true>(ctx, limbs, limbs - 1, ct_in, out, n, si, s);
+        case 12: return launch_rescale_t<12, true>(ctx, limbs, limbs - 1, ct_in, out, n, si, s);
+        case 13: return launch_rescale_t<13, true>(ctx, limbs, limbs - 1, ct_in, out, n, si, s);
+        case 14: return launch_rescale_t<14, true>(ctx, limbs, limbs - 1, ct_in, out, n, si, s);
     }
     return HE_ERR_ARG;
 }
