@@ -13,6 +13,9 @@
 // built on one-row-per-workgroup kernels, stop here (HE_ERR_ARG above).
 #define HE_MAX_LOG2N_IN_LDS 14
 
+// What all eight L2s and the memory-side cache hold.
+constexpr size_t L2_BYTES = 32u << 20, MEMORY_CACHE_BYTES = 256u << 20;
+
 // Per-limb constants handed to kernels by value (16 x 168 B; with the other arguments of the largest kernel well
 // below the 4 KiB that kernel arguments may take).
 struct LimbTable {
@@ -171,6 +174,7 @@ inline int allow_dynamic_lds(const void* kernel, size_t bytes, int device, std::
 // `accumulate` argument of the MAC launchers and kernels: bits
 enum : u32 {
     MAC_ACCUMULATE = 1,   // add the canonical residues that the output holds (HE_ACCUMULATE)
+    MAC_STREAM = 4,       // the output is not to be kept in the caches (set by the launchers)
     MAC_FOR_RESCALE = 2   // the output is the accumulator tensor of a fused layer, read next by the rescale kernel: the
                           // kept limbs of scalar-plaintext sums may be left unreduced (LimbConst::mac_lazy)
 };

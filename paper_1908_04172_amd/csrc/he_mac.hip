@@ -136,10 +136,13 @@ mac_scalar_single_kernel(LimbTable lt, u32 limbs, u32 N, const Tile* tiles, u32 
             v.x = add_mod(v.x, old.x, c.q);
             v.y = add_mod(v.y, old.y, c.q);
         }
-        // (accumulators of a fused layer are read next, other results are written past the caches: 845 ciphertexts of
-        // N = 2^13 at L = 3 142 -> 139 us, 100 19.5 -> 18.0; with the rescale after it 316 -> 329)
-        if (accumulate & MAC_FOR_RESCALE) dst[s * MAC_THREADS + threadIdx.x] = v;
-        else __builtin_nontemporal_store(v, &dst[s * MAC_THREADS + threadIdx.x]);
+        if (accumulate & MAC_STREAM) {
+            asm volatile("; streamed store" ::: "memory");
+            __builtin_nontemporal_store(v, &dst[s * MAC_THREADS + threadIdx.x]);
+            asm volatile("; end" ::: "memory");
+        } else {
+            dst[s * MAC_THREADS + threadIdx.x] = v;
+        }
     }
 }
 
@@ -256,6 +259,9 @@ static int launch_scalar_single(he_ctx* ctx, const he_plan* plan, const ScalarSl
                        plan->owners_dev + sl.table_begin, n_tables, limbs, plan->off_dev, plan->term_pt_dev, pt, wtab, sl.tab_words, sl.tab_skip,
                        sl.t_begin, sl.t_end);
     HE_HIP(hipGetLastError());
+    // (accumulators of a fused layer are read next, other results beyond the L2s are written past the caches: 845 ciphertexts
+    // of N = 2^13 at L = 3 142 -> 139 us; with the rescale after it 316 -> 329)
+    if (!(accumulate & MAC_FOR_RESCALE) && (u64)plan->n_out * 2 * limbs * ctx->N * sizeof(u64) > L2_BYTES) accumulate |= MAC_STREAM;
     const u32 per_thread = ctx->N >= 2048 ? 4 : 2;
     const u64 blocks = (u64)count * limbs * 2 * (ctx->N / (MAC_THREADS * 2 * per_thread));
     auto launch = [&](auto kernel) {

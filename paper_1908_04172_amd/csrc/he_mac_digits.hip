@@ -207,7 +207,7 @@ __device__ __forceinline__ void store_group(const Sums<V, OT>& sums, const MacAr
     asm volatile("" : "+v"(half));  // what follows is derived here, not kept in registers through the loop over terms
     V* dst = w.dst + (size_t)out0 * out_stride + half * (LANE_OUTPUTS * out_stride);
     const u32 lazy = D == 8 && (a.mode & MAC_FOR_RESCALE) && w.limb + 1 < a.limbs ? c.lazy : 0;
-    const bool accumulate = a.mode & MAC_ACCUMULATE;
+    const bool accumulate = a.mode & MAC_ACCUMULATE, stream = a.mode & MAC_STREAM;
     // The bias residues come in with scalar loads, those of the next four outputs while four are reduced.  (Without a
     // bias the loads read the group's descriptor and are masked.)
     const bool has_bias = a.bias != nullptr && w.comp == 0;
@@ -257,9 +257,13 @@ __device__ __forceinline__ void store_group(const Sums<V, OT>& sums, const MacAr
                     row_piece all;
 #pragma unroll
                     for (int k = 0; k < CT; k++) all[k] = v[k];
-                    // (not to be kept in the caches: the stores are most of what a short sum moves, and allocating them cost
-                    // groups of 16 outputs and one term, N = 2^13, L = 4, 800 -> 576 us, the convolution 28x28 297 -> 273)
-                    __builtin_nontemporal_store(all, reinterpret_cast<row_piece*>(at));
+                    if (stream) {
+                        asm volatile("; streamed store" ::: "memory");  // (left to itself the compiler makes one ordinary store of both)
+                        __builtin_nontemporal_store(all, reinterpret_cast<row_piece*>(at));
+                        asm volatile("; end" ::: "memory");
+                    } else {
+                        *reinterpret_cast<row_piece*>(at) = all;
+                    }
                 }
                 __builtin_amdgcn_sched_barrier(0);  // one output at a time: its temporaries are few
             }
@@ -519,6 +523,11 @@ int launch_mac_digits_t(he_ctx* ctx, const he_plan* plan, const ScalarSlice& sl,
                            plan->tiles_s_dev, plan->wbase_s_dev, plan->owners_dev + table0 + t, limbs, plan->off_dev, plan->term_pt_dev, pt, wtab,
                            sl.tab_words, sl.tab_skip, sl.t_begin, sl.t_end, short_sums ? BLOCK_TERMS : CHUNK_TERMS);
     }
+    // Outputs beyond the L2s are written past the caches: the stores are most of what a short sum moves, and allocating their
+    // lines cost groups of 16 outputs and one term, N = 2^13, L = 4, 800 us against 576, the convolution 28x28 297 against
+    // 273.  (What fits the L2s is read from there by the call that adds to it or rescales it: 200 + 113 -> 37 in two calls,
+    // N = 2^13, L = 3, 14 MB, 116 us, 120 past the caches.)
+    if ((u64)plan->n_out * 2 * limbs * ctx->N * sizeof(V) > L2_BYTES) mode |= MAC_STREAM;
     const MacArgs<V> a{plan->digit_tiles_dev, plan->lists_dev, wtab, sl.tab_words, sl.tab_skip, ct_in, bias, out, limbs, ctx->N, sl.t_begin,
                        sl.t_end, mode};
     if constexpr (sizeof(V) == sizeof(u64)) {

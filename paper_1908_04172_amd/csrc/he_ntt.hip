@@ -296,7 +296,6 @@ struct RowMap {
 };
 constexpr u32 NO_LIMB = 0xFFFFFFFFu;
 enum : u32 { STREAM_LOADS = 1, STREAM_STORES = 2 };
-constexpr size_t L2_BYTES = 32u << 20, MEMORY_CACHE_BYTES = 256u << 20;  // all eight L2s, the memory-side cache
 template <int LOGN, bool INVERSE, int KIND = ROWS_PLAIN>
 __global__ void __launch_bounds__(Geo<LOGN>::T, 4)
 ntt_rows_kernel(LimbTable lt, u32 limbs, u64* data, const u64* tw_all, const double* tw_f_all, u32 rows,
