@@ -402,22 +402,31 @@ constexpr u32 lds_pieces(int ot) { return (SHORT ? 1 : RESIDENT_CHUNKS * Form<V>
 
 struct MacClass {
     u32 first, end, per_wg, blocks;  // the class's groups among the plan's tiles, groups per workgroup and workgroups
+    u32 runs;                        // ... workgroups per slice of a row
 };
 
+// Where a workgroup is: slice of the row fastest, then run of groups, then (component, limb): workgroups go to the eight XCDs
+// round-robin and the number of slices is a multiple of eight from N = 2^11 on, so the same slice of neighbouring groups (which
+// read the same or overlapping inputs) runs on the same XCD, close in time, and hits in its L2.
+struct MacPlace {
+    u32 part, run, row;  // row: (limb, component)
+};
+template <typename V>
+__device__ __forceinline__ MacPlace mac_place(u32 b, const MacArgs<V>& a, u32 runs, u32 first_row = 0) {
+    const u32 parts = a.N / Form<V>::SLOTS;
+    const u32 rest = b / parts;
+    return MacPlace{b % parts, rest % runs, first_row + rest / runs};
+}
+
 template <typename V, int OT, bool SHORT>
-__device__ __forceinline__ void mac_class(u32 b, const MacArgs<V>& a, const DigitTable& dt, const MacClass& m, v4i* lds) {
+__device__ __forceinline__ void mac_class(const MacPlace& at_wg, const MacArgs<V>& a, const DigitTable& dt, const MacClass& m, v4i* lds) {
     using F = Form<V>;
-    const u32 parts = a.N / F::SLOTS;
-    const u32 runs = (m.end - m.first + m.per_wg - 1) / m.per_wg;
-    // slice of the row fastest, then run of groups, then (component, limb): workgroups go to the eight XCDs round-robin
-    // and the number of slices is even, so the same slice of neighbouring groups (which read the same or overlapping
-    // inputs) runs on the same XCD, close in time, and hits in its L2
-    const u32 part = b % parts; b /= parts;
-    const u32 tile_first = m.first + (b % runs) * m.per_wg; b /= runs;
+    const u32 part = at_wg.part;
+    const u32 tile_first = m.first + at_wg.run * m.per_wg;
     const u32 tile_end = min(tile_first + m.per_wg, m.end);
     Slice<V> w;
-    w.comp = b & 1;
-    w.limb = b >> 1;
+    w.comp = at_wg.row & 1;
+    w.limb = at_wg.row >> 1;
     w.lane = threadIdx.x % 64;
     w.half = w.lane / 32;
     w.ct_stride = 2 * a.limbs * a.N * sizeof(V);
@@ -464,18 +473,34 @@ template <typename V, int OT, bool SHORT>
 __global__ void __launch_bounds__(THREADS, OT * Form<V>::CT == 8 ? 2 : OT * Form<V>::CT == 4 ? 3 : 4)
 mac_digits_kernel(DigitTable dt, MacArgs<V> a, MacClass m) {
     __shared__ v4i lds[lds_pieces<V, SHORT>(OT)];
-    mac_class<V, OT, SHORT>(blockIdx.x, a, dt, m, lds);
+    const MacPlace at = mac_place(blockIdx.x, a, m.runs);
+    mac_class<V, OT, SHORT>(at, a, dt, m, lds);
 }
 
-// A plan with groups of several classes in one launch: the first workgroups take the largest class, and the smaller
-// ones (often the ragged end of a layer) fill in while it drains.
+// A plan with groups of several classes in one launch, all groups of one slice next to one another: they read the same inputs.
+// (With the workgroups of the largest class first and the others behind them the inputs of a dense layer 96 -> 24 at 2^15, L = 8,
+// came from the memory twice: 186 us, now 150; 845 -> 100 at 2^13, L = 8, 800 and 756.)  In the last `tail` rows, about as
+// many workgroups as the chip holds, the largest class does come first and the smaller ones fill in while it drains.
 template <typename V, bool SHORT>
-__global__ void __launch_bounds__(THREADS, 2) mac_digits_mixed_kernel(DigitTable dt, MacArgs<V> a, MacClass c16, MacClass c8, MacClass c4) {
+__global__ void __launch_bounds__(THREADS, 2) mac_digits_mixed_kernel(DigitTable dt, MacArgs<V> a, MacClass c16, MacClass c8, MacClass c4, u32 tail) {
     constexpr int OT16 = Form<V>::tiles(16), OT8 = Form<V>::tiles(8), OT4 = Form<V>::tiles(4);
     __shared__ v4i lds[lds_pieces<V, SHORT>(OT16)];
-    if (blockIdx.x < c16.blocks) mac_class<V, OT16, SHORT>(blockIdx.x, a, dt, c16, lds);
-    else if (blockIdx.x < c16.blocks + c8.blocks) mac_class<V, OT8, SHORT>(blockIdx.x - c16.blocks, a, dt, c8, lds);
-    else mac_class<V, OT4, SHORT>(blockIdx.x - c16.blocks - c8.blocks, a, dt, c4, lds);
+    const u32 parts = a.N / Form<V>::SLOTS, lead = a.limbs * 2 - tail, runs = c16.runs + c8.runs + c4.runs;
+    u32 b = blockIdx.x, cls;
+    MacPlace at;
+    if (b < lead * parts * runs) {
+        at = mac_place(b, a, runs);
+        cls = at.run < c16.runs ? 0 : at.run < c16.runs + c8.runs ? 1 : 2;
+        at.run -= cls == 0 ? 0 : cls == 1 ? c16.runs : c16.runs + c8.runs;
+    } else {
+        b -= lead * parts * runs;
+        const u32 n16 = tail * parts * c16.runs, n8 = tail * parts * c8.runs;
+        cls = b < n16 ? 0 : b < n16 + n8 ? 1 : 2;
+        at = mac_place(b - (cls == 0 ? 0 : cls == 1 ? n16 : n16 + n8), a, cls == 0 ? c16.runs : cls == 1 ? c8.runs : c4.runs, lead);
+    }
+    if (cls == 0) mac_class<V, OT16, SHORT>(at, a, dt, c16, lds);
+    else if (cls == 1) mac_class<V, OT8, SHORT>(at, a, dt, c8, lds);
+    else mac_class<V, OT4, SHORT>(at, a, dt, c4, lds);
 }
 
 // Groups per workgroup and workgroups of one class over the tiles [first, end).  Several groups per workgroup pay the
@@ -486,8 +511,8 @@ MacClass mac_class_of(const he_ctx* ctx, const he_plan* plan, u32 limbs, u32 cls
     const u32 count = end - first;
     u32 per_wg = plan->min_terms_s[cls] > t_begin ? GROUPS_PER_WG : 1;  // (a stream has no group without terms in it)
     while (per_wg > 1 && (u64)((count + per_wg - 1) / per_wg) * per_run < MIN_WORKGROUPS) per_wg /= 2;
-    const u64 blocks = (u64)((count + per_wg - 1) / per_wg) * per_run;
-    return MacClass{first, end, per_wg, (u32)std::min<u64>(blocks, 0x7FFFFFFFull)};
+    const u32 runs = (count + per_wg - 1) / per_wg;
+    return MacClass{first, end, per_wg, (u32)std::min<u64>(runs * per_run, 0x7FFFFFFFull), runs};
 }
 
 template <typename V, bool SHORT>
@@ -497,7 +522,11 @@ void launch_classes(he_ctx* ctx, const MacArgs<V>& a, const MacClass (&c)[SCALAR
     if (c[3].blocks == blocks) hipLaunchKernelGGL((mac_digits_kernel<V, OT16, SHORT>), grid, block, 0, s, ctx->digits, a, c[3]);
     else if (c[2].blocks == blocks) hipLaunchKernelGGL((mac_digits_kernel<V, OT8, SHORT>), grid, block, 0, s, ctx->digits, a, c[2]);
     else if (c[1].blocks == blocks) hipLaunchKernelGGL((mac_digits_kernel<V, OT4, SHORT>), grid, block, 0, s, ctx->digits, a, c[1]);
-    else hipLaunchKernelGGL((mac_digits_mixed_kernel<V, SHORT>), grid, block, 0, s, ctx->digits, a, c[3], c[2], c[1]);
+    else {
+        const u32 rows = a.limbs * 2;
+        const u32 tail = (u32)std::min<u64>(rows, (2 * 256 * (u64)rows + blocks - 1) / blocks);  // two workgroups per compute unit
+        hipLaunchKernelGGL((mac_digits_mixed_kernel<V, SHORT>), grid, block, 0, s, ctx->digits, a, c[3], c[2], c[1], tail);
+    }
 }
 
 template <typename V>
