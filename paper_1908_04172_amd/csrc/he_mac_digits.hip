@@ -37,7 +37,6 @@ typedef int v16i __attribute__((ext_vector_type(16)));
 constexpr u32 THREADS = 256, WAVES = THREADS / 64;
 constexpr u32 CHUNK_TERMS = LIST_CHUNK;                     // terms that are in flight together (a chunk)
 constexpr u32 RESIDENT_CHUNKS = 4;                          // tables of up to so many chunks stay in the LDS as a whole
-constexpr u32 TILE_WORDS = 128;                             // 64-bit words of a table tile, one operand of 64 lanes x 16 bytes
 constexpr u32 GROUPS_PER_WG = 16;                           // groups a workgroup runs through, at most
 constexpr u64 MIN_WORKGROUPS = 2048;                        // ... while the launch keeps at least this many workgroups
 static_assert(DIGIT_MAX_TERMS % CHUNK_TERMS == 0, "the parts of a long sum are whole chunks");
@@ -73,38 +72,37 @@ __device__ __forceinline__ void lds_barrier() { asm volatile("s_waitcnt lgkmcnt(
 // the block: positions h * LANE_TERMS .. of the order in which the term lists are stored (he_plan::lists_dev).  Row r
 // belongs to half (r >> 2) & 1 of the tile's outputs and there to sum (r & 3) + 4 * (r >> 3) of the 16 of that half's lanes.
 // Terms beyond the group's (up to a multiple of `pad`: whole chunks, or one block for a plan of short sums, see SHORT) and
-// outputs beyond its count are zeros.  One thread: one (term, output, limb).
+// outputs beyond its count are zeros.  One thread: one (term, output) of limb blockIdx.z and table blockIdx.y; the lanes that fill
+// a tile between them are neighbours, the terms of one 16-byte operand next to one another.  (With the limbs fastest every
+// store went to a line of its own: layer 500 -> 256 at 2^12, L = 8 619 -> 601 us, packed 1024 -> 256 101 -> 97.)
 template <typename V>
 __global__ void __launch_bounds__(256) gather_digits_kernel(DigitTable dt, const Tile* tiles, const u64* wbase, const u32* owners, u32 limbs,
                                                             const u32* off, const u32* term_pt, const u64* pt, u64* tab, u64 tab_words,
                                                             u64 tab_skip, u32 t_begin, u32 t_end, u32 pad) {
     using F = Form<V>;
-    const u32 tile_i = uniform_load(owners + blockIdx.y);
+    constexpr u32 LANE_TERMS = F::LANE_TERMS, TILE_OUTPUTS = F::TILE_OUTPUTS;
+    const u32 tile_i = uniform_load(owners + blockIdx.y), limb = blockIdx.z;
     const Tile tile = tiles[tile_i];
     const u32 first = min(t_begin, tile.n_terms), K = min(t_end, tile.n_terms) - first;
-    const u32 ot = F::tiles(tile.count), G = F::TILE_OUTPUTS * ot;
-    const u32 Kp = (K + pad - 1) / pad * pad;
-    const u64 total = (u64)Kp * G * limbs;
-    u64* dst = tab + (wbase[tile_i] - tab_skip);
-    for (u64 i = (u64)blockIdx.x * 256 + threadIdx.x; i < total; i += (u64)gridDim.x * 256) {
-        const u32 limb = (u32)(i % limbs);
-        const u64 rest = i / limbs;
-        const u32 t = (u32)(rest / G), o = (u32)(rest % G);  // (limb fastest, then output: neighbouring plaintexts)
-        const DigitConst& c = dt.c[limb];
+    const u32 ot = F::tiles(tile.count);  // 1, 2 or 4
+    const u32 total = (K + pad - 1) / pad * pad * ot * TILE_OUTPUTS;
+    const DigitConst& c = dt.c[limb];
+    V* dst = reinterpret_cast<V*>(tab + (wbase[tile_i] - tab_skip) + (u64)limb * tab_words);
+    for (u32 i = blockIdx.x * 256 + threadIdx.x; i < total; i += gridDim.x * 256) {
+        // which element of a lane's operand, which half, which of the tile's outputs, which tile of which block
+        const u32 j = i % LANE_TERMS, half = i / LANE_TERMS % 2, oo = i / (2 * LANE_TERMS) % TILE_OUTPUTS;
+        const u32 at_tile = i / (2 * LANE_TERMS * TILE_OUTPUTS);
+        const u32 o = at_tile % ot * TILE_OUTPUTS + oo, block = at_tile / ot;
+        // position `at` of the half's part of its chunk's list order [half][block of 4][2]
+        const u32 at = block % F::CHUNK_BLOCKS * LANE_TERMS + j;
+        const u32 t = block / F::CHUNK_BLOCKS * CHUNK_TERMS + (at >> 1) * 4 + half * 2 + (at & 1);
         V row[F::D] = {};
-        if (o < tile.count && t < K) {
-            plaintext_digits(pt[(size_t)term_pt[off[tile.out0 + o] + first + t] * limbs + limb], c, row);
-        }
-        // where the term is in its chunk's list order [half][block of 4][2], and so in the table
-        const u32 half = (t >> 1) & 1, at = ((t >> 2) & 3) * 2 + (t & 1);
-        const u32 block = t / CHUNK_TERMS * F::CHUNK_BLOCKS + at / F::LANE_TERMS;
-        const u32 oo = o % F::TILE_OUTPUTS;
-        V* out = reinterpret_cast<V*>(dst + (u64)limb * tab_words + ((u64)block * ot + o / F::TILE_OUTPUTS) * TILE_WORDS);
+        if (o < tile.count && t < K) plaintext_digits(pt[(size_t)term_pt[off[tile.out0 + o] + first + t] * limbs + limb], c, row);
+        V* out = dst + ((size_t)at_tile * 64 + 32 * half) * LANE_TERMS + j;
 #pragma unroll
         for (u32 m = 0; m < F::D; m++) {
             const u32 k = oo % F::LANE_OUTPUTS * F::D + m;  // which of the lane's 16 sums
-            const u32 r = (k & 3) + 8 * (k >> 2) + 4 * (oo / F::LANE_OUTPUTS);
-            out[(r + 32 * half) * F::LANE_TERMS + at % F::LANE_TERMS] = row[m];
+            out[((k & 3) + 8 * (k >> 2) + 4 * (oo / F::LANE_OUTPUTS)) * LANE_TERMS] = row[m];
         }
     }
 }
@@ -544,11 +542,11 @@ int launch_mac_digits_t(he_ctx* ctx, const he_plan* plan, const ScalarSlice& sl,
     const u32 table0 = plan->table_s[first];
     const bool short_sums = sizeof(V) == sizeof(u64) && plan->short_sums();  // (packed sums that short run on the vector ALU)
     // about one entry per thread, but no more workgroups than fill the chip a few times
-    const u64 entries = (u64)std::min(plan->max_terms, sl.t_end - sl.t_begin) * 16 * limbs;
+    const u64 entries = (u64)std::min(plan->max_terms, sl.t_end - sl.t_begin) * 16;
     const u32 n_tables = sl.table_end - table0;
-    const u32 per_table = (u32)std::max<u64>(1, std::min<u64>((entries + 255) / 256, std::max<u64>(1, 4096 / n_tables)));
+    const u32 per_table = (u32)std::max<u64>(1, std::min<u64>((entries + 255) / 256, std::max<u64>(1, 4096 / ((u64)n_tables * limbs))));
     for (u32 t = 0; t < n_tables; t += 32768) {  // (the grid's second dimension is limited to 65535)
-        hipLaunchKernelGGL(gather_digits_kernel<V>, dim3(per_table, std::min<u32>(n_tables - t, 32768)), dim3(256), 0, s, ctx->digits,
+        hipLaunchKernelGGL(gather_digits_kernel<V>, dim3(per_table, std::min<u32>(n_tables - t, 32768), limbs), dim3(256), 0, s, ctx->digits,
                            plan->tiles_s_dev, plan->wbase_s_dev, plan->owners_dev + table0 + t, limbs, plan->off_dev, plan->term_pt_dev, pt, wtab,
                            sl.tab_words, sl.tab_skip, sl.t_begin, sl.t_end, short_sums ? BLOCK_TERMS : CHUNK_TERMS);
     }
