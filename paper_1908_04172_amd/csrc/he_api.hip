@@ -710,6 +710,21 @@ int he_plan_create(he_ctx* ctx, uint32_t n_in, uint32_t n_out, uint32_t n_pt, co
         }
     }
     p->tiles_s = ts;
+    {
+        std::vector<u32> seen(n_in, ~0u);  // the last tile that read an input
+        for (u32 cls = 0; cls < SCALAR_CLASSES; ++cls) {
+            u64 terms = 0, shared = 0;
+            for (u32 i = p->class_begin_s[cls]; i < p->class_begin_s[cls + 1]; ++i) {
+                terms += ts[i].n_terms;
+                for (u32 t = 0; t < ts[i].n_terms; ++t) {
+                    u32& last = seen[term_ct[ts[i].term0 + t]];
+                    shared += last + 1 == i && i > p->class_begin_s[cls];
+                    last = i;
+                }
+            }
+            p->shared_inputs_s[cls] = shared * 3 >= terms && terms > 0;
+        }
+    }
     p->one_term_each = p->class_begin_s[1] == p->n_tiles_s && p->min_terms_s[0] == 1 && p->max_terms_s[0] == 1;
     p->wtab_elems = elems;
     if (upload(&p->tiles_s_dev, ts.data(), ts.size()) != HE_OK || upload(&p->tiles_p_dev, tp.data(), tp.size()) != HE_OK ||

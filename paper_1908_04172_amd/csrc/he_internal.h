@@ -123,6 +123,7 @@ struct he_plan {
     u32 min_terms_s[SCALAR_CLASSES];  // fewest terms of any scalar tile of the class (0 for an empty class)
     u32 max_terms_s[SCALAR_CLASSES];  // most terms of any scalar tile of the class
     u32 max_count_s[SCALAR_CLASSES];  // most outputs of any scalar tile of the class
+    bool shared_inputs_s[SCALAR_CLASSES];  // a tile of the class reads, on average, a third of its inputs together with the one before it
     u32 max_terms;         // most terms of any tile
     u32 max_group_terms;   // ... of any tile with several outputs
     bool one_term_each;    // every output is a group of its own with one term: output o takes term o

@@ -156,9 +156,9 @@ __device__ __forceinline__ void enter_group(Cursor& p, const MacArgs<V>& a, u32 
 
 // The chunk after this one; after the last one of the stream the cursor stays (its loads are repeated, never used).
 template <typename V>
-__device__ __forceinline__ void step(Cursor& p, const MacArgs<V>& a, u32 tile_end) {
+__device__ __forceinline__ void step(Cursor& p, const MacArgs<V>& a, u32 tile_end, u32 stride) {
     if (p.chunk + 1 < p.n_chunks) p.chunk = __builtin_amdgcn_readfirstlane(p.chunk + 1);
-    else if (p.tile + 1 < tile_end) enter_group(p, a, p.tile + 1);
+    else if (p.tile + stride < tile_end) enter_group(p, a, p.tile + stride);
 }
 
 // A wavefront's share of a group of outputs: OT x CT result tiles.  Column tile k holds slot k of the lanes' CT adjacent
@@ -288,7 +288,7 @@ __device__ __forceinline__ v4i operand(const u32x4 (&x)[4], int k) {
     return v4i{(int)balanced_digits32(x[0][k]), (int)balanced_digits32(x[1][k]), (int)balanced_digits32(x[2][k]), (int)balanced_digits32(x[3][k])};
 }
 
-// Groups tile_first .. tile_end - 1 as one stream of chunks (16 terms each, the last of a group padded with zero
+// Every `stride`-th of the groups tile_first .. tile_end - 1 as one stream of chunks (16 terms each, the last of a group padded with zero
 // weights).  A wavefront multiplies the inputs it requested a chunk ago, requests those of the next chunk, also across
 // the end of a group, and the term list of the chunk after that; all of it is straight-line code, so that a wait is
 // for the loads it needs and no others.
@@ -299,7 +299,7 @@ __device__ __forceinline__ v4i operand(const u32x4 (&x)[4], int k) {
 // 16 outputs and one term with plaintexts of their own 1000 -> 785 us, 935 on the vector ALU; of two outputs that share their
 // plaintexts 197 -> 135.)
 template <typename V, int OT, bool RESIDENT, bool SHORT>
-__device__ __forceinline__ void mac_stream(const MacArgs<V>& a, const Slice<V>& w, const DigitConst& c, u32 tile_first, u32 tile_end, v4i* lds) {
+__device__ __forceinline__ void mac_stream(const MacArgs<V>& a, const Slice<V>& w, const DigitConst& c, u32 tile_first, u32 tile_end, u32 stride, v4i* lds) {
     using F = Form<V>;
     static_assert(!SHORT || (RESIDENT && F::LANE_TERMS <= 4), "one chunk, its list in one piece");
     constexpr u32 CHUNK_BLOCKS = SHORT ? 1 : F::CHUNK_BLOCKS, LANE_TERMS = F::LANE_TERMS;
@@ -310,9 +310,9 @@ __device__ __forceinline__ void mac_stream(const MacArgs<V>& a, const Slice<V>& 
     Cursor cur, nxt, after;
     enter_group(cur, a, tile_first);
     nxt = cur;
-    step(nxt, a, tile_end);
+    step(nxt, a, tile_end, stride);
     after = nxt;
-    step(after, a, tile_end);
+    step(after, a, tile_end, stride);
 
     u32 idx[8];                            // ciphertexts of the eight terms that this lane reads in the next chunk
     u32x4 x[CHUNK_BLOCKS][LANE_TERMS];     // residues of this chunk, 16 bytes of a row each
@@ -377,7 +377,7 @@ __device__ __forceinline__ void mac_stream(const MacArgs<V>& a, const Slice<V>& 
             if constexpr (!RESIDENT) write_tiles(buf ^ 1);
             buf ^= 1;
             nxt = after;
-            step(after, a, tile_end);
+            step(after, a, tile_end, stride);
         };
         run_chunk(0, std::true_type{});
 #pragma unroll 1
@@ -388,9 +388,9 @@ __device__ __forceinline__ void mac_stream(const MacArgs<V>& a, const Slice<V>& 
             for (u32 j = 0; j < LANE_TERMS; j++) asm volatile("" : "+v"(x[b][j]));  // the next chunk's inputs have arrived
         const DigitTile t = load_tile(a.tiles + tile);
         store_group<V, OT>(sums, a, w, c, t.out0, t.count);
-        if (tile + 1 >= tile_end) break;
-        cur.tile = tile + 1;
-        cur.n_chunks = chunks_of(a, load_tile(a.tiles + tile + 1));
+        if (tile + stride >= tile_end) break;
+        cur.tile = tile + stride;
+        cur.n_chunks = chunks_of(a, load_tile(a.tiles + tile + stride));
     }
 }
 
@@ -401,6 +401,10 @@ constexpr u32 lds_pieces(int ot) { return (SHORT ? 1 : RESIDENT_CHUNKS * Form<V>
 struct MacClass {
     u32 first, end, per_wg, blocks;  // the class's groups among the plan's tiles, groups per workgroup and workgroups
     u32 runs;                        // ... workgroups per slice of a row
+    u32 abreast;                     // 1: the wavefronts of a workgroup take neighbouring groups over one slice of 32 * CT slots,
+                                     // 0: one group over a slice each
+    template <typename V>
+    __host__ __device__ u32 slots() const { return abreast ? Form<V>::SLOTS / WAVES : Form<V>::SLOTS; }
 };
 
 // Where a workgroup is: slice of the row fastest, then run of groups, then (component, limb): workgroups go to the eight XCDs
@@ -409,9 +413,7 @@ struct MacClass {
 struct MacPlace {
     u32 part, run, row;  // row: (limb, component)
 };
-template <typename V>
-__device__ __forceinline__ MacPlace mac_place(u32 b, const MacArgs<V>& a, u32 runs, u32 first_row = 0) {
-    const u32 parts = a.N / Form<V>::SLOTS;
+__device__ __forceinline__ MacPlace mac_place(u32 b, u32 parts, u32 runs, u32 first_row = 0) {
     const u32 rest = b / parts;
     return MacPlace{b % parts, rest % runs, first_row + rest / runs};
 }
@@ -428,7 +430,7 @@ __device__ __forceinline__ void mac_class(const MacPlace& at_wg, const MacArgs<V
     w.lane = threadIdx.x % 64;
     w.half = w.lane / 32;
     w.ct_stride = 2 * a.limbs * a.N * sizeof(V);
-    const size_t at = ((size_t)w.comp * a.limbs + w.limb) * a.N + part * F::SLOTS + threadIdx.x / 64 * (32 * F::CT) + F::CT * (w.lane % 32);
+    const size_t at = ((size_t)w.comp * a.limbs + w.limb) * a.N + part * m.template slots<V>() + (m.abreast ? 0 : threadIdx.x / 64 * (32 * F::CT)) + F::CT * (w.lane % 32);
     w.x_base = reinterpret_cast<const char*>(a.ct_in + at);
     w.dst = a.out + at;
     w.tab = reinterpret_cast<const v4i_mem*>(a.tab + (u64)w.limb * a.tab_words);
@@ -451,14 +453,15 @@ __device__ __forceinline__ void mac_class(const MacPlace& at_wg, const MacArgs<V
             lds_barrier();  // (the table of the groups before is no longer read)
             for (u32 i = threadIdx.x; i < pieces; i += THREADS) lds[i] = w.tab[p.piece + i];
             lds_barrier();
-            mac_stream<V, OT, true, SHORT>(a, w, c, tile, end, lds);
+            const u32 own = m.abreast ? tile + __builtin_amdgcn_readfirstlane(threadIdx.x / 64) : tile;
+            if (own < end) mac_stream<V, OT, true, SHORT>(a, w, c, own, end, m.abreast ? WAVES : 1, lds);
             tile = end;
         } else {
             // the rest of the run: groups with long sums follow one another (tables of a class are in the order of
             // their first use, so a shorter one may still come and takes the same path)
             if constexpr (!SHORT) {
                 lds_barrier();
-                mac_stream<V, OT, false, false>(a, w, c, tile, tile_end, lds);
+                mac_stream<V, OT, false, false>(a, w, c, tile, tile_end, 1, lds);
             }
             tile = tile_end;
         }
@@ -471,7 +474,7 @@ template <typename V, int OT, bool SHORT>
 __global__ void __launch_bounds__(THREADS, OT * Form<V>::CT == 8 ? 2 : OT * Form<V>::CT == 4 ? 3 : 4)
 mac_digits_kernel(DigitTable dt, MacArgs<V> a, MacClass m) {
     __shared__ v4i lds[lds_pieces<V, SHORT>(OT)];
-    const MacPlace at = mac_place(blockIdx.x, a, m.runs);
+    const MacPlace at = mac_place(blockIdx.x, a.N / m.template slots<V>(), m.runs);
     mac_class<V, OT, SHORT>(at, a, dt, m, lds);
 }
 
@@ -487,14 +490,14 @@ __global__ void __launch_bounds__(THREADS, 2) mac_digits_mixed_kernel(DigitTable
     u32 b = blockIdx.x, cls;
     MacPlace at;
     if (b < lead * parts * runs) {
-        at = mac_place(b, a, runs);
+        at = mac_place(b, parts, runs);
         cls = at.run < c16.runs ? 0 : at.run < c16.runs + c8.runs ? 1 : 2;
         at.run -= cls == 0 ? 0 : cls == 1 ? c16.runs : c16.runs + c8.runs;
     } else {
         b -= lead * parts * runs;
         const u32 n16 = tail * parts * c16.runs, n8 = tail * parts * c8.runs;
         cls = b < n16 ? 0 : b < n16 + n8 ? 1 : 2;
-        at = mac_place(b - (cls == 0 ? 0 : cls == 1 ? n16 : n16 + n8), a, cls == 0 ? c16.runs : cls == 1 ? c8.runs : c4.runs, lead);
+        at = mac_place(b - (cls == 0 ? 0 : cls == 1 ? n16 : n16 + n8), parts, cls == 0 ? c16.runs : cls == 1 ? c8.runs : c4.runs, lead);
     }
     if (cls == 0) mac_class<V, OT16, SHORT>(at, a, dt, c16, lds);
     else if (cls == 1) mac_class<V, OT8, SHORT>(at, a, dt, c8, lds);
@@ -503,14 +506,23 @@ __global__ void __launch_bounds__(THREADS, 2) mac_digits_mixed_kernel(DigitTable
 
 // Groups per workgroup and workgroups of one class over the tiles [first, end).  Several groups per workgroup pay the
 // start of a run (descriptor -> term list -> inputs, and a convolution's table) once; a group without terms stays alone.
+// abreast: a convolution's windows that follow one another share most of their inputs.  With a window per wavefront, all over
+// the same slots and in step, what one wavefront reads the next finds in the L1 (loads, not products, bind a convolution with
+// few filters).  Such a workgroup covers a quarter of the slots and takes up to four times the groups.  Only where one table that
+// stays in the LDS serves all groups (unpadded convolutions): 28x28x1, 5x5x5, N = 2^13, L = 4, 274 -> 254 us; 12x12x7, 3x3x16,
+// L = 3 411 -> 392; 30x30x1, 5x5x12, 2^12, 898 and 904.  The runs of a padded one end with every table: 10x10x3, 3x3x5, 2^15
+// 682 -> 755, 16x16x2, 3x3x4, 2^13 234 -> 256.
 template <typename V>
-MacClass mac_class_of(const he_ctx* ctx, const he_plan* plan, u32 limbs, u32 cls, u32 first, u32 end, u32 t_begin) {
-    const u64 per_run = (u64)limbs * 2 * (ctx->N / Form<V>::SLOTS);
-    const u32 count = end - first;
-    u32 per_wg = plan->min_terms_s[cls] > t_begin ? GROUPS_PER_WG : 1;  // (a stream has no group without terms in it)
-    while (per_wg > 1 && (u64)((count + per_wg - 1) / per_wg) * per_run < MIN_WORKGROUPS) per_wg /= 2;
-    const u32 runs = (count + per_wg - 1) / per_wg;
-    return MacClass{first, end, per_wg, (u32)std::min<u64>(runs * per_run, 0x7FFFFFFFull), runs};
+MacClass mac_class_of(const he_ctx* ctx, const he_plan* plan, u32 limbs, u32 cls, u32 first, u32 end, u32 t_begin, bool abreast = false) {
+    MacClass m{first, end, 1, 0, 0, abreast};
+    const u64 per_run = (u64)limbs * 2 * (ctx->N / m.slots<V>());
+    const u32 count = end - first, least = abreast ? WAVES : 1;
+    m.per_wg = plan->min_terms_s[cls] > t_begin ? GROUPS_PER_WG * least : 1;  // (a stream has no group without terms in it)
+    while (m.per_wg > least && (u64)((count + m.per_wg - 1) / m.per_wg) * per_run < MIN_WORKGROUPS) m.per_wg /= 2;
+    m.runs = (count + m.per_wg - 1) / m.per_wg;
+    if (abreast && m.runs) m.per_wg = (count + m.runs * WAVES - 1) / (m.runs * WAVES) * WAVES;  // runs of equal length
+    m.blocks = (u32)std::min<u64>(m.runs * per_run, 0x7FFFFFFFull);
+    return m;
 }
 
 template <typename V, bool SHORT>
@@ -540,6 +552,18 @@ int launch_mac_digits_t(he_ctx* ctx, const he_plan* plan, const ScalarSlice& sl,
     }
     if (blocks == 0) return HE_OK;
     const u32 table0 = plan->table_s[first];
+    if constexpr (sizeof(V) == sizeof(u64)) {
+        for (u32 cls = 1; cls < SCALAR_CLASSES; cls++) {
+            if (c[cls].blocks != blocks || !plan->shared_inputs_s[cls] || plan->short_sums() || plan->min_terms_s[cls] <= sl.t_begin ||
+                plan->max_terms_s[cls] > RESIDENT_CHUNKS * CHUNK_TERMS ||
+                sl.table_end - table0 != 1 || sl.end[cls] - sl.begin[cls] < 2 * WAVES)
+                continue;
+            const MacClass m = mac_class_of<V>(ctx, plan, limbs, cls, sl.begin[cls], sl.end[cls], sl.t_begin, true);
+            if (m.blocks >= 0x7FFFFFFFu) continue;
+            c[cls] = m;
+            blocks = m.blocks;
+        }
+    }
     const bool short_sums = sizeof(V) == sizeof(u64) && plan->short_sums();  // (packed sums that short run on the vector ALU)
     // about one entry per thread, but no more workgroups than fill the chip a few times
     const u64 entries = (u64)std::min(plan->max_terms, sl.t_end - sl.t_begin) * 16;
