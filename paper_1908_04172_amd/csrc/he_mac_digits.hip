@@ -15,9 +15,9 @@
 // the vector ALU, which only splits digits, forms addresses and reduces, about 25 instructions per output at the end.
 // What bounds it: long sums, the inputs' way through the L2 (a dense layer's groups of 16 outputs each read all of
 // them); a convolution window's 27 terms, the memory itself.  Measured against the same loop on 32-bit multiply-adds
-// (the layer's MAC launch alone): dense 845 -> 100 at N = 2^13, L = 4: 1150 -> 355 us; dense 96 -> 24 at 2^15, L = 8:
-// 358 -> 188 us; convolution 32x32x3, 3x3x16, at 2^14, L = 8: 5940 -> 3500 us (17 GB: 4.9 TB/s); 28x28, 5x5x5, at 2^13,
-// L = 4: 435 -> 296 us; dense 64 -> 16 at 2^12, L = 2: 37 -> 15 us.  Packed, dense 1024 -> 256 at 2^12, L = 2: 352 -> 83 us.
+// (the layer's MAC launch alone): dense 845 -> 100 at N = 2^13, L = 4: 1150 -> 345 us; dense 96 -> 24 at 2^15, L = 8:
+// 358 -> 147 us; convolution 32x32x3, 3x3x16, at 2^14, L = 8: 5940 -> 3590 us (16 GB: 4.5 TB/s); 28x28, 5x5x5, at 2^13,
+// L = 4: 435 -> 255 us; dense 64 -> 16 at 2^12, L = 2: 37 -> 15 us.  Packed, dense 1024 -> 256 at 2^12, L = 2: 352 -> 83 us.
 // (On random digits the chip sustains 2.8 to 3.2 int8 POP/s, on constant ones 4.3: a long sum's arithmetic is priced with
 // the former, 235 us of the 330 that 845 -> 96 takes; what else it waits for is the inputs, 75 us, and the meetings of
 // the wavefronts around the table's stages, 35 us.)
