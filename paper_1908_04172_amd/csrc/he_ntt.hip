@@ -293,6 +293,7 @@ struct RowMap {
     u32 stride, first, limb_fixed;  // limb_fixed = NO_LIMB: none
     u32 rotate = 0;                 // 1: workgroups change their place from slab to slab (see the loop of ntt_rows_kernel)
     u32 stream = 0;                 // 1: the results are not to be kept in the caches
+    u32 src_stride = 0, src_first = 0;  // ROWS_HALVES out of place: the long rows of `spread_src` in the same order
 };
 constexpr u32 NO_LIMB = 0xFFFFFFFFu;
 enum : u32 { STREAM_LOADS = 1, STREAM_STORES = 2 };
@@ -326,6 +327,7 @@ ntt_rows_kernel(LimbTable lt, u32 limbs, u64* data, const u64* tw_all, const dou
         } else if constexpr (SQUARE) {
             return spread_src + ((size_t)(w / limbs) * 2 + 1) * limbs * G::N + (size_t)(w % limbs) * G::N;
         } else if constexpr (HALVES) {
+            if (spread_src != nullptr) return spread_src + ((size_t)((w >> 1) * map.src_stride + map.src_first) * 2 + (w & 1u)) * G::N;
             return data + ((size_t)((w >> 1) * map.stride + map.first) * 2 + (w & 1u)) * G::N;
         } else {
             // (plain rows: from `spread_src` if the caller gave one, the transform then being out of place)
@@ -439,7 +441,7 @@ ntt_rows_kernel(LimbTable lt, u32 limbs, u64* data, const u64* tw_all, const dou
 #pragma unroll
             for (u32 e = 0; e < 16; e++) asm volatile("" : "+v"(next[e]) :: "memory");
         }
-        u64* p = HALVES ? const_cast<u64*>(source(work)) : data + (size_t)row * G::N;
+        u64* p = data + (HALVES ? (size_t)long_row * 2 + (work & 1u) : (size_t)row) * G::N;
         store_row<LOGN, POUT>(a, p, tid_s, map.stream);
 #pragma unroll
         for (u32 e = 0; e < 16; e++) a[e] = next[e];
@@ -711,9 +713,10 @@ u32 limbs_differ(const LimbTable& lt, u32 limbs) {
 u32 elementwise_grid(size_t total) { return (u32)std::min<size_t>((total + 255) / 256, 256 * 32); }
 
 // Transforms of `rows` long rows of 2^15 residues in place (mapped by `map`; tw / tw_f: the tables of the direction).
-// top_done: the stage over global memory has been run by the caller (forward only).
+// top_done: the stage over global memory has been run by the caller (forward only).  src (inverse only): where the rows are read from
+// (map.src_stride, map.src_first), if not from `data`.
 int launch_split_transform(he_ctx* ctx, const LimbTable& lt, u32 limbs, u64* data, u32 rows, bool inverse, const u64* tw,
-                           const double* tw_f, RowMap map, hipStream_t s, bool top_done = false) {
+                           const double* tw_f, RowMap map, hipStream_t s, bool top_done = false, const u64* src = nullptr) {
     using G = Geo<14>;
     const size_t lds = lds_row_bytes<14, u64>();
     const u32 halves = rows * 2;
@@ -724,7 +727,7 @@ int launch_split_transform(he_ctx* ctx, const LimbTable& lt, u32 limbs, u64* dat
         static std::atomic<uint32_t> lds_allowed{0};
         if (int rc = allow_dynamic_lds((const void*)ntt_rows_kernel<14, true, ROWS_HALVES>, lds, ctx->device, lds_allowed)) return rc;
         hipLaunchKernelGGL((ntt_rows_kernel<14, true, ROWS_HALVES>), dim3(grid), dim3(G::T), lds, s, lt, limbs, data, tw, tw_f, halves,
-                           (const u64*)nullptr, 1u, 0u, (u64*)nullptr, map);
+                           src, 1u, 0u, (u64*)nullptr, map);
         hipLaunchKernelGGL((split_top_kernel<true>), dim3(elementwise_grid((size_t)rows * HALF_N)), dim3(256), 0, s, lt, limbs, data, tw,
                            rows, map);
     } else {
@@ -740,19 +743,12 @@ int launch_split_transform(he_ctx* ctx, const LimbTable& lt, u32 limbs, u64* dat
     return HE_OK;
 }
 
-// The rescale at ring degree 2^15, in the output tensor itself: the dropped limb's rows are copied into the rows of
-// the last kept limb and brought back to coefficients there (t); one pass writes, for every kept limb i, t - h
+// The rescale at ring degree 2^15, in the output tensor itself: the dropped limb's rows are brought back to coefficients (t) in the
+// rows of the last kept limb (their half rows are read from the input: a copy of them first was a launch of 6.5 us for 24 ciphertexts
+// at L = 8); one pass writes, for every kept limb i, t - h
 // reduced modulo q_i into row i, already through the first stage of its forward transform (the last kept row in
 // place: a thread reads its two values of t before it writes); the half rows are transformed; the last pass combines
 // them with the input rows: out_i = (x_i - correction_i) * p^-1.
-__global__ void __launch_bounds__(256) split_copy_last_kernel(u32 limbs, const u64* in, u64* out, u32 polys) {
-    const size_t total = (size_t)polys * 2 * HALF_N;
-    for (size_t k = (size_t)blockIdx.x * 256 + threadIdx.x; k < total; k += (size_t)gridDim.x * 256) {
-        const size_t p = k / (2 * HALF_N), j = k % (2 * HALF_N);
-        out[(p * (limbs - 1) + (limbs - 2)) * 2 * HALF_N + j] = in[(p * limbs + (limbs - 1)) * 2 * HALF_N + j];
-    }
-}
-
 // (with the first stage of the corrections' forward transforms: a thread takes the pair (j, j + N/2) of its polynomial)
 __global__ void __launch_bounds__(256) split_corrections_kernel(LimbTable lt, DropRow drop, u32 limbs, u64* out, const u64* tw_fwd, u32 polys) {
     const size_t total = (size_t)polys * HALF_N;
@@ -795,11 +791,13 @@ int launch_rescale_split(he_ctx* ctx, u32 limbs, u32 drop_id, const u64* in, u64
     for (u32 i = 0; i < HE_MAX_LIMBS; i++) row.d[i] = ctx->drop[drop_id][i];
     const u32 polys = 2 * n;
     const size_t per_limb = (size_t)2 * HALF_N;
-    hipLaunchKernelGGL(split_copy_last_kernel, dim3(elementwise_grid((size_t)polys * per_limb)), dim3(256), 0, s, limbs, in, out, polys);
     // the dropped limb's constants sit at position limbs - 1 of `lt`; its tables are found from that position
     const u64* tw_inv = ctx->tw_inv + ((size_t)drop_id - (limbs - 1)) * per_limb * 2;
     const double* tw_inv_f = ctx->tw_inv_f + ((size_t)drop_id - (limbs - 1)) * per_limb;
-    if (int rc = launch_split_transform(ctx, lt, limbs, out, polys, true, tw_inv, tw_inv_f, RowMap{limbs - 1, limbs - 2, limbs - 1}, s)) return rc;
+    RowMap t_rows{limbs - 1, limbs - 2, limbs - 1};
+    t_rows.src_stride = limbs;
+    t_rows.src_first = limbs - 1;
+    if (int rc = launch_split_transform(ctx, lt, limbs, out, polys, true, tw_inv, tw_inv_f, t_rows, s, false, in)) return rc;
     hipLaunchKernelGGL(split_corrections_kernel, dim3(elementwise_grid((size_t)polys * HALF_N)), dim3(256), 0, s, lt, row, limbs, out,
                        ctx->tw_fwd, polys);
     if (int rc = launch_split_transform(ctx, lt, limbs - 1, out, polys * (limbs - 1), false, ctx->tw_fwd, ctx->tw_fwd_f, RowMap{1, 0, NO_LIMB}, s,
