@@ -6,6 +6,7 @@
 #include <map>
 #include <mutex>
 #include <new>
+#include <unordered_map>
 
 #include "he_internal.h"
 #include "../../include/he_test.h"
@@ -622,31 +623,30 @@ int he_encode_scalar_host(const he_ctx* ctx, const double* values, size_t n, dou
     return ok ? HE_OK : HE_ERR_ARG;
 }
 
-int he_plan_create(he_ctx* ctx, uint32_t n_in, uint32_t n_out, uint32_t n_pt, const uint32_t* off,
-                   const uint32_t* term_ct, const uint32_t* term_pt, he_plan** out) {
-    if (!out) return HE_ERR_ARG;
-    *out = nullptr;
-    if (!ctx || !off) return HE_ERR_ARG;
-    if (off[0] != 0) return HE_ERR_RANGE;
-    for (u32 o = 0; o < n_out; ++o)
-        if (off[o + 1] < off[o]) return HE_ERR_RANGE;
-    const u32 n_terms = off[n_out];
-    if (n_terms && (!term_ct || !term_pt)) return HE_ERR_ARG;
-    for (u32 t = 0; t < n_terms; ++t)
-        if (term_ct[t] >= n_in || term_pt[t] >= n_pt) return HE_ERR_RANGE;
-    int rc = need_device(ctx);
-    if (rc != HE_OK) return rc;
-    he_plan* p = new (std::nothrow) he_plan();
-    if (!p) return HE_ERR_ARG;
-    p->ctx = ctx;
-    p->device = ctx->device;
-    p->n_in = n_in; p->n_out = n_out; p->n_pt = n_pt; p->n_terms = n_terms;
+namespace {
+
+// The last tile that read an input (none: ~0u).  The inputs are counted by the terms that name them: `n_in` of a plan is the
+// caller's bare number, with no array behind it.
+struct LastReader {
+    std::vector<u32> near;                // where the highest input is not far above the number of terms
+    std::unordered_map<u32, u32> far;
+    LastReader(const std::vector<Tile>& tiles, const u32* term_ct) {
+        u64 terms = 0, top = 0;
+        for (const Tile& t : tiles) {
+            terms += t.n_terms;
+            for (u32 k = 0; k < t.n_terms; ++k) top = std::max<u64>(top, (u64)term_ct[t.term0 + k] + 1);
+        }
+        if (top <= 4 * terms) near.assign(top, ~0u);
+    }
+    u32& operator[](u32 ct) { return near.empty() ? far.emplace(ct, ~0u).first->second : near[ct]; }
+};
+
+}  // namespace
+
+// Everything of a plan that follows from its arrays, and the uploads.
+static int build_plan(he_plan* p, const u32* off, const u32* term_ct, const u32* term_pt) {
+    const u32 n_out = p->n_out, n_terms = p->n_terms;
     p->off.assign(off, off + n_out + 1);
-    p->tiles_s_dev = p->tiles_p_dev = nullptr;
-    p->wbase_s_dev = nullptr;
-    p->owners_dev = p->lists_dev = nullptr;
-    p->digit_tiles_dev = nullptr;
-    p->off_dev = p->term_ct_dev = p->term_pt_dev = nullptr;
     std::vector<Tile> ts, tp;
     build_tiles(off, term_ct, n_out, CAPS_S[SCALAR_CLASSES - 1], ts);
     build_tiles(off, term_ct, n_out, CAPS_P[2], tp);
@@ -710,20 +710,18 @@ int he_plan_create(he_ctx* ctx, uint32_t n_in, uint32_t n_out, uint32_t n_pt, co
         }
     }
     p->tiles_s = ts;
-    {
-        std::vector<u32> seen(n_in, ~0u);  // the last tile that read an input
-        for (u32 cls = 0; cls < SCALAR_CLASSES; ++cls) {
-            u64 terms = 0, shared = 0;
-            for (u32 i = p->class_begin_s[cls]; i < p->class_begin_s[cls + 1]; ++i) {
-                terms += ts[i].n_terms;
-                for (u32 t = 0; t < ts[i].n_terms; ++t) {
-                    u32& last = seen[term_ct[ts[i].term0 + t]];
-                    shared += last + 1 == i && i > p->class_begin_s[cls];
-                    last = i;
-                }
+    LastReader last_reader(ts, term_ct);
+    for (u32 cls = 1; cls < SCALAR_CLASSES; ++cls) {
+        u64 terms = 0, shared = 0;
+        for (u32 i = p->class_begin_s[cls]; i < p->class_begin_s[cls + 1]; ++i) {
+            terms += ts[i].n_terms;
+            for (u32 t = 0; t < ts[i].n_terms; ++t) {
+                u32& last = last_reader[term_ct[ts[i].term0 + t]];
+                shared += last + 1 == i && i > p->class_begin_s[cls];
+                last = i;
             }
-            p->shared_inputs_s[cls] = shared * 3 >= terms && terms > 0;
         }
+        p->shared_inputs_s[cls] = shared * 3 >= terms && terms > 0;
     }
     p->one_term_each = p->class_begin_s[1] == p->n_tiles_s && p->min_terms_s[0] == 1 && p->max_terms_s[0] == 1;
     p->wtab_elems = elems;
@@ -731,9 +729,38 @@ int he_plan_create(he_ctx* ctx, uint32_t n_in, uint32_t n_out, uint32_t n_pt, co
         upload(&p->wbase_s_dev, p->wbase_s.data(), ts.size()) != HE_OK || upload(&p->owners_dev, owners.data(), owners.size()) != HE_OK ||
         upload(&p->digit_tiles_dev, dts.data(), dts.size()) != HE_OK || upload(&p->lists_dev, lists.data(), lists.size()) != HE_OK ||
         upload(&p->off_dev, off, (size_t)n_out + 1) != HE_OK || upload(&p->term_ct_dev, term_ct, n_terms) != HE_OK ||
-        upload(&p->term_pt_dev, term_pt, n_terms) != HE_OK) {
-        he_plan_destroy(p);
+        upload(&p->term_pt_dev, term_pt, n_terms) != HE_OK)
         return HE_ERR_DEVICE;
+    return HE_OK;
+}
+
+int he_plan_create(he_ctx* ctx, uint32_t n_in, uint32_t n_out, uint32_t n_pt, const uint32_t* off,
+                   const uint32_t* term_ct, const uint32_t* term_pt, he_plan** out) {
+    if (!out) return HE_ERR_ARG;
+    *out = nullptr;
+    if (!ctx || !off) return HE_ERR_ARG;
+    if (off[0] != 0) return HE_ERR_RANGE;
+    for (u32 o = 0; o < n_out; ++o)
+        if (off[o + 1] < off[o]) return HE_ERR_RANGE;
+    const u32 n_terms = off[n_out];
+    if (n_terms && (!term_ct || !term_pt)) return HE_ERR_ARG;
+    for (u32 t = 0; t < n_terms; ++t)
+        if (term_ct[t] >= n_in || term_pt[t] >= n_pt) return HE_ERR_RANGE;
+    int rc = need_device(ctx);
+    if (rc != HE_OK) return rc;
+    he_plan* p = new (std::nothrow) he_plan();  // (all pointers null)
+    if (!p) return HE_ERR_ARG;
+    p->ctx = ctx;
+    p->device = ctx->device;
+    p->n_in = n_in; p->n_out = n_out; p->n_pt = n_pt; p->n_terms = n_terms;
+    try {
+        rc = build_plan(p, off, term_ct, term_pt);
+    } catch (const std::bad_alloc&) {  // (several words per term)
+        rc = HE_ERR_RANGE;
+    }
+    if (rc != HE_OK) {
+        he_plan_destroy(p);
+        return rc;
     }
     *out = p;
     return HE_OK;
