@@ -418,10 +418,12 @@ __device__ __forceinline__ MacPlace mac_place(u32 b, u32 parts, u32 runs, u32 fi
     return MacPlace{b % parts, rest % runs, first_row + rest / runs};
 }
 
-template <typename V, int OT, bool SHORT>
+// MIXED: one of several classes of a launch, whose windows never go abreast.
+template <typename V, int OT, bool SHORT, bool MIXED = false>
 __device__ __forceinline__ void mac_class(const MacPlace& at_wg, const MacArgs<V>& a, const DigitTable& dt, const MacClass& m, v4i* lds) {
     using F = Form<V>;
     const u32 part = at_wg.part;
+    const bool abreast = !MIXED && m.abreast;
     const u32 tile_first = m.first + at_wg.run * m.per_wg;
     const u32 tile_end = min(tile_first + m.per_wg, m.end);
     Slice<V> w;
@@ -430,7 +432,7 @@ __device__ __forceinline__ void mac_class(const MacPlace& at_wg, const MacArgs<V
     w.lane = threadIdx.x % 64;
     w.half = w.lane / 32;
     w.ct_stride = 2 * a.limbs * a.N * sizeof(V);
-    const size_t at = ((size_t)w.comp * a.limbs + w.limb) * a.N + part * m.template slots<V>() + (m.abreast ? 0 : threadIdx.x / 64 * (32 * F::CT)) + F::CT * (w.lane % 32);
+    const size_t at = ((size_t)w.comp * a.limbs + w.limb) * a.N + part * (abreast ? F::SLOTS / WAVES : F::SLOTS) + (abreast ? 0 : threadIdx.x / 64 * (32 * F::CT)) + F::CT * (w.lane % 32);
     w.x_base = reinterpret_cast<const char*>(a.ct_in + at);
     w.dst = a.out + at;
     w.tab = reinterpret_cast<const v4i_mem*>(a.tab + (u64)w.limb * a.tab_words);
@@ -453,8 +455,8 @@ __device__ __forceinline__ void mac_class(const MacPlace& at_wg, const MacArgs<V
             lds_barrier();  // (the table of the groups before is no longer read)
             for (u32 i = threadIdx.x; i < pieces; i += THREADS) lds[i] = w.tab[p.piece + i];
             lds_barrier();
-            const u32 own = m.abreast ? tile + __builtin_amdgcn_readfirstlane(threadIdx.x / 64) : tile;
-            if (own < end) mac_stream<V, OT, true, SHORT>(a, w, c, own, end, m.abreast ? WAVES : 1, lds);
+            const u32 own = abreast ? tile + __builtin_amdgcn_readfirstlane(threadIdx.x / 64) : tile;
+            if (own < end) mac_stream<V, OT, true, SHORT>(a, w, c, own, end, abreast ? WAVES : 1, lds);
             tile = end;
         } else {
             // the rest of the run: groups with long sums follow one another (tables of a class are in the order of
@@ -499,9 +501,19 @@ __global__ void __launch_bounds__(THREADS, 2) mac_digits_mixed_kernel(DigitTable
         cls = b < n16 ? 0 : b < n16 + n8 ? 1 : 2;
         at = mac_place(b - (cls == 0 ? 0 : cls == 1 ? n16 : n16 + n8), parts, cls == 0 ? c16.runs : cls == 1 ? c8.runs : c4.runs, lead);
     }
-    if (cls == 0) mac_class<V, OT16, SHORT>(at, a, dt, c16, lds);
-    else if (cls == 1) mac_class<V, OT8, SHORT>(at, a, dt, c8, lds);
-    else mac_class<V, OT4, SHORT>(at, a, dt, c4, lds);
+    // (The place is opaque in each branch: left to itself the compiler derives what the three have in common ahead of them,
+    // in scalar registers that it then has to park: 146 of them, 104 now.  Dense 300 -> 23 at N = 2^13, L = 3 38.9 -> 37.8 us,
+    // 845 -> 20 at L = 4 122 -> 119.5.)
+    if (cls == 0) {
+        asm volatile("; groups of 9 to 16" : "+s"(at.part), "+s"(at.run), "+s"(at.row));
+        mac_class<V, OT16, SHORT, true>(at, a, dt, c16, lds);
+    } else if (cls == 1) {
+        asm volatile("; groups of 5 to 8" : "+s"(at.part), "+s"(at.run), "+s"(at.row));
+        mac_class<V, OT8, SHORT, true>(at, a, dt, c8, lds);
+    } else {
+        asm volatile("; groups of 2 to 4" : "+s"(at.part), "+s"(at.run), "+s"(at.row));
+        mac_class<V, OT4, SHORT, true>(at, a, dt, c4, lds);
+    }
 }
 
 // Groups per workgroup and workgroups of one class over the tiles [first, end).  Several groups per workgroup pay the
