@@ -547,9 +547,12 @@ void launch_classes(he_ctx* ctx, const MacArgs<V>& a, const MacClass (&c)[SCALAR
     else {
         const u32 rows = a.limbs * 2;
         const u64 resident = 2 * 256;  // two workgroups per compute unit
-        // (less than two waves of workgroups are all tail: packed 501 -> 85 at 2^14, 768 workgroups, 103.6 us, 104.7 with 256 of them
-        // in the order of the rows)
-        const u32 tail = blocks < 2 * resident ? rows : (u32)std::min<u64>(rows, (resident * rows + blocks - 1) / blocks);
+        // (Less than two waves of workgroups of which the largest class is four fifths or more are all tail: N = 2^13, L = 3, 300 -> 68,
+        // four runs of groups of 16 and one of 4, 76.7 us, 79.2 with a row in the order of the rows; 300 -> 100 at L = 2 65.0 and 66.5.
+        // Where the classes are closer to one another what they share counts for more: 500 -> 24 at 2^14, L = 3 146 us and 125;
+        // 200 -> 40 at 2^12, L = 8 54.4 and 50.4.)
+        const bool all_tail = blocks < 2 * resident && 4 * (c[2].runs + c[1].runs) <= c[3].runs;
+        const u32 tail = all_tail ? rows : (u32)std::min<u64>(rows, (resident * rows + blocks - 1) / blocks);
         hipLaunchKernelGGL((mac_digits_mixed_kernel<V, SHORT>), grid, block, 0, s, ctx->digits, a, c[3], c[2], c[1], tail);
     }
 }

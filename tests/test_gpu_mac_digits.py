@@ -245,3 +245,17 @@ def test_tables_larger_than_the_fixed_scratch_are_worked_off_in_slices(he, K, M,
     else:
         want = oracle.mac(ct, q, sub.off, sub.term_ct, sub.term_pt, w, oracle.PT_SCALAR, b[some])
     assert np.array_equal(host(out[some]), want)
+
+
+@pytest.mark.parametrize("M", [20, 37, 68, 85])
+@pytest.mark.parametrize("K", [5, 70])
+def test_order_of_the_groups_of_several_classes(he, K, M):
+    """Launches of 384 (one wave of workgroups), 576 and 960 (less than two: the groups of a slice side by side where the classes
+    are close in size, the largest class first where it is four fifths of the launch) and 1152 workgroups."""
+    N = 1 << 11
+    q = wl.modulus_chain([60, 50, 40] * 4, N)
+    ctx = he.Context(11, q)
+    plan = wl.dense_plan(K, M)
+    ct, w, b = operands(plan, q, N, M, False)
+    want = oracle.mac(ct, q, plan.off, plan.term_ct, plan.term_pt, w, oracle.PT_SCALAR, b)
+    assert np.array_equal(run(he, ctx, plan, ct, w, b), want)
