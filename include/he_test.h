@@ -80,6 +80,15 @@ int he_test_mac_for_rescale(he_ctx* ctx, const he_plan* plan, uint32_t limbs, co
 int he_test_mac_groups_per_workgroup(const he_plan* plan, uint32_t limbs, uint32_t outputs, int packed, uint32_t* groups);
 
 /*
+ * In which form the scalar MAC of the plan's groups of `outputs` outputs (2 to 16, as above) is launched by he_ct_pt_mac (packed:
+ * he_ct_pt_mac32) with these flags, as long as its tables fit the workspace: HE_FORM_* bits.
+ */
+enum {
+    HE_FORM_PAST_CACHES = 1 /* the outputs are written past the caches */
+};
+int he_test_mac_form(const he_plan* plan, uint32_t limbs, uint32_t outputs, int packed, uint32_t flags, uint32_t* form);
+
+/*
  * The transforms of limbs below 2^50 run on double-precision FMAs, those of larger limbs on integer butterflies; both
  * produce the same residues.  integer_only = 1 makes every later call on this context use the integer butterflies for
  * all limbs (for tests of those butterflies on such limbs, and for timing one arithmetic against the other);

@@ -711,12 +711,14 @@ static int build_plan(he_plan* p, const u32* off, const u32* term_ct, const u32*
     }
     p->tiles_s = ts;
     LastReader last_reader(ts, term_ct);
-    for (u32 cls = 1; cls < SCALAR_CLASSES; ++cls) {
+    p->n_read = 0;
+    for (u32 cls = 0; cls < SCALAR_CLASSES; ++cls) {
         u64 terms = 0, shared = 0;
         for (u32 i = p->class_begin_s[cls]; i < p->class_begin_s[cls + 1]; ++i) {
             terms += ts[i].n_terms;
             for (u32 t = 0; t < ts[i].n_terms; ++t) {
                 u32& last = last_reader[term_ct[ts[i].term0 + t]];
+                p->n_read += last == ~0u;
                 shared += last + 1 == i && i > p->class_begin_s[cls];
                 last = i;
             }
@@ -1213,6 +1215,13 @@ int he_test_mac_groups_per_workgroup(const he_plan* plan, uint32_t limbs, uint32
     u32 cls = 1;
     while (outputs > CAPS_S[cls]) ++cls;
     *groups = mac_digits_groups_per_workgroup(plan->ctx, plan, limbs, cls, packed != 0);
+    return HE_OK;
+}
+
+int he_test_mac_form(const he_plan* plan, uint32_t limbs, uint32_t outputs, int packed, uint32_t flags, uint32_t* form) {
+    if (!plan || !form || outputs < 2 || outputs > CAPS_S[SCALAR_CLASSES - 1] || (flags & ~(HE_RESCALE | HE_ACCUMULATE))) return HE_ERR_ARG;
+    if (int rc = check_level(plan->ctx, limbs, (flags & HE_RESCALE) ? 2 : 1)) return rc;
+    *form = mac_groups_stream(plan, limbs, plan->ctx->N, packed ? sizeof(u32) : sizeof(u64)) ? (u32)HE_FORM_PAST_CACHES : 0u;
     return HE_OK;
 }
 

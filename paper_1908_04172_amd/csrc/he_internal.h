@@ -116,6 +116,7 @@ struct he_plan {
     he_ctx* ctx;
     int device;            // the context's device, kept so that the plan can be destroyed after its context
     u32 n_in, n_out, n_pt, n_terms;
+    u32 n_read;            // inputs that some term names
     std::vector<u32> off;  // host copy, for argument checks
     // tiles sorted by class
     u32 class_begin_s[SCALAR_CLASSES + 1];
@@ -180,6 +181,15 @@ enum : u32 {
                           // kept limbs of scalar-plaintext sums may be left unreduced (LimbConst::mac_lazy)
 };
 int check_mac_launch(he_ctx* ctx, const he_plan* plan, u32 limbs, int pt_kind);
+// Whether the scalar MAC of groups of outputs writes past the caches: where inputs and outputs together do not fit the
+// memory-side cache, and the outputs not the L2s.  There the stores are most of what a short sum moves, and allocating their
+// lines costs 16 outputs of one term, N = 2^13, L = 4, 800 us against 576, the layer 30 -> 120 at 2^14, L = 8 (60 + 240 MiB) 322
+// against 301.  What does fit is read from the cache by the call that adds to it or rescales it: the layer 100 -> 200 at 2^13,
+// L = 4 (50 + 100 MiB) 174 us, 181 past the caches; 20 -> 300 with a second call that adds, then the rescale, 296 and 326.
+inline bool mac_groups_stream(const he_plan* plan, u32 limbs, u32 N, size_t residue_bytes) {
+    const u64 per_ct = (u64)2 * limbs * N * residue_bytes, out = plan->n_out * per_ct;
+    return out > L2_BYTES && plan->n_read * per_ct + out > MEMORY_CACHE_BYTES;
+}
 // wtab: room for `wtab_bytes` of gathered weights; less than scalar_table_bytes() is worked off in slices, down to
 // min_scalar_table_bytes()
 int launch_mac(he_ctx* ctx, const he_plan* plan, u32 limbs, const u64* ct_in, const u64* pt, int pt_kind,

@@ -592,11 +592,7 @@ int launch_mac_digits_t(he_ctx* ctx, const he_plan* plan, const ScalarSlice& sl,
                            plan->tiles_s_dev, plan->wbase_s_dev, plan->owners_dev + table0 + t, limbs, plan->off_dev, plan->term_pt_dev, pt, wtab,
                            sl.tab_words, sl.tab_skip, sl.t_begin, sl.t_end, short_sums ? BLOCK_TERMS : CHUNK_TERMS);
     }
-    // Outputs beyond the L2s are written past the caches: the stores are most of what a short sum moves, and allocating their
-    // lines cost groups of 16 outputs and one term, N = 2^13, L = 4, 800 us against 576, the convolution 28x28 297 against
-    // 273.  (What fits the L2s is read from there by the call that adds to it or rescales it: 200 + 113 -> 37 in two calls,
-    // N = 2^13, L = 3, 14 MB, 116 us, 120 past the caches.)
-    if ((u64)plan->n_out * 2 * limbs * ctx->N * sizeof(V) > L2_BYTES) mode |= MAC_STREAM;
+    if (mac_groups_stream(plan, limbs, ctx->N, sizeof(V))) mode |= MAC_STREAM;
     const MacArgs<V> a{plan->digit_tiles_dev, plan->lists_dev, wtab, sl.tab_words, sl.tab_skip, ct_in, bias, out, limbs, ctx->N, sl.t_begin,
                        sl.t_end, mode};
     if constexpr (sizeof(V) == sizeof(u64)) {

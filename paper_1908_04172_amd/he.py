@@ -17,6 +17,7 @@ RATE_MAD32, RATE_MAC_TERM, RATE_SHOUP_EXACT, RATE_SHOUP_CHEAP = 0, 1, 2, 3
 RATE_BUTTERFLY_MODE0, RATE_BUTTERFLY_MODE1, RATE_BUTTERFLY_MODE2, RATE_BUTTERFLY_INV = 4, 5, 6, 7
 RATE_BUTTERFLY_FP64, RATE_BUTTERFLY_FP64_INV = 9, 10
 DIGITS_CANONICAL, DIGITS_BELOW_6Q, DIGITS_BELOW_4Q, DIGITS_PACKED = 0, 1, 2, 3
+FORM_PAST_CACHES = 1
 PT_SCALAR = 0
 PT_POLY = 1
 RESCALE = 1
@@ -32,7 +33,7 @@ EXPORTS = [
     "he_plan_create", "he_plan_destroy", "he_plan_workspace_bytes", "he_ct_pt_mac", "he_ct_pt_mac_static", "he_ct_pt_add", "he_rescale",
     "he_ntt_fwd", "he_ntt_inv", "he_check_reduced", "he_host_mulmod", "he_host_reduce128", "he_host_shoup_mulmod", "he_host_shoup_lazy",
     "he_host_mac_accumulate", "he_host_mac_accumulate_add", "he_host_mac_accumulate_lazy", "he_test_mac_for_rescale", "he_measure_rate",
-    "he_host_barrett64", "he_host_shoup32", "he_host_mac_digits", "he_host_digit_reduce", "he_test_mac_groups_per_workgroup", "he_host_ntt_forward_fp64", "he_host_ntt_expand_fp64", "he_host_ntt_inverse_fp64", "he_test_integer_transforms", "he_square_relin_workspace_bytes", "he_ct_square_relin", "he_pack32", "he_unpack32", "he_ct_pt_mac32", "he_ct_pt_add32", "he_rescale32", "he_ntt_fwd32", "he_ntt_inv32",
+    "he_host_barrett64", "he_host_shoup32", "he_host_mac_digits", "he_host_digit_reduce", "he_test_mac_groups_per_workgroup", "he_test_mac_form", "he_host_ntt_forward_fp64", "he_host_ntt_expand_fp64", "he_host_ntt_inverse_fp64", "he_test_integer_transforms", "he_square_relin_workspace_bytes", "he_ct_square_relin", "he_pack32", "he_unpack32", "he_ct_pt_mac32", "he_ct_pt_add32", "he_rescale32", "he_ntt_fwd32", "he_ntt_inv32",
 ]
 
 _lib = None
@@ -91,6 +92,7 @@ def lib():
         "he_host_ntt_inverse_fp64": (i32, [vp, u32, vp, vp, ctypes.POINTER(ctypes.c_double)]),
         "he_test_integer_transforms": (i32, [vp, i32]),
         "he_test_mac_groups_per_workgroup": (i32, [vp, u32, u32, i32, ctypes.POINTER(u32)]),
+        "he_test_mac_form": (i32, [vp, u32, u32, i32, u32, ctypes.POINTER(u32)]),
         "he_host_barrett64": (u32, [u64, u32]),
         "he_host_shoup32": (u32, [u32, u32, u32]),
         "he_pack32": (i32, [vp, vp, vp, sz, vp]),
@@ -461,6 +463,12 @@ class Plan:
         """he_test_mac_groups_per_workgroup."""
         n = ctypes.c_uint32()
         _check(lib().he_test_mac_groups_per_workgroup(self._h, limbs, outputs, int(packed), ctypes.byref(n)), "he_test_mac_groups_per_workgroup")
+        return int(n.value)
+
+    def mac_form(self, limbs: int, outputs: int, packed: bool = False, flags: int = 0) -> int:
+        """he_test_mac_form: FORM_* bits."""
+        n = ctypes.c_uint32()
+        _check(lib().he_test_mac_form(self._h, limbs, outputs, int(packed), flags, ctypes.byref(n)), "he_test_mac_form")
         return int(n.value)
 
     def close(self):
