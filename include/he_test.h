@@ -80,8 +80,8 @@ int he_test_mac_for_rescale(he_ctx* ctx, const he_plan* plan, uint32_t limbs, co
 int he_test_mac_groups_per_workgroup(const he_plan* plan, uint32_t limbs, uint32_t outputs, int packed, uint32_t* groups);
 
 /*
- * In which form the scalar MAC of the plan's groups of `outputs` outputs (2 to 16, as above) is launched by he_ct_pt_mac (packed:
- * he_ct_pt_mac32) with these flags, as long as its tables fit the workspace: HE_FORM_* bits.
+ * In which form the scalar MAC of the plan's groups of `outputs` outputs (1; 2 to 16, as above) is launched by he_ct_pt_mac
+ * (packed: he_ct_pt_mac32, 2 to 16) with these flags, as long as its tables fit the workspace: HE_FORM_* bits.
  */
 enum {
     HE_FORM_PAST_CACHES = 1 /* the outputs are written past the caches */

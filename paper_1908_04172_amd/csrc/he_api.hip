@@ -1219,9 +1219,12 @@ int he_test_mac_groups_per_workgroup(const he_plan* plan, uint32_t limbs, uint32
 }
 
 int he_test_mac_form(const he_plan* plan, uint32_t limbs, uint32_t outputs, int packed, uint32_t flags, uint32_t* form) {
-    if (!plan || !form || outputs < 2 || outputs > CAPS_S[SCALAR_CLASSES - 1] || (flags & ~(HE_RESCALE | HE_ACCUMULATE))) return HE_ERR_ARG;
+    if (!plan || !form || outputs < 1 || outputs > CAPS_S[SCALAR_CLASSES - 1] || (packed && outputs == 1) || (flags & ~(HE_RESCALE | HE_ACCUMULATE)))
+        return HE_ERR_ARG;
     if (int rc = check_level(plan->ctx, limbs, (flags & HE_RESCALE) ? 2 : 1)) return rc;
-    *form = mac_groups_stream(plan, limbs, plan->ctx->N, packed ? sizeof(u32) : sizeof(u64)) ? (u32)HE_FORM_PAST_CACHES : 0u;
+    const u32 N = plan->ctx->N;
+    const bool past = outputs == 1 ? mac_singles_stream(plan, limbs, N, flags & HE_RESCALE) : mac_groups_stream(plan, limbs, N, packed ? sizeof(u32) : sizeof(u64));
+    *form = past ? (u32)HE_FORM_PAST_CACHES : 0u;
     return HE_OK;
 }
 

@@ -190,6 +190,15 @@ inline bool mac_groups_stream(const he_plan* plan, u32 limbs, u32 N, size_t resi
     const u64 per_ct = (u64)2 * limbs * N * residue_bytes, out = plan->n_out * per_ct;
     return out > L2_BYTES && plan->n_read * per_ct + out > MEMORY_CACHE_BYTES;
 }
+// ... and of outputs that share their inputs with no other (64-bit residues), where no rescale follows in the same call: there
+// only if the inputs alone do fit, or sums of three or more terms read them again.  Past the caches and through them, MAC and rescale as
+// a pair (and with a call that adds between them): N = 2^13, L = 4, 150 + 150 MiB, 2 terms 174 / 270 us and 178 / 276, 4 terms 197 / 322
+// and 209 / 335; 2^14, L = 8, 600 + 600 MiB, 4 terms 751 / 1261 and 808 / 1331.  One or two terms of more inputs: 845 ciphertexts of 2^13
+// at L = 3 324 and 312, 500 + 500 MiB of two terms 528 and 514.  What fits altogether: 50 + 50 MiB, 20 terms, 100 / 164 and 96 / 155.
+inline bool mac_singles_stream(const he_plan* plan, u32 limbs, u32 N, bool for_rescale) {
+    const u64 in = (u64)plan->n_read * 2 * limbs * N * sizeof(u64);
+    return !for_rescale && (in <= MEMORY_CACHE_BYTES || plan->max_terms_s[0] > 2) && mac_groups_stream(plan, limbs, N, sizeof(u64));
+}
 // wtab: room for `wtab_bytes` of gathered weights; less than scalar_table_bytes() is worked off in slices, down to
 // min_scalar_table_bytes()
 int launch_mac(he_ctx* ctx, const he_plan* plan, u32 limbs, const u64* ct_in, const u64* pt, int pt_kind,

@@ -259,9 +259,7 @@ static int launch_scalar_single(he_ctx* ctx, const he_plan* plan, const ScalarSl
                        plan->owners_dev + sl.table_begin, n_tables, limbs, plan->off_dev, plan->term_pt_dev, pt, wtab, sl.tab_words, sl.tab_skip,
                        sl.t_begin, sl.t_end);
     HE_HIP(hipGetLastError());
-    // (accumulators of a fused layer are read next, other results beyond the L2s are written past the caches: 845 ciphertexts
-    // of N = 2^13 at L = 3 142 -> 139 us; with the rescale after it 316 -> 329)
-    if (!(accumulate & MAC_FOR_RESCALE) && (u64)plan->n_out * 2 * limbs * ctx->N * sizeof(u64) > L2_BYTES) accumulate |= MAC_STREAM;
+    if (mac_singles_stream(plan, limbs, ctx->N, accumulate & MAC_FOR_RESCALE)) accumulate |= MAC_STREAM;
     const u32 per_thread = ctx->N >= 2048 ? 4 : 2;
     const u64 blocks = (u64)count * limbs * 2 * (ctx->N / (MAC_THREADS * 2 * per_thread));
     auto launch = [&](auto kernel) {

@@ -1,5 +1,6 @@
 """Sums that are written past the caches: on both sides of each line at which that begins, with every flag, against the same
 outputs in a call of their own that is small enough for the caches."""
+import numpy as np
 import pytest
 import torch
 
@@ -41,3 +42,41 @@ def test_sums_around_the_sizes_of_the_caches(packed, K, M, streamed):
     mac(hp, x, w, he.PT_SCALAR, bias=b, flags=he.ACCUMULATE, out=acc)
     mac(few, x, w_tail, he.PT_SCALAR, bias=b_tail, flags=he.ACCUMULATE, out=acc_tail)
     assert torch.equal(acc[M - tail:], acc_tail)
+
+
+def windows(n, terms):
+    """Output o is the sum of `terms` inputs from input o on, round the end: no two share all their inputs."""
+    off = np.arange(n + 1, dtype=np.uint32) * terms
+    term_ct = ((np.arange(n)[:, None] + np.arange(terms)) % n).astype(np.uint32).reshape(-1)
+    return wl.Plan(n, n, n * terms, off, term_ct, np.arange(n * terms, dtype=np.uint32))
+
+
+# (128 KiB a ciphertext again, as many inputs as outputs)
+@pytest.mark.parametrize("n,terms,streamed", [(1024, 2, False), (1025, 1, True), (1500, 5, True), (2048, 2, True),
+                                              (2049, 1, False), (2049, 2, False), (2049, 3, True)])
+def test_sums_of_their_own_around_the_sizes_of_the_cache(n, terms, streamed):
+    N = 1 << 12
+    q = wl.modulus_chain([60, 40], N)
+    ctx = he.Context(12, q, device=0)
+    p = windows(n, terms)
+    hp = ctx.plan(p.n_in, p.n_out, p.n_pt, p.off, p.term_ct, p.term_pt)
+    assert [bool(hp.mac_form(2, 1, False, flags) & he.FORM_PAST_CACHES) for flags in (0, he.ACCUMULATE, he.RESCALE)] == [streamed, streamed, False]
+    x, w = residues((n, 2), q, N, 1), residues((p.n_pt,), q, 1, 2)[..., 0].contiguous()
+    b, acc = residues((n,), q, 1, 3)[..., 0].contiguous(), residues((n, 2), q, N, 4)
+    # the same outputs in three calls that fit the cache: inputs [first, first + count + terms - 1), round the end
+    sums, third = torch.empty_like(acc), -(-n // 3)
+    for first in range(0, n, third):
+        count = min(third, n - first)
+        off = np.arange(count + 1, dtype=np.uint32) * terms
+        term_ct = (np.arange(count)[:, None] + np.arange(terms)).astype(np.uint32).reshape(-1)
+        few = ctx.plan(count + terms - 1, count, count * terms, off, term_ct, np.arange(count * terms, dtype=np.uint32))
+        assert not few.mac_form(2, 1) & he.FORM_PAST_CACHES
+        at = (torch.arange(first, first + count + terms - 1) % n).cuda()
+        sums[first:first + count] = ctx.ct_pt_mac(few, x[at], w[first * terms:(first + count) * terms].contiguous(), he.PT_SCALAR,
+                                                  bias=b[first:first + count].contiguous())
+    assert torch.equal(ctx.ct_pt_mac(hp, x, w, he.PT_SCALAR, bias=b), sums)
+    assert torch.equal(ctx.ct_pt_mac(hp, x, w, he.PT_SCALAR, bias=b, flags=he.RESCALE), ctx.rescale(sums))
+    moduli = torch.tensor([int(m) for m in q], dtype=torch.int64, device="cuda").view(1, 1, -1, 1)
+    want = acc + sums
+    want -= torch.where(want >= moduli, moduli, torch.zeros_like(moduli))
+    assert torch.equal(ctx.ct_pt_mac(hp, x, w, he.PT_SCALAR, bias=b, flags=he.ACCUMULATE, out=acc), want)
