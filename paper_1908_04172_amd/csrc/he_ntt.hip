@@ -878,7 +878,7 @@ int launch_ntt_square_t(he_ctx* ctx, u32 limbs, const u64* ct, u64* d2, u64* dig
 // position: it gets a table with drop_id's constants at the last position and the inverse twiddles
 // shifted so that the last position finds drop_id's.
 template <int LOGN, bool SCALED>
-int launch_rescale_t(he_ctx* ctx, u32 limbs, u32 drop_id, const u64* in, u64* out, u32 n, const ScaledInput& si, hipStream_t s) {
+int launch_rescale_t(he_ctx* ctx, u32 limbs, u32 drop_id, const u64* in, u64* out, u32 n, const ScaledInput& si, u32 n_read, hipStream_t s) {
     using G = Geo<LOGN>;
     LimbTable lt = ctx->limbs;
     lt.c[limbs - 1] = ctx->limbs.c[drop_id];
@@ -901,8 +901,9 @@ int launch_rescale_t(he_ctx* ctx, u32 limbs, u32 drop_id, const u64* in, u64* ou
     // Accumulators that do not fit the memory-side cache (256 MiB) are read past the caches, so that the parked t stays
     // there (845 ciphertexts of N = 2^13 at L = 3, 332 MB: 191 -> 185 us); smaller ones lie in it when a MAC has just written
     // them (300 at L = 4, 157 MB: 93 us, 101 past the caches).  Results of calls beyond the L2s (8 x 4 MiB) are written past them.
-    const size_t row_bytes = (size_t)G::N * sizeof(u64), in_bytes = 2 * n * limbs * row_bytes, out_bytes = 2 * n * (limbs - 1) * row_bytes;
-    const u32 stream = (in_bytes > MEMORY_CACHE_BYTES ? STREAM_LOADS : 0) | (in_bytes + out_bytes > L2_BYTES ? STREAM_STORES : 0);
+    // SCALED: inputs that several outputs read count once (845 outputs of N = 2^13 at L = 3 over 64 inputs: 205 us past the caches, 190).
+    const size_t per_ct = (size_t)2 * G::N * sizeof(u64), in_bytes = n_read * limbs * per_ct, rows_bytes = (size_t)n * (2 * limbs - 1) * per_ct;
+    const u32 stream = (in_bytes > MEMORY_CACHE_BYTES ? STREAM_LOADS : 0) | (rows_bytes > L2_BYTES ? STREAM_STORES : 0);
     const dim3 grid(2 * n, parts), block(G::T);
     if constexpr (SCALED)
         hipLaunchKernelGGL((scaled_rescale_kernel<LOGN>), grid, block, lds, s, lt, row, limbs, shares, stream, in, out, ctx->tw_fwd, tw_inv,
@@ -981,11 +982,11 @@ int launch_rescale_drop(he_ctx* ctx, u32 limbs, u32 drop_id, const u64* in, u64*
     if (n > 0x3FFFFFFFu) return HE_ERR_RANGE;
     const ScaledInput none = {};
     switch (ctx->log2N) {
-        case 10: return launch_rescale_t<10, false>(ctx, limbs, drop_id, in, out, n, none, s);
-        case 11: return launch_rescale_t<11, false>(ctx, limbs, drop_id, in, out, n, none, s);
-        case 12: return launch_rescale_t<12, false>(ctx, limbs, drop_id, in, out, n, none, s);
-        case 13: return launch_rescale_t<13, false>(ctx, limbs, drop_id, in, out, n, none, s);
-        case 14: return launch_rescale_t<14, false>(ctx, limbs, drop_id, in, out, n, none, s);
+        case 10: return launch_rescale_t<10, false>(ctx, limbs, drop_id, in, out, n, none, n, s);
+        case 11: return launch_rescale_t<11, false>(ctx, limbs, drop_id, in, out, n, none, n, s);
+        case 12: return launch_rescale_t<12, false>(ctx, limbs, drop_id, in, out, n, none, n, s);
+        case 13: return launch_rescale_t<13, false>(ctx, limbs, drop_id, in, out, n, none, n, s);
+        case 14: return launch_rescale_t<14, false>(ctx, limbs, drop_id, in, out, n, none, n, s);
         case 15:
             if ((u64)n * 2 * (limbs - 1) > 0x3FFFFFFFull) return HE_ERR_RANGE;
             return launch_rescale_split(ctx, limbs, drop_id, in, out, n, s);
@@ -998,11 +999,11 @@ int launch_rescale_scaled(he_ctx* ctx, const he_plan* plan, u32 limbs, const u64
     const u32 n = plan->n_out;
     const ScaledInput si{plan->term_ct_dev, plan->term_pt_dev, pt, bias};
     switch (ctx->log2N) {
-        case 10: return launch_rescale_t<10, true>(ctx, limbs, limbs - 1, ct_in, out, n, si, s);
-        case 11: return launch_rescale_t<11, true>(ctx, limbs, limbs - 1, ct_in, out, n, si, s);
-        case 12: return launch_rescale_t<12, true>(ctx, limbs, limbs - 1, ct_in, out, n, si, s);
-        case 13: return launch_rescale_t<13, true>(ctx, limbs, limbs - 1, ct_in, out, n, si, s);
-        case 14: return launch_rescale_t<14, true>(ctx, limbs, limbs - 1, ct_in, out, n, si, s);
+        case 10: return launch_rescale_t<10, true>(ctx, limbs, limbs - 1, ct_in, out, n, si, plan->n_read, s);
+        case 11: return launch_rescale_t<11, true>(ctx, limbs, limbs - 1, ct_in, out, n, si, plan->n_read, s);
+        case 12: return launch_rescale_t<12, true>(ctx, limbs, limbs - 1, ct_in, out, n, si, plan->n_read, s);
+        case 13: return launch_rescale_t<13, true>(ctx, limbs, limbs - 1, ct_in, out, n, si, plan->n_read, s);
+        case 14: return launch_rescale_t<14, true>(ctx, limbs, limbs - 1, ct_in, out, n, si, plan->n_read, s);
     }
     return HE_ERR_ARG;
 }

@@ -66,3 +66,17 @@ def test_many_outputs(log2N, bits, n):
     b = wl.uniform_residues_torch((n,), q, 1, 5, "cuda")[..., 0].contiguous()
     got = ctx.ct_pt_mac(hp, x, w, he.PT_SCALAR, bias=b, flags=he.RESCALE)
     assert torch.equal(got, ctx.rescale(ctx.ct_pt_mac(hp, x, w, he.PT_SCALAR, bias=b)))
+
+
+@pytest.mark.parametrize("log2N,bits,n,n_in", [(12, [60, 40], 2100, 2048), (12, [60, 40], 2100, 2049), (12, [60, 40], 2100, 3), (13, [60, 50, 50], 700, 60)])
+def test_many_outputs_of_shared_inputs(log2N, bits, n, n_in):
+    """Inputs that several outputs read: on both sides of the memory-side cache's size (2048 ciphertexts of 128 KiB), and few of them."""
+    N = 1 << log2N
+    q = wl.modulus_chain(bits, N)
+    ctx = he.Context(log2N, q, device=0)
+    hp, _ = plan_of(ctx, np.arange(n) % n_in, np.arange(n) % 5, n_in, 5)
+    x = wl.uniform_residues_torch((n_in, 2), q, N, 3, "cuda", chunk=2048)
+    w = wl.uniform_residues_torch((5,), q, 1, 4, "cuda")[..., 0].contiguous()
+    b = wl.uniform_residues_torch((n,), q, 1, 5, "cuda")[..., 0].contiguous()
+    got = ctx.ct_pt_mac(hp, x, w, he.PT_SCALAR, bias=b, flags=he.RESCALE)
+    assert torch.equal(got, ctx.rescale(ctx.ct_pt_mac(hp, x, w, he.PT_SCALAR, bias=b)))
