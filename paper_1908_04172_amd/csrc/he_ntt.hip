@@ -469,7 +469,7 @@ ntt_rows_kernel(LimbTable lt, u32 limbs, u64* data, const u64* tw_all, const dou
 // of a compute unit leave room for beside their rows: three at every ring degree), and rows that pass by the caches when a call
 // is larger than they are (launch_rescale_t).  Before and with all three: 1024 ciphertexts of N = 2^14 at L = 8 1360 -> 1231 us,
 // 768 of 2^13 at L = 4 226 -> 213, 2048 of 2^12 at L = 4 327 -> 260, 128 of 2^12 at L = 4 27.9 -> 23.0.
-// Four wavefronts per SIMD: 108 to 122 registers, no spills.
+// Four wavefronts per SIMD: 111 to 122 registers, 111 to 128 where the rows are multiplied as they are read (SCALED); no spills.
 constexpr u32 LDS_BYTES = 160u << 10;  // of a compute unit
 constexpr u32 RESCALE_WAVES = 4;
 

@@ -25,7 +25,9 @@ namespace {
 // for the whole run of ciphertexts (read for every one of them they were as many bytes again as digits and sums
 // together, out of the caches), and the sums are MacAcc ones, of which P * d_k is one more term: four multiply-adds per
 // product and one reduction per sum.  256 ciphertexts, seven limbs and P, N = 2^14 (2.9 GB): 767 -> 574 us.  The digits are
-// read past the caches (the whole square of 200 ciphertexts, four limbs and P, N = 2^13: 408 -> 391 us; of 60 at 2^14 262 -> 249).
+// read past the caches (the whole square of 200 ciphertexts, four limbs and P, N = 2^13: 408 -> 391 us; of 60 at 2^14 262 -> 249),
+// at every size: with 125 to 280 MiB of them that is 2 to 6 % of the square (30 ciphertexts, seven limbs and P, 2^14, 295 -> 279), with
+// 90 MiB and less neither way is faster (37 sizes from 1 ciphertext on, all within 0.8 %), with 420 and 700 MiB it is 1 % at most.
 // A run of one ciphertext has nothing to keep the key for, and holding it only costs wavefronts (186 registers at l = 15):
 // such launches read it term by term (eight ciphertexts at N = 2^13, l = 15: 52 -> 34 us; l = 10: 24 -> 20).
 struct SpecialPrimeResidues {
