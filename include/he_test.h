@@ -75,7 +75,8 @@ int he_test_mac_for_rescale(he_ctx* ctx, const he_plan* plan, uint32_t limbs, co
 
 /*
  * How many groups of `outputs` outputs (2 to 16: groups of 2..4, 5..8 and 9..16 go together) a workgroup of the matrix-core
- * MAC runs through for this plan and level, packed or not: what a test of the transitions between groups has to know.
+ * MAC runs through for this plan and level, packed or not (where its wavefronts take neighbouring groups, all four together): what
+ * a test of the transitions between groups has to know.
  */
 int he_test_mac_groups_per_workgroup(const he_plan* plan, uint32_t limbs, uint32_t outputs, int packed, uint32_t* groups);
 
@@ -84,7 +85,8 @@ int he_test_mac_groups_per_workgroup(const he_plan* plan, uint32_t limbs, uint32
  * (packed: he_ct_pt_mac32, 2 to 16) with these flags, as long as its tables fit the workspace: HE_FORM_* bits.
  */
 enum {
-    HE_FORM_PAST_CACHES = 1 /* the outputs are written past the caches */
+    HE_FORM_PAST_CACHES = 1, /* the outputs are written past the caches */
+    HE_FORM_ABREAST = 2      /* the wavefronts of a workgroup take neighbouring groups */
 };
 int he_test_mac_form(const he_plan* plan, uint32_t limbs, uint32_t outputs, int packed, uint32_t flags, uint32_t* form);
 

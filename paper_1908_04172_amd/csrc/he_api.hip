@@ -1214,7 +1214,8 @@ int he_test_mac_groups_per_workgroup(const he_plan* plan, uint32_t limbs, uint32
     if (int rc = check_level(plan->ctx, limbs, 1)) return rc;
     u32 cls = 1;
     while (outputs > CAPS_S[cls]) ++cls;
-    *groups = mac_digits_groups_per_workgroup(plan->ctx, plan, limbs, cls, packed != 0);
+    bool abreast;
+    *groups = mac_digits_groups_per_workgroup(plan->ctx, plan, limbs, cls, packed != 0, &abreast);
     return HE_OK;
 }
 
@@ -1223,8 +1224,15 @@ int he_test_mac_form(const he_plan* plan, uint32_t limbs, uint32_t outputs, int 
         return HE_ERR_ARG;
     if (int rc = check_level(plan->ctx, limbs, (flags & HE_RESCALE) ? 2 : 1)) return rc;
     const u32 N = plan->ctx->N;
-    const bool past = outputs == 1 ? mac_singles_stream(plan, limbs, N, flags & HE_RESCALE) : mac_groups_stream(plan, limbs, N, packed ? sizeof(u32) : sizeof(u64));
-    *form = past ? (u32)HE_FORM_PAST_CACHES : 0u;
+    bool past = mac_groups_stream(plan, limbs, N, packed ? sizeof(u32) : sizeof(u64)), abreast = false;
+    if (outputs == 1) {
+        past = mac_singles_stream(plan, limbs, N, flags & HE_RESCALE);
+    } else {
+        u32 cls = 1;
+        while (outputs > CAPS_S[cls]) ++cls;
+        (void)mac_digits_groups_per_workgroup(plan->ctx, plan, limbs, cls, packed != 0, &abreast);
+    }
+    *form = (past ? (u32)HE_FORM_PAST_CACHES : 0u) | (abreast ? (u32)HE_FORM_ABREAST : 0u);
     return HE_OK;
 }
 

@@ -219,7 +219,7 @@ int launch_mac_digits(he_ctx* ctx, const he_plan* plan, const ScalarSlice& sl, u
 int launch_mac_digits32(he_ctx* ctx, const he_plan* plan, const ScalarSlice& sl, u32 limbs, const u32* ct_in, const u64* pt, const u64* bias,
                         u32* out, u64* wtab, u32 mode, hipStream_t s);
 u64 mac_digits_blocks(const he_ctx* ctx, const he_plan* plan, u32 limbs);
-u32 mac_digits_groups_per_workgroup(const he_ctx* ctx, const he_plan* plan, u32 limbs, u32 cls, bool packed);
+u32 mac_digits_groups_per_workgroup(const he_ctx* ctx, const he_plan* plan, u32 limbs, u32 cls, bool packed, bool* abreast);
 int launch_ntt(he_ctx* ctx, u32 limbs, u64* data, u32 n_polys, bool inverse, hipStream_t s, const u64* src = nullptr);
 int launch_rescale(he_ctx* ctx, u32 limbs, const u64* in, u64* out, u32 n, hipStream_t s);
 int launch_rescale_scaled(he_ctx* ctx, const he_plan* plan, u32 limbs, const u64* ct_in, const u64* pt, const u64* bias, u64* out, hipStream_t s);

@@ -17,7 +17,7 @@
 // them); a convolution window's 27 terms, the memory itself.  Measured against the same loop on 32-bit multiply-adds
 // (the layer's MAC launch alone): dense 845 -> 100 at N = 2^13, L = 4: 1150 -> 345 us; dense 96 -> 24 at 2^15, L = 8:
 // 358 -> 147 us; convolution 32x32x3, 3x3x16, at 2^14, L = 8: 5940 -> 3590 us (16 GB: 4.5 TB/s); 28x28, 5x5x5, at 2^13,
-// L = 4: 435 -> 255 us; dense 64 -> 16 at 2^12, L = 2: 37 -> 15 us.  Packed, dense 1024 -> 256 at 2^12, L = 2: 352 -> 83 us.
+// L = 4: 435 -> 255 us; dense 64 -> 16 at 2^12, L = 2: 37 -> 13 us.  Packed, dense 1024 -> 256 at 2^12, L = 2: 352 -> 83 us.
 // (On random digits the chip sustains 2.8 to 3.2 int8 POP/s, on constant ones 4.3: a long sum's arithmetic is priced with
 // the former, 235 us of the 330 that 845 -> 96 takes; what else it waits for is the inputs, 75 us, and the meetings of
 // the wavefronts around the table's stages, 35 us.)
@@ -408,7 +408,7 @@ struct MacClass {
 };
 
 // Where a workgroup is: slice of the row fastest, then run of groups, then (component, limb): workgroups go to the eight XCDs
-// round-robin and the number of slices is a multiple of eight from N = 2^11 on, so the same slice of neighbouring groups (which
+// round-robin and the number of slices is a multiple of eight from N = 2^11 on (packed residues: 2^12), so the same slice of neighbouring groups (which
 // read the same or overlapping inputs) runs on the same XCD, close in time, and hits in its L2.
 struct MacPlace {
     u32 part, run, row;  // row: (limb, component)
@@ -537,6 +537,18 @@ MacClass mac_class_of(const he_ctx* ctx, const he_plan* plan, u32 limbs, u32 cls
     return m;
 }
 
+// Whether the groups [first, end) of a class go abreast (mac_class_of) where they are all that a launch over `n_tables` tables has.
+template <typename V>
+bool go_abreast(const he_ctx* ctx, const he_plan* plan, u32 limbs, u32 cls, u32 first, u32 end, u32 t_begin, u32 n_tables, MacClass& m) {
+    if (sizeof(V) != sizeof(u64) || !plan->shared_inputs_s[cls] || plan->short_sums() || plan->min_terms_s[cls] <= t_begin ||
+        plan->max_terms_s[cls] > RESIDENT_CHUNKS * CHUNK_TERMS || n_tables != 1 || end - first < 2 * WAVES)
+        return false;
+    const MacClass abreast = mac_class_of<V>(ctx, plan, limbs, cls, first, end, t_begin, true);
+    if (abreast.blocks >= 0x7FFFFFFFu) return false;
+    m = abreast;
+    return true;
+}
+
 template <typename V, bool SHORT>
 void launch_classes(he_ctx* ctx, const MacArgs<V>& a, const MacClass (&c)[SCALAR_CLASSES], u64 blocks, hipStream_t s) {
     const dim3 grid((u32)blocks), block(THREADS);
@@ -570,17 +582,9 @@ int launch_mac_digits_t(he_ctx* ctx, const he_plan* plan, const ScalarSlice& sl,
     }
     if (blocks == 0) return HE_OK;
     const u32 table0 = plan->table_s[first];
-    if constexpr (sizeof(V) == sizeof(u64)) {
-        for (u32 cls = 1; cls < SCALAR_CLASSES; cls++) {
-            if (c[cls].blocks != blocks || !plan->shared_inputs_s[cls] || plan->short_sums() || plan->min_terms_s[cls] <= sl.t_begin ||
-                plan->max_terms_s[cls] > RESIDENT_CHUNKS * CHUNK_TERMS ||
-                sl.table_end - table0 != 1 || sl.end[cls] - sl.begin[cls] < 2 * WAVES)
-                continue;
-            const MacClass m = mac_class_of<V>(ctx, plan, limbs, cls, sl.begin[cls], sl.end[cls], sl.t_begin, true);
-            if (m.blocks >= 0x7FFFFFFFu) continue;
-            c[cls] = m;
-            blocks = m.blocks;
-        }
+    for (u32 cls = 1; cls < SCALAR_CLASSES; cls++) {
+        if (c[cls].blocks == blocks && go_abreast<V>(ctx, plan, limbs, cls, sl.begin[cls], sl.end[cls], sl.t_begin, sl.table_end - table0, c[cls]))
+            blocks = c[cls].blocks;
     }
     const bool short_sums = sizeof(V) == sizeof(u64) && plan->short_sums();  // (packed sums that short run on the vector ALU)
     // about one entry per thread, but no more workgroups than fill the chip a few times
@@ -605,7 +609,8 @@ int launch_mac_digits_t(he_ctx* ctx, const he_plan* plan, const ScalarSlice& sl,
 
 }  // namespace
 
-// an upper bound of the workgroups that launch_mac_digits starts for the whole plan, in either form
+// an upper bound of the workgroups that launch_mac_digits starts for the whole plan in either form, but for windows abreast (nine of
+// them go as three runs of four): that form is checked where it is chosen
 u64 mac_digits_blocks(const he_ctx* ctx, const he_plan* plan, u32 limbs) {
     u64 blocks = 0;
     for (u32 cls = 1; cls < SCALAR_CLASSES; cls++)
@@ -613,10 +618,14 @@ u64 mac_digits_blocks(const he_ctx* ctx, const he_plan* plan, u32 limbs) {
     return blocks;
 }
 
-// groups of a class that a workgroup runs through, in a pass from the first term on
-u32 mac_digits_groups_per_workgroup(const he_ctx* ctx, const he_plan* plan, u32 limbs, u32 cls, bool packed) {
+// groups of a class that a workgroup runs through, in a launch of the whole plan from the first term on, and whether they go abreast
+u32 mac_digits_groups_per_workgroup(const he_ctx* ctx, const he_plan* plan, u32 limbs, u32 cls, bool packed, bool* abreast) {
     const u32 first = plan->class_begin_s[cls], end = plan->class_begin_s[cls + 1];
-    return packed ? mac_class_of<u32>(ctx, plan, limbs, cls, first, end, 0).per_wg : mac_class_of<u64>(ctx, plan, limbs, cls, first, end, 0).per_wg;
+    const bool alone = plan->n_tiles_s - plan->class_begin_s[1] == end - first;
+    MacClass m = packed ? mac_class_of<u32>(ctx, plan, limbs, cls, first, end, 0) : mac_class_of<u64>(ctx, plan, limbs, cls, first, end, 0);
+    *abreast = !packed && alone && first < end &&
+               go_abreast<u64>(ctx, plan, limbs, cls, first, end, 0, (u32)plan->table_end.size() - plan->table_s[first], m);
+    return m.per_wg;
 }
 
 int launch_mac_digits(he_ctx* ctx, const he_plan* plan, const ScalarSlice& sl, u32 limbs, const u64* ct_in, const u64* pt, const u64* bias,

@@ -17,7 +17,7 @@ RATE_MAD32, RATE_MAC_TERM, RATE_SHOUP_EXACT, RATE_SHOUP_CHEAP = 0, 1, 2, 3
 RATE_BUTTERFLY_MODE0, RATE_BUTTERFLY_MODE1, RATE_BUTTERFLY_MODE2, RATE_BUTTERFLY_INV = 4, 5, 6, 7
 RATE_BUTTERFLY_FP64, RATE_BUTTERFLY_FP64_INV = 9, 10
 DIGITS_CANONICAL, DIGITS_BELOW_6Q, DIGITS_BELOW_4Q, DIGITS_PACKED = 0, 1, 2, 3
-FORM_PAST_CACHES = 1
+FORM_PAST_CACHES, FORM_ABREAST = 1, 2
 PT_SCALAR = 0
 PT_POLY = 1
 RESCALE = 1

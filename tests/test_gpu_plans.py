@@ -58,6 +58,7 @@ def test_inputs_named_far_apart():
     x[::spread] = dev(ct)
     far = ctx.plan(n_in, p.n_out, p.n_pt, p.off, p.term_ct * np.uint32(spread), p.term_pt)
     near = ctx.plan(p.n_in, p.n_out, p.n_pt, p.off, p.term_ct, p.term_pt)
+    assert far.mac_form(2, 2) == near.mac_form(2, 2) == he.FORM_ABREAST
     assert far.groups_per_workgroup(2, 2) == near.groups_per_workgroup(2, 2)
     for hp, ins in ((near, dev(ct)), (far, x)):
         assert np.array_equal(ctx.ct_pt_mac(hp, ins, dev(w), he.PT_SCALAR).cpu().numpy().view(np.uint64), want)
