@@ -47,12 +47,49 @@ def test_large_squares_equal_their_slices(log2N, l, n):
     assert torch.equal(ctx.ct_square_relin(ct, evk), want)
 
 
+# (the squares' inverse transforms are 256 MiB of rows and more, the digits a multiple of that)
+@pytest.mark.parametrize("log2N,l,n", [(12, 2, 4100), (13, 3, 1400)])
+def test_larger_squares_equal_their_slices(log2N, l, n):
+    N = 1 << log2N
+    q = wl.modulus_chain([60] + [50] * (l - 1) + [60], N)
+    ctx = he.Context(log2N, q, device=0)
+    ct, evk = residues((n, 2), q[:l], N, 6), residues((l, 2), q, N, 7)
+    assert n * l * N * 8 > 256 << 20
+    got, eighth = ctx.ct_square_relin(ct, evk), -(-n // 8)
+    for k in range(0, n, eighth):
+        assert torch.equal(got[k:k + eighth], ctx.ct_square_relin(ct[k:k + eighth].contiguous(), evk))
+
+
+def test_large_calls_at_the_largest_ring_degree_equal_their_slices():
+    """Half rows beyond 256 MiB, in place and (the rescale's inverse transforms) from the input."""
+    N, n = 1 << 15, 530
+    q = wl.modulus_chain([60, 50, 50], N)
+    ctx = he.Context(15, q, device=0)
+    x = residues((n, 2), q, N, 5)
+    assert n * 2 * N * 8 > 256 << 20
+    third = -(-n // 3)
+    got = ctx.rescale(x)
+    for k in range(0, n, third):
+        assert torch.equal(got[k:k + third], ctx.rescale(x[k:k + third].contiguous()))
+    rows = x.clone()
+    ctx.ntt_fwd(rows)
+    for k in range(0, n, third):
+        part = x[k:k + third].clone()
+        ctx.ntt_fwd(part)
+        assert torch.equal(rows[k:k + third], part)
+    ctx.ntt_inv(rows)
+    assert torch.equal(rows, x)
+
+
+WIDTHS = [60, 40, 50, 30, 55, 61, 45, 50, 62, 40, 58, 50, 60, 30, 50, 61]
+
+
 @pytest.mark.parametrize("log2N", [10, 11, 12, 13, 14])
-@pytest.mark.parametrize("bits", [[40, 60], [60, 40, 50], [60, 50, 30, 40, 55]])
-def test_rescale_of_every_number_of_kept_limbs(log2N, bits):
+@pytest.mark.parametrize("limbs", range(2, 17))
+def test_rescale_of_every_number_of_kept_limbs(log2N, limbs):
     """More polynomials than the chip holds workgroups, so that one workgroup takes all kept limbs."""
     N = 1 << log2N
-    q = wl.modulus_chain(bits, N)
+    q = wl.modulus_chain(WIDTHS[:limbs], N)
     ctx = he.Context(log2N, q, device=0)
     n = 1 + (256 * 16 * 1024 // N) // 2
     x = residues((n, 2), q, N, 8)
