@@ -152,7 +152,7 @@ def test_device_calls_fail_loudly_on_a_host_only_context():
     with pytest.raises(he.HeError) as e:
         ctx.plan(p.n_in, p.n_out, p.n_pt, p.off, p.term_ct, p.term_pt)
     assert e.value.status == -5
-    dummy = np.zeros(4, dtype=np.uint64)
+    dummy = np.zeros(2 * c.N, dtype=np.uint64)  # (whole, so that it shares no memory with the other one wherever the two lie)
     other = np.zeros(2 * 2 * c.N, dtype=np.uint64)
     assert he.lib().he_rescale(ctx._h, 2, other.ctypes.data, dummy.ctypes.data, 1, None) == -5
     # output sharing memory with the input is refused before anything is launched
