@@ -418,7 +418,10 @@ __device__ __forceinline__ MacPlace mac_place(u32 b, u32 parts, u32 runs, u32 fi
     return MacPlace{b % parts, rest % runs, first_row + rest / runs};
 }
 
-// MIXED: one of several classes of a launch, whose windows never go abreast.
+// MIXED: one of several classes of a launch, whose windows never go abreast.  (With the choice left open the three branches of that kernel
+// had 146 scalar registers parked in vector lanes, 112 without: dense 300 -> 37 at N = 2^13, L = 2 32.8 -> 32.2 us, 300 -> 23 at L = 3
+// 39.2 -> 38.6.  An opaque place in each branch parks 92 to 104 and was better for some launches, 845 -> 20 at L = 4 119 -> 110 to 116, and
+// worse for others, 200 + 113 -> 37 in two calls 116.7 -> 118.4.)
 template <typename V, int OT, bool SHORT, bool MIXED = false>
 __device__ __forceinline__ void mac_class(const MacPlace& at_wg, const MacArgs<V>& a, const DigitTable& dt, const MacClass& m, v4i* lds) {
     using F = Form<V>;
@@ -501,19 +504,9 @@ __global__ void __launch_bounds__(THREADS, 2) mac_digits_mixed_kernel(DigitTable
         cls = b < n16 ? 0 : b < n16 + n8 ? 1 : 2;
         at = mac_place(b - (cls == 0 ? 0 : cls == 1 ? n16 : n16 + n8), parts, cls == 0 ? c16.runs : cls == 1 ? c8.runs : c4.runs, lead);
     }
-    // (The place is opaque in each branch: left to itself the compiler derives what the three have in common ahead of them,
-    // in scalar registers that it then has to park: 146 of them, 104 now.  Dense 300 -> 23 at N = 2^13, L = 3 38.9 -> 37.8 us,
-    // 845 -> 20 at L = 4 122 -> 119.5.)
-    if (cls == 0) {
-        asm volatile("; groups of 9 to 16" : "+s"(at.part), "+s"(at.run), "+s"(at.row));
-        mac_class<V, OT16, SHORT, true>(at, a, dt, c16, lds);
-    } else if (cls == 1) {
-        asm volatile("; groups of 5 to 8" : "+s"(at.part), "+s"(at.run), "+s"(at.row));
-        mac_class<V, OT8, SHORT, true>(at, a, dt, c8, lds);
-    } else {
-        asm volatile("; groups of 2 to 4" : "+s"(at.part), "+s"(at.run), "+s"(at.row));
-        mac_class<V, OT4, SHORT, true>(at, a, dt, c4, lds);
-    }
+    if (cls == 0) mac_class<V, OT16, SHORT, true>(at, a, dt, c16, lds);
+    else if (cls == 1) mac_class<V, OT8, SHORT, true>(at, a, dt, c8, lds);
+    else mac_class<V, OT4, SHORT, true>(at, a, dt, c4, lds);
 }
 
 // Groups per workgroup and workgroups of one class over the tiles [first, end).  Several groups per workgroup pay the
