@@ -126,7 +126,8 @@ int he_decode_vector(he_ctx* ctx, const uint64_t* poly, size_t n, double scale, 
  * off has n_out+1 entries, off[0] = 0, non-decreasing; term_ct[t] < n_in; term_pt[t] < n_pt.
  * Outputs that read the same ciphertexts in the same order (the output channels of one
  * convolution window, the outputs of a dense layer) are grouped so that each input is loaded once
- * per group.  Needs a device context.
+ * per group.  Needs a device context.  Takes host memory by the terms (HE_ERR_RANGE if there is too little), whatever n_in and
+ * n_pt are.
  */
 int he_plan_create(he_ctx* ctx, uint32_t n_in, uint32_t n_out, uint32_t n_pt, const uint32_t* off,
                    const uint32_t* term_ct, const uint32_t* term_pt, he_plan** out);
@@ -134,10 +135,10 @@ int he_plan_create(he_ctx* ctx, uint32_t n_in, uint32_t n_out, uint32_t n_pt, co
  * call on a plan needs its context alive. */
 int he_plan_destroy(he_plan* plan);
 /* Device bytes he_ct_pt_mac needs in `workspace` for this plan, level and flags: with HE_RESCALE the accumulators of all
- * outputs, and with HE_PT_SCALAR the plaintexts as the kernels read them, once for all groups that multiply by the same
- * ones.  The latter are, per limb, 8 bytes a term for an output that shares its ciphertexts with no other, and 256, 512 or
- * 1024 bytes a term for a group of 2..4, 5..8 or 9..16 outputs, the terms of a group rounded up to a multiple of 16 (of 4
- * if no group of the plan has more than 4). */
+ * outputs (also for a plan of one term per output, whose call writes none up to log2N = 14), and with HE_PT_SCALAR the
+ * plaintexts as the kernels read them, once for all groups that multiply by the same ones.  The latter are, per limb, 8 bytes a
+ * term for an output that shares its ciphertexts with no other, and 256, 512 or 1024 bytes a term for a group of 2..4, 5..8 or
+ * 9..16 outputs, the terms of a group rounded up to a multiple of 16 (of 4 if no group of the plan has more than 4). */
 int he_plan_workspace_bytes(const he_plan* plan, uint32_t limbs, int pt_kind, uint32_t flags,
                             size_t* bytes);
 
