@@ -176,7 +176,6 @@ inline int allow_dynamic_lds(const void* kernel, size_t bytes, int device, std::
 // `accumulate` argument of the MAC launchers and kernels: bits
 enum : u32 {
     MAC_ACCUMULATE = 1,   // add the canonical residues that the output holds (HE_ACCUMULATE)
-    MAC_STREAM = 4,       // the output is not to be kept in the caches (set by the launchers)
     MAC_FOR_RESCALE = 2   // the output is the accumulator tensor of a fused layer, read next by the rescale kernel: the
                           // kept limbs of scalar-plaintext sums may be left unreduced (LimbConst::mac_lazy)
 };

@@ -5,6 +5,7 @@
 // Products are accumulated unreduced (MacAcc) and reduced once at the end (or every LimbConst::reduce_every terms),
 // then the bias residue is added on component 0.
 #include <algorithm>
+#include <type_traits>
 
 #include "he_internal.h"
 
@@ -70,7 +71,8 @@ __device__ __forceinline__ void housekeeping(MacAcc (&acc)[A], u32& f, u32& r, u
 // WAVES: the wavefronts per SIMD, no more and no fewer.  The registers allow five, which longer sums want; up to two terms the
 // fifth only adds rows to what the memory is working on at once.  N = 2^14, L = 4, four and five (the launch): one term
 // of 500 ciphertexts 196 and 204 us, two terms of 300 149 and 151, four 210 and 200, nine 285 and 252.
-template <int SL, int WAVES>
+// STREAM: the stores go past the caches (mac_singles_stream).
+template <int SL, int WAVES, bool STREAM>
 __global__ void __launch_bounds__(MAC_THREADS) __attribute__((amdgpu_waves_per_eu(WAVES, WAVES)))
 mac_scalar_single_kernel(LimbTable lt, u32 limbs, u32 N, const Tile* tiles, u32 n_tiles, const u64* wbase, const u32* term_ct,
                          const u64* wtab, u64 tab_words, u64 tab_skip, u32 t_begin, u32 t_end, const u64* ct_in, const u64* bias, u64* out,
@@ -136,13 +138,8 @@ mac_scalar_single_kernel(LimbTable lt, u32 limbs, u32 N, const Tile* tiles, u32 
             v.x = add_mod(v.x, old.x, c.q);
             v.y = add_mod(v.y, old.y, c.q);
         }
-        if (accumulate & MAC_STREAM) {
-            asm volatile("; streamed store" ::: "memory");
-            __builtin_nontemporal_store(v, &dst[s * MAC_THREADS + threadIdx.x]);
-            asm volatile("; end" ::: "memory");
-        } else {
-            dst[s * MAC_THREADS + threadIdx.x] = v;
-        }
+        if constexpr (STREAM) __builtin_nontemporal_store(v, &dst[s * MAC_THREADS + threadIdx.x]);
+        else dst[s * MAC_THREADS + threadIdx.x] = v;
     }
 }
 
@@ -259,16 +256,20 @@ static int launch_scalar_single(he_ctx* ctx, const he_plan* plan, const ScalarSl
                        plan->owners_dev + sl.table_begin, n_tables, limbs, plan->off_dev, plan->term_pt_dev, pt, wtab, sl.tab_words, sl.tab_skip,
                        sl.t_begin, sl.t_end);
     HE_HIP(hipGetLastError());
-    if (mac_singles_stream(plan, limbs, ctx->N, accumulate & MAC_FOR_RESCALE)) accumulate |= MAC_STREAM;
     const u32 per_thread = ctx->N >= 2048 ? 4 : 2;
     const u64 blocks = (u64)count * limbs * 2 * (ctx->N / (MAC_THREADS * 2 * per_thread));
     auto launch = [&](auto kernel) {
         hipLaunchKernelGGL(kernel, dim3((u32)blocks), dim3(MAC_THREADS), 0, s, ctx->limbs, limbs, ctx->N, tiles + begin, count, plan->wbase_s_dev + begin,
                            plan->term_ct_dev, wtab, sl.tab_words, sl.tab_skip, sl.t_begin, sl.t_end, ct_in, bias, out, accumulate);
     };
-    if (per_thread == 2) launch(mac_scalar_single_kernel<2, 8>);
-    else if (plan->max_terms_s[0] <= 2) launch(mac_scalar_single_kernel<4, 4>);
-    else launch(mac_scalar_single_kernel<4, 5>);
+    auto launch_form = [&](auto stream) {
+        constexpr bool STREAM = decltype(stream)::value;
+        if (per_thread == 2) launch(mac_scalar_single_kernel<2, 8, STREAM>);
+        else if (plan->max_terms_s[0] <= 2) launch(mac_scalar_single_kernel<4, 4, STREAM>);
+        else launch(mac_scalar_single_kernel<4, 5, STREAM>);
+    };
+    if (mac_singles_stream(plan, limbs, ctx->N, accumulate & MAC_FOR_RESCALE)) launch_form(std::true_type{});
+    else launch_form(std::false_type{});
     HE_HIP(hipGetLastError());
     return HE_OK;
 }

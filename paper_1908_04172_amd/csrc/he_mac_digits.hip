@@ -195,7 +195,10 @@ struct Slice {
 
 // Final reduction, bias (Alg. 4) and store of one group.  The caller has waited for its loads in flight: a later wait
 // for one of them would wait for these stores as well.
-template <typename V, int OT>
+// STREAM: the stores go past the caches (mac_groups_stream), an instance of its own of every kernel.  Chosen by a branch per output
+// instead, both kinds were slower: dense 64 -> 16 at N = 2^12 16.5 us, 16.2 now; packed, 512 outputs of 16 terms in groups of 16 at 2^13 28.2
+// and 27.4; past the caches 4096 outputs of one term in groups of 16, N = 2^13, L = 4, 564 and 538.
+template <typename V, int OT, bool STREAM>
 __device__ __forceinline__ void store_group(const Sums<V, OT>& sums, const MacArgs<V>& a, const Slice<V>& w, const DigitConst& c, u32 out0, u32 count) {
     using F = Form<V>;
     constexpr u32 LANE_OUTPUTS = F::LANE_OUTPUTS, TILE_OUTPUTS = F::TILE_OUTPUTS, D = F::D;
@@ -205,7 +208,7 @@ __device__ __forceinline__ void store_group(const Sums<V, OT>& sums, const MacAr
     asm volatile("" : "+v"(half));  // what follows is derived here, not kept in registers through the loop over terms
     V* dst = w.dst + (size_t)out0 * out_stride + half * (LANE_OUTPUTS * out_stride);
     const u32 lazy = D == 8 && (a.mode & MAC_FOR_RESCALE) && w.limb + 1 < a.limbs ? c.lazy : 0;
-    const bool accumulate = a.mode & MAC_ACCUMULATE, stream = a.mode & MAC_STREAM;
+    const bool accumulate = a.mode & MAC_ACCUMULATE;
     // The bias residues come in with scalar loads, those of the next four outputs while four are reduced.  (Without a
     // bias the loads read the group's descriptor and are masked.)
     const bool has_bias = a.bias != nullptr && w.comp == 0;
@@ -255,13 +258,8 @@ __device__ __forceinline__ void store_group(const Sums<V, OT>& sums, const MacAr
                     row_piece all;
 #pragma unroll
                     for (int k = 0; k < CT; k++) all[k] = v[k];
-                    if (stream) {
-                        asm volatile("; streamed store" ::: "memory");  // (left to itself the compiler makes one ordinary store of both)
-                        __builtin_nontemporal_store(all, reinterpret_cast<row_piece*>(at));
-                        asm volatile("; end" ::: "memory");
-                    } else {
-                        *reinterpret_cast<row_piece*>(at) = all;
-                    }
+                    if constexpr (STREAM) __builtin_nontemporal_store(all, reinterpret_cast<row_piece*>(at));
+                    else *reinterpret_cast<row_piece*>(at) = all;
                 }
                 __builtin_amdgcn_sched_barrier(0);  // one output at a time: its temporaries are few
             }
@@ -298,7 +296,7 @@ __device__ __forceinline__ v4i operand(const u32x4 (&x)[4], int k) {
 // one block: with the other three as padding a quarter of the loads and products were of use.  (N = 2^13, L = 4: 256 groups of
 // 16 outputs and one term with plaintexts of their own 1000 -> 785 us, 935 on the vector ALU; of two outputs that share their
 // plaintexts 197 -> 135.)
-template <typename V, int OT, bool RESIDENT, bool SHORT>
+template <typename V, int OT, bool RESIDENT, bool SHORT, bool STREAM>
 __device__ __forceinline__ void mac_stream(const MacArgs<V>& a, const Slice<V>& w, const DigitConst& c, u32 tile_first, u32 tile_end, u32 stride, v4i* lds) {
     using F = Form<V>;
     static_assert(!SHORT || (RESIDENT && F::LANE_TERMS <= 4), "one chunk, its list in one piece");
@@ -387,7 +385,7 @@ __device__ __forceinline__ void mac_stream(const MacArgs<V>& a, const Slice<V>& 
 #pragma unroll
             for (u32 j = 0; j < LANE_TERMS; j++) asm volatile("" : "+v"(x[b][j]));  // the next chunk's inputs have arrived
         const DigitTile t = load_tile(a.tiles + tile);
-        store_group<V, OT>(sums, a, w, c, t.out0, t.count);
+        store_group<V, OT, STREAM>(sums, a, w, c, t.out0, t.count);
         if (tile + stride >= tile_end) break;
         cur.tile = tile + stride;
         cur.n_chunks = chunks_of(a, load_tile(a.tiles + tile + stride));
@@ -419,14 +417,14 @@ __device__ __forceinline__ MacPlace mac_place(u32 b, u32 parts, u32 runs, u32 fi
 }
 
 // MIXED: one of several classes of a launch, whose windows never go abreast.  (With the choice left open the three branches of that kernel
-// had 146 scalar registers parked in vector lanes, 112 without: dense 300 -> 37 at N = 2^13, L = 2 32.8 -> 32.2 us, 300 -> 23 at L = 3
+// had 146 scalar registers parked in vector lanes, 103 now: dense 300 -> 37 at N = 2^13, L = 2 32.8 -> 32.2 us, 300 -> 23 at L = 3
 // 39.2 -> 38.6.  An opaque place in each branch parks 92 to 104 and was better for some launches, 845 -> 20 at L = 4 119 -> 110 to 116, and
 // worse for others, 200 + 113 -> 37 in two calls 116.7 -> 118.4.)
-template <typename V, int OT, bool SHORT, bool MIXED = false>
+template <typename V, int OT, bool SHORT, bool STREAM, bool MIXED = false>
 __device__ __forceinline__ void mac_class(const MacPlace& at_wg, const MacArgs<V>& a, const DigitTable& dt, const MacClass& m, v4i* lds) {
     using F = Form<V>;
     const u32 part = at_wg.part;
-    const bool abreast = !MIXED && m.abreast;
+    const bool abreast = !MIXED && !SHORT && sizeof(V) == sizeof(u64) && m.abreast;  // (go_abreast)
     const u32 tile_first = m.first + at_wg.run * m.per_wg;
     const u32 tile_end = min(tile_first + m.per_wg, m.end);
     Slice<V> w;
@@ -450,7 +448,7 @@ __device__ __forceinline__ void mac_class(const MacPlace& at_wg, const MacArgs<V
         if (p.n_chunks == 0) {  // no terms: the bias alone
             Sums<V, OT> zero;
             zero.clear();
-            store_group<V, OT>(zero, a, w, c, t.out0, t.count);
+            store_group<V, OT, STREAM>(zero, a, w, c, t.out0, t.count);
             tile++;
         } else if (SHORT || p.n_chunks <= RESIDENT_CHUNKS) {
             const u32 end = min(tile_end, t.same_until);
@@ -459,14 +457,14 @@ __device__ __forceinline__ void mac_class(const MacPlace& at_wg, const MacArgs<V
             for (u32 i = threadIdx.x; i < pieces; i += THREADS) lds[i] = w.tab[p.piece + i];
             lds_barrier();
             const u32 own = abreast ? tile + __builtin_amdgcn_readfirstlane(threadIdx.x / 64) : tile;
-            if (own < end) mac_stream<V, OT, true, SHORT>(a, w, c, own, end, abreast ? WAVES : 1, lds);
+            if (own < end) mac_stream<V, OT, true, SHORT, STREAM>(a, w, c, own, end, abreast ? WAVES : 1, lds);
             tile = end;
         } else {
             // the rest of the run: groups with long sums follow one another (tables of a class are in the order of
             // their first use, so a shorter one may still come and takes the same path)
             if constexpr (!SHORT) {
                 lds_barrier();
-                mac_stream<V, OT, false, false>(a, w, c, tile, tile_end, 1, lds);
+                mac_stream<V, OT, false, false, STREAM>(a, w, c, tile, tile_end, 1, lds);
             }
             tile = tile_end;
         }
@@ -475,19 +473,19 @@ __device__ __forceinline__ void mac_class(const MacPlace& at_wg, const MacArgs<V
 
 // 64-bit residues: groups of 9..16 (OT = 4), 5..8 (2) and 2..4 (1) outputs; packed ones: of 9..16 (2) and up to 8 (1).
 // The accumulators, OT x CT x 16 registers, set how many wavefronts a SIMD holds.
-template <typename V, int OT, bool SHORT>
+template <typename V, int OT, bool SHORT, bool STREAM>
 __global__ void __launch_bounds__(THREADS, OT * Form<V>::CT == 8 ? 2 : OT * Form<V>::CT == 4 ? 3 : 4)
 mac_digits_kernel(DigitTable dt, MacArgs<V> a, MacClass m) {
     __shared__ v4i lds[lds_pieces<V, SHORT>(OT)];
     const MacPlace at = mac_place(blockIdx.x, a.N / m.template slots<V>(), m.runs);
-    mac_class<V, OT, SHORT>(at, a, dt, m, lds);
+    mac_class<V, OT, SHORT, STREAM>(at, a, dt, m, lds);
 }
 
 // A plan with groups of several classes in one launch, all groups of one slice next to one another: they read the same inputs.
 // (With the workgroups of the largest class first and the others behind them the inputs of a dense layer 96 -> 24 at 2^15, L = 8,
 // came from the memory twice: 186 us, now 150; 845 -> 100 at 2^13, L = 8, 800 and 756.)  In the last `tail` rows, about as
 // many workgroups as the chip holds, the largest class does come first and the smaller ones fill in while it drains.
-template <typename V, bool SHORT>
+template <typename V, bool SHORT, bool STREAM>
 __global__ void __launch_bounds__(THREADS, 2) mac_digits_mixed_kernel(DigitTable dt, MacArgs<V> a, MacClass c16, MacClass c8, MacClass c4, u32 tail) {
     constexpr int OT16 = Form<V>::tiles(16), OT8 = Form<V>::tiles(8), OT4 = Form<V>::tiles(4);
     __shared__ v4i lds[lds_pieces<V, SHORT>(OT16)];
@@ -504,9 +502,9 @@ __global__ void __launch_bounds__(THREADS, 2) mac_digits_mixed_kernel(DigitTable
         cls = b < n16 ? 0 : b < n16 + n8 ? 1 : 2;
         at = mac_place(b - (cls == 0 ? 0 : cls == 1 ? n16 : n16 + n8), parts, cls == 0 ? c16.runs : cls == 1 ? c8.runs : c4.runs, lead);
     }
-    if (cls == 0) mac_class<V, OT16, SHORT, true>(at, a, dt, c16, lds);
-    else if (cls == 1) mac_class<V, OT8, SHORT, true>(at, a, dt, c8, lds);
-    else mac_class<V, OT4, SHORT, true>(at, a, dt, c4, lds);
+    if (cls == 0) mac_class<V, OT16, SHORT, STREAM, true>(at, a, dt, c16, lds);
+    else if (cls == 1) mac_class<V, OT8, SHORT, STREAM, true>(at, a, dt, c8, lds);
+    else mac_class<V, OT4, SHORT, STREAM, true>(at, a, dt, c4, lds);
 }
 
 // Groups per workgroup and workgroups of one class over the tiles [first, end).  Several groups per workgroup pay the
@@ -542,13 +540,13 @@ bool go_abreast(const he_ctx* ctx, const he_plan* plan, u32 limbs, u32 cls, u32 
     return true;
 }
 
-template <typename V, bool SHORT>
+template <typename V, bool SHORT, bool STREAM>
 void launch_classes(he_ctx* ctx, const MacArgs<V>& a, const MacClass (&c)[SCALAR_CLASSES], u64 blocks, hipStream_t s) {
     const dim3 grid((u32)blocks), block(THREADS);
     constexpr int OT16 = Form<V>::tiles(16), OT8 = Form<V>::tiles(8), OT4 = Form<V>::tiles(4);
-    if (c[3].blocks == blocks) hipLaunchKernelGGL((mac_digits_kernel<V, OT16, SHORT>), grid, block, 0, s, ctx->digits, a, c[3]);
-    else if (c[2].blocks == blocks) hipLaunchKernelGGL((mac_digits_kernel<V, OT8, SHORT>), grid, block, 0, s, ctx->digits, a, c[2]);
-    else if (c[1].blocks == blocks) hipLaunchKernelGGL((mac_digits_kernel<V, OT4, SHORT>), grid, block, 0, s, ctx->digits, a, c[1]);
+    if (c[3].blocks == blocks) hipLaunchKernelGGL((mac_digits_kernel<V, OT16, SHORT, STREAM>), grid, block, 0, s, ctx->digits, a, c[3]);
+    else if (c[2].blocks == blocks) hipLaunchKernelGGL((mac_digits_kernel<V, OT8, SHORT, STREAM>), grid, block, 0, s, ctx->digits, a, c[2]);
+    else if (c[1].blocks == blocks) hipLaunchKernelGGL((mac_digits_kernel<V, OT4, SHORT, STREAM>), grid, block, 0, s, ctx->digits, a, c[1]);
     else {
         const u32 rows = a.limbs * 2;
         const u64 resident = 2 * 256;  // two workgroups per compute unit
@@ -558,7 +556,7 @@ void launch_classes(he_ctx* ctx, const MacArgs<V>& a, const MacClass (&c)[SCALAR
         // 200 -> 40 at 2^12, L = 8 54.4 and 50.4.)
         const bool all_tail = blocks < 2 * resident && 4 * (c[2].runs + c[1].runs) <= c[3].runs;
         const u32 tail = all_tail ? rows : (u32)std::min<u64>(rows, (resident * rows + blocks - 1) / blocks);
-        hipLaunchKernelGGL((mac_digits_mixed_kernel<V, SHORT>), grid, block, 0, s, ctx->digits, a, c[3], c[2], c[1], tail);
+        hipLaunchKernelGGL((mac_digits_mixed_kernel<V, SHORT, STREAM>), grid, block, 0, s, ctx->digits, a, c[3], c[2], c[1], tail);
     }
 }
 
@@ -589,13 +587,17 @@ int launch_mac_digits_t(he_ctx* ctx, const he_plan* plan, const ScalarSlice& sl,
                            plan->tiles_s_dev, plan->wbase_s_dev, plan->owners_dev + table0 + t, limbs, plan->off_dev, plan->term_pt_dev, pt, wtab,
                            sl.tab_words, sl.tab_skip, sl.t_begin, sl.t_end, short_sums ? BLOCK_TERMS : CHUNK_TERMS);
     }
-    if (mac_groups_stream(plan, limbs, ctx->N, sizeof(V))) mode |= MAC_STREAM;
     const MacArgs<V> a{plan->digit_tiles_dev, plan->lists_dev, wtab, sl.tab_words, sl.tab_skip, ct_in, bias, out, limbs, ctx->N, sl.t_begin,
                        sl.t_end, mode};
+    auto launch_form = [&](auto short_form) {
+        constexpr bool SHORT = decltype(short_form)::value;
+        if (mac_groups_stream(plan, limbs, ctx->N, sizeof(V))) launch_classes<V, SHORT, true>(ctx, a, c, blocks, s);
+        else launch_classes<V, SHORT, false>(ctx, a, c, blocks, s);
+    };
     if constexpr (sizeof(V) == sizeof(u64)) {
-        if (short_sums) launch_classes<V, true>(ctx, a, c, blocks, s);
+        if (short_sums) launch_form(std::true_type{});
     }
-    if (!short_sums) launch_classes<V, false>(ctx, a, c, blocks, s);
+    if (!short_sums) launch_form(std::false_type{});
     HE_HIP(hipGetLastError());
     return HE_OK;
 }

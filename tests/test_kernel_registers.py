@@ -70,6 +70,6 @@ def test_other_kernels_do_not_spill(built, pattern, registers):
 def test_launches_of_several_classes_keep_to_their_scalar_registers(built):
     """What only launches of one class choose between stays out of their three branches: it is parked in lanes of vector registers and
     fetched back in the loop over the terms (146, 118 and 79 of them cost launches of two classes 2 %)."""
-    for pattern, most in ((r"mac_digits_mixed_kernelImLb0E", 115), (r"mac_digits_mixed_kernelImLb1E", 80), (r"mac_digits_mixed_kernelIjLb0E", 50)):
+    for pattern, most in ((r"mac_digits_mixed_kernelImLb0E", 110), (r"mac_digits_mixed_kernelImLb1E", 75), (r"mac_digits_mixed_kernelIjLb0E", 48)):
         for name, k in matching(built, pattern).items():
             assert k[".sgpr_spill_count"] <= most, (name, k[".sgpr_spill_count"])
