@@ -182,7 +182,7 @@ enum : u32 {
 int check_mac_launch(he_ctx* ctx, const he_plan* plan, u32 limbs, int pt_kind);
 // Whether the scalar MAC of groups of outputs writes past the caches: where inputs and outputs together do not fit the
 // memory-side cache, and the outputs not the L2s.  There the stores are most of what a short sum moves, and allocating their
-// lines costs 16 outputs of one term, N = 2^13, L = 4, 800 us against 576, the layer 30 -> 120 at 2^14, L = 8 (60 + 240 MiB) 322
+// lines costs 256 groups of 16 outputs of one term, N = 2^13, L = 4, 800 us against 540, the layer 30 -> 120 at 2^14, L = 8 (60 + 240 MiB) 322
 // against 301.  What does fit is read from the cache by the call that adds to it or rescales it: the layer 100 -> 200 at 2^13,
 // L = 4 (50 + 100 MiB) 174 us, 181 past the caches; 20 -> 300 with a second call that adds, then the rescale, 296 and 326.
 inline bool mac_groups_stream(const he_plan* plan, u32 limbs, u32 N, size_t residue_bytes) {
