@@ -902,7 +902,7 @@ int launch_rescale_t(he_ctx* ctx, u32 limbs, u32 drop_id, const u64* in, u64* ou
     // there (845 ciphertexts of N = 2^13 at L = 3, 332 MB: 191 -> 185 us); smaller ones lie in it when a MAC has just written
     // them (300 at L = 4, 157 MB: 93 us, 101 past the caches).  Results of calls beyond the L2s (8 x 4 MiB) are written past them.
     // SCALED: inputs that several outputs read count once (845 outputs of N = 2^13 at L = 3 over 64 inputs: 205 us past the caches, 190).
-    const size_t per_ct = (size_t)2 * G::N * sizeof(u64), in_bytes = n_read * limbs * per_ct, rows_bytes = (size_t)n * (2 * limbs - 1) * per_ct;
+    const size_t per_ct = (size_t)2 * G::N * sizeof(u64), in_bytes = (size_t)n_read * limbs * per_ct, rows_bytes = (size_t)n * (2 * limbs - 1) * per_ct;
     const u32 stream = (in_bytes > MEMORY_CACHE_BYTES ? STREAM_LOADS : 0) | (rows_bytes > L2_BYTES ? STREAM_STORES : 0);
     const dim3 grid(2 * n, parts), block(G::T);
     if constexpr (SCALED)
